@@ -542,7 +542,8 @@ void chunk_key(const qeq_plan* pl, std::vector<unsigned char>& key) {
                           pl->spc_atom, pl->spc_dpinv, pl->spc_tpart, pl->spc_s, pl->spc_scal,
                           pl->spc_sd, pl->spc_u, pl->spc_psi, (const void*)(size_t)pl->spc_nm,
                           (const void*)(size_t)pl->spc_npad, (const void*)(size_t)pl->direct, pl->np_pos,
-                          pl->np_ypart, (const void*)(size_t)pl->np_nsplit, (const void*)(size_t)pl->np_tps,
+                          pl->np_ypart, (const void*)(size_t)pl->np_nsplit, (const void*)(size_t)pl->np_per,
+                          pl->np_mat, (const void*)(size_t)pl->np_ld,
                           (const void*)(size_t)pl->ew_active, pl->ew_modes, pl->ew_w, pl->ew_sf, pl->ew_y,
                           pl->ew_yrec, (const void*)(size_t)pl->ew_nm, (const void*)(size_t)pl->ew_fs,
                           (const void*)(size_t)pl->ew_ms, (const void*)(size_t)pl->pw_active, pl->pw_ones,

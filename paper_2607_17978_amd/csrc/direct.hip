@@ -13,6 +13,12 @@
 // the splits are added in a fixed order by the epilogue (deterministic).
 // Differences of positions, squared distances, products with the source and
 // all sums are FP64; the kernel values K(r) and K'(r)/r are FP32.
+//
+// The kernel values do not change during a solve, so the FP32 matrix K_ij is
+// evaluated once per solve (k_np_build) and every product without forces reads
+// it from memory (k_np_mv).  Clusters whose matrix does not fit (NP_MAT_MAX,
+// half of the free memory) evaluate the values in every product (k_np_pairs),
+// and so does the final product, which also needs K'(r)/r.
 #include <math.h>
 #include <string.h>
 
@@ -24,6 +30,8 @@ namespace {
 
 constexpr int NP_TILE = 256;
 constexpr int NP_SPLIT_MAX = 64;
+constexpr int NP_MT = 64;              // rows and columns of a tile of the stored kernel values
+constexpr size_t NP_MAT_MAX = (size_t)16 << 30;   // most bytes of stored kernel values (65,536 atoms)
 constexpr double NP_RSQPI = 0.56418958354775628695;   // 1/sqrt(pi)
 
 // Validate, identity order, per-atom data; partial sums [sum chi, sum 1/D] in
@@ -86,7 +94,7 @@ __device__ __forceinline__ void np_kernel(float r2, float a, float& K, float& dK
 // Partial products over the pair sum: ypart[split][i] = sum_{j in split, j != i}
 // K_ij src_j; with FIN also fpart[split][i][c] = sum_j K'_ij / r_ij src_j (r_i - r_j)_c.
 template <bool FIN>
-__global__ __launch_bounds__(NP_TILE) void k_np_pairs(int n, int tiles_per_split, const double4* __restrict__ npos,
+__global__ __launch_bounds__(NP_TILE) void k_np_pairs(int n, int per, const double4* __restrict__ npos,
                                                       const double* __restrict__ src, double* __restrict__ ypart,
                                                       double* __restrict__ fpart, const int* __restrict__ done) {
     if (done && *done) return;
@@ -94,20 +102,21 @@ __global__ __launch_bounds__(NP_TILE) void k_np_pairs(int n, int tiles_per_split
     __shared__ double sj[NP_TILE];
     const int i = blockIdx.x * NP_TILE + threadIdx.x;
     const int sp = blockIdx.y;
-    const int ntiles = (n + NP_TILE - 1) / NP_TILE;
-    const int t0 = sp * tiles_per_split, t1 = min(ntiles, t0 + tiles_per_split);
+    const int j0 = sp * per, j1 = min(n, j0 + per);
     const double4 pi = i < n ? npos[i] : make_double4(0.0, 0.0, 0.0, 1.0);
     const float si2 = (float)pi.w;
     double y = 0.0, g[3] = {0.0, 0.0, 0.0};
-    for (int t = t0; t < t1; ++t) {
-        const int j = t * NP_TILE + threadIdx.x;
+    for (int jt = j0; jt < j1; jt += NP_TILE) {
+        const int j = jt + threadIdx.x;
         __syncthreads();
-        // padded atoms far away with zero source: finite terms times zero
-        pj[threadIdx.x] = j < n ? npos[j] : make_double4(1e10, 1e10, 1e10, 1.0);
-        sj[threadIdx.x] = j < n ? src[j] : 0.0;
+        if (j < j1) {
+            pj[threadIdx.x] = npos[j];
+            sj[threadIdx.x] = src[j];
+        }
         __syncthreads();
-        const int self = i - t * NP_TILE;   // in [0, NP_TILE) only on the diagonal tile
-        for (int jj = 0; jj < NP_TILE; ++jj) {
+        const int self = i - jt;   // the atom itself, where this tile holds it
+        const int cnt = min(NP_TILE, j1 - jt);
+        for (int jj = 0; jj < cnt; ++jj) {
             const double4 q = pj[jj];
             const double dx = pi.x - q.x, dy = pi.y - q.y, dz = pi.z - q.z;
             const float r2 = (float)(dx * dx + dy * dy + dz * dz);
@@ -131,6 +140,82 @@ __global__ __launch_bounds__(NP_TILE) void k_np_pairs(int n, int tiles_per_split
     }
 }
 
+// Kernel values of all pairs, K[j][i] (ld floats per row, ld a multiple of
+// 64): a block evaluates one 64 x 64 tile of the upper triangle and writes it
+// and its transpose (the values of (i, j) and (j, i) are the same bits: the
+// squared distance and the width are symmetric).  The atom itself and the
+// padding past n: 0.  Bound by the erf evaluations, half of those of one
+// k_np_pairs product (16,384 atoms: 0.31 ms).
+__global__ __launch_bounds__(NP_TILE) void k_np_build(int n, int ld, int nt, const double4* __restrict__ npos,
+                                                      float* __restrict__ mat) {
+    __shared__ double4 pr[NP_MT];
+    __shared__ float tile[NP_MT][NP_MT + 1];
+    // block -> (I, J), I <= J, through the folded triangle of nt rows
+    int I = blockIdx.y, J = blockIdx.x;
+    if (J < I) {
+        I = nt - I;
+        J = nt - 1 - J;
+        if (I == (int)blockIdx.y) return;   // the middle row of an even nt comes once
+    }
+    const int r0 = I * NP_MT, c0 = J * NP_MT;
+    const int tid = threadIdx.x;
+    const double4 far = make_double4(0.0, 0.0, 0.0, 1.0);
+    if (tid < NP_MT) pr[tid] = r0 + tid < n ? npos[r0 + tid] : far;
+    constexpr int RG = NP_TILE / NP_MT;   // rows in flight
+    const int c = tid & (NP_MT - 1), rg = tid / NP_MT;
+    const int j = c0 + c;
+    const double4 q = j < n ? npos[j] : far;
+    __syncthreads();
+    for (int r = rg; r < NP_MT; r += RG) {
+        const double4 pi = pr[r];
+        const int i = r0 + r;
+        const double dx = pi.x - q.x, dy = pi.y - q.y, dz = pi.z - q.z;
+        const float r2 = (float)(dx * dx + dy * dy + dz * dz);
+        const float a = rsqrtf(2.f * ((float)pi.w + (float)q.w));
+        float K, dKr;
+        np_kernel(r2, a, K, dKr);
+        if (i >= n || j >= n || i == j) K = 0.f;
+        tile[r][c] = K;
+        if (i < n) mat[(size_t)i * ld + j] = K;
+    }
+    if (I == J) return;
+    __syncthreads();
+    for (int r = rg; r < NP_MT; r += RG)
+        if (c0 + r < n) mat[(size_t)(c0 + r) * ld + r0 + c] = tile[c][r];
+}
+
+// Product with the stored values: ypart[split][i] = sum over the split's
+// atoms j, in their order, of K_ij src_j: the same FP64 sums as k_np_pairs, so
+// the charges are the same bits whichever of the two runs (CG amplifies a
+// change of the summation order: two splittings of the pair sum end up to
+// 2e-7 apart in the charges of a 2,000-atom cluster).  One lane per atom i
+// (coalesced rows), U loads in flight per lane.  Bound by HBM: n^2 floats,
+// 1.07 GB in 195 us (5.5 TB/s) at 16,384 atoms against 499 us for evaluating
+// the values (solve 26.8 -> 11.7 ms); at 517 atoms 5.1 against 45 us (2.12 ->
+// 0.57 ms).  A triangle read once for both halves needs another order of the
+// sums and was slower at 16,384 atoms (345 us a product).
+template <int U>
+__global__ __launch_bounds__(64) void k_np_mv(int n, int ld, int per, const float* __restrict__ mat,
+                                              const double* __restrict__ src, double* __restrict__ ypart,
+                                              const int* __restrict__ done) {
+    if (done && *done) return;
+    const int i = blockIdx.x * 64 + threadIdx.x;   // below ld: the padding is stored as 0
+    const int j0 = blockIdx.y * per, j1 = min(n, j0 + per);
+    const float* col = mat + (size_t)j0 * ld + i;
+    double y = 0.0;
+    int j = j0;
+    for (; j + U <= j1; j += U) {
+        float v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) v[u] = col[(size_t)u * ld];
+#pragma unroll
+        for (int u = 0; u < U; ++u) y += (double)v[u] * src[j + u];
+        col += (size_t)U * ld;
+    }
+    for (; j < j1; ++j, col += ld) y += (double)*col * src[j];
+    if (i < n) ypart[(size_t)blockIdx.y * n + i] = y;
+}
+
 // Epilogue of one product, with the partial sums of the periodic path's
 // matvec in the same slots: CG mode y = (E + diag J) src, slots [src.y, sum y];
 // FINAL mode y = E src, forces -src_i sum_j ..., the gradient g = y + J q +
@@ -148,6 +233,7 @@ __global__ void k_np_finish(int n, int nsplit, const double* __restrict__ src, c
     if (i < n) {
         const double vi = src[i];
         double y = dself[i] * vi;
+#pragma unroll 8
         for (int sp = 0; sp < nsplit; ++sp) y += ypart[(size_t)sp * n + i];
         if (MODE == QEQ_MODE_CG) {
             y += Jv[i] * vi;
@@ -189,8 +275,36 @@ void np_free(qeq_plan* pl) {
     double* ptrs[] = {pl->np_pos, pl->np_ypart, pl->np_fpart};
     for (double* q : ptrs)
         if (q) (void)hipFree(q);
+    if (pl->np_mat) (void)hipFree(pl->np_mat);
     pl->np_pos = pl->np_ypart = pl->np_fpart = nullptr;
+    pl->np_mat = nullptr;
     pl->np_cap = 0;
+    pl->np_mat_cap = 0;
+    pl->np_ld = 0;
+}
+
+// Room for the kernel values of n atoms; np_ld = 0 (values evaluated in every
+// product) where they exceed NP_MAT_MAX or half of the free memory.
+static void np_matrix_room(qeq_plan* pl, int n) {
+    const size_t ld = ((size_t)n + NP_MT - 1) / NP_MT * NP_MT;
+    const size_t count = ld * (size_t)n;
+    pl->np_ld = 0;
+    if (count > pl->np_mat_cap) {
+        if (pl->np_mat) (void)hipFree(pl->np_mat);
+        pl->np_mat = nullptr;
+        pl->np_mat_cap = 0;
+        size_t avail = 0, total = 0;
+        if (hipMemGetInfo(&avail, &total) != hipSuccess) return;
+        if (count * sizeof(float) > NP_MAT_MAX || count * sizeof(float) > avail / 2) return;
+        if (hipMalloc((void**)&pl->np_mat, count * sizeof(float)) != hipSuccess) {
+            pl->np_mat = nullptr;
+            (void)hipGetLastError();
+            return;
+        }
+        debug_poison(pl->np_mat, count * sizeof(float));
+        pl->np_mat_cap = count;
+    }
+    pl->np_ld = (int)ld;
 }
 
 int np_setup(qeq_plan* pl, int n, const double* pos, const double* sigma, const double* J, const double* chi,
@@ -213,11 +327,19 @@ int np_setup(qeq_plan* pl, int n, const double* pos, const double* sigma, const 
     k.bg_pref = 0.0;          // no neutralising background: isolated system
     k.q_tot = q_tot;
     k.tol = pl->prm.tol;
-    // atom splits: about 2048 blocks in all, each split a whole number of tiles
+    // atom splits of the CG products: about 2048 blocks in all, each split a
+    // whole number of tiles
     const int ntiles = (n + NP_TILE - 1) / NP_TILE;
-    int ns = std::max(1, std::min({NP_SPLIT_MAX, ntiles, (2048 + ntiles - 1) / ntiles}));
-    pl->np_tps = (ntiles + ns - 1) / ns;
-    pl->np_nsplit = (ntiles + pl->np_tps - 1) / pl->np_tps;
+    const int ns = std::max(1, std::min({NP_SPLIT_MAX, ntiles, (2048 + ntiles - 1) / ntiles}));
+    pl->np_per = (ntiles + ns - 1) / ns * NP_TILE;
+    pl->np_nsplit = (n + pl->np_per - 1) / pl->np_per;
+    // the final product (no CG after it) goes down to 16 atoms a split, so
+    // that a small cluster fills more of the chip (517 atoms: 9 blocks -> 99,
+    // 86 -> 10 us)
+    const int nf = std::max(1, std::min({NP_SPLIT_MAX, n / 16, (2048 + ntiles - 1) / ntiles}));
+    pl->np_fper = (n + nf - 1) / nf;
+    pl->np_fsplit = (n + pl->np_fper - 1) / pl->np_fper;
+    np_matrix_room(pl, n);
     QEQ_HIP(hipMemsetAsync(pl->sc, 0, sizeof(CgScalars), pl->stream));
     const int nb = nblocks(n);
     hipLaunchKernelGGL(k_np_stage, dim3(nb), dim3(QEQ_BLOCK), 0, pl->stream, n, pos, sigma, J, chi, pl->perm,
@@ -232,35 +354,52 @@ int np_setup(qeq_plan* pl, int n, const double* pos, const double* sigma, const 
     QEQ_HIP(hipMemcpyAsync(pl->sc_host, pl->sc, sizeof(CgScalars), hipMemcpyDeviceToHost, pl->stream));
     QEQ_HIP(hipStreamSynchronize(pl->stream));
     if (pl->sc_host->err & QEQ_ERRBIT_INPUT) return QEQ_EINVAL;
+    if (pl->np_ld) {
+        // rows I and nt - I of the triangle share one grid row
+        const int nt = pl->np_ld / NP_MT;
+        hipLaunchKernelGGL(k_np_build, dim3(nt, nt / 2 + 1), dim3(NP_TILE), 0, pl->stream, n, pl->np_ld, nt,
+                           (const double4*)pl->np_pos, pl->np_mat);
+        QEQ_TRY(qeq_check(hipGetLastError()));
+    }
     return QEQ_OK;
+}
+
+// Partial products without forces into np_ypart: from the stored kernel
+// values, or by evaluating them.
+static void np_products(qeq_plan* pl, const double* src, const int* done) {
+    const int n = pl->kp.n;
+    if (pl->np_ld)
+        hipLaunchKernelGGL(k_np_mv<32>, dim3(pl->np_ld / 64, pl->np_nsplit), dim3(64), 0, pl->stream, n, pl->np_ld,
+                           pl->np_per, pl->np_mat, src, pl->np_ypart, done);
+    else
+        hipLaunchKernelGGL(k_np_pairs<false>, dim3((n + NP_TILE - 1) / NP_TILE, pl->np_nsplit), dim3(NP_TILE), 0,
+                           pl->stream, n, pl->np_per, (const double4*)pl->np_pos, src, pl->np_ypart, pl->np_fpart,
+                           done);
 }
 
 int launch_np_matvec(qeq_plan* pl, const double* src, double* dst, int mode) {
     const int n = pl->kp.n;
-    const int ntiles = (n + NP_TILE - 1) / NP_TILE;
-    const dim3 grid(ntiles, pl->np_nsplit);
-    const double4* npos = (const double4*)pl->np_pos;
+    const int nb = nblocks(n);
     // QEQ_MODE_MATVEC: the CG product without the convergence flag (timing)
     const int* done = mode == QEQ_MODE_CG ? &pl->sc->done : nullptr;
     double* part = pl->part;
     if (mode == QEQ_MODE_FINAL) {
-        hipLaunchKernelGGL(k_np_pairs<true>, grid, dim3(NP_TILE), 0, pl->stream, n, pl->np_tps, npos, src,
-                           pl->np_ypart, pl->np_fpart, done);
-        hipLaunchKernelGGL(k_np_finish<QEQ_MODE_FINAL>, dim3(nblocks(n)), dim3(QEQ_BLOCK), 0, pl->stream, n,
-                           pl->np_nsplit, src, pl->np_ypart, pl->np_fpart, pl->dself, pl->Jv, pl->chi_raw, pl->chi,
+        const dim3 grid((n + NP_TILE - 1) / NP_TILE, pl->np_fsplit);
+        hipLaunchKernelGGL(k_np_pairs<true>, grid, dim3(NP_TILE), 0, pl->stream, n, pl->np_fper,
+                           (const double4*)pl->np_pos, src, pl->np_ypart, pl->np_fpart, done);
+        hipLaunchKernelGGL(k_np_finish<QEQ_MODE_FINAL>, dim3(nb), dim3(QEQ_BLOCK), 0, pl->stream, n,
+                           pl->np_fsplit, src, pl->np_ypart, pl->np_fpart, pl->dself, pl->Jv, pl->chi_raw, pl->chi,
                            pl->sig, dst, pl->fdst, pl->gtmp, part, done);
-    } else if (mode == QEQ_MODE_ELEC) {
-        hipLaunchKernelGGL(k_np_pairs<false>, grid, dim3(NP_TILE), 0, pl->stream, n, pl->np_tps, npos, src,
-                           pl->np_ypart, pl->np_fpart, nullptr);
-        hipLaunchKernelGGL(k_np_finish<QEQ_MODE_ELEC>, dim3(nblocks(n)), dim3(QEQ_BLOCK), 0, pl->stream, n,
-                           pl->np_nsplit, src, pl->np_ypart, pl->np_fpart, pl->dself, pl->Jv, pl->chi_raw, pl->chi,
-                           pl->sig, dst, pl->fdst, pl->gtmp, part, nullptr);
-    } else {
-        hipLaunchKernelGGL(k_np_pairs<false>, grid, dim3(NP_TILE), 0, pl->stream, n, pl->np_tps, npos, src,
-                           pl->np_ypart, pl->np_fpart, done);
-        hipLaunchKernelGGL(k_np_finish<QEQ_MODE_CG>, dim3(nblocks(n)), dim3(QEQ_BLOCK), 0, pl->stream, n,
-                           pl->np_nsplit, src, pl->np_ypart, pl->np_fpart, pl->dself, pl->Jv, pl->chi_raw, pl->chi,
-                           pl->sig, dst, pl->fdst, pl->gtmp, part, done);
+        return qeq_check(hipGetLastError());
     }
+    np_products(pl, src, done);
+    if (mode == QEQ_MODE_ELEC)
+        hipLaunchKernelGGL(k_np_finish<QEQ_MODE_ELEC>, dim3(nb), dim3(QEQ_BLOCK), 0, pl->stream, n, pl->np_nsplit, src,
+                           pl->np_ypart, pl->np_fpart, pl->dself, pl->Jv, pl->chi_raw, pl->chi, pl->sig, dst, pl->fdst, pl->gtmp,
+                           part, nullptr);
+    else
+        hipLaunchKernelGGL(k_np_finish<QEQ_MODE_CG>, dim3(nb), dim3(QEQ_BLOCK), 0, pl->stream, n, pl->np_nsplit, src,
+                           pl->np_ypart, pl->np_fpart, pl->dself, pl->Jv, pl->chi_raw, pl->chi, pl->sig, dst, pl->fdst, pl->gtmp,
+                           part, done);
     return qeq_check(hipGetLastError());
 }

@@ -240,7 +240,11 @@ struct qeq_plan {
     bool geom_valid = false;      // sorted geometry and pair list of the last periodic set-up
     int np_cap = 0;               // atoms allocated
     int np_nsplit = 0;            // atom splits of the pair sum
-    int np_tps = 0;               // tiles of 256 atoms per split
+    int np_per = 0;               // atoms per split
+    int np_fper = 0, np_fsplit = 0;   // the final product's splits
+    int np_ld = 0;                // row length of the stored kernel values (0: none)
+    float* np_mat = nullptr;      // K[j][i], n rows of np_ld
+    size_t np_mat_cap = 0;        // floats
     double* np_pos = nullptr;     // double4 (x, y, z, sigma^2) per atom
     double* np_ypart = nullptr;   // [split][atom] partial products
     double* np_fpart = nullptr;   // [split][atom][3] partial force sums
