@@ -10,6 +10,7 @@
 #include <vector>
 
 #include "internal.h"
+#include "mesh_len.h"
 
 int qeq_check(hipError_t e) {
     if (e == hipSuccess) return QEQ_OK;
@@ -421,25 +422,51 @@ int prepare(qeq_plan* pl, int n, const double* cell, double q_tot) {
         if (!tws && spread_fits(w) && (size_t)K[0] * (K[1] / w) >= 512) tws = w;
     for (int w : {32, 24, 16, 12, 8})
         if (!tws && spread_fits(w)) tws = w;
-    if (!tws) {
-        tws = 16;
-        while (tws > 4 && (K[1] % tws != 0 || (size_t)K[2] * 8 + (size_t)K[2] * tws * 4 > 32768)) tws >>= 1;
-    }
     int tw = 16;
     while (tw > 4 && !tile_fits(tw)) tw >>= 1;
+    // Lengths without uniform tiles of their own: the compile-time kernels with
+    // tiles as equal as possible (mesh_len.h), for any axis-2 length and
+    // spline order.  Against the runtime-sized kernels, whose radix stages
+    // index through memory and whose power-of-two tiles shrink to four rows
+    // where 8 does not divide the axis: the mesh part of a product on 180^3
+    // 808 -> 71 us (spread 289 -> 15, axis-1 200 -> 21, axis-2 2 x 58 -> 2 x 11,
+    // complex-to-real 202 -> 12 us with the interpolation).
+    k.rag_s = !tws;
+    k.rag = !mesh_tile_compiled(K[0], K[2], tw, p);
     // tile widths set with qeq_set_tiles (e.g. by the autotuner) replace the rule
-    if (pl->tile_set[0] > 0) tws = pl->tile_set[0];
-    if (pl->tile_set[1] > 0) tw = pl->tile_set[1];
-    if (K[1] % tws != 0 || K[1] < tws + p - 1) return QEQ_EPLAN;
-    if (K[1] % tw != 0 || K[1] < tw + p - 1) return QEQ_EPLAN;
-    if ((size_t)K[2] * 8 + (size_t)K[2] * tws * 4 > 61440 || (size_t)K[0] * tw * 8 + K[0] * 8 > 61440 ||
-        (size_t)K[2] * (tw / 2) * 8 + (size_t)(K[2] / 2 + 1) * tw * 8 + K[2] * 8 > 61440)
-        return QEQ_EPLAN;
-    k.TW = tw;
-    k.TWlog2 = ilog2(tw);
-    k.ntile = K[1] / tw;
-    k.TWS = tws;
-    k.ntile_s = K[1] / tws;
+    if (pl->tile_set[0] > 0) {
+        tws = pl->tile_set[0];
+        k.rag_s = 0;
+    }
+    if (pl->tile_set[1] > 0) {
+        tw = pl->tile_set[1];
+        k.rag = 0;
+    }
+    if (k.rag_s) {
+        k.TWS = LEN_TW;
+        k.ntile_s = len_tiles(K[1]);
+    } else {
+        if (K[1] % tws != 0 || K[1] < tws + p - 1) return QEQ_EPLAN;
+        if ((size_t)K[2] * 8 + (size_t)K[2] * tws * 4 > 61440) return QEQ_EPLAN;
+        k.TWS = tws;
+        k.ntile_s = K[1] / tws;
+    }
+    if (k.rag) {
+        k.TW = LEN_TW;
+        k.ntile = len_tiles(K[1]);
+    } else {
+        if (K[1] % tw != 0 || K[1] < tw + p - 1) return QEQ_EPLAN;
+        if ((size_t)K[0] * tw * 8 + K[0] * 8 > 61440 ||
+            (size_t)K[2] * (tw / 2) * 8 + (size_t)(K[2] / 2 + 1) * tw * 8 + K[2] * 8 > 61440)
+            return QEQ_EPLAN;
+        // every FFT stage must fit the per-thread register budget
+        if ((size_t)K[0] * tw > (size_t)QEQ_FFT_EMAX * QEQ_FFT_THREADS ||
+            (size_t)K[2] * (tw / 2) > (size_t)QEQ_FFT_EMAX * QEQ_FFT_THREADS)
+            return QEQ_EPLAN;
+        k.TW = tw;
+        k.ntile = K[1] / tw;
+    }
+    k.TWlog2 = ilog2(k.TW);
     int nr = 16;
     while (nr > 1 && (size_t)K[1] * nr * 8 > 32768) nr >>= 1;
     // grids beyond the ~256 MB Infinity Cache stream from HBM: there 4 rows
@@ -447,15 +474,15 @@ int prepare(qeq_plan* pl, int n, const double* cell, double q_tot) {
     // 46 us); cache-resident grids keep the larger blocks
     const size_t grid_bytes = (size_t)K[0] * K[1] * K[2] * 4 + (size_t)K[0] * K[1] * (K[2] / 2 + 1) * 8;
     if (grid_bytes > ((size_t)192 << 20) && nr > 4) nr = 4;
-    if (pl->tile_set[2] > 0) nr = pl->tile_set[2];
-    if ((size_t)K[1] * (nr + 2) * 8 > 61440) return QEQ_EPLAN;
+    // lengths without an axis-2 kernel of their own: the width they are compiled for
+    if (!rows_compiled(K[1], nr)) nr = len_nr(K[1]);
+    if (pl->tile_set[2] > 0) {
+        nr = pl->tile_set[2];
+        if ((size_t)K[1] * (nr + 2) * 8 > 61440) return QEQ_EPLAN;
+        if ((size_t)K[1] * nr > (size_t)QEQ_FFT_EMAX * QEQ_FFT_THREADS) return QEQ_EPLAN;
+    }
     k.NR = nr;
     k.NRlog2 = ilog2(nr);
-    // every FFT stage must fit the per-thread register budget
-    if ((size_t)K[0] * tw > (size_t)QEQ_FFT_EMAX * QEQ_FFT_THREADS ||
-        (size_t)K[1] * nr > (size_t)QEQ_FFT_EMAX * QEQ_FFT_THREADS ||
-        (size_t)K[2] * (tw / 2) > (size_t)QEQ_FFT_EMAX * QEQ_FFT_THREADS)
-        return QEQ_EPLAN;
     // real-space cells: at least half a cutoff wide
     double rc = pl->prm.r_cut;
     int ncell = 1;

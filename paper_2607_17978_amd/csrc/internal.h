@@ -40,6 +40,7 @@ struct KParams {
     int TW, TWlog2, ntile;    // axis-2 row tile of the C2R and axis-1 passes
     int TWS, ntile_s;         // axis-2 row tile of the spread + R2C pass
     int NR, NRlog2;           // rows per block of the axis-2 pass
+    int rag, rag_s;           // tiles as equal as possible (mesh_len.h) instead of uniform ones
     int nc[3];                // real-space cell-list dims
     int ns[3];                // stencil half-widths in cells
     int parts;                // operator parts (QEQ_PART_*)
@@ -420,6 +421,10 @@ int launch_mesh_potential(qeq_plan* pl, const double* src, const int* done);
 int launch_mesh_cg(qeq_plan* pl, const double* src, const int* done, bool* partials);
 // whether the spread pass has a compile-time kernel for this length and tile width
 bool spread_tile_compiled(int K3, int tws, int p);
+// whether the axis-1 and complex-to-real passes have uniform compile-time tiles
+bool mesh_tile_compiled(int K1, int K3, int tw, int p);
+// whether the axis-2 pass has a kernel for nr rows of this length in mesh.hip
+bool rows_compiled(int K2, int nr);
 size_t qeq_mesh_max_smem(const KParams& k);
 // Inverse transforms only (grid_c already holds a spectrum) -> grid_r.
 int launch_mesh_inverse(qeq_plan* pl);

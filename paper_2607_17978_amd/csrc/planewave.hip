@@ -166,7 +166,7 @@ __global__ __launch_bounds__(PW_NT) void k_pw_spread(KParams k, PwGeom g, const 
 // acc[g3][row] viewed as buf[g3][row pair]) and the half spectra written
 // transposed, C[m3][g1][g2] (m2 contiguous).
 __device__ __forceinline__ void pw_tile_r2c(const KParams& k, const FftAxis& ax3, float2* buf, const float2* tw,
-                                            int g1, int g20, float2* __restrict__ C, int tid) {
+                                            int g1, int g20, int W, float2* __restrict__ C, int tid) {
     const int K1 = k.K1, K2 = k.K2, K3 = k.K3, TW = k.TW, ncol = TW >> 1;
     int twl = 0;
     while ((1 << twl) < TW) ++twl;
@@ -176,6 +176,7 @@ __device__ __forceinline__ void pw_tile_r2c(const KParams& k, const FftAxis& ax3
     for (int t = tid; t < K3h * TW; t += PW_NT) {
         const int r = t & (TW - 1);
         const int m = t >> twl;
+        if (r >= W) continue;
         const int pr = r >> 1;
         const float2 Z = buf[m * ncol + pr];
         float2 Zc = buf[(m == 0 ? 0 : K3 - m) * ncol + pr];
@@ -206,21 +207,25 @@ __global__ __launch_bounds__(PW_NT) void k_pw_r2c(KParams k, FftAxis ax3, const 
     const int tid = threadIdx.x;
     const int blk = xcd_remap(blockIdx.x, gridDim.x);
     const int g1 = blk / k.ntile;
-    const int g20 = (blk - g1 * k.ntile) * TW;
+    // the axis-1 / complex-to-real tiles: uniform, or as equal as possible
+    const int t2 = blk - g1 * k.ntile, np = K2 >> 1;
+    const int g20 = k.rag ? 2 * (t2 * np / k.ntile) : t2 * TW;
+    const int W = k.rag ? 2 * ((t2 + 1) * np / k.ntile) - g20 : TW;
     for (int t = tid; t < K3; t += PW_NT) tw[t] = ax3.tw[t];
     // row index fastest: consecutive lanes write consecutive LDS words (the
     // transposed [g3][row] layout the FFT needs); each lane loads 4 values
     // of its row (K3 % 4 == 0)
     for (int e = tid; e < TW * (K3 >> 2); e += PW_NT) {
         const int r = e & (TW - 1), c4 = e / TW;
-        const float4 x = *reinterpret_cast<const float4*>(R + ((size_t)g1 * K2 + g20 + r) * K3 + 4 * c4);
+        const float4 x = r < W ? *reinterpret_cast<const float4*>(R + ((size_t)g1 * K2 + g20 + r) * K3 + 4 * c4)
+                               : make_float4(0.f, 0.f, 0.f, 0.f);
         acc[(4 * c4) * TW + r] = x.x;
         acc[(4 * c4 + 1) * TW + r] = x.y;
         acc[(4 * c4 + 2) * TW + r] = x.z;
         acc[(4 * c4 + 3) * TW + r] = x.w;
     }
     __syncthreads();
-    pw_tile_r2c(k, ax3, buf, tw, g1, g20, C, tid);
+    pw_tile_r2c(k, ax3, buf, tw, g1, g20, W, C, tid);
 }
 
 // y_i = sum_g theta_i(g) phi(g); with FIN the forces of that product for the
