@@ -140,7 +140,7 @@ template <> __device__ __forceinline__ void dft<8>(float2* v, bool inv) {
 }
 
 // ---------------------------------------------------------------------------
-// Composite small DFTs (radix 6, 10, 12, 16, 20) in registers: for
+// Composite small DFTs (radix 6, 9, 10, 12, 15, 16, 18, 20) in registers: for
 // N = R1 R2, n = R2 n1 + n2 and k = k1 + R1 k2,
 //   X[k1 + R1 k2] = sum_n2 W_R2^{n2 k2} W_N^{n2 k1} (sum_n1 x[R2 n1 + n2] W_R1^{n1 k1}),
 // i.e. R2 DFTs of length R1, constant twiddles W_N^{n2 k1}, R1 DFTs of
@@ -234,9 +234,12 @@ __device__ __forceinline__ void dft_ct2(float2* v, bool inv) {
 }
 
 template <> __device__ __forceinline__ void dft<6>(float2* v, bool inv) { dft_ct2<3, 2>(v, inv); }
+template <> __device__ __forceinline__ void dft<9>(float2* v, bool inv) { dft_ct2<3, 3>(v, inv); }
 template <> __device__ __forceinline__ void dft<10>(float2* v, bool inv) { dft_ct2<5, 2>(v, inv); }
 template <> __device__ __forceinline__ void dft<12>(float2* v, bool inv) { dft_ct2<4, 3>(v, inv); }
+template <> __device__ __forceinline__ void dft<15>(float2* v, bool inv) { dft_ct2<5, 3>(v, inv); }
 template <> __device__ __forceinline__ void dft<16>(float2* v, bool inv) { dft_ct2<4, 4>(v, inv); }
+template <> __device__ __forceinline__ void dft<18>(float2* v, bool inv) { dft_ct2<6, 3>(v, inv); }
 template <> __device__ __forceinline__ void dft<20>(float2* v, bool inv) { dft_ct2<5, 4>(v, inv); }
 
 // One Stockham (decimation-in-time, self-sorting) stage of radix R on ncol
@@ -311,12 +314,13 @@ __device__ __forceinline__ void fft_lds(float2* buf, const FftAxis& ax, int ncol
 // ---------------------------------------------------------------------------
 // Stage radices of a compile-time length.  Composite plan: the fewest stages
 // (one LDS pass each) over the radices 2, 3, 4, 5, 8 and the register
-// composites 6, 10, 12, 16, 20; among those the smallest largest radix;
+// composites 6, 9, 10, 12, 15, 16, 18, 20; among those the smallest largest radix;
 // larger radices first (192 = 16 x 12, 96 = 12 x 8, 320 = 20 x 16).
 // Lengths that need more than three such stages, and the plain plan, take
 // 5s, 3s, 8s, then 4 or 2 (192 = 3 x 8 x 8).
 constexpr bool ct_radix_ok(int r) {
-    return r == 2 || r == 3 || r == 4 || r == 5 || r == 6 || r == 8 || r == 10 || r == 12 || r == 16 || r == 20;
+    return r == 2 || r == 3 || r == 4 || r == 5 || r == 6 || r == 8 || r == 9 || r == 10 || r == 12 || r == 15 ||
+           r == 16 || r == 18 || r == 20;
 }
 constexpr int ct_radix_plan(int K, int s, bool composite) {
     if (!composite) {
