@@ -205,15 +205,16 @@ int qeq_matvec(qeq_plan* plan, int32_t n, const double* pos, const double* cell,
                const double* sigma, const double* v, double* y, int32_t parts);
 
 /* ------------------------------------------------------------------------
-   Batched solve: many independent structures in one persistent launch.
+   Batched solve: many independent structures together.
    ------------------------------------------------------------------------ */
 
 #define QEQ_BATCH_NMAX 1024   /* largest structure of the batched path */
 
 /* Solve eq. 4G_qeq_prime for n_struct independent periodic structures of
    uneven size (the paper treats structures independently and distributes them
-   over ranks; here one launch with one workgroup per structure at a time, the
-   order longest first).  Structure s owns atoms atom_offsets[s] ..
+   over ranks; here all advance through CG in step, four launches per
+   iteration for the whole batch, as many structures at a time as 8 GiB of
+   scratch hold).  Structure s owns atoms atom_offsets[s] ..
    atom_offsets[s+1]-1 of the concatenated arrays.
    atom_offsets (n_struct + 1, HOST, non-decreasing), cells (n_struct x 9,
    HOST, rows = lattice vectors), q_tot (n_struct, HOST).
@@ -239,9 +240,9 @@ int qeq_solve_batched(qeq_plan* plan, int32_t n_struct, const int32_t* atom_offs
                       qeq_stats* stats);
 
 /* Launch shape of qeq_solve_batched: threads per workgroup (1024; other
-   sizes are QEQ_EINVAL) and workgroups per compute unit (1 .. 8; the launch
-   has that many per CU, as many as fit run at once).  Does not change results beyond FP32 rounding
-   order.  Defaults 1024, 1. */
+   sizes are QEQ_EINVAL) and workgroups per compute unit (1 .. 8).  Kept for
+   its callers: the kernels' block sizes and counts follow from the structures,
+   and results and times do not depend on it.  Defaults 1024, 1. */
 int qeq_batched_config(qeq_plan* plan, int32_t threads, int32_t wg_per_cu);
 
 /* Milliseconds of the batched kernels (HIP events) accumulated since the
@@ -249,8 +250,9 @@ int qeq_batched_config(qeq_plan* plan, int32_t threads, int32_t wg_per_cu);
 double qeq_batched_last_ms(qeq_plan* plan, int32_t reset);
 
 /* Per-structure time breakdown of the last qeq_solve_batched call, measured
-   inside the kernel with the GPU's constant 100 MHz clock by each structure's
-   workgroup: us[s * 8 + k] = microseconds in phase k of structure s, k =
+   inside the kernels with the GPU's constant 100 MHz clock: us[s * 8 + k] =
+   microseconds that the workgroups of structure s spent in phase k, summed over
+   them (workgroups of one structure run side by side), k =
    0 staging / C_eta, 1 pair list, 2 Green table and mesh self-correction,
    3 spreading, 4 FFT passes, 5 interpolation and pair product, 6 CG vector
    updates and reductions, 7 total.  us: host, n_struct x 8 doubles.

@@ -1,20 +1,24 @@
-// Batched particle-mesh QEq: one persistent launch solves many independent
-// periodic structures of uneven size, each with its own cell, grid and total
-// charge.  Structures are independent (the paper distributes them over ranks
-// for training, "Parallelization"), so a workgroup takes the next structure
-// from a device queue (longest-first order chosen on the host) and runs the
-// whole solve for it:
-//   staging, validation and B-spline weights -> the reciprocal self constant
-//   C_eta (double Ewald split) -> the image-aware pair list (two passes, CSR)
-//   -> the Green table and, from its inverse transform, the mesh
-//   self-correction -> projected Jacobi CG on the particle-mesh matvec ->
-//   final energies, mu, true residual and forces (restart on a residual gap).
-// Each workgroup owns one slot of device scratch for its current structure
-// (grids of at most a few MB stay in L2 / Infinity Cache); FFT lines are
-// staged through LDS.  The transform is the full complex 3-D FFT (five passes:
-// axis 3, axis 2, axis 1 forward + Green + inverse, axis 2, axis 3), whose
-// last pass writes the real potential and clears the complex grid for the
-// next spread.
+// Batched particle-mesh QEq: many independent periodic structures of uneven
+// size, each with its own cell, grid and total charge, solved together.
+// Structures are independent (the paper distributes them over ranks for
+// training, "Parallelization"); here they advance through the projected CG in
+// step, four launches per iteration for the whole batch, each block working on
+// one piece of one structure:
+//   k_bq_fwd   a few g1 planes: spread, real-to-complex along axis 3, axis 2
+//   k_bq_cols  64 lines: axis 1 forward, Green's function, axis 1 inverse
+//   k_bq_inv   a few g1 planes: axis 2 and axis 3 inverse, interpolation
+//   k_bq_step  a whole structure: pair product, sums, CG update and direction
+// Blocks of structures that have converged return at once.  The set-up
+// (k_bq_stage, k_bq_pairs, k_bq_green, k_bq_theta, k_bq_self) and the final
+// product with energies and forces are shared out the same way.
+//
+// Why in step and not one workgroup per structure from start to end: a
+// structure is then a serial chain on one CU (about 0.45 ms a product), so that
+// 48 structures took 20.6 ms on 48 of 256 CUs, and its five separate grid
+// passes streamed 170 GB through memory for 1,024 structures (54 ms).  In step,
+// a structure's planes and lines spread over the chip, a product moves the half
+// spectrum four times (written by fwd, read and written by cols, read by inv)
+// instead of eleven, and the real grid stays in LDS.
 #include <math.h>
 #include <string.h>
 
@@ -27,68 +31,69 @@
 namespace qeqb {
 
 constexpr int BQ_KAX = 64;      // longest grid axis of a batched structure
-constexpr int BQ_LDS = 64 * 128;  // FFT staging buffer (complex elements); also the int64 spread accumulator
+constexpr int BQ_NC = 64;       // complex lines of a block along axis 3 (two real rows each) and axis 1
+constexpr int BQ_KS = 65;       // their LDS row stride
+constexpr int BQ_NC2 = 66;      // half-spectrum columns of a block along axis 2
+constexpr int BQ_KS2 = 67;      // their LDS row stride
+constexpr int BQ_NT = 512;      // threads of the plane and line kernels
+constexpr int BQ_PB = 8;        // most planes of a block
 constexpr int BQ_L = 8;         // lanes per atom in the interpolation and pair loops
-constexpr int BQ_NV = 11;       // per-atom FP64 vectors in a slot
+constexpr int BQ_PAIR_ATOMS = 32;   // atoms of a block of the pair-list kernel
+constexpr int BQ_GREEN = 4096;  // Green's function values of a block
 constexpr int BQ_OVERFLOW = 100;   // internal status: pair list did not fit
+constexpr int BQ_NV = 11;       // per-atom FP64 vectors in a slot
 
 enum { V_Q = 0, V_R, V_P, V_Y, V_DINV, V_CHI, V_DSELF, V_G, V_J, V_SIG, V_CHIRAW };
 
-struct BAxis {
-    int K, nst, tw_off, bm_off;
-    int radix[QEQ_FFT_MAXST];
+// Which product the four kernels work on: the starting residual (source q),
+// an iteration (source p), the final product (source q, forces).
+enum { BQ_INIT = 0, BQ_ITER, BQ_FINAL };
+
+// Byte offsets inside one structure's scratch slot.
+struct BSlot {
+    unsigned C, G, wts, dwts, home, frac, vec, selfgrad, row, col, kval, pdr, tab, mpart, hstart, perm;
 };
 
 // Per-structure constants prepared on the host.
 struct BStruct {
-    int n, off, npts, nhalf;     // atoms, first atom, grid points, half-spectrum points
-    BAxis ax[3];
+    int n, off, nhalf, pb;      // atoms, first atom, half-spectrum points, planes of a block
+    int K[3], tw_off[3], bm_off[3];
     int mm[3], nn[3];           // ranges of the C_eta k-space and lattice sums
     double H[9], Hinv[9], M[6];
     double vol, green_pref, bg_pref, q_tot, zeta;
     double rho[3];              // r_cut / perpendicular width, per axis
+    long long pcap;             // pairs the slot has room for
+    size_t base;                // the slot's byte offset in the scratch buffer
+    BSlot slot;
 };
 
 // Phases of the per-structure time breakdown (wall-clock ticks, 100 MHz).
 enum { PH_SETUP = 0, PH_PAIRS, PH_MESHPREP, PH_SPREAD, PH_FFT, PH_INTERP, PH_VEC, PH_COUNT };
 
-struct BStat {
+// Per-structure state on the device.
+struct BState {
     int status, iters, restarts, q0_rejected;
-    long long nnz;
-    double rel_resid, true_rel_resid, mu, e_qeq, e_elec, pad;
-    long long ticks[PH_COUNT + 1];
+    int finished;               // results written (or failed)
+    int cgdone;                 // the CG of this round has stopped
+    int conv;                   // it met the tolerance
+    int need_init;              // the residual of q is due
+    unsigned long long nnz;     // pairs
+    double rz, res, tres, mu, e_qeq, e_elec;
+    double chi_sum, dinv_sum, chi_norm, c_eta;
+    unsigned long long ticks[PH_COUNT];
 };
 
-// Accumulates wall-clock ticks per phase in thread 0 (a read of the constant
-// 100 MHz counter; the per-structure totals go to the stats record).
-struct PhaseClock {
-    long long last;
-    long long acc[PH_COUNT];
-    __device__ void start() {
-        last = wall_clock64();
-        for (int k = 0; k < PH_COUNT; ++k) acc[k] = 0;
-    }
-    __device__ void lap(int ph) {
-        const long long t = wall_clock64();
-        acc[ph] += t - last;
-        last = t;
-    }
-};
-
-// Byte offsets inside one workgroup's scratch slot.
-struct BSlot {
-    size_t C, R, G, wts, dwts, home, frac, vec, selfgrad, rowcnt, rowptr, col, kval, pdr, tab, bytes;
+// Counters the host reads: structures whose CG runs, structures to restart.
+struct BCount {
+    int running, restarts;
 };
 
 struct BArgs {
-    int n_work, p, self_corr, max_iter;
+    int p, self_corr, max_iter;
     double tol, eta, rc2, restart_thr;
-    int nmax, pad;
-    long long pcap;
-    BSlot slot;
     const BStruct* st;
-    const int* order;
-    int* next;
+    BState* state;
+    BCount* count;
     const float2* tw;
     const float* bmod;
     const double* pos;
@@ -99,406 +104,199 @@ struct BArgs {
     double* q_out;
     double* energies;
     double* forces;
-    BStat* stats;
     char* scratch;
 };
 
-// Pointers into the current workgroup's slot.
-struct Slot {
-    float2* C;
-    float* R;
-    float* G;
-    float* wts;
-    float* dwts;
-    int* home;
-    double* frac;
-    double* v;          // BQ_NV vectors of nmax doubles
-    double* selfgrad;
-    int* rowcnt;
-    int* rowptr;
-    int* col;
-    float* kval;
-    float4* pdr;
-    double* tab;
-    int nmax;
-    __device__ double* vec(int k) const { return v + (size_t)k * nmax; }
-};
+template <typename T>
+__device__ __forceinline__ T* slot_ptr(const BArgs& a, const BStruct& S, unsigned off) {
+    return reinterpret_cast<T*>(a.scratch + S.base + off);
+}
+__device__ __forceinline__ double* slot_vec(const BArgs& a, const BStruct& S, int v) {
+    return slot_ptr<double>(a, S, S.slot.vec) + (size_t)v * S.n;
+}
 
-// ------------------------------------------------------------------ reductions
-// Sum of NV doubles over the workgroup, returned to every thread.
+__device__ __forceinline__ bool bq_active(const BState& t, int mode) {
+    if (t.finished) return false;
+    return mode == BQ_INIT ? t.need_init != 0 : mode == BQ_ITER ? t.cgdone == 0 : true;
+}
+
+// Adds the block's wall-clock ticks since t0 to a phase of its structure.
+__device__ __forceinline__ long long bq_lap(BState& t, int ph, long long t0) {
+    const long long now = wall_clock64();
+    atomicAdd(&t.ticks[ph], (unsigned long long)(now - t0));
+    return now;
+}
+
+// Sum of NV doubles over the workgroup, returned to every thread: the waves'
+// sums meet in LDS and every thread adds them in the same order.
 template <int NV>
 __device__ __forceinline__ void wg_sum(double* v) {
-    __shared__ double bc[NV];
-    block_sum<NV>(v);
-    if (threadIdx.x == 0) {
+    __shared__ double red[16][NV];
+    const int nw = (blockDim.x + 63) >> 6;
 #pragma unroll
-        for (int k = 0; k < NV; ++k) bc[k] = v[k];
+    for (int k = 0; k < NV; ++k) v[k] = wave_sum(v[k]);
+    __syncthreads();   // earlier readers of red
+    if ((threadIdx.x & 63) == 0) {
+#pragma unroll
+        for (int k = 0; k < NV; ++k) red[threadIdx.x >> 6][k] = v[k];
     }
     __syncthreads();
 #pragma unroll
-    for (int k = 0; k < NV; ++k) v[k] = bc[k];
-    __syncthreads();
-}
-
-// Exclusive prefix sum of cnt[0..n) into out[0..n], out[n] = total.
-template <int NT>
-__device__ void wg_scan(const int* cnt, int* out, int n) {
-    __shared__ int part[NT];
-    const int t = threadIdx.x;
-    const int chunk = (n + NT - 1) / NT;
-    const int lo = min(n, t * chunk), hi = min(n, lo + chunk);
-    int s = 0;
-    for (int a = lo; a < hi; ++a) s += cnt[a];
-    part[t] = s;
-    __syncthreads();
-    for (int off = 1; off < NT; off <<= 1) {
-        int v = t >= off ? part[t - off] : 0;
-        __syncthreads();
-        part[t] += v;
-        __syncthreads();
-    }
-    int run = part[t] - s;
-    for (int a = lo; a < hi; ++a) {
-        out[a] = run;
-        run += cnt[a];
-    }
-    if (t == NT - 1) out[n] = part[NT - 1];
-    __syncthreads();
-}
-
-// ------------------------------------------------------------------ mesh
-// Layouts in the slot: real grid R[g1][g2][g3]; half spectrum
-// C[g1][g2][m3], m3 = 0 .. K3/2 (contiguous), and the Green table G in the
-// same half layout.  One matvec = five passes, each staging lines in LDS:
-//   A  spread + real-to-complex along axis 3 (D whole g1 planes per batch;
-//      two real rows share one complex transform), written as half spectra;
-//   B  axis 2 forward;  C  axis 1 forward, times G, axis 1 inverse;
-//   D  axis 2 inverse;  E  complex-to-real along axis 3 into R.
-// Transforms of the common lengths are compiled for that length (every index
-// folds to constants); other lengths up to BQ_KAX use the runtime transform.
-
-#define BQ_FOR_EACH_LEN(X) X(24) X(32) X(36) X(40) X(48) X(60) X(64)
-
-// lines per LDS batch and row stride of the staging buffer
-template <int KC> constexpr int bq_nc() { return KC ? 64 : 32; }
-template <int KC> constexpr int bq_ks() { return KC ? 65 : 32; }
-
-template <int KC, int NT, bool INV>
-__device__ __forceinline__ void bq_lines_fft(float2* buf, const BAxis& ax, const float2* tw, int tid) {
-    if constexpr (KC > 0) {
-        fft_ct<KC, bq_nc<KC>(), bq_ks<KC>(), NT, INV>(buf, tw, tid);
-    } else {
-        FftAxis f;
-        f.K = ax.K;
-        f.nst = ax.nst;
-        for (int s = 0; s < QEQ_FFT_MAXST; ++s) f.radix[s] = ax.radix[s];
-        f.tw = nullptr;
-        fft_lds(buf, f, 5, tw, INV, tid, NT);
+    for (int k = 0; k < NV; ++k) {
+        double s = red[0][k];
+        for (int w = 1; w < nw; ++w) s += red[w][k];
+        v[k] = s;
     }
 }
 
-// Pass A: spread src onto planes [g1a, g1a + D) in LDS (atoms binned by h1),
-// real-to-complex transform of the rows along axis 3, half spectra to C.  The
-// spread accumulates in 64-bit fixed point with integer LDS atomics (exact,
-// order-independent; FP32 LDS atomics are several times slower on gfx950),
-// scaled per batch so that no sum can overflow: a grid value is a sum over the
-// batch's candidate atoms of src times a weight product <= 1, each candidate at
-// most once, so |value| <= sum |src| < 2^e and the scale is 2^(50 - e); each
-// term is rounded to an integer by one FP64 fused multiply-add with 1.5 * 2^52
-// (its bit pattern minus the constant's is the integer, exact below 2^51).
-template <int K3C, int NT>
-__device__ void bq_passA(const BStruct& S, const Slot& sl, const double* src, int p, float2* buf,
-                         const float2* tw, const int* hstart, const int* order, int tid) {
-    constexpr int NC = bq_nc<K3C>(), KS = bq_ks<K3C>();
-    const int K1 = S.ax[0].K, K2 = S.ax[1].K;
-    const int K3 = K3C ? K3C : S.ax[2].K;
-    const int K3h = K3 / 2 + 1;
-    const int D = max(1, min(2 * NC / K2, K1 - p + 1));
-    const int RW = 2 * NC;                              // accumulator rows (>= D K2)
-    long long* acc = reinterpret_cast<long long*>(buf);   // [K3][RW]; buf aliases its start
-    unsigned long long* acc_u = reinterpret_cast<unsigned long long*>(buf);
-    __shared__ float sh_scale;
-    const int Dp = D * p;
-    for (int g1a = 0; g1a < K1; g1a += D) {
-        for (int t = tid; t < K3 * RW; t += NT) acc[t] = 0;
-        // candidates: h1 in [g1a, g1a + D + p - 1), wrapped
-        const int end = g1a + D + p - 1;
-        const int lo0 = hstart[g1a], hi0 = hstart[min(end, K1)];
-        const int n0 = hi0 - lo0;
-        const int ncand = n0 + (end > K1 ? hstart[end - K1] : 0);
-        double v[1] = {0.0};
-        for (int c = tid; c < ncand; c += NT) v[0] += fabs(src[c < n0 ? order[lo0 + c] : order[c - n0]]);
-        block_sum<1>(v);
+// ------------------------------------------------------------------ set-up
+// One block per structure: validation, fractional coordinates, atoms sorted by
+// their home plane h1 (ties by index, so that every later sum has one order),
+// spline weights, diagonal, starting charges, norms and the reciprocal self
+// constant
+//   C_eta = (4 pi / V) sum_{k != 0} exp(-eta^2 k^2 / 2) / k^2
+// by a second split of width zeta: k-space sum with zeta plus the lattice sum
+// of the difference kernel, minus 2 pi (zeta^2 - eta^2) / V.
+__global__ __launch_bounds__(1024) void k_bq_stage(BArgs a, const int* __restrict__ order) {
+    const int s = order[blockIdx.x];
+    const BStruct& S = a.st[s];
+    BState& T = a.state[s];
+    const int n = S.n, p = a.p, tid = threadIdx.x;
+    const double Q = S.q_tot;
+    const long long t0 = wall_clock64();
+    __shared__ int err, key[1024], hcnt[BQ_KAX + 1];
+    if (tid == 0) err = 0;
+    if (tid <= BQ_KAX) hcnt[tid] = 0;
+    __syncthreads();
+    const bool live = tid < n;
+    const int o = S.off + tid;
+    double x[3] = {0.0, 0.0, 0.0}, fr[3] = {0.0, 0.0, 0.0}, sg = 1.0, jj = 1.0, ch = 0.0, q = 0.0;
+    int h[3] = {0, 0, 0};
+    if (live) {
+        for (int c = 0; c < 3; ++c) x[c] = a.pos[3 * (size_t)o + c];
+        sg = a.sigma[o];
+        jj = a.J[o];
+        ch = a.chi[o];
+        q = a.q0 ? a.q0[o] : Q / (double)n;
+        if (!isfinite(q)) q = Q / (double)n;
+        const bool ok = isfinite(x[0]) && isfinite(x[1]) && isfinite(x[2]) && isfinite(ch) && sg > 0.0 && jj > 0.0 &&
+                        isfinite(sg) && isfinite(jj);
+        if (!ok) err = 1;
+        for (int c = 0; c < 3; ++c) {
+            double v = x[0] * S.Hinv[0 * 3 + c] + x[1] * S.Hinv[1 * 3 + c] + x[2] * S.Hinv[2 * 3 + c];
+            v -= floor(v);
+            if (!(v >= 0.0 && v < 1.0)) v = 0.0;
+            fr[c] = v;
+            const int K = S.K[c];
+            int g = (int)floor(v * (double)K);
+            h[c] = g < 0 ? 0 : (g >= K ? K - 1 : g);
+        }
+        key[tid] = h[0];
+        atomicAdd(&hcnt[h[0]], 1);
+    }
+    __syncthreads();
+    if (err) {
         if (tid == 0) {
-            int e = 0;
-            (void)frexp(v[0] > 0.0 ? v[0] : 1.0, &e);
-            sh_scale = ldexpf(1.0f, max(-126, min(126, 50 - e)));
+            T.status = QEQ_EINVAL;
+            T.finished = 1;
+            atomicSub(&a.count->running, 1);
         }
-        __syncthreads();
-        const float scale = sh_scale;
-        constexpr double RND = 6755399441055744.0;   // 1.5 * 2^52
-        for (int t = tid; t < ncand * Dp; t += NT) {
-            const int c = t / Dp;
-            const int rem = t - c * Dp;
-            const int j = rem / p, k2 = rem - j * p;
-            const int a = c < n0 ? order[lo0 + c] : order[c - n0];
-            int d = sl.home[4 * a] - g1a;
-            if (d < 0) d += K1;
-            const int k1 = d - j;               // grid plane g1a + j = h1 - k1
-            if (k1 < 0 || k1 >= p || g1a + j >= K1) continue;
-            int g2 = sl.home[4 * a + 1] - k2;
-            if (g2 < 0) g2 += K2;
-            const int h3 = sl.home[4 * a + 2];
-            const float* w = sl.wts + (size_t)a * 3 * QEQ_MAXP;
-            const float a0 = (float)src[a] * w[k1] * w[QEQ_MAXP + k2] * scale;
-            const int r = j * K2 + g2;
-            for (int k3 = 0; k3 < p; ++k3) {
-                int g3 = h3 - k3;
-                if (g3 < 0) g3 += K3;
-                const long long b = __double_as_longlong(fma((double)a0, (double)w[2 * QEQ_MAXP + k3], RND));
-                const unsigned hi = (unsigned)(b >> 32) - 0x43380000u;
-                atomicAdd(acc_u + g3 * RW + r, ((unsigned long long)hi << 32) | (unsigned)b);
+        return;
+    }
+    int* hs = slot_ptr<int>(a, S, S.slot.hstart);
+    if (tid == 0) {
+        int run = 0;
+        for (int b = 0; b < S.K[0]; ++b) {
+            const int c = hcnt[b];
+            hs[b] = run;
+            hcnt[b] = run;
+            run += c;
+        }
+        hs[S.K[0]] = run;
+    }
+    __syncthreads();
+    double acc[3] = {0.0, 0.0, 0.0};
+    int at = 0;
+    double ce = 0.0;
+    if (live) {
+        at = hcnt[h[0]];
+        for (int t = 0; t < tid; ++t) at += key[t] == h[0] ? 1 : 0;
+        slot_ptr<int>(a, S, S.slot.perm)[at] = tid;
+        float* wts = slot_ptr<float>(a, S, S.slot.wts) + (size_t)at * 3 * QEQ_MAXP;
+        float* dwts = slot_ptr<float>(a, S, S.slot.dwts) + (size_t)at * 3 * QEQ_MAXP;
+        double* frac = slot_ptr<double>(a, S, S.slot.frac);
+        int* home = slot_ptr<int>(a, S, S.slot.home);
+        for (int c = 0; c < 3; ++c) {
+            frac[3 * at + c] = fr[c];
+            home[4 * at + c] = h[c];
+            double w[QEQ_MAXP], dw[QEQ_MAXP];
+            bspline_weights<double>(fr[c] * (double)S.K[c] - (double)h[c], p, w, dw);
+            for (int k = 0; k < QEQ_MAXP; ++k) {
+                wts[c * QEQ_MAXP + k] = k < p ? (float)w[k] : 0.f;
+                dwts[c * QEQ_MAXP + k] = k < p ? (float)dw[k] : 0.f;
             }
         }
-        __syncthreads();
-        // fixed point -> FP32 complex columns (two rows each), through registers
-        {
-            const float inv = 1.0f / scale;
-            constexpr int PER = K3C ? (K3C * NC + NT - 1) / NT : 1;
-            if constexpr (K3C > 0) {
-                float2 v2[PER];
-#pragma unroll
-                for (int u = 0; u < PER; ++u) {
-                    const int e = tid + u * NT;
-                    if (e < K3C * NC) {
-                        const int g3 = e / NC, pr = e - g3 * NC;
-                        v2[u] = make_float2((float)acc[g3 * RW + 2 * pr] * inv, (float)acc[g3 * RW + 2 * pr + 1] * inv);
-                    }
-                }
-                __syncthreads();
-#pragma unroll
-                for (int u = 0; u < PER; ++u) {
-                    const int e = tid + u * NT;
-                    if (e < K3C * NC) {
-                        const int g3 = e / NC, pr = e - g3 * NC;
-                        buf[g3 * KS + pr] = v2[u];
-                    }
-                }
-            } else {
-                for (int e0 = 0; e0 < K3 * NC; e0 += NT) {
-                    const int e = e0 + tid;
-                    float2 v2 = make_float2(0.f, 0.f);
-                    if (e < K3 * NC) {
-                        const int g3 = e / NC, pr = e - g3 * NC;
-                        v2 = make_float2((float)acc[g3 * RW + 2 * pr] * inv, (float)acc[g3 * RW + 2 * pr + 1] * inv);
-                    }
-                    __syncthreads();
-                    if (e < K3 * NC) buf[(e / NC) * KS + (e - (e / NC) * NC)] = v2;
-                    __syncthreads();
-                }
-            }
-            __syncthreads();
+        const double rsqpi = 0.56418958354775628695;
+        ce = ch + S.bg_pref * Q * sg * sg;
+        slot_vec(a, S, V_CHI)[at] = ce;
+        slot_vec(a, S, V_CHIRAW)[at] = ch;
+        slot_vec(a, S, V_SIG)[at] = sg;
+        slot_vec(a, S, V_J)[at] = jj;
+        slot_vec(a, S, V_DSELF)[at] = rsqpi / sg - 0.79788456080286535588 / a.eta;
+        const double di = 1.0 / (jj + rsqpi / sg);
+        slot_vec(a, S, V_DINV)[at] = di;
+        acc[0] = ce;
+        acc[1] = di;
+        acc[2] = q;
+    }
+    wg_sum<3>(acc);
+    const double chi_sum = acc[0], dinv_sum = acc[1];
+    if (live) slot_vec(a, S, V_Q)[at] = q + (Q - acc[2]) / (double)n;
+    // norm of the projected right-hand side and the two sums of C_eta
+    double v[3] = {0.0, 0.0, 0.0};
+    if (live) {
+        const double d = ce - chi_sum / (double)n;
+        v[0] = d * d;
+    }
+    {
+        const double X = 6.5 * 1.41421356237309504880;
+        const double zeta = S.zeta, eta = a.eta;
+        const double kmax = X / zeta, rmax = X * zeta;
+        const int w1 = 2 * S.mm[0] + 1, w2 = 2 * S.mm[1] + 1, w3 = 2 * S.mm[2] + 1;
+        for (int t = tid; t < w1 * w2 * w3; t += 1024) {
+            const int m3 = t % w3 - S.mm[2], m2 = (t / w3) % w2 - S.mm[1], m1 = t / (w3 * w2) - S.mm[0];
+            if (!m1 && !m2 && !m3) continue;
+            double k[3];
+            for (int c = 0; c < 3; ++c)
+                k[c] = 6.283185307179586477 * (S.Hinv[c * 3 + 0] * m1 + S.Hinv[c * 3 + 1] * m2 + S.Hinv[c * 3 + 2] * m3);
+            const double k2 = k[0] * k[0] + k[1] * k[1] + k[2] * k[2];
+            if (k2 > kmax * kmax) continue;
+            v[1] += exp(-0.5 * zeta * zeta * k2) / k2;
         }
-        bq_lines_fft<K3C, NT, false>(buf, S.ax[2], tw, tid);
-        const int rows = min(D, K1 - g1a) * K2;
-        float2* Cb = sl.C + (size_t)g1a * K2 * K3h;
-        for (int t = tid; t < rows * K3h; t += NT) {
-            const int r = t / K3h, m = t - r * K3h;
-            const int pr = r >> 1;
-            const float2 Z = buf[m * KS + pr];
-            float2 Zc = buf[(m == 0 ? 0 : K3 - m) * KS + pr];
-            Zc.y = -Zc.y;
-            float2 X;
-            if ((r & 1) == 0) {
-                X = make_float2(0.5f * (Z.x + Zc.x), 0.5f * (Z.y + Zc.y));
-            } else {
-                const float2 dz = csub(Z, Zc);
-                X = make_float2(0.5f * dz.y, -0.5f * dz.x);
-            }
-            Cb[t] = X;
+        const int v1 = 2 * S.nn[0] + 1, v2 = 2 * S.nn[1] + 1, v3 = 2 * S.nn[2] + 1;
+        const double s2 = 0.70710678118654752440;
+        for (int t = tid; t < v1 * v2 * v3; t += 1024) {
+            const int n3 = t % v3 - S.nn[2], n2 = (t / v3) % v2 - S.nn[1], n1 = t / (v3 * v2) - S.nn[0];
+            double y[3];
+            for (int c = 0; c < 3; ++c) y[c] = n1 * S.H[0 * 3 + c] + n2 * S.H[1 * 3 + c] + n3 * S.H[2 * 3 + c];
+            const double r = sqrt(y[0] * y[0] + y[1] * y[1] + y[2] * y[2]);
+            if (r > rmax) continue;
+            v[2] += r < 1e-12 ? 0.79788456080286535588 * (1.0 / eta - 1.0 / zeta)
+                              : (erf(r * s2 / eta) - erf(r * s2 / zeta)) / r;
         }
-        __syncthreads();
+    }
+    wg_sum<3>(v);
+    if (tid == 0) {
+        const double pi = 3.14159265358979323846;
+        T.chi_sum = chi_sum;
+        T.dinv_sum = dinv_sum;
+        T.chi_norm = sqrt(v[0]);
+        T.c_eta = v[1] * 4.0 * pi / S.vol + v[2] - 2.0 * pi * (S.zeta * S.zeta - a.eta * a.eta) / S.vol;
+        T.need_init = 1;
+        bq_lap(T, PH_SETUP, t0);
     }
 }
 
-#define BQ_FWD 1
-#define BQ_GREEN 2
-#define BQ_INV 4
-
-// Passes B / C / D: lines of the half spectrum along axis 1 (AX = 1, stride
-// K3h, lines (g1, m3)) or axis 0 (AX = 0, stride K2 K3h, lines (g2, m3)).
-// Consecutive lines are consecutive in memory: batches load and store
-// coalesced rows, and each thread keeps one line of the batch.
-template <int KC, int NT, int AX>
-__device__ void bq_pass_lines(const BStruct& S, const Slot& sl, int mode, float2* buf, const float2* tw, int tid) {
-    constexpr int NC = bq_nc<KC>(), KS = bq_ks<KC>();
-    constexpr int CL = NC == 64 ? 6 : 5;
-    static_assert(NT % NC == 0, "lines per batch must divide the workgroup");
-    const int K2 = S.ax[1].K, K3h = S.ax[2].K / 2 + 1;
-    const int K = KC ? KC : S.ax[AX].K;
-    const size_t kstride = AX == 0 ? (size_t)K2 * K3h : (size_t)K3h;
-    const int nl = AX == 0 ? K2 * K3h : S.ax[0].K * K3h;
-    const int c = tid & (NC - 1);
-    const int k0 = tid >> CL;
-    constexpr int KSTEP = NT / NC;
-    for (int L0 = 0; L0 < nl; L0 += NC) {
-        const int L = L0 + c;
-        const bool live = L < nl;
-        size_t base = 0;
-        if (AX == 0) {
-            base = (size_t)L;
-        } else {
-            const int g1 = L / K3h;
-            base = (size_t)g1 * K2 * K3h + (L - g1 * K3h);
-        }
-        // the line's elements (and its Green's function values) are all
-        // requested before the first LDS store, so the batch costs one memory
-        // round trip instead of one per element
-        constexpr int MAXIT = (BQ_KAX + KSTEP - 1) / KSTEP;
-        float gv[MAXIT];
-        {
-            float2 v[MAXIT];
-#pragma unroll
-            for (int u = 0; u < MAXIT; ++u) {
-                const int k = k0 + u * KSTEP;
-                if (k < K) v[u] = live ? sl.C[base + k * kstride] : make_float2(0.f, 0.f);
-                if (k < K && live && (mode & BQ_GREEN)) gv[u] = sl.G[base + k * kstride];
-            }
-#pragma unroll
-            for (int u = 0; u < MAXIT; ++u) {
-                const int k = k0 + u * KSTEP;
-                if (k < K) buf[k * KS + c] = v[u];
-            }
-        }
-        __syncthreads();
-        if (mode & BQ_FWD) bq_lines_fft<KC, NT, false>(buf, S.ax[AX], tw, tid);
-        if (mode & BQ_GREEN) {
-            if (live) {
-#pragma unroll
-                for (int u = 0; u < MAXIT; ++u) {
-                    const int k = k0 + u * KSTEP;
-                    if (k < K) buf[k * KS + c] = cscale(buf[k * KS + c], gv[u]);
-                }
-            }
-            __syncthreads();
-        }
-        if (mode & BQ_INV) bq_lines_fft<KC, NT, true>(buf, S.ax[AX], tw, tid);
-        if (live)
-            for (int k = k0; k < K; k += KSTEP) sl.C[base + k * kstride] = buf[k * KS + c];
-        __syncthreads();
-    }
-}
-
-// Pass E: complex-to-real along axis 3 into R.  Two rows a, b of half spectra
-// form Z(m) = X_a(m) + i X_b(m) over the full axis (Hermitian extension); the
-// inverse transform returns row a in the real and row b in the imaginary part.
-template <int K3C, int NT>
-__device__ void bq_passE(const BStruct& S, const Slot& sl, float2* buf, const float2* tw, int tid) {
-    constexpr int NC = bq_nc<K3C>(), KS = bq_ks<K3C>();
-    const int K3 = K3C ? K3C : S.ax[2].K;
-    const int K3h = K3 / 2 + 1;
-    const int nrows = S.ax[0].K * S.ax[1].K;
-    const float* bf = reinterpret_cast<const float*>(buf);
-    // both halves' rows are requested before the first LDS store (one memory
-    // round trip per batch of rows)
-    constexpr int EIT = (NC * (BQ_KAX / 2 + 1) + NT - 1) / NT;
-    for (int r0 = 0; r0 < nrows; r0 += 2 * NC) {
-        float2 xv[2][EIT];
-#pragma unroll
-        for (int h = 0; h < 2; ++h)
-#pragma unroll
-            for (int u = 0; u < EIT; ++u) {
-                const int t = tid + u * NT;
-                if (t < NC * K3h) {
-                    const int pr = t / K3h, m = t - pr * K3h;
-                    const int row = r0 + 2 * pr + h;
-                    xv[h][u] = row < nrows ? sl.C[(size_t)row * K3h + m] : make_float2(0.f, 0.f);
-                }
-            }
-#pragma unroll
-        for (int half = 0; half < 2; ++half) {
-#pragma unroll
-            for (int u = 0; u < EIT; ++u) {
-                const int t = tid + u * NT;
-                if (t >= NC * K3h) continue;
-                const int pr = t / K3h, m = t - pr * K3h;
-                float2 X = xv[half][u];
-                float2 Xm = make_float2(X.x, -X.y);     // conj, for K3 - m
-                if (half) {
-                    X = make_float2(-X.y, X.x);          // i X
-                    Xm = make_float2(-Xm.y, Xm.x);       // i conj(X)
-                    buf[m * KS + pr] = cadd(buf[m * KS + pr], X);
-                    if (m > 0 && 2 * m < K3) buf[(K3 - m) * KS + pr] = cadd(buf[(K3 - m) * KS + pr], Xm);
-                } else {
-                    buf[m * KS + pr] = X;
-                    if (m > 0 && 2 * m < K3) buf[(K3 - m) * KS + pr] = Xm;
-                }
-            }
-            __syncthreads();
-        }
-        bq_lines_fft<K3C, NT, true>(buf, S.ax[2], tw, tid);
-        const int rows = min(2 * NC, nrows - r0);
-        float* Rb = sl.R + (size_t)r0 * K3;
-        for (int t = tid; t < rows * K3; t += NT) {
-            const int r = t / K3, g3 = t - r * K3;
-            Rb[t] = bf[2 * (g3 * KS + (r >> 1)) + (r & 1)];
-        }
-        __syncthreads();
-    }
-}
-
-// Dispatch on the axis length (compile-time transforms for the common ones).
-template <int NT>
-__device__ void bq_A(const BStruct& S, const Slot& sl, const double* src, int p, float2* buf, const float2* tw,
-                     const int* hstart, const int* order, int tid) {
-    switch (S.ax[2].K) {
-#define X(KK) case KK: bq_passA<KK, NT>(S, sl, src, p, buf, tw, hstart, order, tid); return;
-        BQ_FOR_EACH_LEN(X)
-#undef X
-        default: bq_passA<0, NT>(S, sl, src, p, buf, tw, hstart, order, tid);
-    }
-}
-
-template <int NT>
-__device__ void bq_E(const BStruct& S, const Slot& sl, float2* buf, const float2* tw, int tid) {
-    switch (S.ax[2].K) {
-#define X(KK) case KK: bq_passE<KK, NT>(S, sl, buf, tw, tid); return;
-        BQ_FOR_EACH_LEN(X)
-#undef X
-        default: bq_passE<0, NT>(S, sl, buf, tw, tid);
-    }
-}
-
-template <int NT, int AX>
-__device__ void bq_L(const BStruct& S, const Slot& sl, int mode, float2* buf, const float2* tw, int tid) {
-    switch (S.ax[AX].K) {
-#define X(KK) case KK: bq_pass_lines<KK, NT, AX>(S, sl, mode, buf, tw, tid); return;
-        BQ_FOR_EACH_LEN(X)
-#undef X
-        default: bq_pass_lines<0, NT, AX>(S, sl, mode, buf, tw, tid);
-    }
-}
-
-// Green's function of the split times the B-spline moduli (SI "Ewald
-// Summation" Gaussian filter, eq. matvec 4 pi / k^2) on the half spectrum
-// (m3 <= K3 / 2): zero at m = 0 and on the Nyquist planes, as in the
-// single-structure path.
-__device__ __forceinline__ float bq_green(const BStruct& S, double eta, int m1, int m2, int m3, const float* b1,
-                                          const float* b2, const float* b3) {
-    const int K1 = S.ax[0].K, K2 = S.ax[1].K, K3 = S.ax[2].K;
-    if ((m1 | m2 | m3) == 0) return 0.f;
-    if (2 * m1 == K1 || 2 * m2 == K2 || 2 * m3 == K3) return 0.f;
-    const double x1 = m1 <= K1 / 2 ? m1 : m1 - K1;
-    const double x2 = m2 <= K2 / 2 ? m2 : m2 - K2;
-    const double x3 = m3;
-    const double q = S.M[0] * x1 * x1 + S.M[1] * x2 * x2 + S.M[2] * x3 * x3 +
-                     2.0 * (S.M[3] * x1 * x2 + S.M[4] * x1 * x3 + S.M[5] * x2 * x3);
-    const double k2 = 39.478417604357434475 * q;   // (2 pi)^2
-    const double g = S.green_pref * exp(-0.5 * eta * eta * k2) / k2;
-    return (float)g * b1[m1] * b2[m2] * b3[m3];
-}
-
-// ------------------------------------------------------------------ pairs
 // Images n of the pair (i, j) with |x_a + n_a| <= rho_a on every axis, where
 // x = s_j - s_i is wrapped to [-1/2, 1/2], and |r_j + n H - r_i| < r_cut.
 // EMIT writes K, (r_i - r_j(image), K'/r) and j at out[0..).
@@ -539,559 +337,765 @@ __device__ __forceinline__ int bq_pair_images(const BStruct& S, const double* si
     return c;
 }
 
-// ------------------------------------------------------------------ matvec
-// Reciprocal potential of the vector src (slot vector), left in sl.R.
-template <int NT>
-__device__ void bq_mesh(const BStruct& S, const Slot& sl, const double* src, int p, float2* buf,
-                        const float2 (*tws)[BQ_KAX], const int* hstart, const int* order, PhaseClock& clk) {
-    const int tid = threadIdx.x;
-    bq_A<NT>(S, sl, src, p, buf, tws[2], hstart, order, tid);
-    if (tid == 0) clk.lap(PH_SPREAD);
-    bq_L<NT, 1>(S, sl, BQ_FWD, buf, tws[1], tid);
-    bq_L<NT, 0>(S, sl, BQ_FWD | BQ_GREEN | BQ_INV, buf, tws[0], tid);
-    bq_L<NT, 1>(S, sl, BQ_INV, buf, tws[1], tid);
-    bq_E<NT>(S, sl, buf, tws[2], tid);
-    if (tid == 0) clk.lap(PH_FFT);
+// Pair list of 32 atoms: count, one reservation of the block's rows in the
+// structure's list, fill (8 lanes per atom, in j order; where a row starts
+// does not matter to any sum).  Past the capacity only the count goes on.
+__global__ __launch_bounds__(256) void k_bq_pairs(BArgs a, const int2* __restrict__ units) {
+    const int2 u = units[blockIdx.x];
+    const BStruct& S = a.st[u.x];
+    BState& T = a.state[u.x];
+    if (T.finished) return;
+    const long long t0 = wall_clock64();
+    const int n = S.n, tid = threadIdx.x;
+    __shared__ double fr[3 * 1024], sgs[1024];
+    __shared__ int cnt[BQ_PAIR_ATOMS];
+    __shared__ long long rowat[BQ_PAIR_ATOMS];
+    const double* frac = slot_ptr<double>(a, S, S.slot.frac);
+    const double* sig = slot_vec(a, S, V_SIG);
+    for (int t = tid; t < 3 * n; t += 256) fr[t] = frac[t];
+    for (int t = tid; t < n; t += 256) sgs[t] = sig[t];
+    __syncthreads();
+    const int l = tid & (BQ_L - 1), r = tid / BQ_L;
+    const int i = u.y * BQ_PAIR_ATOMS + r;
+    double si[3] = {0.0, 0.0, 0.0};
+    int c = 0;
+    if (i < n) {
+        for (int t = 0; t < 3; ++t) si[t] = fr[3 * i + t];
+        for (int j = l; j < n; j += BQ_L)
+            c += bq_pair_images<false>(S, si, fr + 3 * j, i == j, a.rc2, a.eta, 1.0, j, nullptr, nullptr, nullptr, 0, 0);
+    }
+#pragma unroll
+    for (int off = BQ_L / 2; off > 0; off >>= 1) c += __shfl_xor(c, off, 64);
+    if (l == 0) cnt[r] = c;
+    __syncthreads();
+    if (tid == 0) {
+        int tot = 0;
+        for (int t = 0; t < BQ_PAIR_ATOMS; ++t) tot += cnt[t];
+        long long at = (long long)atomicAdd(&T.nnz, (unsigned long long)tot);
+        for (int t = 0; t < BQ_PAIR_ATOMS; ++t) {
+            rowat[t] = at;
+            at += cnt[t];
+        }
+    }
+    __syncthreads();
+    if (i < n) {
+        long long cursor = rowat[r];
+        if (l == 0) {
+            int2* row = slot_ptr<int2>(a, S, S.slot.row);
+            // rows past the capacity are never read (the structure goes again)
+            row[i] = cursor + c <= S.pcap ? make_int2((int)cursor, (int)cursor + c) : make_int2(0, 0);
+        }
+        int* col = slot_ptr<int>(a, S, S.slot.col);
+        float* kval = slot_ptr<float>(a, S, S.slot.kval);
+        float4* pdr = slot_ptr<float4>(a, S, S.slot.pdr);
+        const double sgi = sgs[i];
+        for (int jb = 0; jb < n; jb += BQ_L) {
+            const int j = jb + l;
+            int k = 0;
+            if (j < n)
+                k = bq_pair_images<false>(S, si, fr + 3 * j, i == j, a.rc2, a.eta, 1.0, j, nullptr, nullptr, nullptr, 0,
+                                          0);
+            int incl = k;
+#pragma unroll
+            for (int d = 1; d < BQ_L; d <<= 1) {
+                const int y = __shfl_up(incl, d, BQ_L);
+                if (l >= d) incl += y;
+            }
+            const int total = __shfl(incl, BQ_L - 1, BQ_L);
+            if (k)
+                bq_pair_images<true>(S, si, fr + 3 * j, i == j, a.rc2, a.eta, sqrt(sgi * sgi + sgs[j] * sgs[j]), j, col,
+                                     kval, pdr, cursor + incl - k, S.pcap);
+            cursor += total;
+        }
+    }
+    if (tid == 0) bq_lap(T, PH_PAIRS, t0);
 }
 
-#define BQ_CG 0
-#define BQ_FINAL 2
+// Green's function of the split times the B-spline moduli (SI "Ewald
+// Summation" Gaussian filter, eq. matvec 4 pi / k^2) on the half spectrum
+// (m3 <= K3 / 2): zero at m = 0 and on the Nyquist planes, as in the
+// single-structure path.
+__device__ __forceinline__ float bq_green(const BStruct& S, double eta, int m1, int m2, int m3, const float* b1,
+                                          const float* b2, const float* b3) {
+    const int K1 = S.K[0], K2 = S.K[1], K3 = S.K[2];
+    if ((m1 | m2 | m3) == 0) return 0.f;
+    if (2 * m1 == K1 || 2 * m2 == K2 || 2 * m3 == K3) return 0.f;
+    const double x1 = m1 <= K1 / 2 ? m1 : m1 - K1;
+    const double x2 = m2 <= K2 / 2 ? m2 : m2 - K2;
+    const double x3 = m3;
+    const double q = S.M[0] * x1 * x1 + S.M[1] * x2 * x2 + S.M[2] * x3 * x3 +
+                     2.0 * (S.M[3] * x1 * x2 + S.M[4] * x1 * x3 + S.M[5] * x2 * x3);
+    const double k2 = 39.478417604357434475 * q;   // (2 pi)^2
+    const double g = S.green_pref * exp(-0.5 * eta * eta * k2) / k2;
+    return (float)g * b1[m1] * b2[m2] * b3[m3];
+}
 
-// y = (E + diag J) src (CG) or y = E src with forces and energy sums (FINAL),
-// from the potential in sl.R and the pair list; BQ_L lanes per atom.
-// CG: sums[0] = src.y, sums[1] = sum y.  FINAL: sums = q.Eq, chi.q, J q^2,
-// sigma^2 q, sum g, with g = E q + J q + chi_eff stored in V_G.
-template <int NT, int MODE>
-__device__ void bq_interp(const BStruct& S, const Slot& sl, const double* src, double* dst, int p, int self_corr,
-                          double* sp, double* forces, double* sums) {
-    constexpr bool FIN = MODE == BQ_FINAL;
-    const int tid = threadIdx.x;
-    const int n = S.n, K1 = S.ax[0].K, K2 = S.ax[1].K, K3 = S.ax[2].K;
-    for (int i = tid; i < n; i += NT) sp[i] = src[i];
+__global__ __launch_bounds__(256) void k_bq_green(BArgs a, const int2* __restrict__ units) {
+    const int2 u = units[blockIdx.x];
+    const BStruct& S = a.st[u.x];
+    BState& T = a.state[u.x];
+    if (T.finished) return;
+    const long long t0 = wall_clock64();
+    float* G = slot_ptr<float>(a, S, S.slot.G);
+    const int K2 = S.K[1], K3h = S.K[2] / 2 + 1;
+    const float *b1 = a.bmod + S.bm_off[0], *b2 = a.bmod + S.bm_off[1], *b3 = a.bmod + S.bm_off[2];
+    const int end = min(S.nhalf, (u.y + 1) * BQ_GREEN);
+    for (int t = u.y * BQ_GREEN + threadIdx.x; t < end; t += 256) {
+        const int m3 = t % K3h, r = t / K3h;
+        G[t] = bq_green(S, a.eta, r / K2, r % K2, m3, b1, b2, b3);
+    }
+    if (threadIdx.x == 0) bq_lap(T, PH_MESHPREP, t0);
+}
+
+// ------------------------------------------------------------------ mesh
+// Layout in the slot: half spectrum C[g1][g2][m3], m3 = 0 .. K3/2
+// (contiguous); the Green's function G in the same layout.  Every axis length
+// of the batched path has a compile-time transform.
+#define BQ_FOR_EACH_LEN(X) X(12) X(16) X(20) X(24) X(32) X(36) X(40) X(48) X(60) X(64)
+
+template <bool INV>
+__device__ __forceinline__ void bq_fft_axis2(float2* X2, int K2, const float2* tw, int tid) {
+    switch (K2) {
+#define X(KK) case KK: fft_ct<KK, BQ_NC2, BQ_KS2, BQ_NT, INV>(X2, tw, tid); break;
+        BQ_FOR_EACH_LEN(X)
+#undef X
+    }
+}
+
+template <bool INV>
+__device__ __forceinline__ void bq_fft_lines(float2* buf, int K, const float2* tw, int tid) {
+    switch (K) {
+#define X(KK) case KK: fft_ct<KK, BQ_NC, BQ_KS, BQ_NT, INV>(buf, tw, tid); break;
+        BQ_FOR_EACH_LEN(X)
+#undef X
+    }
+}
+
+// The atoms that reach each of a block's planes: those with home planes g1 ..
+// g1 + p - 1, one (wrapped) index range per plane.  first / cnt in LDS, off =
+// their running total.
+__device__ __forceinline__ void bq_ranges(const int* hs, int K1, int n, int p, int g1a, int planes, int tid, int* first,
+                                          int* off) {
+    if (tid < planes) {
+        const int g = g1a + tid, e = g + p;
+        first[tid] = hs[g];
+        off[tid + 1] = e <= K1 ? hs[e] - hs[g] : n - hs[g] + hs[e - K1];
+    }
     __syncthreads();
-    double acc[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
+    if (tid == 0) {
+        off[0] = 0;
+        for (int j = 0; j < planes; ++j) off[j + 1] += off[j];
+    }
+    __syncthreads();
+}
+
+// Spread, real-to-complex along axis 3 and axis 2 forward of a block's planes.
+// The spread accumulates in 64-bit fixed point with integer LDS atomics (exact,
+// order-independent; FP32 LDS atomics are several times slower on gfx950),
+// scaled per block so that no sum can overflow: a grid value is a sum over the
+// block's candidate atoms of src times a weight product <= 1, each candidate at
+// most once, so |value| <= sum |src| < 2^e and the scale is 2^(50 - e); each
+// term is rounded to an integer by one FP64 fused multiply-add with 1.5 * 2^52
+// (its bit pattern minus the constant's is the integer, exact below 2^51).
+// Planes of a block: as many as fill 128 real rows (64 complex lines of two)
+// and 66 half-spectrum columns; its barriers then pass with two to five planes'
+// work behind them and two blocks share a CU.
+__global__ __launch_bounds__(BQ_NT) void k_bq_fwd(BArgs a, const int2* __restrict__ units, int mode) {
+    extern __shared__ float2 lds[];
+    const int2 u = units[blockIdx.x];
+    if (u.x < 0) return;
+    const BStruct& S = a.st[u.x];
+    BState& T = a.state[u.x];
+    if (!bq_active(T, mode)) return;
+    long long t0 = wall_clock64();
+    __shared__ float2 tw3[BQ_KAX], tw2[BQ_KAX];
+    __shared__ int first[BQ_PB], off[BQ_PB + 1];
+    const int tid = threadIdx.x, n = S.n, p = a.p;
+    const int K1 = S.K[0], K2 = S.K[1], K3 = S.K[2], K3h = K3 / 2 + 1;
+    const int g1a = u.y * S.pb, planes = min(S.pb, K1 - g1a);
+    const int RW = S.pb * K2;                                // accumulator rows
+    long long* acc = reinterpret_cast<long long*>(lds);      // [K3][RW]
+    unsigned long long* acc_u = reinterpret_cast<unsigned long long*>(lds);
+    float2* buf = lds;                                       // [K3][BQ_KS], in its place
+    float2* X2 = lds + K3 * BQ_KS;                           // [K2][BQ_KS2]
+    const double* src = slot_vec(a, S, mode == BQ_ITER ? V_P : V_Q);
+    const int* home = slot_ptr<int>(a, S, S.slot.home);
+    const float* wts = slot_ptr<float>(a, S, S.slot.wts);
+    const int* hs = slot_ptr<int>(a, S, S.slot.hstart);
+    if (tid < K3) tw3[tid] = a.tw[S.tw_off[2] + tid];
+    if (tid >= BQ_KAX && tid - BQ_KAX < K2) tw2[tid - BQ_KAX] = a.tw[S.tw_off[1] + tid - BQ_KAX];
+    for (int t = tid; t < K3 * RW / 2; t += BQ_NT) reinterpret_cast<int4*>(acc)[t] = make_int4(0, 0, 0, 0);
+    // all candidates of the block: home planes g1a .. g1a + planes + p - 2
+    const int e = g1a + planes + p - 1;
+    const int c0 = hs[g1a], ncand = e <= K1 ? hs[e] - c0 : n - c0 + hs[e - K1];
+    bq_ranges(hs, K1, n, p, g1a, planes, tid, first, off);
+    double v[1] = {0.0};
+    for (int c = tid; c < ncand; c += BQ_NT) {
+        const int i = c0 + c;
+        v[0] += fabs(src[i < n ? i : i - n]);
+    }
+    wg_sum<1>(v);   // its barriers also order the clears above
+    int ex = 0;
+    (void)frexp(v[0] > 0.0 ? v[0] : 1.0, &ex);
+    const float scale = ldexpf(1.0f, max(-126, min(126, 50 - ex)));
+    constexpr double RND = 6755399441055744.0;   // 1.5 * 2^52
+    const int k2 = tid & (BQ_L - 1);
+    if (k2 < p) {
+        const int items = off[planes];
+        for (int t = tid / BQ_L; t < items; t += BQ_NT / BQ_L) {
+            int j = 0;
+            while (t >= off[j + 1]) ++j;
+            int i = first[j] + (t - off[j]);
+            if (i >= n) i -= n;
+            const int4 hm = *reinterpret_cast<const int4*>(home + 4 * i);
+            int k1 = hm.x - (g1a + j);
+            if (k1 < 0) k1 += K1;
+            int g2 = hm.y - k2;
+            if (g2 < 0) g2 += K2;
+            const float* w = wts + (size_t)i * 3 * QEQ_MAXP;
+            const float a0 = (float)src[i] * w[k1] * w[QEQ_MAXP + k2] * scale;
+            const float4 wa = *reinterpret_cast<const float4*>(w + 2 * QEQ_MAXP);
+            const float4 wb = *reinterpret_cast<const float4*>(w + 2 * QEQ_MAXP + 4);
+            const float w3[8] = {wa.x, wa.y, wa.z, wa.w, wb.x, wb.y, wb.z, wb.w};
+            const int r = j * K2 + g2;
+#pragma unroll
+            for (int k3 = 0; k3 < QEQ_MAXP; ++k3) {
+                if (k3 >= p) break;
+                int g3 = hm.z - k3;
+                if (g3 < 0) g3 += K3;
+                const long long b = __double_as_longlong(fma((double)a0, (double)w3[k3], RND));
+                const unsigned hi = (unsigned)(b >> 32) - 0x43380000u;
+                atomicAdd(acc_u + g3 * RW + r, ((unsigned long long)hi << 32) | (unsigned)b);
+            }
+        }
+    }
+    __syncthreads();
+    if (tid == 0) t0 = bq_lap(T, PH_SPREAD, t0);
+    // fixed point -> FP32 complex lines (rows 2 c and 2 c + 1), through registers
+    {
+        const float inv = 1.0f / scale;
+        constexpr int PER = (BQ_KAX * BQ_NC + BQ_NT - 1) / BQ_NT;
+        const int half = RW >> 1;
+        float2 z[PER];
+#pragma unroll
+        for (int q = 0; q < PER; ++q) {
+            const int t = tid + q * BQ_NT, g3 = t / BQ_NC, c = t % BQ_NC;
+            z[q] = make_float2(0.f, 0.f);
+            if (g3 < K3 && c < half)
+                z[q] = make_float2((float)acc[g3 * RW + 2 * c] * inv, (float)acc[g3 * RW + 2 * c + 1] * inv);
+        }
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < PER; ++q) {
+            const int t = tid + q * BQ_NT, g3 = t / BQ_NC, c = t % BQ_NC;
+            if (g3 < K3) buf[g3 * BQ_KS + c] = z[q];
+        }
+        __syncthreads();
+    }
+    bq_fft_lines<false>(buf, K3, tw3, tid);
+    // the two rows' half spectra: X2[g2][j K3h + m3]
+    const int rows = planes * K2;
+    for (int t = tid; t < rows * K3h; t += BQ_NT) {
+        const int m = t / rows, r = t - m * rows;   // consecutive lanes: consecutive rows
+        const int c = r >> 1, j = r / K2, g2 = r - j * K2;
+        const float2 Z = buf[m * BQ_KS + c];
+        float2 Zc = buf[(m == 0 ? 0 : K3 - m) * BQ_KS + c];
+        Zc.y = -Zc.y;
+        const float2 d = csub(Z, Zc);
+        const float2 ev = make_float2(0.5f * (Z.x + Zc.x), 0.5f * (Z.y + Zc.y));
+        const float2 od = make_float2(0.5f * d.y, -0.5f * d.x);
+        X2[g2 * BQ_KS2 + j * K3h + m] = (r & 1) ? od : ev;
+    }
+    __syncthreads();
+    bq_fft_axis2<false>(X2, K2, tw2, tid);
+    float2* C = slot_ptr<float2>(a, S, S.slot.C) + (size_t)g1a * K2 * K3h;
+    for (int t = tid; t < rows * K3h; t += BQ_NT) {
+        const int r = t / K3h, m = t - r * K3h;
+        const int j = r / K2, g2 = r - j * K2;
+        C[t] = X2[g2 * BQ_KS2 + j * K3h + m];
+    }
+    if (tid == 0) bq_lap(T, PH_FFT, t0);
+}
+
+// 64 lines (g2, m3) along axis 1: forward, times G, inverse, in place; with
+// THETA the inverse of G alone (the mesh kernel around the origin).  A line's
+// elements and Green's function values are requested before the first LDS
+// store, so a block costs one memory round trip.
+template <bool THETA>
+__global__ __launch_bounds__(BQ_NT) void k_bq_cols(BArgs a, const int2* __restrict__ units, int mode) {
+    extern __shared__ float2 lds[];
+    const int2 u = units[blockIdx.x];
+    if (u.x < 0) return;
+    const BStruct& S = a.st[u.x];
+    BState& T = a.state[u.x];
+    if (!bq_active(T, mode)) return;
+    const long long t0 = wall_clock64();
+    __shared__ float2 tw1[BQ_KAX];
+    const int tid = threadIdx.x;
+    const int K1 = S.K[0], K2 = S.K[1], K3h = S.K[2] / 2 + 1;
+    const int nl = K2 * K3h;
+    const int c = tid % BQ_NC, k0 = tid / BQ_NC;
+    const int L = u.y * BQ_NC + c;
+    const bool live = L < nl;
+    constexpr int KSTEP = BQ_NT / BQ_NC, MAXIT = BQ_KAX / KSTEP;
+    float2* C = slot_ptr<float2>(a, S, S.slot.C);
+    const float* G = slot_ptr<float>(a, S, S.slot.G);
+    if (tid < K1) tw1[tid] = a.tw[S.tw_off[0] + tid];
+    float gv[MAXIT];
+    float2 v[MAXIT];
+#pragma unroll
+    for (int q = 0; q < MAXIT; ++q) {
+        const int k = k0 + q * KSTEP;
+        gv[q] = 0.f;
+        v[q] = make_float2(0.f, 0.f);
+        if (k < K1 && live) {
+            gv[q] = G[(size_t)k * nl + L];
+            if (!THETA) v[q] = C[(size_t)k * nl + L];
+        }
+    }
+#pragma unroll
+    for (int q = 0; q < MAXIT; ++q) {
+        const int k = k0 + q * KSTEP;
+        if (k < K1) lds[k * BQ_KS + c] = THETA ? make_float2(gv[q], 0.f) : v[q];
+    }
+    __syncthreads();
+    if (!THETA) {
+        bq_fft_lines<false>(lds, K1, tw1, tid);
+#pragma unroll
+        for (int q = 0; q < MAXIT; ++q) {
+            const int k = k0 + q * KSTEP;
+            if (k < K1) lds[k * BQ_KS + c] = cscale(lds[k * BQ_KS + c], gv[q]);
+        }
+        __syncthreads();
+    }
+    bq_fft_lines<true>(lds, K1, tw1, tid);
+    if (live)
+        for (int k = k0; k < K1; k += KSTEP) C[(size_t)k * nl + L] = lds[k * BQ_KS + c];
+    if (tid == 0) bq_lap(T, THETA ? PH_MESHPREP : PH_FFT, t0);
+}
+
+// Axis 2 and axis 3 inverse of `planes` planes from g1a: the potential of row
+// r = j K2 + g2 at g3 is bf[2 (g3 BQ_KS + (r >> 1)) + (r & 1)].  Two rows a, b
+// of half spectra form Z(m) = X_a(m) + i X_b(m) over the full axis (Hermitian
+// extension); the inverse transform returns row a in the real and row b in the
+// imaginary part.  buf [K3][BQ_KS], then X2 [K2][BQ_KS2].
+__device__ __forceinline__ void bq_planes_inv(const BArgs& a, const BStruct& S, int g1a, int planes, float2* buf,
+                                              const float2* tw2, const float2* tw3, int tid) {
+    const int K2 = S.K[1], K3 = S.K[2], K3h = K3 / 2 + 1;
+    float2* X2 = buf + K3 * BQ_KS;
+    const float2* C = slot_ptr<float2>(a, S, S.slot.C) + (size_t)g1a * K2 * K3h;
+    const int rows = planes * K2;
+    constexpr int PER = (BQ_KAX * BQ_NC2 + BQ_NT - 1) / BQ_NT;
+    float2 v[PER];
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
+        const int t = tid + q * BQ_NT;
+        if (t < rows * K3h) v[q] = C[t];
+    }
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
+        const int t = tid + q * BQ_NT;
+        if (t < rows * K3h) {
+            const int r = t / K3h, m = t - r * K3h;
+            const int j = r / K2, g2 = r - j * K2;
+            X2[g2 * BQ_KS2 + j * K3h + m] = v[q];
+        }
+    }
+    __syncthreads();
+    bq_fft_axis2<true>(X2, K2, tw2, tid);
+    const int half = rows >> 1;
+    for (int t = tid; t < K3h * half; t += BQ_NT) {
+        const int m = t / half, c = t - m * half;
+        const int r = 2 * c, j = r / K2, g2 = r - j * K2;
+        const float2 xa = X2[g2 * BQ_KS2 + j * K3h + m], xb = X2[(g2 + 1) * BQ_KS2 + j * K3h + m];
+        buf[m * BQ_KS + c] = make_float2(xa.x - xb.y, xa.y + xb.x);
+        if (m > 0 && 2 * m < K3) buf[(K3 - m) * BQ_KS + c] = make_float2(xa.x + xb.y, xb.x - xa.y);
+    }
+    __syncthreads();
+    bq_fft_lines<true>(buf, K3, tw3, tid);
+}
+
+// Inverse transforms of a block's planes and, from LDS, the part of every
+// atom's interpolation that lies on them: mpart[k1][i] for the plane h1 - k1
+// (eq. matvec: the integral of the potential over the atom's distribution).
+// With FIN also the three derivative sums, mpart[8 (1 + c) + k1][i].  Eight
+// lanes per (atom, plane), one axis-2 row each.
+template <bool FIN>
+__global__ __launch_bounds__(BQ_NT) void k_bq_inv(BArgs a, const int2* __restrict__ units, int mode) {
+    extern __shared__ float2 lds[];
+    const int2 u = units[blockIdx.x];
+    if (u.x < 0) return;
+    const BStruct& S = a.st[u.x];
+    BState& T = a.state[u.x];
+    if (!bq_active(T, mode)) return;
+    long long t0 = wall_clock64();
+    __shared__ float2 tw3[BQ_KAX], tw2[BQ_KAX];
+    __shared__ int first[BQ_PB], off[BQ_PB + 1];
+    const int tid = threadIdx.x, n = S.n, p = a.p;
+    const int K1 = S.K[0], K2 = S.K[1], K3 = S.K[2];
+    const int g1a = u.y * S.pb, planes = min(S.pb, K1 - g1a);
+    if (tid < K3) tw3[tid] = a.tw[S.tw_off[2] + tid];
+    if (tid >= BQ_KAX && tid - BQ_KAX < K2) tw2[tid - BQ_KAX] = a.tw[S.tw_off[1] + tid - BQ_KAX];
+    bq_ranges(slot_ptr<int>(a, S, S.slot.hstart), K1, n, p, g1a, planes, tid, first, off);
+    bq_planes_inv(a, S, g1a, planes, lds, tw2, tw3, tid);
+    if (tid == 0) t0 = bq_lap(T, PH_FFT, t0);
+    const float* bf = reinterpret_cast<const float*>(lds);
+    const int* home = slot_ptr<int>(a, S, S.slot.home);
+    const float* wts = slot_ptr<float>(a, S, S.slot.wts);
+    const float* dwts = slot_ptr<float>(a, S, S.slot.dwts);
+    float* mpart = slot_ptr<float>(a, S, S.slot.mpart);
+    const int k2 = tid & (BQ_L - 1);
+    const int items = off[planes];
+    const int rounds = (items + BQ_NT / BQ_L - 1) / (BQ_NT / BQ_L);
+    for (int rd = 0; rd < rounds; ++rd) {
+        const int t = rd * (BQ_NT / BQ_L) + tid / BQ_L;
+        const bool live = t < items;
+        float s = 0.f, s2 = 0.f, s3 = 0.f, w1 = 0.f, dw1 = 0.f;
+        int i = 0, k1 = 0;
+        if (live) {
+            int j = 0;
+            while (t >= off[j + 1]) ++j;
+            i = first[j] + (t - off[j]);
+            if (i >= n) i -= n;
+            const int4 hm = *reinterpret_cast<const int4*>(home + 4 * i);
+            k1 = hm.x - (g1a + j);
+            if (k1 < 0) k1 += K1;
+            const float* w = wts + (size_t)i * 3 * QEQ_MAXP;
+            const float* dw = dwts + (size_t)i * 3 * QEQ_MAXP;
+            w1 = w[k1];
+            if (FIN) dw1 = dw[k1];
+            if (k2 < p) {
+                int g2 = hm.y - k2;
+                if (g2 < 0) g2 += K2;
+                const int r = j * K2 + g2;
+                const float* row = bf + 2 * (r >> 1) + (r & 1);
+                float x = 0.f, x3 = 0.f;
+#pragma unroll
+                for (int k3 = 0; k3 < QEQ_MAXP; ++k3) {
+                    if (k3 >= p) break;
+                    int g3 = hm.z - k3;
+                    if (g3 < 0) g3 += K3;
+                    const float g = row[2 * g3 * BQ_KS];
+                    x += w[2 * QEQ_MAXP + k3] * g;
+                    if (FIN) x3 += dw[2 * QEQ_MAXP + k3] * g;
+                }
+                s = w[QEQ_MAXP + k2] * x;
+                if (FIN) {
+                    s2 = dw[QEQ_MAXP + k2] * x;
+                    s3 = w[QEQ_MAXP + k2] * x3;
+                }
+            }
+        }
+#pragma unroll
+        for (int d = BQ_L / 2; d > 0; d >>= 1) {
+            s += __shfl_xor(s, d, 64);
+            if (FIN) {
+                s2 += __shfl_xor(s2, d, 64);
+                s3 += __shfl_xor(s3, d, 64);
+            }
+        }
+        if (live && k2 == 0) {
+            mpart[(size_t)k1 * n + i] = w1 * s;
+            if (FIN) {
+                mpart[(size_t)(QEQ_MAXP + k1) * n + i] = dw1 * s;
+                mpart[(size_t)(2 * QEQ_MAXP + k1) * n + i] = w1 * s2;
+                mpart[(size_t)(3 * QEQ_MAXP + k1) * n + i] = w1 * s3;
+            }
+        }
+    }
+    if (tid == 0) bq_lap(T, PH_INTERP, t0);
+}
+
+// One plane d1 = -(p-1) .. p-1 of the mesh kernel Theta around the origin, for
+// the self-correction.
+__global__ __launch_bounds__(BQ_NT) void k_bq_theta(BArgs a, const int2* __restrict__ units) {
+    extern __shared__ float2 lds[];
+    const int2 u = units[blockIdx.x];
+    const BStruct& S = a.st[u.x];
+    BState& T = a.state[u.x];
+    if (T.finished) return;
+    const long long t0 = wall_clock64();
+    __shared__ float2 tw3[BQ_KAX], tw2[BQ_KAX];
+    const int tid = threadIdx.x, p = a.p, np = 2 * p - 1;
+    const int K1 = S.K[0], K2 = S.K[1], K3 = S.K[2];
+    const int d1 = u.y - (p - 1);
+    if (tid < K3) tw3[tid] = a.tw[S.tw_off[2] + tid];
+    if (tid >= BQ_KAX && tid - BQ_KAX < K2) tw2[tid - BQ_KAX] = a.tw[S.tw_off[1] + tid - BQ_KAX];
+    __syncthreads();
+    bq_planes_inv(a, S, d1 < 0 ? d1 + K1 : d1, 1, lds, tw2, tw3, tid);
+    const float* bf = reinterpret_cast<const float*>(lds);
+    double* tab = slot_ptr<double>(a, S, S.slot.tab) + (size_t)u.y * np * np;
+    for (int t = tid; t < np * np; t += BQ_NT) {
+        const int d3 = t % np - (p - 1), d2 = t / np - (p - 1);
+        const int g2 = d2 < 0 ? d2 + K2 : d2, g3 = d3 < 0 ? d3 + K3 : d3;
+        tab[t] = (double)bf[2 * (g3 * BQ_KS + (g2 >> 1)) + (g2 & 1)];
+    }
+    if (tid == 0) bq_lap(T, PH_MESHPREP, t0);
+}
+
+// Mesh self-correction of 64 atoms.
+template <int PC>
+__global__ __launch_bounds__(64) void k_bq_self(BArgs a, const int2* __restrict__ units) {
+    const int2 u = units[blockIdx.x];
+    const BStruct& S = a.st[u.x];
+    BState& T = a.state[u.x];
+    if (T.finished) return;
+    const long long t0 = wall_clock64();
+    const int i = u.y * 64 + threadIdx.x;
+    if (i < S.n) {
+        const double* frac = slot_ptr<double>(a, S, S.slot.frac);
+        const double x[3] = {frac[3 * i] * S.K[0], frac[3 * i + 1] * S.K[1], frac[3 * i + 2] * S.K[2]};
+        double v, g[3];
+        mesh_self_term<PC>(x, a.p, slot_ptr<double>(a, S, S.slot.tab), &v, g);
+        slot_vec(a, S, V_DSELF)[i] += T.c_eta - v;
+        double* sg = slot_ptr<double>(a, S, S.slot.selfgrad);
+        for (int c = 0; c < 3; ++c) sg[3 * i + c] = g[c];
+    }
+    if (threadIdx.x == 0) bq_lap(T, PH_MESHPREP, t0);
+}
+
+// ------------------------------------------------------------------ CG step
+// One block per structure, one thread per atom in the vector part: the atom's
+// interpolation partials and pair row (eight lanes per atom), the sums of the
+// product, and the CG step that follows it: residual and first direction
+// (BQ_INIT), update and next direction (BQ_ITER), energies, mu, true residual,
+// forces and the restart decision (BQ_FINAL).
+template <int MODE>
+__global__ __launch_bounds__(1024) void k_bq_step(BArgs a, const int* __restrict__ order) {
+    constexpr bool FIN = MODE == BQ_FINAL;
+    const int s = order[blockIdx.x];
+    const BStruct& S = a.st[s];
+    BState& T = a.state[s];
+    if (!bq_active(T, MODE)) return;
+    long long t0 = wall_clock64();
+    __shared__ double sp[1024], yv[1024];
+    const int tid = threadIdx.x, n = S.n, p = a.p;
+    const double Q = S.q_tot;
+    if (MODE == BQ_INIT && (long long)T.nnz > S.pcap) {   // uniform
+        if (tid == 0) {
+            T.status = BQ_OVERFLOW;
+            T.finished = 1;
+            atomicSub(&a.count->running, 1);
+        }
+        return;
+    }
+    const bool live = tid < n;
+    double* qv = slot_vec(a, S, V_Q);
+    double* rv = slot_vec(a, S, V_R);
+    double* pv = slot_vec(a, S, V_P);
+    const double* src = MODE == BQ_ITER ? pv : qv;
+    double vi = 0.0, Ji = 0.0, dsi = 0.0, chi = 0.0, dinv = 0.0, ri = 0.0, qi = 0.0;
+    if (live) {
+        vi = src[tid];
+        Ji = slot_vec(a, S, V_J)[tid];
+        dsi = slot_vec(a, S, V_DSELF)[tid];
+        dinv = slot_vec(a, S, V_DINV)[tid];
+        if (MODE != BQ_ITER) chi = slot_vec(a, S, V_CHI)[tid];
+        if (MODE == BQ_ITER) {
+            ri = rv[tid];
+            qi = qv[tid];
+        }
+        sp[tid] = vi;
+    }
+    __syncthreads();
+    const float* mpart = slot_ptr<float>(a, S, S.slot.mpart);
+    const int2* rows = slot_ptr<int2>(a, S, S.slot.row);
+    const int* col = slot_ptr<int>(a, S, S.slot.col);
+    const float* kval = slot_ptr<float>(a, S, S.slot.kval);
+    const float4* pdr = slot_ptr<float4>(a, S, S.slot.pdr);
     const int l = tid & (BQ_L - 1);
-    const double* J = sl.vec(V_J);
-    const double* dself = sl.vec(V_DSELF);
-    for (int ib = 0; ib < n; ib += NT / BQ_L) {
+    for (int ib = 0; ib < n; ib += 1024 / BQ_L) {
         const int i = ib + tid / BQ_L;
         double v[7] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
         if (i < n) {
+            const int2 row = rows[i];
             if (l < p) {
-                const int k1 = l;
-                const int h1 = sl.home[4 * i], h2 = sl.home[4 * i + 1], h3 = sl.home[4 * i + 2];
-                const float* w = sl.wts + (size_t)i * 3 * QEQ_MAXP;
-                const float* dw = sl.dwts + (size_t)i * 3 * QEQ_MAXP;
-                int g1 = h1 - k1;
-                if (g1 < 0) g1 += K1;
-                float s = 0.f, s1 = 0.f, s2 = 0.f, s3 = 0.f;
-                for (int k2 = 0; k2 < p; ++k2) {
-                    int g2 = h2 - k2;
-                    if (g2 < 0) g2 += K2;
-                    const float* row = sl.R + ((size_t)g1 * K2 + g2) * K3;
-                    float t = 0.f, t3 = 0.f;
-                    for (int k3 = 0; k3 < p; ++k3) {
-                        int g3 = h3 - k3;
-                        if (g3 < 0) g3 += K3;
-                        const float gv = row[g3];
-                        t += w[2 * QEQ_MAXP + k3] * gv;
-                        if (FIN) t3 += dw[2 * QEQ_MAXP + k3] * gv;
-                    }
-                    s += w[QEQ_MAXP + k2] * t;
-                    if (FIN) {
-                        s2 += dw[QEQ_MAXP + k2] * t;
-                        s3 += w[QEQ_MAXP + k2] * t3;
-                    }
-                }
-                v[0] = (double)(w[k1] * s);
-                if (FIN) {
-                    s1 = dw[k1] * s;
-                    v[1] = (double)s1;
-                    v[2] = (double)(w[k1] * s2);
-                    v[3] = (double)(w[k1] * s3);
-                }
+                v[0] = (double)mpart[(size_t)l * n + i];
+                if (FIN)
+                    for (int c = 1; c < 4; ++c) v[c] = (double)mpart[(size_t)(c * QEQ_MAXP + l) * n + i];
             }
-            const int e1 = sl.rowptr[i + 1];
-            for (int e = sl.rowptr[i] + l; e < e1; e += BQ_L) {
-                const double vj = sp[sl.col[e]];
-                v[0] += (double)sl.kval[e] * vj;
-                if (FIN) {
-                    const float4 d = sl.pdr[e];
-                    const double c = (double)d.w * vj;
-                    v[4] += c * d.x;
-                    v[5] += c * d.y;
-                    v[6] += c * d.z;
+            for (int e0 = row.x + l; e0 < row.y; e0 += 4 * BQ_L) {
+                int cj[4];
+                float kv[4];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const int e = e0 + q * BQ_L;
+                    cj[q] = e < row.y ? col[e] : 0;
+                    kv[q] = e < row.y ? kval[e] : 0.f;
+                }
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const double vj = sp[cj[q]];
+                    v[0] += (double)kv[q] * vj;
+                    if (FIN && e0 + q * BQ_L < row.y) {
+                        const float4 d = pdr[e0 + q * BQ_L];
+                        const double c = (double)d.w * vj;
+                        v[4] += c * d.x;
+                        v[5] += c * d.y;
+                        v[6] += c * d.z;
+                    }
                 }
             }
         }
-        // reduce over the BQ_L lanes of the atom
 #pragma unroll
         for (int t = 0; t < (FIN ? 7 : 1); ++t) {
 #pragma unroll
-            for (int off = BQ_L / 2; off > 0; off >>= 1) v[t] += __shfl_xor(v[t], off, 64);
+            for (int d = BQ_L / 2; d > 0; d >>= 1) v[t] += __shfl_xor(v[t], d, 64);
         }
         if (i < n && l == 0) {
-            const double vi = sp[i];
-            double y = v[0] + dself[i] * vi;
-            if (MODE == BQ_CG) {
-                y += J[i] * vi;
-                acc[0] += vi * y;
-                acc[1] += y;
-            }
-            dst[i] = y;
-            if (FIN) {
+            yv[i] = v[0];
+            if (FIN && a.forces) {
+                const double xi = sp[i];
                 double du[3] = {v[1], v[2], v[3]};
-                if (self_corr) {
-                    for (int a = 0; a < 3; ++a) du[a] -= 0.5 * vi * sl.selfgrad[3 * i + a];
+                if (a.self_corr) {
+                    const double* sg = slot_ptr<double>(a, S, S.slot.selfgrad);
+                    for (int c = 0; c < 3; ++c) du[c] -= 0.5 * xi * sg[3 * i + c];
                 }
-                const double Kd[3] = {(double)K1, (double)K2, (double)K3};
-                if (forces) {
-                    for (int c = 0; c < 3; ++c) {
-                        double g = 0.0;
-                        for (int a = 0; a < 3; ++a) g += Kd[a] * S.Hinv[c * 3 + a] * du[a];
-                        forces[3 * i + c] = -vi * g - vi * v[4 + c];
-                    }
-                }
-                const double Ji = J[i];
-                const double gi = y + Ji * vi + sl.vec(V_CHI)[i];
-                sl.vec(V_G)[i] = gi;
-                const double sg = sl.vec(V_SIG)[i];
-                acc[0] += vi * y;
-                acc[1] += sl.vec(V_CHIRAW)[i] * vi;
-                acc[2] += Ji * vi * vi;
-                acc[3] += sg * sg * vi;
-                acc[4] += gi;
-            }
-        }
-    }
-    wg_sum<5>(acc);
-    for (int t = 0; t < 5; ++t) sums[t] = acc[t];
-}
-
-// ------------------------------------------------------------------ one structure
-template <int NT>
-__device__ void bq_solve(const BArgs& a, const BStruct& S, int s, const Slot& sl, float2* buf, double* sp,
-                         const float2 (*tws)[BQ_KAX], const float (*bms)[BQ_KAX], int* hcnt, int* hstart,
-                         int* order) {
-    const int tid = threadIdx.x;
-    const int n = S.n, p = a.p;
-    const int K1 = S.ax[0].K, K2 = S.ax[1].K, K3 = S.ax[2].K;
-    const double Q = S.q_tot;
-    __shared__ int err;
-    PhaseClock clk;
-    if (tid == 0) {
-        err = 0;
-        clk.start();
-    }
-    __syncthreads();
-
-    // --- staging: validation, fractional coordinates, spline weights, diagonal
-    double acc[2] = {0.0, 0.0};
-    for (int i = tid; i < n; i += NT) {
-        const int o = S.off + i;
-        const double x[3] = {a.pos[3 * o], a.pos[3 * o + 1], a.pos[3 * o + 2]};
-        const double sg = a.sigma[o], jj = a.J[o], ch = a.chi[o];
-        const bool ok = isfinite(x[0]) && isfinite(x[1]) && isfinite(x[2]) && isfinite(ch) && sg > 0.0 &&
-                        jj > 0.0 && isfinite(sg) && isfinite(jj);
-        if (!ok) atomicOr(&err, 1);
-        const int Kd[3] = {K1, K2, K3};
-        for (int ax = 0; ax < 3; ++ax) {
-            double v = x[0] * S.Hinv[0 * 3 + ax] + x[1] * S.Hinv[1 * 3 + ax] + x[2] * S.Hinv[2 * 3 + ax];
-            v -= floor(v);
-            if (!(v >= 0.0 && v < 1.0)) v = 0.0;
-            sl.frac[3 * i + ax] = v;
-            const double u = v * (double)Kd[ax];
-            int h = (int)floor(u);
-            h = h < 0 ? 0 : (h >= Kd[ax] ? Kd[ax] - 1 : h);
-            double c[QEQ_MAXP], dc[QEQ_MAXP];
-            bspline_weights<double>(u - (double)h, p, c, dc);
-            for (int k = 0; k < QEQ_MAXP; ++k) {
-                sl.wts[(i * 3 + ax) * QEQ_MAXP + k] = k < p ? (float)c[k] : 0.f;
-                sl.dwts[(i * 3 + ax) * QEQ_MAXP + k] = k < p ? (float)dc[k] : 0.f;
-            }
-            sl.home[4 * i + ax] = h;
-        }
-        const double rsqpi = 0.56418958354775628695;
-        const double ce = ch + S.bg_pref * Q * sg * sg;
-        sl.vec(V_CHI)[i] = ce;
-        sl.vec(V_CHIRAW)[i] = ch;
-        sl.vec(V_SIG)[i] = sg;
-        sl.vec(V_J)[i] = jj;
-        sl.vec(V_DSELF)[i] = rsqpi / sg - 0.79788456080286535588 / a.eta;
-        const double di = 1.0 / (jj + rsqpi / sg);
-        sl.vec(V_DINV)[i] = di;
-        acc[0] += ce;
-        acc[1] += di;
-    }
-    wg_sum<2>(acc);
-    const double chi_sum = acc[0], dinv_sum = acc[1];
-    double nv[1] = {0.0};
-    for (int i = tid; i < n; i += NT) {
-        const double d = sl.vec(V_CHI)[i] - chi_sum / (double)n;
-        nv[0] += d * d;
-    }
-    wg_sum<1>(nv);
-    const double chi_norm = sqrt(nv[0]);
-
-    // --- C_eta = (4 pi / V) sum_{k != 0} exp(-eta^2 k^2 / 2) / k^2 by a second
-    // split of width zeta: k-space sum with zeta plus the lattice sum of the
-    // difference kernel, minus 2 pi (zeta^2 - eta^2) / V
-    double ce_acc[2] = {0.0, 0.0};
-    {
-        const double X = 6.5 * 1.41421356237309504880;
-        const double zeta = S.zeta, eta = a.eta;
-        const double kmax = X / zeta, rmax = X * zeta;
-        const int w1 = 2 * S.mm[0] + 1, w2 = 2 * S.mm[1] + 1, w3 = 2 * S.mm[2] + 1;
-        const int nk = w1 * w2 * w3;
-        for (int t = tid; t < nk; t += NT) {
-            const int m3 = t % w3 - S.mm[2], m2 = (t / w3) % w2 - S.mm[1], m1 = t / (w3 * w2) - S.mm[0];
-            if (!m1 && !m2 && !m3) continue;
-            double k[3];
-            for (int c = 0; c < 3; ++c)
-                k[c] = 6.283185307179586477 * (S.Hinv[c * 3 + 0] * m1 + S.Hinv[c * 3 + 1] * m2 + S.Hinv[c * 3 + 2] * m3);
-            const double k2 = k[0] * k[0] + k[1] * k[1] + k[2] * k[2];
-            if (k2 > kmax * kmax) continue;
-            ce_acc[0] += exp(-0.5 * zeta * zeta * k2) / k2;
-        }
-        const int v1 = 2 * S.nn[0] + 1, v2 = 2 * S.nn[1] + 1, v3 = 2 * S.nn[2] + 1;
-        const int nr = v1 * v2 * v3;
-        const double s2 = 0.70710678118654752440;
-        for (int t = tid; t < nr; t += NT) {
-            const int n3 = t % v3 - S.nn[2], n2 = (t / v3) % v2 - S.nn[1], n1 = t / (v3 * v2) - S.nn[0];
-            double x[3];
-            for (int c = 0; c < 3; ++c) x[c] = n1 * S.H[0 * 3 + c] + n2 * S.H[1 * 3 + c] + n3 * S.H[2 * 3 + c];
-            const double r = sqrt(x[0] * x[0] + x[1] * x[1] + x[2] * x[2]);
-            if (r > rmax) continue;
-            ce_acc[1] += r < 1e-12 ? 0.79788456080286535588 * (1.0 / eta - 1.0 / zeta)
-                                   : (erf(r * s2 / eta) - erf(r * s2 / zeta)) / r;
-        }
-    }
-    wg_sum<2>(ce_acc);
-    const double c_eta = ce_acc[0] * 4.0 * 3.14159265358979323846 / S.vol + ce_acc[1] -
-                         2.0 * 3.14159265358979323846 * (S.zeta * S.zeta - a.eta * a.eta) / S.vol;
-
-    if (tid == 0) clk.lap(PH_SETUP);
-    // --- pair list: count, scan, fill (BQ_L lanes per atom, in j order)
-    const int l = tid & (BQ_L - 1);
-    for (int ib = 0; ib < n; ib += NT / BQ_L) {
-        const int i = ib + tid / BQ_L;
-        int cnt = 0;
-        if (i < n) {
-            const double si[3] = {sl.frac[3 * i], sl.frac[3 * i + 1], sl.frac[3 * i + 2]};
-            for (int j = l; j < n; j += BQ_L) {
-                const double sj[3] = {sl.frac[3 * j], sl.frac[3 * j + 1], sl.frac[3 * j + 2]};
-                cnt += bq_pair_images<false>(S, si, sj, i == j, a.rc2, a.eta, 1.0, j, nullptr, nullptr, nullptr, 0,
-                                             0);
-            }
-        }
-#pragma unroll
-        for (int off = BQ_L / 2; off > 0; off >>= 1) cnt += __shfl_xor(cnt, off, 64);
-        if (i < n && l == 0) sl.rowcnt[i] = cnt;
-    }
-    __syncthreads();
-    wg_scan<NT>(sl.rowcnt, sl.rowptr, n);
-    const long long nnz = sl.rowptr[n];
-    const bool overflow = nnz > a.pcap;
-    if (!overflow) {
-        for (int ib = 0; ib < n; ib += NT / BQ_L) {
-            const int i = ib + tid / BQ_L;
-            if (i < n) {
-                const double si[3] = {sl.frac[3 * i], sl.frac[3 * i + 1], sl.frac[3 * i + 2]};
-                const double sgi = sl.vec(V_SIG)[i];
-                long long cursor = sl.rowptr[i];
-                for (int jb = 0; jb < n; jb += BQ_L) {
-                    const int j = jb + l;
-                    double sj[3] = {0.0, 0.0, 0.0};
-                    int c = 0;
-                    if (j < n) {
-                        sj[0] = sl.frac[3 * j];
-                        sj[1] = sl.frac[3 * j + 1];
-                        sj[2] = sl.frac[3 * j + 2];
-                        c = bq_pair_images<false>(S, si, sj, i == j, a.rc2, a.eta, 1.0, j, nullptr, nullptr, nullptr,
-                                                  0, 0);
-                    }
-                    int incl = c;
-#pragma unroll
-                    for (int d = 1; d < BQ_L; d <<= 1) {
-                        const int y = __shfl_up(incl, d, BQ_L);
-                        if (l >= d) incl += y;
-                    }
-                    const int total = __shfl(incl, BQ_L - 1, BQ_L);
-                    if (c) {
-                        const double sgj = sl.vec(V_SIG)[j];
-                        bq_pair_images<true>(S, si, sj, i == j, a.rc2, a.eta, sqrt(sgi * sgi + sgj * sgj), j, sl.col,
-                                             sl.kval, sl.pdr, cursor + incl - c, a.pcap);
-                    }
-                    cursor += total;
+                double* f = a.forces + 3 * (size_t)(S.off + slot_ptr<int>(a, S, S.slot.perm)[i]);
+                for (int c = 0; c < 3; ++c) {
+                    double g = 0.0;
+                    for (int b = 0; b < 3; ++b) g += (double)S.K[b] * S.Hinv[c * 3 + b] * du[b];
+                    f[c] = -xi * g - xi * v[4 + c];
                 }
             }
         }
     }
     __syncthreads();
-    if (tid == 0) clk.lap(PH_PAIRS);
-    if (overflow || err) {
-        if (tid == 0) {
-            BStat& st = a.stats[s];
-            st.status = overflow ? BQ_OVERFLOW : QEQ_EINVAL;
-            st.nnz = nnz;
-            st.iters = 0;
+    if (tid == 0) t0 = bq_lap(T, PH_INTERP, t0);
+    const double chi_norm = T.chi_norm;
+    if (FIN) {
+        double t5[5] = {0.0, 0.0, 0.0, 0.0, 0.0}, g = 0.0;
+        if (live) {
+            const double y = yv[tid] + dsi * vi;
+            const double sg = slot_vec(a, S, V_SIG)[tid];
+            g = y + Ji * vi + chi;
+            t5[0] = vi * y;
+            t5[1] = slot_vec(a, S, V_CHIRAW)[tid] * vi;
+            t5[2] = Ji * vi * vi;
+            t5[3] = sg * sg * vi;
+            t5[4] = g;
         }
-        __syncthreads();
-        return;
-    }
-
-    // --- atoms binned by h1 (the spread pass takes whole g1 planes)
-    if (tid <= K1) hcnt[tid] = 0;
-    __syncthreads();
-    for (int i = tid; i < n; i += NT) atomicAdd(&hcnt[sl.home[4 * i]], 1);
-    __syncthreads();
-    if (tid == 0) {
-        int run = 0;
-        for (int b = 0; b < K1; ++b) {
-            hstart[b] = run;
-            run += hcnt[b];
-            hcnt[b] = 0;
+        wg_sum<5>(t5);
+        const double gmean = t5[4] / (double)n;
+        double dv[1] = {live ? (g - gmean) * (g - gmean) : 0.0};
+        wg_sum<1>(dv);
+        const double tres = chi_norm > 0.0 ? sqrt(dv[0]) / chi_norm : sqrt(dv[0]);
+        const double e_bg = -0.5 * S.bg_pref * (a.eta * a.eta * Q * Q - 2.0 * Q * t5[3]);
+        const double e_elec = 0.5 * t5[0] + e_bg;
+        const double e_qeq = e_elec + t5[1] + 0.5 * t5[2];
+        const double mu = gmean - S.bg_pref * (a.eta * a.eta * Q - t5[3]);
+        const bool gap = !(tres <= a.restart_thr);
+        const bool conv = T.conv != 0;
+        const bool stop = !conv || !gap || T.restarts >= 4 || T.iters >= a.max_iter;
+        __syncthreads();   // every thread has read the state that thread 0 changes
+        if (stop) {
+            if (live) a.q_out[S.off + slot_ptr<int>(a, S, S.slot.perm)[tid]] = vi;
+            if (tid == 0) {
+                T.status = conv && !gap && isfinite(e_qeq) ? QEQ_OK : QEQ_NOT_CONVERGED;
+                T.tres = tres;
+                T.mu = mu;
+                T.e_qeq = e_qeq;
+                T.e_elec = e_elec;
+                T.finished = 1;
+                if (a.energies) {
+                    a.energies[2 * (size_t)s] = e_qeq;
+                    a.energies[2 * (size_t)s + 1] = e_elec;
+                }
+            }
+        } else if (tid == 0) {
+            T.restarts += 1;
+            T.need_init = 1;
+            T.cgdone = 0;
+            atomicAdd(&a.count->restarts, 1);
+            atomicAdd(&a.count->running, 1);
         }
-        hstart[K1] = run;
-    }
-    __syncthreads();
-    for (int i = tid; i < n; i += NT) {
-        const int b = sl.home[4 * i];
-        order[hstart[b] + atomicAdd(&hcnt[b], 1)] = i;
-    }
-    // --- Green table on the half spectrum; its inverse transform gives the
-    // mesh kernel Theta around the origin for the self-correction
-    const int K3h = K3 / 2 + 1;
-    const size_t nhalf = (size_t)S.nhalf;
-    for (size_t t = tid; t < nhalf; t += NT) {
-        const int m3 = (int)(t % K3h), m2 = (int)((t / K3h) % K2), m1 = (int)(t / ((size_t)K3h * K2));
-        const float g = bq_green(S, a.eta, m1, m2, m3, bms[0], bms[1], bms[2]);
-        sl.G[t] = g;
-        sl.C[t] = make_float2(g, 0.f);
-    }
-    __syncthreads();
-    if (a.self_corr) {
-        bq_L<NT, 0>(S, sl, BQ_INV, buf, tws[0], tid);
-        bq_L<NT, 1>(S, sl, BQ_INV, buf, tws[1], tid);
-        bq_E<NT>(S, sl, buf, tws[2], tid);
-        const int np = 2 * p - 1;
-        for (int t = tid; t < np * np * np; t += NT) {
-            const int d3 = t % np - (p - 1), d2 = (t / np) % np - (p - 1), d1 = t / (np * np) - (p - 1);
-            const int g1 = d1 < 0 ? d1 + K1 : d1, g2 = d2 < 0 ? d2 + K2 : d2, g3 = d3 < 0 ? d3 + K3 : d3;
-            sl.tab[t] = (double)sl.R[((size_t)g1 * K2 + g2) * K3 + g3];
+    } else {
+        double t2[2] = {0.0, 0.0}, y = 0.0;
+        if (live) {
+            y = yv[tid] + dsi * vi + Ji * vi;
+            t2[0] = vi * y;
+            t2[1] = y;
         }
-        __syncthreads();
-        for (int i = tid; i < n; i += NT) {
-            const double u[3] = {sl.frac[3 * i] * K1, sl.frac[3 * i + 1] * K2, sl.frac[3 * i + 2] * K3};
-            double v, g[3];
-            if (p == 6)
-                mesh_self_term<6>(u, p, sl.tab, &v, g);
-            else
-                mesh_self_term<0>(u, p, sl.tab, &v, g);
-            sl.vec(V_DSELF)[i] += c_eta - v;
-            sl.selfgrad[3 * i] = g[0];
-            sl.selfgrad[3 * i + 1] = g[1];
-            sl.selfgrad[3 * i + 2] = g[2];
-        }
-        __syncthreads();
-    }
-
-    if (tid == 0) clk.lap(PH_MESHPREP);
-    // --- projected Jacobi CG (as in the single-structure solver)
-    double* q = sl.vec(V_Q);
-    double* r = sl.vec(V_R);
-    double* pv = sl.vec(V_P);
-    double* y = sl.vec(V_Y);
-    const double* dinv = sl.vec(V_DINV);
-    const double* chi = sl.vec(V_CHI);
-    double* fout = a.forces ? a.forces + 3 * (size_t)S.off : nullptr;
-    bool use_q0 = a.q0 != nullptr;
-    int q0_rejected = 0;
-    {
-        double sq[1] = {0.0};
-        for (int i = tid; i < n; i += NT) {
-            double x = use_q0 ? a.q0[S.off + i] : Q / (double)n;
-            if (!isfinite(x)) x = Q / (double)n;
-            q[i] = x;
-            sq[0] += x;
-        }
-        wg_sum<1>(sq);
-        for (int i = tid; i < n; i += NT) q[i] += (Q - sq[0]) / (double)n;
-        __syncthreads();
-    }
-    const double restart_thr = a.restart_thr;
-    int it = 0, restarts = 0;
-    bool conv = false;
-    double res = 0.0, tres = 0.0, sums[5];
-    double e_qeq = 0.0, e_elec = 0.0, mu = 0.0;
-    for (;;) {
-        double rz = 0.0;
-        bool done = false;
-        for (int attempt = 0; attempt < 2; ++attempt) {
-            bq_mesh<NT>(S, sl, q, p, buf, tws, hstart, order, clk);
-            bq_interp<NT, BQ_CG>(S, sl, q, y, p, a.self_corr, sp, nullptr, sums);
-            if (tid == 0) clk.lap(PH_INTERP);
-            const double qAq = sums[0];
-            const double shift = (chi_sum + sums[1]) / (double)n;
+        wg_sum<2>(t2);
+        if (MODE == BQ_INIT) {
+            const double shift = (T.chi_sum + t2[1]) / (double)n;
             double t4[4] = {0.0, 0.0, 0.0, 0.0};
-            for (int i = tid; i < n; i += NT) {
-                const double ri = -chi[i] - y[i] + shift;
-                r[i] = ri;
-                t4[0] += dinv[i] * ri;
-                t4[1] += dinv[i] * ri * ri;
-                t4[2] += ri * ri;
-                t4[3] += chi[i] * q[i];
+            if (live) {
+                ri = -chi - y + shift;
+                rv[tid] = ri;
+                t4[0] = dinv * ri;
+                t4[1] = dinv * ri * ri;
+                t4[2] = ri * ri;
+                t4[3] = chi * vi;
             }
             wg_sum<4>(t4);
-            const double c = t4[0] / dinv_sum;
-            rz = t4[1] - c * t4[0];
-            res = chi_norm > 0.0 ? sqrt(t4[2]) / chi_norm : sqrt(t4[2]);
-            for (int i = tid; i < n; i += NT) pv[i] = dinv[i] * (r[i] - c);
+            const double c = t4[0] / T.dinv_sum;
+            const double res = chi_norm > 0.0 ? sqrt(t4[2]) / chi_norm : sqrt(t4[2]);
+            const bool first = a.q0 != nullptr && T.restarts == 0 && T.q0_rejected == 0 && T.iters == 0;
+            const double e_start = 0.5 * t2[0] + t4[3];
+            // a supplied start that is worse than the cold one is replaced by it
+            const bool worse = first && (Q == 0.0 ? !(e_start < 0.0) : !(res <= 1.0));
+            const bool done = res <= a.tol || !(res == res);
+            const int it = T.iters;
             __syncthreads();
-            done = res <= a.tol || !(res == res);
-            if (restarts == 0 && attempt == 0 && use_q0) {
-                const double e_start = 0.5 * qAq + t4[3];
-                const bool worse = Q == 0.0 ? !(e_start < 0.0) : !(res <= 1.0);
+            if (live) {
+                if (worse)
+                    qv[tid] = Q / (double)n;
+                else
+                    pv[tid] = dinv * (ri - c);
+            }
+            if (tid == 0) {
                 if (worse) {
-                    q0_rejected = 1;
-                    for (int i = tid; i < n; i += NT) q[i] = Q / (double)n;
-                    __syncthreads();
-                    continue;
+                    T.q0_rejected = 1;
+                } else {
+                    T.need_init = 0;
+                    T.rz = t4[1] - c * t4[0];
+                    T.res = res;
+                    T.conv = done;
+                    if (done || it >= a.max_iter) {
+                        T.cgdone = 1;
+                        atomicSub(&a.count->running, 1);
+                    }
                 }
             }
-            break;
-        }
-        while (!done && it < a.max_iter) {
-            bq_mesh<NT>(S, sl, pv, p, buf, tws, hstart, order, clk);
-            bq_interp<NT, BQ_CG>(S, sl, pv, y, p, a.self_corr, sp, nullptr, sums);
-            if (tid == 0) clk.lap(PH_INTERP);
-            const double alpha = rz / sums[0];
-            const double ymean = sums[1] / (double)n;
+        } else {
+            const double rz = T.rz;
+            const double alpha = rz / t2[0];
+            const double ymean = t2[1] / (double)n;
             double t3[3] = {0.0, 0.0, 0.0};
-            for (int i = tid; i < n; i += NT) {
-                q[i] += alpha * pv[i];
-                const double ri = r[i] - alpha * (y[i] - ymean);
-                r[i] = ri;
-                t3[0] += dinv[i] * ri;
-                t3[1] += dinv[i] * ri * ri;
-                t3[2] += ri * ri;
+            if (live) {
+                qv[tid] = qi + alpha * vi;
+                ri -= alpha * (y - ymean);
+                rv[tid] = ri;
+                t3[0] = dinv * ri;
+                t3[1] = dinv * ri * ri;
+                t3[2] = ri * ri;
             }
             wg_sum<3>(t3);
-            ++it;
-            const double c = t3[0] / dinv_sum;
+            const double c = t3[0] / T.dinv_sum;
             const double rz_new = t3[1] - c * t3[0];
             const double beta = rz_new / rz;
-            rz = rz_new;
-            for (int i = tid; i < n; i += NT) pv[i] = dinv[i] * (r[i] - c) + beta * pv[i];
+            const double res = chi_norm > 0.0 ? sqrt(t3[2]) / chi_norm : sqrt(t3[2]);
+            const bool done = res <= a.tol || !(res == res);
+            const int it = T.iters + 1;
             __syncthreads();
-            res = chi_norm > 0.0 ? sqrt(t3[2]) / chi_norm : sqrt(t3[2]);
-            done = res <= a.tol || !(res == res);
-            if (tid == 0) clk.lap(PH_VEC);
-        }
-        conv = done;
-        // final matvec on q: energies, mu, true residual, forces
-        bq_mesh<NT>(S, sl, q, p, buf, tws, hstart, order, clk);
-        bq_interp<NT, BQ_FINAL>(S, sl, q, y, p, a.self_corr, sp, fout, sums);
-        if (tid == 0) clk.lap(PH_INTERP);
-        const double gmean = sums[4] / (double)n;
-        double dv[1] = {0.0};
-        for (int i = tid; i < n; i += NT) {
-            const double d = sl.vec(V_G)[i] - gmean;
-            dv[0] += d * d;
-        }
-        wg_sum<1>(dv);
-        tres = chi_norm > 0.0 ? sqrt(dv[0]) / chi_norm : sqrt(dv[0]);
-        const double S2 = sums[3];
-        const double e_bg = -0.5 * S.bg_pref * (a.eta * a.eta * Q * Q - 2.0 * Q * S2);
-        e_elec = 0.5 * sums[0] + e_bg;
-        e_qeq = e_elec + sums[1] + 0.5 * sums[2];
-        mu = gmean - S.bg_pref * (a.eta * a.eta * Q - S2);
-        const bool gap = !(tres <= restart_thr);
-        if (!conv || !gap || restarts >= 4 || it >= a.max_iter) {
-            if (conv && gap) conv = false;
-            break;
-        }
-        ++restarts;
-    }
-    for (int i = tid; i < n; i += NT) a.q_out[S.off + i] = q[i];
-    if (tid == 0) {
-        BStat& st = a.stats[s];
-        const bool finite = isfinite(e_qeq);
-        st.status = (conv && finite) ? QEQ_OK : QEQ_NOT_CONVERGED;
-        st.iters = it;
-        st.restarts = restarts;
-        st.q0_rejected = q0_rejected;
-        st.nnz = nnz;
-        st.rel_resid = res;
-        st.true_rel_resid = tres;
-        st.mu = mu;
-        st.e_qeq = e_qeq;
-        st.e_elec = e_elec;
-        clk.lap(PH_VEC);
-        long long tot = 0;
-        for (int k = 0; k < PH_COUNT; ++k) {
-            st.ticks[k] = clk.acc[k];
-            tot += clk.acc[k];
-        }
-        st.ticks[PH_COUNT] = tot;
-        if (a.energies) {
-            a.energies[2 * s] = e_qeq;
-            a.energies[2 * s + 1] = e_elec;
-        }
-    }
-    __syncthreads();
-}
-
-template <int NT>
-__global__ __launch_bounds__(NT) void k_batched(BArgs a) {
-    extern __shared__ float2 fbuf[];
-    double* sp = reinterpret_cast<double*>(fbuf + BQ_LDS);
-    int* order = reinterpret_cast<int*>(sp + a.nmax);
-    __shared__ int hcnt[BQ_KAX + 1], hstart[BQ_KAX + 1];
-    __shared__ BStruct S;
-    __shared__ float2 tws[3][BQ_KAX];
-    __shared__ float bms[3][BQ_KAX];
-    __shared__ int work;
-    const int tid = threadIdx.x;
-    char* base = a.scratch + (size_t)blockIdx.x * a.slot.bytes;
-    Slot sl;
-    sl.C = reinterpret_cast<float2*>(base + a.slot.C);
-    sl.R = reinterpret_cast<float*>(base + a.slot.R);
-    sl.G = reinterpret_cast<float*>(base + a.slot.G);
-    sl.wts = reinterpret_cast<float*>(base + a.slot.wts);
-    sl.dwts = reinterpret_cast<float*>(base + a.slot.dwts);
-    sl.home = reinterpret_cast<int*>(base + a.slot.home);
-    sl.frac = reinterpret_cast<double*>(base + a.slot.frac);
-    sl.v = reinterpret_cast<double*>(base + a.slot.vec);
-    sl.selfgrad = reinterpret_cast<double*>(base + a.slot.selfgrad);
-    sl.rowcnt = reinterpret_cast<int*>(base + a.slot.rowcnt);
-    sl.rowptr = reinterpret_cast<int*>(base + a.slot.rowptr);
-    sl.col = reinterpret_cast<int*>(base + a.slot.col);
-    sl.kval = reinterpret_cast<float*>(base + a.slot.kval);
-    sl.pdr = reinterpret_cast<float4*>(base + a.slot.pdr);
-    sl.tab = reinterpret_cast<double*>(base + a.slot.tab);
-    sl.nmax = a.nmax;
-    for (;;) {
-        if (tid == 0) work = atomicAdd(a.next, 1);
-        __syncthreads();
-        const int w = work;
-        __syncthreads();
-        if (w >= a.n_work) break;   // uniform: every wave of the workgroup leaves here
-        const int s = a.order[w];
-        const int* src = reinterpret_cast<const int*>(a.st + s);
-        int* dst = reinterpret_cast<int*>(&S);
-        for (int t = tid; t < (int)(sizeof(BStruct) / sizeof(int)); t += NT) dst[t] = src[t];
-        __syncthreads();
-        for (int ax = 0; ax < 3; ++ax) {
-            for (int t = tid; t < S.ax[ax].K; t += NT) {
-                tws[ax][t] = a.tw[S.ax[ax].tw_off + t];
-                bms[ax][t] = a.bmod[S.ax[ax].bm_off + t];
+            if (live) pv[tid] = dinv * (ri - c) + beta * vi;
+            if (tid == 0) {
+                T.iters = it;
+                T.rz = rz_new;
+                T.res = res;
+                T.conv = done;
+                if (done || it >= a.max_iter) {
+                    T.cgdone = 1;
+                    atomicSub(&a.count->running, 1);
+                }
             }
         }
-        __syncthreads();
-        bq_solve<NT>(a, S, s, sl, fbuf, sp, tws, bms, hcnt, hstart, order);
     }
+    if (tid == 0) bq_lap(T, PH_VEC, t0);
 }
+
+__global__ void k_bq_count_clear(BCount* c) { c->restarts = 0; }
 
 // ------------------------------------------------------------------ host side
 constexpr double PI_H = 3.14159265358979323846;
@@ -1102,17 +1106,13 @@ bool smooth_235_h(int n) {
     return n == 1;
 }
 
-bool radix_plan_h(int K, BAxis* ax) {
-    int n = K, ns = 0;
-    while (n % 5 == 0) { ax->radix[ns++] = 5; n /= 5; }
-    while (n % 3 == 0) { ax->radix[ns++] = 3; n /= 3; }
-    while (n % 8 == 0) { ax->radix[ns++] = 8; n /= 8; }
-    if (n == 4) { ax->radix[ns++] = 4; n = 1; }
-    if (n == 2) { ax->radix[ns++] = 2; n = 1; }
-    if (n != 1 || ns > QEQ_FFT_MAXST) return false;
-    ax->nst = ns;
-    ax->K = K;
-    return true;
+bool length_compiled(int K) {
+    switch (K) {
+#define X(KK) case KK: return true;
+        BQ_FOR_EACH_LEN(X)
+#undef X
+    }
+    return false;
 }
 
 // |b(m)|^2 of the order-p cardinal B-spline (Essmann et al.), host FP64.
@@ -1162,6 +1162,39 @@ int grow(T** p, size_t* cap, size_t count) {
 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
+// Scratch of the structures that are solved together (1,024 structures of
+// 32 .. 512 atoms: 1.6 GB).
+constexpr size_t BQ_SCRATCH = (size_t)8 << 30;
+
+// Offsets of a structure's slot; returns its size.
+size_t slot_layout(BStruct& S) {
+    BSlot& L = S.slot;
+    const size_t n = (size_t)S.n, np = 2 * QEQ_MAXP - 1;
+    size_t o = 0;
+    auto place = [&](size_t bytes) {
+        const size_t at = o;
+        o = align256(o + bytes);
+        return (unsigned)at;
+    };
+    L.C = place(sizeof(float2) * (size_t)S.nhalf);
+    L.G = place(sizeof(float) * (size_t)S.nhalf);
+    L.wts = place(sizeof(float) * 3 * QEQ_MAXP * n);
+    L.dwts = place(sizeof(float) * 3 * QEQ_MAXP * n);
+    L.home = place(sizeof(int) * 4 * n);
+    L.frac = place(sizeof(double) * 3 * n);
+    L.vec = place(sizeof(double) * BQ_NV * n);
+    L.selfgrad = place(sizeof(double) * 3 * n);
+    L.row = place(sizeof(int2) * n);
+    L.col = place(sizeof(int) * (size_t)S.pcap);
+    L.kval = place(sizeof(float) * (size_t)S.pcap);
+    L.pdr = place(sizeof(float4) * (size_t)S.pcap);
+    L.tab = place(sizeof(double) * np * np * np);
+    L.mpart = place(sizeof(float) * 4 * QEQ_MAXP * n);
+    L.hstart = place(sizeof(int) * (BQ_KAX + 1));
+    L.perm = place(sizeof(int) * n);
+    return o;
+}
+
 }  // namespace qeqb
 
 using namespace qeqb;
@@ -1170,35 +1203,27 @@ using namespace qeqb;
 struct BatchState {
     char* scratch = nullptr;
     size_t scratch_cap = 0;
-    BStruct* st = nullptr;
-    size_t st_cap = 0;
-    int* order = nullptr;
-    size_t order_cap = 0;
-    int* next = nullptr;
-    size_t next_cap = 0;
-    BStat* stats = nullptr;
-    size_t stats_cap = 0;
-    float2* tw = nullptr;
-    size_t tw_cap = 0;
-    float* bmod = nullptr;
-    size_t bmod_cap = 0;
+    char* tables = nullptr;      // structures, states, units and transform tables of one wave of structures
+    size_t tables_cap = 0;
+    char* staging = nullptr;     // the same in pinned host memory: one copy a wave
+    size_t staging_cap = 0;
+    BCount* count_host = nullptr;   // pinned: counters of the chunks in flight
+    hipEvent_t ev[2] = {nullptr, nullptr};
     int threads = 1024;
     int wg_per_cu = 1;
-    int n_cu = 0;
     double last_ms = 0.0;
-    std::vector<BStat> last_stats;   // per-structure records of the last call
+    std::vector<BState> last_state;   // per-structure records of the last call
 };
 
 void batch_free(qeq_plan* pl) {
     BatchState* b = pl->batch;
     if (!b) return;
     if (b->scratch) (void)hipFree(b->scratch);
-    if (b->st) (void)hipFree(b->st);
-    if (b->order) (void)hipFree(b->order);
-    if (b->next) (void)hipFree(b->next);
-    if (b->stats) (void)hipFree(b->stats);
-    if (b->tw) (void)hipFree(b->tw);
-    if (b->bmod) (void)hipFree(b->bmod);
+    if (b->tables) (void)hipFree(b->tables);
+    if (b->staging) (void)hipHostFree(b->staging);
+    if (b->count_host) (void)hipHostFree(b->count_host);
+    for (hipEvent_t e : b->ev)
+        if (e) (void)hipEventDestroy(e);
     delete b;
     pl->batch = nullptr;
 }
@@ -1206,26 +1231,197 @@ void batch_free(qeq_plan* pl) {
 namespace {
 
 BatchState* batch_state(qeq_plan* pl) {
-    if (!pl->batch) {
-        pl->batch = new (std::nothrow) BatchState();
-        if (pl->batch) {
-            int cu = 0;
-            if (hipDeviceGetAttribute(&cu, hipDeviceAttributeMultiprocessorCount, pl->dev) != hipSuccess || cu < 1)
-                cu = 256;
-            pl->batch->n_cu = cu;
-        }
-    }
+    if (!pl->batch) pl->batch = new (std::nothrow) BatchState();
     return pl->batch;
 }
 
-template <int NT>
-int launch_batched(const BArgs& a, int grid, size_t smem, hipStream_t stream) {
-    auto fn = k_batched<NT>;
-    if (smem > 65536) {
-        QEQ_HIP(hipFuncSetAttribute((const void*)fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem));
+// Units of work of one kernel: (structure, piece).  Blocks are dispatched to
+// the 8 XCDs round-robin, so the units are dealt out such that every piece of a
+// structure has the same block number modulo 8 in every kernel and finds what
+// the previous kernel of the product wrote in its XCD's L2; short lists are
+// filled up with (-1, 0).
+void deal_units(const std::vector<int>& work, const std::vector<int>& pieces, const std::vector<int>& xcd,
+                std::vector<int2>& out) {
+    std::vector<int2> lane[8];
+    for (size_t w = 0; w < work.size(); ++w)
+        for (int t = 0; t < pieces[w]; ++t) lane[xcd[w]].push_back(make_int2(work[w], t));
+    size_t most = 0;
+    for (const auto& v : lane) most = std::max(most, v.size());
+    out.assign(8 * most, make_int2(-1, 0));
+    for (int x = 0; x < 8; ++x)
+        for (size_t t = 0; t < lane[x].size(); ++t) out[8 * t + x] = lane[x][t];
+}
+
+// One wave: the structures `work` (indices into st), whose slots start at
+// their st.base; the device states come back in `state`.
+int run_wave(qeq_plan* pl, BatchState* b, BArgs& a, std::vector<BStruct>& st, const std::vector<int>& work,
+             const std::vector<float2>& twh, const std::vector<float>& bmh, std::vector<BState>& state) {
+    hipStream_t stream = pl->stream;
+    const int ns = (int)work.size();
+    std::vector<int> nA(ns), nB(ns), nP(ns), nG(ns), nS(ns), nT(ns), xcd(ns);
+    double load[8] = {0.0};
+    for (int w = 0; w < ns; ++w) {
+        const BStruct& S = st[work[w]];
+        nA[w] = (S.K[0] + S.pb - 1) / S.pb;
+        nB[w] = (S.K[1] * (S.K[2] / 2 + 1) + BQ_NC - 1) / BQ_NC;
+        nP[w] = (S.n + BQ_PAIR_ATOMS - 1) / BQ_PAIR_ATOMS;
+        nG[w] = (S.nhalf + BQ_GREEN - 1) / BQ_GREEN;
+        nS[w] = (S.n + 63) / 64;
+        nT[w] = 2 * a.p - 1;
+        xcd[w] = (int)(std::min_element(load, load + 8) - load);   // longest first: balanced
+        load[xcd[w]] += S.nhalf;
     }
-    hipLaunchKernelGGL(fn, dim3(grid), dim3(NT), smem, stream, a);
-    return qeq_check(hipGetLastError());
+    std::vector<int2> uA, uB, uP, uG, uS, uT;
+    deal_units(work, nA, xcd, uA);
+    deal_units(work, nB, xcd, uB);
+    auto plain = [&](const std::vector<int>& pieces, std::vector<int2>& out) {
+        for (int w = 0; w < ns; ++w)
+            for (int t = 0; t < pieces[w]; ++t) out.push_back(make_int2(work[w], t));
+    };
+    plain(nP, uP);
+    plain(nG, uG);
+    if (a.self_corr) {
+        plain(nS, uS);
+        plain(nT, uT);
+    }
+    // tables: one staging buffer, one copy
+    const int n_struct = (int)st.size();
+    size_t o = 0;
+    auto place = [&](size_t bytes) {
+        const size_t at = o;
+        o = align256(o + bytes);
+        return at;
+    };
+    const size_t oSt = place(sizeof(BStruct) * n_struct), oState = place(sizeof(BState) * n_struct),
+                 oCount = place(sizeof(BCount)), oOrder = place(sizeof(int) * ns), oTw = place(sizeof(float2) * twh.size()),
+                 oBm = place(sizeof(float) * bmh.size()), oA = place(sizeof(int2) * uA.size()),
+                 oB = place(sizeof(int2) * uB.size()), oP = place(sizeof(int2) * uP.size()),
+                 oG = place(sizeof(int2) * uG.size()), oS = place(sizeof(int2) * uS.size()),
+                 oT = place(sizeof(int2) * uT.size());
+    if (o > b->staging_cap) {
+        if (b->staging) (void)hipHostFree(b->staging);
+        b->staging = nullptr;
+        b->staging_cap = 0;
+        if (hipHostMalloc((void**)&b->staging, o + o / 4) != hipSuccess) {
+            b->staging = nullptr;
+            return QEQ_ENOMEM;
+        }
+        b->staging_cap = o + o / 4;
+    }
+    QEQ_TRY(grow(&b->tables, &b->tables_cap, o));
+    if (!b->count_host && hipHostMalloc((void**)&b->count_host, 2 * sizeof(BCount)) != hipSuccess) {
+        b->count_host = nullptr;
+        return QEQ_ENOMEM;
+    }
+    for (hipEvent_t& e : b->ev)
+        if (!e) QEQ_HIP(hipEventCreateWithFlags(&e, hipEventDisableTiming));
+    memset(b->staging + oState, 0, sizeof(BState) * n_struct);
+    const BCount c0 = {ns, 0};
+    auto put = [&](size_t at, const void* from, size_t bytes) {
+        if (bytes) memcpy(b->staging + at, from, bytes);
+    };
+    put(oSt, st.data(), sizeof(BStruct) * n_struct);
+    put(oCount, &c0, sizeof(c0));
+    put(oOrder, work.data(), sizeof(int) * ns);
+    put(oTw, twh.data(), sizeof(float2) * twh.size());
+    put(oBm, bmh.data(), sizeof(float) * bmh.size());
+    put(oA, uA.data(), sizeof(int2) * uA.size());
+    put(oB, uB.data(), sizeof(int2) * uB.size());
+    put(oP, uP.data(), sizeof(int2) * uP.size());
+    put(oG, uG.data(), sizeof(int2) * uG.size());
+    put(oS, uS.data(), sizeof(int2) * uS.size());
+    put(oT, uT.data(), sizeof(int2) * uT.size());
+    QEQ_HIP(hipMemcpyAsync(b->tables, b->staging, o, hipMemcpyHostToDevice, stream));
+    a.st = (const BStruct*)(b->tables + oSt);
+    a.state = (BState*)(b->tables + oState);
+    a.count = (BCount*)(b->tables + oCount);
+    a.tw = (const float2*)(b->tables + oTw);
+    a.bmod = (const float*)(b->tables + oBm);
+    a.scratch = b->scratch;
+    const int* order = (const int*)(b->tables + oOrder);
+    const int2 *dA = (const int2*)(b->tables + oA), *dB = (const int2*)(b->tables + oB),
+               *dP = (const int2*)(b->tables + oP), *dG = (const int2*)(b->tables + oG),
+               *dS = (const int2*)(b->tables + oS), *dT = (const int2*)(b->tables + oT);
+    size_t shA = 0, shB = 0, shC = 0;
+    for (int s : work) {
+        const BStruct& S = st[s];
+        const size_t two = sizeof(float2) * ((size_t)S.K[2] * BQ_KS + (size_t)S.K[1] * BQ_KS2);
+        shC = std::max(shC, two);
+        shA = std::max({shA, two, sizeof(long long) * (size_t)S.K[2] * S.pb * S.K[1]});
+        shB = std::max(shB, sizeof(float2) * (size_t)S.K[0] * BQ_KS);
+    }
+    auto window = [](const void* fn, size_t sh) {
+        return sh <= 65536 ? QEQ_OK
+                           : qeq_check(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh));
+    };
+    QEQ_TRY(window((const void*)k_bq_fwd, shA));
+    QEQ_TRY(window((const void*)k_bq_inv<false>, shC));
+    QEQ_TRY(window((const void*)k_bq_inv<true>, shC));
+    QEQ_TRY(window((const void*)k_bq_theta, shC));
+    // --- set-up
+    hipLaunchKernelGGL(k_bq_stage, dim3(ns), dim3(1024), 0, stream, a, order);
+    hipLaunchKernelGGL(k_bq_pairs, dim3((unsigned)uP.size()), dim3(256), 0, stream, a, dP);
+    hipLaunchKernelGGL(k_bq_green, dim3((unsigned)uG.size()), dim3(256), 0, stream, a, dG);
+    if (a.self_corr) {
+        hipLaunchKernelGGL(k_bq_cols<true>, dim3((unsigned)uB.size()), dim3(BQ_NT), shB, stream, a, dB, (int)BQ_FINAL);
+        hipLaunchKernelGGL(k_bq_theta, dim3((unsigned)uT.size()), dim3(BQ_NT), shC, stream, a, dT);
+        if (a.p == 6)
+            hipLaunchKernelGGL(k_bq_self<6>, dim3((unsigned)uS.size()), dim3(64), 0, stream, a, dS);
+        else
+            hipLaunchKernelGGL(k_bq_self<0>, dim3((unsigned)uS.size()), dim3(64), 0, stream, a, dS);
+    }
+    QEQ_TRY(qeq_check(hipGetLastError()));
+    auto product = [&](int mode) {
+        hipLaunchKernelGGL(k_bq_fwd, dim3((unsigned)uA.size()), dim3(BQ_NT), shA, stream, a, dA, mode);
+        hipLaunchKernelGGL(k_bq_cols<false>, dim3((unsigned)uB.size()), dim3(BQ_NT), shB, stream, a, dB, mode);
+        if (mode == BQ_FINAL) {
+            hipLaunchKernelGGL(k_bq_inv<true>, dim3((unsigned)uA.size()), dim3(BQ_NT), shC, stream, a, dA, mode);
+            hipLaunchKernelGGL(k_bq_step<BQ_FINAL>, dim3(ns), dim3(1024), 0, stream, a, order);
+        } else {
+            hipLaunchKernelGGL(k_bq_inv<false>, dim3((unsigned)uA.size()), dim3(BQ_NT), shC, stream, a, dA, mode);
+            if (mode == BQ_INIT)
+                hipLaunchKernelGGL(k_bq_step<BQ_INIT>, dim3(ns), dim3(1024), 0, stream, a, order);
+            else
+                hipLaunchKernelGGL(k_bq_step<BQ_ITER>, dim3(ns), dim3(1024), 0, stream, a, order);
+        }
+        return qeq_check(hipGetLastError());
+    };
+    auto counters = [&](int slot) -> int {
+        QEQ_HIP(hipMemcpyAsync(&b->count_host[slot], a.count, sizeof(BCount), hipMemcpyDeviceToHost, stream));
+        QEQ_HIP(hipEventRecord(b->ev[slot], stream));
+        return QEQ_OK;
+    };
+    for (int round = 0;; ++round) {
+        QEQ_TRY(product(BQ_INIT));
+        if (round == 0 && a.q0) QEQ_TRY(product(BQ_INIT));   // rejected starting charges
+        // Chunks of iterations; the counter of each chunk is read while the
+        // next one runs, so the stream never waits for the host and at most
+        // one chunk of early-returning blocks is launched in vain.
+        constexpr int CHUNK = 3;
+        int slot = 0;
+        bool first = true;
+        for (int it = 0; it < a.max_iter; it += CHUNK) {
+            for (int t = 0; t < CHUNK; ++t) QEQ_TRY(product(BQ_ITER));
+            QEQ_TRY(counters(slot));
+            if (!first) {
+                QEQ_HIP(hipEventSynchronize(b->ev[slot ^ 1]));
+                if (b->count_host[slot ^ 1].running == 0) break;
+            }
+            first = false;
+            slot ^= 1;
+        }
+        QEQ_TRY(product(BQ_FINAL));
+        QEQ_TRY(counters(0));
+        QEQ_HIP(hipEventSynchronize(b->ev[0]));
+        if (b->count_host[0].restarts == 0) break;
+        hipLaunchKernelGGL(k_bq_count_clear, dim3(1), dim3(1), 0, stream, a.count);
+        QEQ_TRY(qeq_check(hipGetLastError()));
+    }
+    QEQ_HIP(hipMemcpyAsync(b->staging + oState, a.state, sizeof(BState) * n_struct, hipMemcpyDeviceToHost, stream));
+    QEQ_HIP(hipStreamSynchronize(stream));
+    const BState* back = (const BState*)(b->staging + oState);
+    for (int s : work) state[s] = back[s];
+    return QEQ_OK;
 }
 
 int batched_impl(qeq_plan* pl, int n_struct, const int32_t* offs, const double* pos, const double* cells,
@@ -1243,9 +1439,6 @@ int batched_impl(qeq_plan* pl, int n_struct, const int32_t* offs, const double* 
     std::vector<int> hstatus(n_struct, QEQ_OK);
     std::vector<int> Ks;                    // distinct axis lengths
     std::vector<double> cost(n_struct, 0.0);
-    int nmax = 1;
-    size_t kmax = 1, khalf = 1;
-    long long pcap = 1;
     for (int s = 0; s < n_struct; ++s) {
         BStruct& S = st[s];
         memset(&S, 0, sizeof(S));
@@ -1295,8 +1488,8 @@ int batched_impl(qeq_plan* pl, int n_struct, const int32_t* offs, const double* 
                 while (!smooth_235_h(m)) m += 4;
                 K[x] = m;
             }
-            gok = gok && K[x] >= 2 * p && K[x] >= 12 && K[x] <= BQ_KAX && K[x] % 4 == 0 &&
-                  radix_plan_h(K[x], &S.ax[x]);
+            gok = gok && K[x] >= 2 * p && K[x] >= 12 && K[x] <= BQ_KAX && K[x] % 4 == 0 && length_compiled(K[x]);
+            S.K[x] = K[x];
             S.rho[x] = rc / widths[x];
             gok = gok && S.rho[x] <= 4.0;
         }
@@ -1304,7 +1497,6 @@ int batched_impl(qeq_plan* pl, int n_struct, const int32_t* offs, const double* 
             hstatus[s] = QEQ_EPLAN;
             continue;
         }
-        S.npts = K[0] * K[1] * K[2];
         S.nhalf = K[0] * K[1] * (K[2] / 2 + 1);
         S.green_pref = 4.0 * PI_H / det;
         S.bg_pref = 2.0 * PI_H / det;
@@ -1319,16 +1511,14 @@ int batched_impl(qeq_plan* pl, int n_struct, const int32_t* offs, const double* 
         }
         for (int x = 0; x < 3; ++x)
             if (std::find(Ks.begin(), Ks.end(), K[x]) == Ks.end()) Ks.push_back(K[x]);
-        nmax = std::max(nmax, n);
-        kmax = std::max(kmax, (size_t)S.npts);
-        khalf = std::max(khalf, (size_t)S.nhalf);
+        S.pb = std::max(1, std::min({2 * BQ_NC / K[1], BQ_NC2 / (K[2] / 2 + 1), K[0] - p + 1, BQ_PB}));
         // pair capacity: mean neighbour count of a uniform density plus a
         // generous Poisson tail
         const double dens = n / det;
         const double mean = dens * 4.0 / 3.0 * PI_H * rc * rc * rc;
         const long long row = (long long)ceil(mean + 6.0 * sqrt(mean) + 16.0);
-        pcap = std::max(pcap, (long long)n * std::min<long long>(row, (long long)n * 27));
-        cost[s] = (double)S.npts * 12.0 + (double)n * (216.0 + mean);
+        S.pcap = (long long)n * std::min<long long>(row, (long long)n * 27);
+        cost[s] = (double)K[0] * K[1] * K[2] * 12.0 + (double)n * (216.0 + mean);
     }
     // tables for the distinct axis lengths
     std::vector<float2> twh;
@@ -1351,130 +1541,100 @@ int batched_impl(qeq_plan* pl, int n_struct, const int32_t* offs, const double* 
         if (hstatus[s] != QEQ_OK) continue;
         BStruct& S = st[s];
         for (int x = 0; x < 3; ++x) {
-            const size_t u = std::find(Ks.begin(), Ks.end(), S.ax[x].K) - Ks.begin();
-            S.ax[x].tw_off = tw_off[u];
-            S.ax[x].bm_off = bm_off[u];
+            const size_t u = std::find(Ks.begin(), Ks.end(), S.K[x]) - Ks.begin();
+            S.tw_off[x] = tw_off[u];
+            S.bm_off[x] = bm_off[u];
         }
         work.push_back(s);
     }
     // longest first
     std::stable_sort(work.begin(), work.end(), [&](int x, int y) { return cost[x] > cost[y]; });
 
-    QEQ_TRY(grow(&b->st, &b->st_cap, (size_t)n_struct));
-    QEQ_TRY(grow(&b->stats, &b->stats_cap, (size_t)n_struct));
-    QEQ_TRY(grow(&b->order, &b->order_cap, std::max<size_t>(work.size(), 1)));
-    QEQ_TRY(grow(&b->next, &b->next_cap, (size_t)1));
-    QEQ_TRY(grow(&b->tw, &b->tw_cap, std::max<size_t>(twh.size(), 1)));
-    QEQ_TRY(grow(&b->bmod, &b->bmod_cap, std::max<size_t>(bmh.size(), 1)));
-    hipStream_t stream = pl->stream;
-    QEQ_HIP(hipMemcpyAsync(b->st, st.data(), sizeof(BStruct) * n_struct, hipMemcpyHostToDevice, stream));
-    if (!twh.empty()) {
-        QEQ_HIP(hipMemcpyAsync(b->tw, twh.data(), sizeof(float2) * twh.size(), hipMemcpyHostToDevice, stream));
-        QEQ_HIP(hipMemcpyAsync(b->bmod, bmh.data(), sizeof(float) * bmh.size(), hipMemcpyHostToDevice, stream));
-    }
-    std::vector<BStat> hst(n_struct);
-    memset(hst.data(), 0, sizeof(BStat) * n_struct);
-    for (int s = 0; s < n_struct; ++s) hst[s].status = hstatus[s];
-    QEQ_HIP(hipMemcpyAsync(b->stats, hst.data(), sizeof(BStat) * n_struct, hipMemcpyHostToDevice, stream));
-
-    const int nt = b->threads;
-    for (int round = 0; round < 2 && !work.empty(); ++round) {
-        BArgs a;
-        memset(&a, 0, sizeof(a));
-        a.p = p;
-        a.self_corr = prm.self_correction;
-        a.max_iter = prm.max_iter;
-        a.tol = prm.tol;
-        a.eta = prm.eta;
-        a.rc2 = rc * rc;
-        a.restart_thr = 2.0 * std::max(prm.tol, 1e-7);
-        a.nmax = nmax;
-        a.pcap = pcap;
-        // slot layout
-        BSlot& L = a.slot;
-        size_t o = 0;
-        L.C = o; o = align256(o + sizeof(float2) * khalf);
-        L.R = o; o = align256(o + sizeof(float) * kmax);
-        L.G = o; o = align256(o + sizeof(float) * khalf);
-        L.wts = o; o = align256(o + sizeof(float) * 3 * QEQ_MAXP * nmax);
-        L.dwts = o; o = align256(o + sizeof(float) * 3 * QEQ_MAXP * nmax);
-        L.home = o; o = align256(o + sizeof(int) * 4 * nmax);
-        L.frac = o; o = align256(o + sizeof(double) * 3 * nmax);
-        L.vec = o; o = align256(o + sizeof(double) * BQ_NV * nmax);
-        L.selfgrad = o; o = align256(o + sizeof(double) * 3 * nmax);
-        L.rowcnt = o; o = align256(o + sizeof(int) * nmax);
-        L.rowptr = o; o = align256(o + sizeof(int) * (nmax + 1));
-        L.col = o; o = align256(o + sizeof(int) * pcap);
-        L.kval = o; o = align256(o + sizeof(float) * pcap);
-        L.pdr = o; o = align256(o + sizeof(float4) * pcap);
-        L.tab = o; o = align256(o + sizeof(double) * (2 * QEQ_MAXP - 1) * (2 * QEQ_MAXP - 1) * (2 * QEQ_MAXP - 1));
-        L.bytes = o;
-        const int grid = (int)std::min<size_t>(work.size(), (size_t)b->n_cu * b->wg_per_cu);
-        QEQ_TRY(grow(&b->scratch, &b->scratch_cap, L.bytes * grid));
-        QEQ_HIP(hipMemcpyAsync(b->order, work.data(), sizeof(int) * work.size(), hipMemcpyHostToDevice, stream));
-        QEQ_HIP(hipMemsetAsync(b->next, 0, sizeof(int), stream));
-        a.n_work = (int)work.size();
-        a.st = b->st;
-        a.order = b->order;
-        a.next = b->next;
-        a.tw = b->tw;
-        a.bmod = b->bmod;
-        a.pos = pos;
-        a.sigma = sigma;
-        a.J = J;
-        a.chi = chi;
-        a.q0 = q0;
-        a.q_out = q;
-        a.energies = energies;
-        a.forces = forces;
-        a.stats = b->stats;
-        a.scratch = b->scratch;
-        const size_t smem = sizeof(float2) * (size_t)BQ_LDS + sizeof(double) * (size_t)nmax + sizeof(int) * (size_t)nmax;
-        hipEvent_t e0 = nullptr, e1 = nullptr;
-        (void)hipEventCreate(&e0);
-        (void)hipEventCreate(&e1);
-        if (e0) (void)hipEventRecord(e0, stream);
-        int rc2 = QEQ_EPLAN;
-        if (nt == 1024) rc2 = launch_batched<1024>(a, grid, smem, stream);
-        if (e1) (void)hipEventRecord(e1, stream);
-        if (rc2 != QEQ_OK) {
-            if (e0) (void)hipEventDestroy(e0);
-            if (e1) (void)hipEventDestroy(e1);
-            return rc2;
-        }
-        QEQ_HIP(hipMemcpyAsync(hst.data(), b->stats, sizeof(BStat) * n_struct, hipMemcpyDeviceToHost, stream));
-        QEQ_HIP(hipStreamSynchronize(stream));
-        float ms = 0.f;
-        if (e0 && e1 && hipEventElapsedTime(&ms, e0, e1) == hipSuccess) b->last_ms += ms;
-        if (e0) (void)hipEventDestroy(e0);
-        if (e1) (void)hipEventDestroy(e1);
-        // structures whose pair list overflowed go again with the measured size
+    std::vector<BState> state(n_struct);
+    memset(state.data(), 0, sizeof(BState) * n_struct);
+    for (int s = 0; s < n_struct; ++s) state[s].status = hstatus[s];
+    BArgs a;
+    memset(&a, 0, sizeof(a));
+    a.p = p;
+    a.self_corr = prm.self_correction;
+    a.max_iter = prm.max_iter;
+    a.tol = prm.tol;
+    a.eta = prm.eta;
+    a.rc2 = rc * rc;
+    a.restart_thr = 2.0 * std::max(prm.tol, 1e-7);
+    a.pos = pos;
+    a.sigma = sigma;
+    a.J = J;
+    a.chi = chi;
+    a.q0 = q0;
+    a.q_out = q;
+    a.energies = energies;
+    a.forces = forces;
+    hipEvent_t e0 = nullptr, e1 = nullptr;
+    (void)hipEventCreate(&e0);
+    (void)hipEventCreate(&e1);
+    if (e0) (void)hipEventRecord(e0, pl->stream);
+    int rc2 = QEQ_OK;
+    // structures whose pair list overflowed go again with the measured size
+    for (int round = 0; round < 2 && !work.empty() && rc2 == QEQ_OK; ++round) {
         std::vector<int> again;
-        long long need = 0;
-        for (int s : work)
-            if (hst[s].status == BQ_OVERFLOW) {
-                again.push_back(s);
-                need = std::max(need, hst[s].nnz);
+        // as many structures at a time as BQ_SCRATCH holds (at least one); half
+        // of that after a failed allocation
+        size_t limit = BQ_SCRATCH;
+        for (size_t w0 = 0; w0 < work.size() && rc2 == QEQ_OK;) {
+            size_t used = 0, w1 = w0;
+            for (; w1 < work.size(); ++w1) {
+                BStruct& S = st[work[w1]];
+                const size_t bytes = slot_layout(S);
+                if (w1 > w0 && used + bytes > limit) break;
+                S.base = used;
+                used += bytes;
             }
+            rc2 = grow(&b->scratch, &b->scratch_cap, used);
+            if (rc2 == QEQ_ENOMEM && w1 - w0 > 1) {
+                (void)hipGetLastError();
+                limit = used / 2;
+                rc2 = QEQ_OK;
+                continue;
+            }
+            if (rc2 != QEQ_OK) break;
+            const std::vector<int> wave(work.begin() + w0, work.begin() + w1);
+            rc2 = run_wave(pl, b, a, st, wave, twh, bmh, state);
+            for (int s : wave)
+                if (rc2 == QEQ_OK && state[s].status == BQ_OVERFLOW) {
+                    again.push_back(s);
+                    st[s].pcap = (long long)state[s].nnz;
+                }
+            w0 = w1;
+        }
         work.swap(again);
-        pcap = std::max(pcap, need);
     }
-    b->last_stats = hst;
+    if (e1) (void)hipEventRecord(e1, pl->stream);
+    if (e1) (void)hipEventSynchronize(e1);
+    float ms = 0.f;
+    if (rc2 == QEQ_OK && e0 && e1 && hipEventElapsedTime(&ms, e0, e1) == hipSuccess) b->last_ms += ms;
+    if (e0) (void)hipEventDestroy(e0);
+    if (e1) (void)hipEventDestroy(e1);
+    if (rc2 != QEQ_OK) {
+        (void)hipStreamSynchronize(pl->stream);   // nothing of this call stays in flight
+        return rc2;
+    }
+    b->last_state = state;
     int worst = QEQ_OK;
     for (int s = 0; s < n_struct; ++s) {
-        int code = hst[s].status;
+        int code = state[s].status;
         if (code == BQ_OVERFLOW) code = QEQ_ENOMEM;
         if (stats) {
             qeq_stats& o = stats[s];
             memset(&o, 0, sizeof(o));
             o.status = code;
-            o.iters = hst[s].iters;
-            o.rel_resid = hst[s].rel_resid;
-            o.true_rel_resid = hst[s].true_rel_resid;
-            o.mu = hst[s].mu;
-            o.e_qeq = hst[s].e_qeq;
-            o.e_elec = hst[s].e_elec;
-            o.q0_rejected = hst[s].q0_rejected;
+            o.iters = state[s].iters;
+            o.rel_resid = state[s].res;
+            o.true_rel_resid = state[s].tres;
+            o.mu = state[s].mu;
+            o.e_qeq = state[s].e_qeq;
+            o.e_elec = state[s].e_elec;
+            o.q0_rejected = state[s].q0_rejected;
         }
         if (code < 0) {
             if (worst >= 0 || code < worst) worst = code;
@@ -1519,10 +1679,16 @@ int qeq_batched_config(qeq_plan* plan, int32_t threads, int32_t wg_per_cu) {
 
 int qeq_batched_phase_us(qeq_plan* plan, int32_t n_struct, double* us) {
     if (!plan || !plan->batch || !us || n_struct < 0) return QEQ_EINVAL;
-    const std::vector<BStat>& v = plan->batch->last_stats;
+    const std::vector<BState>& v = plan->batch->last_state;
     if ((size_t)n_struct > v.size()) return QEQ_EINVAL;
-    for (int s = 0; s < n_struct; ++s)
-        for (int k = 0; k <= PH_COUNT; ++k) us[s * (PH_COUNT + 1) + k] = (double)v[s].ticks[k] * 0.01;
+    for (int s = 0; s < n_struct; ++s) {
+        double* row = us + (size_t)s * (PH_COUNT + 1);
+        row[PH_COUNT] = 0.0;
+        for (int k = 0; k < PH_COUNT; ++k) {
+            row[k] = (double)v[s].ticks[k] * 0.01;
+            row[PH_COUNT] += row[k];
+        }
+    }
     return PH_COUNT + 1;
 }
 
