@@ -471,6 +471,32 @@ __device__ __forceinline__ void bq_fft_lines(float2* buf, int K, const float2* t
     }
 }
 
+// Element t = (j K2 + g2) K3h + m of a block's half spectra, for t = tid, tid +
+// BQ_NT, ...: carries instead of two divisions per element.
+struct BqWalk {
+    int K2, K3h, dr, dm, j, g2, m;
+    __device__ __forceinline__ BqWalk(int tid, int k2, int k3h) : K2(k2), K3h(k3h) {
+        dr = BQ_NT / K3h;
+        dm = BQ_NT - dr * K3h;
+        const int r = tid / K3h;
+        m = tid - r * K3h;
+        j = r / K2;
+        g2 = r - j * K2;
+    }
+    __device__ __forceinline__ void next() {
+        m += dm;
+        g2 += dr;
+        if (m >= K3h) {
+            m -= K3h;
+            ++g2;
+        }
+        while (g2 >= K2) {
+            g2 -= K2;
+            ++j;
+        }
+    }
+};
+
 // The atoms that reach each of a block's planes: those with home planes g1 ..
 // g1 + p - 1, one (wrapped) index range per plane.  first / cnt in LDS, off =
 // their running total.
@@ -593,27 +619,30 @@ __global__ __launch_bounds__(BQ_NT) void k_bq_fwd(BArgs a, const int2* __restric
         __syncthreads();
     }
     bq_fft_lines<false>(buf, K3, tw3, tid);
-    // the two rows' half spectra: X2[g2][j K3h + m3]
+    // the two rows' half spectra: X2[g2][j K3h + m3], a thread keeps its row
     const int rows = planes * K2;
-    for (int t = tid; t < rows * K3h; t += BQ_NT) {
-        const int m = t / rows, r = t - m * rows;   // consecutive lanes: consecutive rows
-        const int c = r >> 1, j = r / K2, g2 = r - j * K2;
-        const float2 Z = buf[m * BQ_KS + c];
-        float2 Zc = buf[(m == 0 ? 0 : K3 - m) * BQ_KS + c];
-        Zc.y = -Zc.y;
-        const float2 d = csub(Z, Zc);
-        const float2 ev = make_float2(0.5f * (Z.x + Zc.x), 0.5f * (Z.y + Zc.y));
-        const float2 od = make_float2(0.5f * d.y, -0.5f * d.x);
-        X2[g2 * BQ_KS2 + j * K3h + m] = (r & 1) ? od : ev;
+    {
+        const int r = tid & (2 * BQ_NC - 1);
+        if (r < rows) {
+            const int j = r / K2, g2 = r - j * K2;
+            const float2* z = buf + (r >> 1);
+            float2* x = X2 + g2 * BQ_KS2 + j * K3h;
+            for (int m = tid / (2 * BQ_NC); m < K3h; m += BQ_NT / (2 * BQ_NC)) {
+                const float2 Z = z[m * BQ_KS];
+                float2 Zc = z[(m == 0 ? 0 : K3 - m) * BQ_KS];
+                Zc.y = -Zc.y;
+                const float2 d = csub(Z, Zc);
+                const float2 ev = make_float2(0.5f * (Z.x + Zc.x), 0.5f * (Z.y + Zc.y));
+                const float2 od = make_float2(0.5f * d.y, -0.5f * d.x);
+                x[m] = (r & 1) ? od : ev;
+            }
+        }
     }
     __syncthreads();
     bq_fft_axis2<false>(X2, K2, tw2, tid);
     float2* C = slot_ptr<float2>(a, S, S.slot.C) + (size_t)g1a * K2 * K3h;
-    for (int t = tid; t < rows * K3h; t += BQ_NT) {
-        const int r = t / K3h, m = t - r * K3h;
-        const int j = r / K2, g2 = r - j * K2;
-        C[t] = X2[g2 * BQ_KS2 + j * K3h + m];
-    }
+    BqWalk w(tid, K2, K3h);
+    for (int t = tid; t < rows * K3h; t += BQ_NT, w.next()) C[t] = X2[w.g2 * BQ_KS2 + w.j * K3h + w.m];
     if (tid == 0) bq_lap(T, PH_FFT, t0);
 }
 
@@ -692,24 +721,31 @@ __device__ __forceinline__ void bq_planes_inv(const BArgs& a, const BStruct& S, 
         const int t = tid + q * BQ_NT;
         if (t < rows * K3h) v[q] = C[t];
     }
+    BqWalk w(tid, K2, K3h);
 #pragma unroll
     for (int q = 0; q < PER; ++q) {
-        const int t = tid + q * BQ_NT;
-        if (t < rows * K3h) {
-            const int r = t / K3h, m = t - r * K3h;
-            const int j = r / K2, g2 = r - j * K2;
-            X2[g2 * BQ_KS2 + j * K3h + m] = v[q];
-        }
+        if (tid + q * BQ_NT < rows * K3h) X2[w.g2 * BQ_KS2 + w.j * K3h + w.m] = v[q];
+        w.next();
     }
     __syncthreads();
     bq_fft_axis2<true>(X2, K2, tw2, tid);
-    const int half = rows >> 1;
-    for (int t = tid; t < K3h * half; t += BQ_NT) {
-        const int m = t / half, c = t - m * half;
-        const int r = 2 * c, j = r / K2, g2 = r - j * K2;
-        const float2 xa = X2[g2 * BQ_KS2 + j * K3h + m], xb = X2[(g2 + 1) * BQ_KS2 + j * K3h + m];
-        buf[m * BQ_KS + c] = make_float2(xa.x - xb.y, xa.y + xb.x);
-        if (m > 0 && 2 * m < K3) buf[(K3 - m) * BQ_KS + c] = make_float2(xa.x + xb.y, xb.x - xa.y);
+    // a thread keeps its row; the even one of a pair packs Z(m), the odd one Z(K3 - m)
+    {
+        const int r = tid & (2 * BQ_NC - 1);
+        const int j = r / K2, g2 = r - j * K2;
+        const float2* x = X2 + g2 * BQ_KS2 + j * K3h;
+        float2* z = buf + (r >> 1);
+        const bool odd = (r & 1) != 0;
+        if (r < rows) {   // whole pairs: rows is even
+            for (int m = tid / (2 * BQ_NC); m < K3h; m += BQ_NT / (2 * BQ_NC)) {
+                const float2 own = x[m];
+                const float2 oth = make_float2(__shfl_xor(own.x, 1, 64), __shfl_xor(own.y, 1, 64));
+                if (!odd)
+                    z[m * BQ_KS] = make_float2(own.x - oth.y, own.y + oth.x);
+                else if (m > 0 && 2 * m < K3)
+                    z[(K3 - m) * BQ_KS] = make_float2(oth.x + own.y, own.x - oth.y);
+            }
+        }
     }
     __syncthreads();
     bq_fft_lines<true>(buf, K3, tw3, tid);
