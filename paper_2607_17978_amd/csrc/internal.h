@@ -36,7 +36,9 @@
 struct KParams {
     int n;
     int p;                    // spline order
-    int K1, K2, K3, K3h;      // grid; K3h = K3 / 2 + 1 (half spectrum along axis 3)
+    int K1, K2, K3;           // grid
+    int K3h;                  // m3 planes of the half spectrum that are kept (at most K3 / 2 + 1)
+    int M2;                   // kept along axis 2: |m2| <= M2 (K2: all)
     int TW, TWlog2, ntile;    // axis-2 row tile of the C2R and axis-1 passes
     int TWS, ntile_s;         // axis-2 row tile of the spread + R2C pass
     int NR, NRlog2;           // rows per block of the axis-2 pass

@@ -50,11 +50,12 @@ namespace {
 //   row scales are finer.
 //   Then two real rows per complex line for the axis-3 transform (the
 //   conversion inside its first radix stage), their half spectra unpacked
-//   to X[g2][m3] (row stride K3/2 + 1), the axis-2 transform of every m3
-//   column, and C[m3][g1][m2] written.
+//   to X[g2][m3] (row stride K3/2 + 1), the axis-2 transform of NCOL m3
+//   columns (at least the kept ones: 80 of 97 at 192^3 are one round of
+//   radix-16 butterflies for the block, 97 two), and C[m3][g1][m2] written.
 constexpr int PLANE_NT = 1024;
 
-template <int K2C, int K3C>
+template <int K2C, int K3C, int NCOL>
 __global__ __launch_bounds__(PLANE_NT) void k_plane_fwd(KParams k, FftAxis ax2, FftAxis ax3,
                                                        const double* __restrict__ src,
                                                        const int* __restrict__ bin_start,
@@ -260,7 +261,7 @@ __global__ __launch_bounds__(PLANE_NT) void k_plane_fwd(KParams k, FftAxis ax2, 
     // unpack the two rows' half spectra, m3 = 0 .. K3/2: every LDS read of the
     // thread first (the rows overwrite the packed lines)
     {
-        constexpr int NI = NP * KS, PI = (NI + PLANE_NT - 1) / PLANE_NT;
+        constexpr int NI = NP * NCOL, PI = (NI + PLANE_NT - 1) / PLANE_NT;
         float2 za[PI], zb[PI];
 #pragma unroll
         for (int u = 0; u < PI; ++u) {
@@ -285,13 +286,13 @@ __global__ __launch_bounds__(PLANE_NT) void k_plane_fwd(KParams k, FftAxis ax2, 
         }
         __syncthreads();
     }
-    // axis-2 transform of every m3 column, then C[m3][g1][m2]
-    fft_ct<K2C, KS, KS, PLANE_NT, false>(X, tw2, tid);
+    // axis-2 transform of the first NCOL m3 columns, then C[m3][g1][m2]
+    fft_ct<K2C, NCOL, KS, PLANE_NT, false>(X, tw2, tid);
     __syncthreads();
 #pragma unroll 4
-    for (int t = tid; t < KS * K2C; t += PLANE_NT) {
+    for (int t = tid; t < k.K3h * K2C; t += PLANE_NT) {
         const int m3 = t / K2C, m2 = t - m3 * K2C;
-        C[((size_t)m3 * K1 + g1) * K2C + m2] = X[m2 * KS + m3];
+        if (m2_kept(k, m2)) C[((size_t)m3 * K1 + g1) * K2C + m2] = X[m2 * KS + m3];
     }
 }
 
@@ -314,7 +315,7 @@ __global__ __launch_bounds__(PLANE_NT) void k_plane_fwd(KParams k, FftAxis ax2, 
 //   here), as the fused tile pass does.
 constexpr int SLAB_NT = 1024;
 
-template <int K2C, int K3C, bool INTERP = false>
+template <int K2C, int K3C, int NCOL, bool INTERP = false>
 __global__ __launch_bounds__(SLAB_NT) void k_slab_inv(KParams k, FftAxis ax2, FftAxis ax3,
                                                      const float2* __restrict__ C, float* __restrict__ R,
                                                      const int* __restrict__ done,
@@ -349,12 +350,16 @@ __global__ __launch_bounds__(SLAB_NT) void k_slab_inv(KParams k, FftAxis ax2, Ff
             bhi[k1] = bin_start[(h1 + 1) * K2C];
         }
     }
-    // The three twiddle tables (K2C + K3C + NH entries) and the plane, in two
-    // groups of m3 columns: the axis-2 transforms of the first group run
-    // while the second group's loads are in flight (barriers wait on LDS
-    // only), and the columns are independent.
-    constexpr int CA = (K3H + 1) / 2, CB = K3H - CA;
-    auto ld_col = [&](int m3, int m2) { return C[((size_t)m3 * K1 + g1) * K2C + m2]; };
+    // The three twiddle tables (K2C + K3C + NH entries) and the plane's first
+    // NCOL m3 columns (at least the kept ones; the others are zero).  All
+    // columns: in two groups, the axis-2 transforms of the first running while
+    // the second's loads are in flight (barriers wait on LDS only).  Fewer: in
+    // one, whose radix-16 stage is then one round of the block (192^3: 80
+    // columns).
+    constexpr int CA = NCOL == K3H ? (K3H + 1) / 2 : NCOL, CB = NCOL - CA;
+    auto ld_col = [&](int m3, int m2) {
+        return m3 < k.K3h && m2_kept(k, m2) ? C[((size_t)m3 * K1 + g1) * K2C + m2] : make_float2(0.f, 0.f);
+    };
     {
         auto ld_tw = [&](int t) {
             return t < K2C ? ax2.tw[t] : (t < K2C + K3C ? ax3.tw[t - K2C] : ax3.tw[2 * (t - K2C - K3C)]);
@@ -370,8 +375,12 @@ __global__ __launch_bounds__(SLAB_NT) void k_slab_inv(KParams k, FftAxis ax2, Ff
         };
         stage2_ct<K2C + K3C + NH, CA * K2C, SLAB_NT, float2>(tid, ld_tw, st_tw, ld, st);
     }
+    for (int t = tid; t < (K3H - NCOL) * K2C; t += SLAB_NT) {
+        const int m3 = t / K2C, m2 = t - m3 * K2C;
+        X[m2 * KS + NCOL + m3] = make_float2(0.f, 0.f);
+    }
     constexpr int PB = (CB * K2C + SLAB_NT - 1) / SLAB_NT;
-    float2 vb[PB];
+    float2 vb[PB > 0 ? PB : 1];
 #pragma unroll
     for (int u = 0; u < PB; ++u) {
         const int t = tid + u * SLAB_NT;
@@ -382,16 +391,18 @@ __global__ __launch_bounds__(SLAB_NT) void k_slab_inv(KParams k, FftAxis ax2, Ff
     }
     __syncthreads();
     fft_ct<K2C, CA, KS, SLAB_NT, true>(X, tw2, tid);
+    if constexpr (CB > 0) {
 #pragma unroll
-    for (int u = 0; u < PB; ++u) {
-        const int t = tid + u * SLAB_NT;
-        if ((CB * K2C) % SLAB_NT == 0 || t < CB * K2C) {
-            const int m3 = t / K2C, m2 = t - m3 * K2C;
-            X[m2 * KS + CA + m3] = vb[u];
+        for (int u = 0; u < PB; ++u) {
+            const int t = tid + u * SLAB_NT;
+            if ((CB * K2C) % SLAB_NT == 0 || t < CB * K2C) {
+                const int m3 = t / K2C, m2 = t - m3 * K2C;
+                X[m2 * KS + CA + m3] = vb[u];
+            }
         }
+        __syncthreads();
+        fft_ct<K2C, CB, KS, SLAB_NT, true>(X + CA, tw2, tid);
     }
-    __syncthreads();
-    fft_ct<K2C, CB, KS, SLAB_NT, true>(X + CA, tw2, tid);
     // Length-NH inverse transform along each row g2 of the packed sequence
     // z(n) = (X(n) + conj X(NH - n)) + i (X(n) - conj X(NH - n)) e^{2 pi i n / K3}
     // (two real outputs per complex one).  Its first radix stage builds z
@@ -534,7 +545,7 @@ size_t smem_spread(const KParams& k) {
 size_t smem_rows(const KParams& k) { return sizeof(float2) * ((size_t)k.K2 + (size_t)k.K2 * (k.NR + 1)); }
 size_t smem_cols(const KParams& k) { return sizeof(float2) * ((size_t)k.K1 + (size_t)k.K1 * k.TW); }
 size_t smem_c2r(const KParams& k) {
-    return sizeof(float2) * ((size_t)k.K3 + (size_t)k.K3h * k.TW + (size_t)k.K3 * (k.TW / 2));
+    return sizeof(float2) * ((size_t)k.K3 + (size_t)(k.K3 / 2 + 1) * k.TW + (size_t)k.K3 * (k.TW / 2));
 }
 
 // Lengths with uniform tiles of their own; other lengths take the ragged tiles
@@ -680,7 +691,7 @@ int c2r_interp_pass(qeq_plan* pl, const int* done) {
     const KParams& k = pl->kp;
     dim3 g(k.K1 * k.ntile), b(NT);
     const size_t sh = smem_c2r(k);
-    const size_t sh_ct = sizeof(float2) * ((size_t)k.K3 + (size_t)k.K3h * k.TW);   // Z in place of X
+    const size_t sh_ct = sizeof(float2) * ((size_t)k.K3 + (size_t)(k.K3 / 2 + 1) * k.TW);   // Z in place of X
     ProfScope ps(pl, PK_C2R);
     if (k.rag)
         return mesh_len({pl, LEN_C2R_INTERP, nullptr, 0, nullptr, nullptr, nullptr, nullptr, done, ps.start(), ps.stop()},
@@ -702,60 +713,56 @@ size_t smem_slab(int K2, int K3) {
     return sizeof(float2) * ((size_t)K2 + K3 + K3 / 2 + (size_t)K2 * (K3 / 2 + 1));
 }
 
-// Lengths with a fused slab kernel; the slab must fit the LDS of one CU.
-#define QEQ_FOR_EACH_SLAB(X) X(96, 96) X(192, 192)
+// Lengths with a fused slab kernel; the slab must fit the LDS of one CU.  Third:
+// the m3 columns of the narrower instance.
+#define QEQ_FOR_EACH_SLAB(X) X(96, 96, 40) X(192, 192, 80)
 
 bool slab_available(const qeq_plan* pl) {
     const KParams& k = pl->kp;
     if (!pl->fused_inverse || k.K1 < 64) return false;
-#define X(A, B) if (k.K2 == A && k.K3 == B) return true;
+#define X(A, B, N) if (k.K2 == A && k.K3 == B) return true;
     QEQ_FOR_EACH_SLAB(X)
 #undef X
     return false;
 }
 
-int slab_interp_pass(qeq_plan* pl, const int* done) {
+template <int A, int B, int N, bool INTERP>
+int slab_launch(qeq_plan* pl, const int* done, hipEvent_t e0, hipEvent_t e1) {
+    const KParams& k = pl->kp;
+    const size_t sh = smem_slab(A, B);
+    QEQ_HIP(hipFuncSetAttribute((const void*)k_slab_inv<A, B, N, INTERP>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                (int)sh));
+    hipExtLaunchKernelGGL((k_slab_inv<A, B, N, INTERP>), dim3(k.K1), dim3(SLAB_NT), sh, pl->stream, e0, e1, 0, k,
+                          pl->axes.ax[1], pl->axes.ax[2], pl->grid_c, pl->grid_r, done,
+                          INTERP ? pl->bin_start : nullptr, INTERP ? pl->home : nullptr, INTERP ? pl->wts : nullptr,
+                          INTERP ? pl->mpart : nullptr);
+    return qeq_check(hipGetLastError());
+}
+
+template <bool INTERP>
+int slab_pass(qeq_plan* pl, const int* done) {
     const KParams& k = pl->kp;
     ProfScope ps(pl, PK_C2R);
-#define X(A, B)                                                                                    \
-    if (k.K2 == A && k.K3 == B && k.p == 6) {                                                      \
-        const size_t sh = smem_slab(A, B);                                                         \
-        QEQ_HIP(hipFuncSetAttribute((const void*)k_slab_inv<A, B, true>,                           \
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh));         \
-        hipExtLaunchKernelGGL((k_slab_inv<A, B, true>), dim3(k.K1), dim3(SLAB_NT), sh, pl->stream, ps.start(), \
-                              ps.stop(), 0, k, pl->axes.ax[1], pl->axes.ax[2], pl->grid_c, pl->grid_r, done, \
-                              pl->bin_start, pl->home, pl->wts, pl->mpart);                         \
-        return qeq_check(hipGetLastError());                                                       \
+#define X(A, B, N)                                                                             \
+    if (k.K2 == A && k.K3 == B && (!INTERP || k.p == 6)) {                                      \
+        if (k.K3h <= N) return slab_launch<A, B, N, INTERP>(pl, done, ps.start(), ps.stop());   \
+        return slab_launch<A, B, B / 2 + 1, INTERP>(pl, done, ps.start(), ps.stop());           \
     }
     QEQ_FOR_EACH_SLAB(X)
 #undef X
     return QEQ_EPLAN;
 }
+
+int slab_interp_pass(qeq_plan* pl, const int* done) { return slab_pass<true>(pl, done); }
 
 bool slab_interp_available(const qeq_plan* pl) {
     return slab_available(pl) && pl->fused_interp && pl->kp.p == 6 && pl->mpart != nullptr;
 }
 
-int slab_inv_pass(qeq_plan* pl, const int* done) {
-    const KParams& k = pl->kp;
-    ProfScope ps(pl, PK_C2R);
-#define X(A, B)                                                                                    \
-    if (k.K2 == A && k.K3 == B) {                                                                  \
-        const size_t sh = smem_slab(A, B);                                                         \
-        QEQ_HIP(hipFuncSetAttribute((const void*)k_slab_inv<A, B>,                                 \
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh));         \
-        hipExtLaunchKernelGGL((k_slab_inv<A, B>), dim3(k.K1), dim3(SLAB_NT), sh, pl->stream, ps.start(), \
-                              ps.stop(), 0, k, pl->axes.ax[1], pl->axes.ax[2], pl->grid_c, pl->grid_r, done, \
-                              nullptr, nullptr, nullptr, nullptr);                                  \
-        return qeq_check(hipGetLastError());                                                       \
-    }
-    QEQ_FOR_EACH_SLAB(X)
-#undef X
-    return QEQ_EPLAN;
-}
+int slab_inv_pass(qeq_plan* pl, const int* done) { return slab_pass<false>(pl, done); }
 
 // Lengths with a fused forward plane kernel (spread + axis-3 + axis-2).
-#define QEQ_FOR_EACH_PLANE_FWD(X) X(192, 192)
+#define QEQ_FOR_EACH_PLANE_FWD(X) X(192, 192, 80)
 
 size_t smem_plane_fwd(int K2, int K3) {
     return sizeof(float2) * ((size_t)K2 + K3 + (size_t)K2 * (K3 / 2 + 1));
@@ -764,24 +771,30 @@ size_t smem_plane_fwd(int K2, int K3) {
 bool plane_fwd_available(const qeq_plan* pl) {
     const KParams& k = pl->kp;
     if (!pl->fused_forward || k.K1 < 64 || k.p != 6) return false;
-#define X(A, B) if (k.K2 == A && k.K3 == B) return true;
+#define X(A, B, N) if (k.K2 == A && k.K3 == B) return true;
     QEQ_FOR_EACH_PLANE_FWD(X)
 #undef X
     return false;
 }
 
+template <int A, int B, int N>
+int plane_fwd_launch(qeq_plan* pl, const double* src, const int* done, hipEvent_t e0, hipEvent_t e1) {
+    const KParams& k = pl->kp;
+    const size_t sh = smem_plane_fwd(A, B);
+    QEQ_HIP(hipFuncSetAttribute((const void*)k_plane_fwd<A, B, N>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                (int)sh));
+    hipExtLaunchKernelGGL((k_plane_fwd<A, B, N>), dim3(k.K1), dim3(PLANE_NT), sh, pl->stream, e0, e1, 0, k,
+                          pl->axes.ax[1], pl->axes.ax[2], src, pl->bin_start, pl->home, pl->wts, pl->grid_c, done);
+    return qeq_check(hipGetLastError());
+}
+
 int plane_fwd_pass(qeq_plan* pl, const double* src, const int* done) {
     const KParams& k = pl->kp;
     ProfScope ps(pl, PK_SPREAD_R2C);
-#define X(A, B)                                                                                    \
+#define X(A, B, N)                                                                                  \
     if (k.K2 == A && k.K3 == B && k.p == 6) {                                                      \
-        const size_t sh = smem_plane_fwd(A, B);                                                    \
-        QEQ_HIP(hipFuncSetAttribute((const void*)k_plane_fwd<A, B>,                                \
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh));         \
-        hipExtLaunchKernelGGL((k_plane_fwd<A, B>), dim3(k.K1), dim3(PLANE_NT), sh, pl->stream, ps.start(), \
-                              ps.stop(), 0, k, pl->axes.ax[1], pl->axes.ax[2], src, pl->bin_start, \
-                              pl->home, pl->wts, pl->grid_c, done);                                 \
-        return qeq_check(hipGetLastError());                                                       \
+        if (k.K3h <= N) return plane_fwd_launch<A, B, N>(pl, src, done, ps.start(), ps.stop());    \
+        return plane_fwd_launch<A, B, B / 2 + 1>(pl, src, done, ps.start(), ps.stop());            \
     }
     QEQ_FOR_EACH_PLANE_FWD(X)
 #undef X

@@ -17,6 +17,9 @@ constexpr int NT = QEQ_FFT_THREADS;
 
 __device__ __forceinline__ int ilog2_dev(int x) { return 31 - __clz(x); }
 
+// Whether the passes carry index m2 (KParams::M2).
+__device__ __forceinline__ bool m2_kept(const KParams& k, int m2) { return m2 <= k.M2 || m2 >= k.K2 - k.M2; }
+
 // First row and row count of axis-2 tile t.  Uniform tiles of TW rows, or
 // (RAG) ntile tiles of an even number of rows, at most TW, as equal as
 // possible: any axis-2 length, no tile much narrower than the others (an
@@ -277,7 +280,7 @@ __global__ __launch_bounds__(NT) void k_spread_r2c(KParams k, FftAxis ax3, const
         fft_lds(buf, ax3, ilog2_dev(ncol), tw, false, tid, NT);
     }
     // unpack the two real rows of each complex column and write the half spectra
-    const int K3h = K3 / 2 + 1;
+    const int K3h = k.K3h;
     if constexpr (KC > 0 && TWC > 0) {
         // compile-time tiles: every LDS read of the thread first, then the
         // unpacking (both rows' formulas, selected) and the stores
@@ -288,6 +291,7 @@ __global__ __launch_bounds__(NT) void k_spread_r2c(KParams k, FftAxis ax3, const
             const int t = tid + u * NT;
             if (NW % NT == 0 || t < NW) {
                 const int m = t / TWC, pr = (t - m * TWC) >> 1;
+                if (m >= k.K3h) break;   // planes that are not kept
                 zv[u] = buf[m * NCS + pr];
                 zc[u] = buf[(m == 0 ? 0 : KC - m) * NCS + pr];
             }
@@ -297,6 +301,7 @@ __global__ __launch_bounds__(NT) void k_spread_r2c(KParams k, FftAxis ax3, const
             const int t = tid + u * NT;
             if (NW % NT == 0 || t < NW) {
                 const int m = t / TWC, r = t - m * TWC;
+                if (m >= k.K3h) break;
                 const float2 Z = zv[u], Zc = make_float2(zc[u].x, -zc[u].y);
                 const float2 ev = make_float2(0.5f * (Z.x + Zc.x), 0.5f * (Z.y + Zc.y));
                 const float2 d = csub(Z, Zc);
@@ -345,7 +350,8 @@ __global__ __launch_bounds__(NT) void k_fft_rows(KParams k, FftAxis ax2, float2*
     auto st_tw = [&](int t, float2 v) { tw[t] = v; };
     auto ld = [&](int t) {
         const int row = t / K2, kk = t - row * K2;
-        return (row0 + row < nrows) ? C[(size_t)(row0 + row) * K2 + kk] : make_float2(0.f, 0.f);
+        return (row0 + row < nrows && (!INV || m2_kept(k, kk))) ? C[(size_t)(row0 + row) * K2 + kk]
+                                                                 : make_float2(0.f, 0.f);
     };
     auto st = [&](int t, float2 v) {
         const int row = t / K2, kk = t - row * K2;
@@ -368,7 +374,7 @@ __global__ __launch_bounds__(NT) void k_fft_rows(KParams k, FftAxis ax2, float2*
     };
     auto st_out = [&](int t, float2 v) {
         const int row = t / K2, kk = t - row * K2;
-        if (row0 + row < nrows) C[(size_t)(row0 + row) * K2 + kk] = v;
+        if (row0 + row < nrows && (INV || m2_kept(k, kk))) C[(size_t)(row0 + row) * K2 + kk] = v;
     };
     if constexpr (KC > 0 && NRC > 0)
         stage_ct<NRC * KC, NT, float2>(tid, ld_out, st_out);   // LDS reads first, then the stores
@@ -422,6 +428,7 @@ __global__ __launch_bounds__(NT) void k_fft_cols(KParams k, FftAxis ax1, float2*
     const int m3 = blockIdx.x / k.ntile;
     int g20, W;
     tile_of<RAG>(blockIdx.x - m3 * k.ntile, k.ntile, K2, TW, g20, W);
+    if (!m2_kept(k, g20) && !m2_kept(k, g20 + W - 1)) return;   // no column of the tile is kept
     float2* base = C + (size_t)m3 * K1 * K2 + g20;
     constexpr bool CT = KC > 0 && TWC > 0;
     if constexpr (CT) {
@@ -442,7 +449,7 @@ __global__ __launch_bounds__(NT) void k_fft_cols(KParams k, FftAxis ax1, float2*
             constexpr int ITL = (PERL * TWC + NT - 1) / NT;
             constexpr int PT = (KC + NT - 1) / NT;
             const int c = tid & (TWC - 1);
-            const bool live = !RAG || c < W;   // the columns of a narrower tile
+            const bool live = (!RAG || c < W) && m2_kept(k, g20 + c);
             const int m2 = live ? g20 + c : g20;
             float2 twv[PT], v[IT0][R0];
             float bmv[IT0][R0];
@@ -577,7 +584,7 @@ __global__ __launch_bounds__(NT) void k_fft_cols(KParams k, FftAxis ax1, float2*
     auto st_tw = [&](int t, float2 v) { tw[t] = v; };
     auto ld = [&](int t) {
         const int c = t & (TW - 1), g1 = t >> twl;
-        return !RAG || c < W ? base[(size_t)g1 * K2 + c] : make_float2(0.f, 0.f);
+        return (!RAG || c < W) && m2_kept(k, g20 + c) ? base[(size_t)g1 * K2 + c] : make_float2(0.f, 0.f);
     };
     auto st = [&](int t, float2 v) { buf[t] = v; };
     if constexpr (CT) {
@@ -650,7 +657,7 @@ __global__ __launch_bounds__(NT) void k_fft_cols(KParams k, FftAxis ax1, float2*
     }
     for (int t = tid; t < K1 * TW; t += NT) {
         const int c = t & (TW - 1), g1 = t >> twl;
-        if (!RAG || c < W) base[(size_t)g1 * K2 + c] = buf[t];
+        if ((!RAG || c < W) && m2_kept(k, g20 + c)) base[(size_t)g1 * K2 + c] = buf[t];
     }
 }
 
@@ -679,7 +686,7 @@ __global__ __launch_bounds__(NT) void k_c2r(KParams k, FftAxis ax3, const float2
         auto st_tw = [&](int t, float2 v) { tw[t] = v; };
         auto ld = [&](int t) {
             const int r = t & (TW - 1), m = t >> twl;
-            return !RAG || r < W ? C[((size_t)m * K1 + g1) * K2 + g20 + r] : make_float2(0.f, 0.f);
+            return m < k.K3h && (!RAG || r < W) ? C[((size_t)m * K1 + g1) * K2 + g20 + r] : make_float2(0.f, 0.f);
         };
         auto st = [&](int t, float2 v) { X[t] = v; };
         if constexpr (KC > 0 && TWC > 0) {
@@ -785,7 +792,7 @@ __global__ __launch_bounds__(NT) void k_c2r_interp(KParams k, FftAxis ax3, const
         auto st_tw = [&](int t, float2 v) { tw[t] = v; };
         auto ld = [&](int t) {
             const int r = t & (TW - 1), m = t >> twl;
-            return !RAG || r < W ? C[((size_t)m * K1 + g1) * K2 + g20 + r] : make_float2(0.f, 0.f);
+            return m < k.K3h && (!RAG || r < W) ? C[((size_t)m * K1 + g1) * K2 + g20 + r] : make_float2(0.f, 0.f);
         };
         auto st = [&](int t, float2 v) { X[t] = v; };
         if constexpr (CT) {
@@ -958,7 +965,7 @@ __global__ __launch_bounds__(NT) void k_cols_virial(KParams k, FftAxis ax1, cons
     const float2* base = C + (size_t)m3 * K1 * K2 + g20;
     for (int t = tid; t < K1 * TW; t += NT) {
         const int c = t & (TW - 1), g1 = t >> twl;
-        buf[t] = !RAG || c < W ? base[(size_t)g1 * K2 + c] : make_float2(0.f, 0.f);
+        buf[t] = (!RAG || c < W) && m2_kept(k, g20 + c) ? base[(size_t)g1 * K2 + c] : make_float2(0.f, 0.f);
     }
     __syncthreads();
     if constexpr (KC > 0 && TWC > 0)
@@ -970,7 +977,7 @@ __global__ __launch_bounds__(NT) void k_cols_virial(KParams k, FftAxis ax1, cons
     const float eta = (float)k.eta;
     for (int t = tid; t < K1 * TW; t += NT) {
         const int c = t & (TW - 1), m1 = t >> twl;
-        if (RAG && c >= W) continue;
+        if ((RAG && c >= W) || !m2_kept(k, g20 + c)) continue;
         const float g = green_value(k, m1, g20 + c, m3, b1, b2, b3);
         if (g == 0.f) continue;
         const float2 x = buf[t];
