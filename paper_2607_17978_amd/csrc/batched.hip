@@ -33,8 +33,8 @@ namespace qeqb {
 constexpr int BQ_KAX = 64;      // longest grid axis of a batched structure
 constexpr int BQ_NC = 64;       // complex lines of a block along axis 3 (two real rows each) and axis 1
 constexpr int BQ_KS = 65;       // their LDS row stride
-constexpr int BQ_NC2 = 66;      // half-spectrum columns of a block along axis 2
-constexpr int BQ_KS2 = 67;      // their LDS row stride
+constexpr int BQ_NC2 = 56;      // half-spectrum columns of a block along axis 2
+constexpr int BQ_KS2 = 57;      // their LDS row stride
 constexpr int BQ_NT = 512;      // threads of the plane and line kernels
 constexpr int BQ_PB = 8;        // most planes of a block
 constexpr int BQ_L = 8;         // lanes per atom in the interpolation and pair loops
@@ -51,12 +51,13 @@ enum { BQ_INIT = 0, BQ_ITER, BQ_FINAL };
 
 // Byte offsets inside one structure's scratch slot.
 struct BSlot {
-    unsigned C, G, wts, dwts, home, frac, vec, selfgrad, row, col, kval, pdr, tab, mpart, hstart, perm;
+    unsigned C, G, wts, dwts, home, frac, vec, selfgrad, row, col, kval, pdr, tab, mpart, hstart, perm, fpair;
 };
 
 // Per-structure constants prepared on the host.
 struct BStruct {
-    int n, off, nhalf, pb;      // atoms, first atom, half-spectrum points, planes of a block
+    int n, off, nhalf, pb;      // atoms, first atom, kept half-spectrum points, planes of a block
+    int km, nm2;                // kept modes: m3 < km, nm2 of the K2 axis-2 ones (|m2| <= (nm2 - 1) / 2, or all)
     int K[3], tw_off[3], bm_off[3];
     int mm[3], nn[3];           // ranges of the C_eta k-space and lattice sums
     double H[9], Hinv[9], M[6];
@@ -411,6 +412,9 @@ __global__ __launch_bounds__(256) void k_bq_pairs(BArgs a, const int2* __restric
     if (tid == 0) bq_lap(T, PH_PAIRS, t0);
 }
 
+// Axis-2 index of the kept row e of a plane of the half spectrum.
+__device__ __forceinline__ int bq_m2(const BStruct& S, int e) { return e < ((S.nm2 + 1) >> 1) ? e : e + (S.K[1] - S.nm2); }
+
 // Green's function of the split times the B-spline moduli (SI "Ewald
 // Summation" Gaussian filter, eq. matvec 4 pi / k^2) on the half spectrum
 // (m3 <= K3 / 2): zero at m = 0 and on the Nyquist planes, as in the
@@ -437,20 +441,22 @@ __global__ __launch_bounds__(256) void k_bq_green(BArgs a, const int2* __restric
     if (T.finished) return;
     const long long t0 = wall_clock64();
     float* G = slot_ptr<float>(a, S, S.slot.G);
-    const int K2 = S.K[1], K3h = S.K[2] / 2 + 1;
+    const int nm2 = S.nm2, K3h = S.km;
     const float *b1 = a.bmod + S.bm_off[0], *b2 = a.bmod + S.bm_off[1], *b3 = a.bmod + S.bm_off[2];
     const int end = min(S.nhalf, (u.y + 1) * BQ_GREEN);
     for (int t = u.y * BQ_GREEN + threadIdx.x; t < end; t += 256) {
         const int m3 = t % K3h, r = t / K3h;
-        G[t] = bq_green(S, a.eta, r / K2, r % K2, m3, b1, b2, b3);
+        G[t] = bq_green(S, a.eta, r / nm2, bq_m2(S, r % nm2), m3, b1, b2, b3);
     }
     if (threadIdx.x == 0) bq_lap(T, PH_MESHPREP, t0);
 }
 
 // ------------------------------------------------------------------ mesh
-// Layout in the slot: half spectrum C[g1][g2][m3], m3 = 0 .. K3/2
-// (contiguous); the Green's function G in the same layout.  Every axis length
-// of the batched path has a compile-time transform.
+// Layout in the slot: half spectrum C[g1][e][m3] of the kept modes (m3
+// contiguous, below km; e counts the kept m2), the Green's function G in the
+// same layout: modes with exp(-eta^2 k^2 / 2) below 2^-30 are left out as in
+// the single-structure passes (64% of the modes stay at 0.8 bohr and eta = 2).
+// Every axis length of the batched path has a compile-time transform.
 #define BQ_FOR_EACH_LEN(X) X(12) X(16) X(20) X(24) X(32) X(36) X(40) X(48) X(60) X(64)
 
 template <bool INV>
@@ -471,27 +477,31 @@ __device__ __forceinline__ void bq_fft_lines(float2* buf, int K, const float2* t
     }
 }
 
-// Element t = (j K2 + g2) K3h + m of a block's half spectra, for t = tid, tid +
-// BQ_NT, ...: carries instead of two divisions per element.
+// Element t = (j nm2 + e) km + m of a block's half spectra, for t = tid, tid +
+// BQ_NT, ...: carries instead of two divisions per element.  at: its place in
+// X2[m2][j km + m].
 struct BqWalk {
-    int K2, K3h, dr, dm, j, g2, m;
-    __device__ __forceinline__ BqWalk(int tid, int k2, int k3h) : K2(k2), K3h(k3h) {
-        dr = BQ_NT / K3h;
-        dm = BQ_NT - dr * K3h;
-        const int r = tid / K3h;
-        m = tid - r * K3h;
-        j = r / K2;
-        g2 = r - j * K2;
+    int nm2, km, half, skip, dr, dm, j, e, m;
+    __device__ __forceinline__ BqWalk(int tid, const BStruct& S) : nm2(S.nm2), km(S.km) {
+        half = (nm2 + 1) >> 1;
+        skip = S.K[1] - nm2;
+        dr = BQ_NT / km;
+        dm = BQ_NT - dr * km;
+        const int r = tid / km;
+        m = tid - r * km;
+        j = r / nm2;
+        e = r - j * nm2;
     }
+    __device__ __forceinline__ int at() const { return (e < half ? e : e + skip) * BQ_KS2 + j * km + m; }
     __device__ __forceinline__ void next() {
         m += dm;
-        g2 += dr;
-        if (m >= K3h) {
-            m -= K3h;
-            ++g2;
+        e += dr;
+        if (m >= km) {
+            m -= km;
+            ++e;
         }
-        while (g2 >= K2) {
-            g2 -= K2;
+        while (e >= nm2) {
+            e -= nm2;
             ++j;
         }
     }
@@ -524,7 +534,7 @@ __device__ __forceinline__ void bq_ranges(const int* hs, int K1, int n, int p, i
 // term is rounded to an integer by one FP64 fused multiply-add with 1.5 * 2^52
 // (its bit pattern minus the constant's is the integer, exact below 2^51).
 // Planes of a block: as many as fill 128 real rows (64 complex lines of two)
-// and 66 half-spectrum columns; its barriers then pass with two to five planes'
+// and 56 half-spectrum columns; its barriers then pass with two to five planes'
 // work behind them and two blocks share a CU.
 __global__ __launch_bounds__(BQ_NT) void k_bq_fwd(BArgs a, const int2* __restrict__ units, int mode) {
     extern __shared__ float2 lds[];
@@ -537,7 +547,7 @@ __global__ __launch_bounds__(BQ_NT) void k_bq_fwd(BArgs a, const int2* __restric
     __shared__ float2 tw3[BQ_KAX], tw2[BQ_KAX];
     __shared__ int first[BQ_PB], off[BQ_PB + 1];
     const int tid = threadIdx.x, n = S.n, p = a.p;
-    const int K1 = S.K[0], K2 = S.K[1], K3 = S.K[2], K3h = K3 / 2 + 1;
+    const int K1 = S.K[0], K2 = S.K[1], K3 = S.K[2], km = S.km;
     const int g1a = u.y * S.pb, planes = min(S.pb, K1 - g1a);
     const int RW = S.pb * K2;                                // accumulator rows
     long long* acc = reinterpret_cast<long long*>(lds);      // [K3][RW]
@@ -619,15 +629,15 @@ __global__ __launch_bounds__(BQ_NT) void k_bq_fwd(BArgs a, const int2* __restric
         __syncthreads();
     }
     bq_fft_lines<false>(buf, K3, tw3, tid);
-    // the two rows' half spectra: X2[g2][j K3h + m3], a thread keeps its row
+    // the two rows' half spectra: X2[g2][j km + m3], a thread keeps its row
     const int rows = planes * K2;
     {
         const int r = tid & (2 * BQ_NC - 1);
         if (r < rows) {
             const int j = r / K2, g2 = r - j * K2;
             const float2* z = buf + (r >> 1);
-            float2* x = X2 + g2 * BQ_KS2 + j * K3h;
-            for (int m = tid / (2 * BQ_NC); m < K3h; m += BQ_NT / (2 * BQ_NC)) {
+            float2* x = X2 + g2 * BQ_KS2 + j * km;
+            for (int m = tid / (2 * BQ_NC); m < km; m += BQ_NT / (2 * BQ_NC)) {
                 const float2 Z = z[m * BQ_KS];
                 float2 Zc = z[(m == 0 ? 0 : K3 - m) * BQ_KS];
                 Zc.y = -Zc.y;
@@ -640,16 +650,75 @@ __global__ __launch_bounds__(BQ_NT) void k_bq_fwd(BArgs a, const int2* __restric
     }
     __syncthreads();
     bq_fft_axis2<false>(X2, K2, tw2, tid);
-    float2* C = slot_ptr<float2>(a, S, S.slot.C) + (size_t)g1a * K2 * K3h;
-    BqWalk w(tid, K2, K3h);
-    for (int t = tid; t < rows * K3h; t += BQ_NT, w.next()) C[t] = X2[w.g2 * BQ_KS2 + w.j * K3h + w.m];
+    float2* C = slot_ptr<float2>(a, S, S.slot.C) + (size_t)g1a * S.nm2 * km;
+    const int count = planes * S.nm2 * km;
+    BqWalk w(tid, S);
+    for (int t = tid; t < count; t += BQ_NT, w.next()) C[t] = X2[w.at()];
     if (tid == 0) bq_lap(T, PH_FFT, t0);
 }
 
-// 64 lines (g2, m3) along axis 1: forward, times G, inverse, in place; with
+// Real-space pair product of 64 atoms, eight lanes per atom: V_Y[i] = sum_j K_ij
+// src_j; for the final product also fpair[i] = sum_j K'_ij / r_ij src_j (r_i - r_j).
+// It needs nothing of the mesh, so its blocks ride with the axis-1 lines, the
+// lightest of the product's launches (in k_bq_step, one block per structure, it
+// took two thirds of that kernel's 17 us for 512 atoms).
+__device__ __forceinline__ void bq_pair_product(const BArgs& a, const BStruct& S, int chunk, int mode) {
+    const int tid = threadIdx.x, n = S.n;
+    const int l = tid & (BQ_L - 1), i = chunk * (BQ_NT / BQ_L) + tid / BQ_L;
+    const bool fin = mode == BQ_FINAL;
+    const double* src = slot_vec(a, S, mode == BQ_ITER ? V_P : V_Q);
+    const int* col = slot_ptr<int>(a, S, S.slot.col);
+    const float* kval = slot_ptr<float>(a, S, S.slot.kval);
+    const float4* pdr = slot_ptr<float4>(a, S, S.slot.pdr);
+    double v = 0.0, f[3] = {0.0, 0.0, 0.0};
+    if (i < n) {
+        const int2 row = slot_ptr<int2>(a, S, S.slot.row)[i];
+        for (int e0 = row.x + l; e0 < row.y; e0 += 4 * BQ_L) {
+            int cj[4];
+            float kv[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int e = e0 + q * BQ_L;
+                cj[q] = e < row.y ? col[e] : 0;
+                kv[q] = e < row.y ? kval[e] : 0.f;
+            }
+            double vj[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) vj[q] = src[cj[q]];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                v += (double)kv[q] * vj[q];
+                if (fin && e0 + q * BQ_L < row.y) {
+                    const float4 d = pdr[e0 + q * BQ_L];
+                    const double c = (double)d.w * vj[q];
+                    f[0] += c * d.x;
+                    f[1] += c * d.y;
+                    f[2] += c * d.z;
+                }
+            }
+        }
+    }
+#pragma unroll
+    for (int d = BQ_L / 2; d > 0; d >>= 1) v += __shfl_xor(v, d, 64);
+    if (fin) {
+        for (int c = 0; c < 3; ++c)
+#pragma unroll
+            for (int d = BQ_L / 2; d > 0; d >>= 1) f[c] += __shfl_xor(f[c], d, 64);
+    }
+    if (i < n && l == 0) {
+        slot_vec(a, S, V_Y)[i] = v;
+        if (fin) {
+            double* fp = slot_ptr<double>(a, S, S.slot.fpair);
+            for (int c = 0; c < 3; ++c) fp[3 * i + c] = f[c];
+        }
+    }
+}
+
+// 64 lines (m2, m3) along axis 1: forward, times G, inverse, in place; with
 // THETA the inverse of G alone (the mesh kernel around the origin).  A line's
 // elements and Green's function values are requested before the first LDS
-// store, so a block costs one memory round trip.
+// store, so a block costs one memory round trip.  Units with a negative piece
+// -1 - c: the pair product of atoms 64 c ...
 template <bool THETA>
 __global__ __launch_bounds__(BQ_NT) void k_bq_cols(BArgs a, const int2* __restrict__ units, int mode) {
     extern __shared__ float2 lds[];
@@ -659,10 +728,16 @@ __global__ __launch_bounds__(BQ_NT) void k_bq_cols(BArgs a, const int2* __restri
     BState& T = a.state[u.x];
     if (!bq_active(T, mode)) return;
     const long long t0 = wall_clock64();
+    if (!THETA && u.y < 0) {
+        // (a pair list that did not fit is never read: the structure goes again)
+        if ((long long)T.nnz <= S.pcap) bq_pair_product(a, S, -1 - u.y, mode);
+        if (threadIdx.x == 0) bq_lap(T, PH_INTERP, t0);
+        return;
+    }
     __shared__ float2 tw1[BQ_KAX];
     const int tid = threadIdx.x;
-    const int K1 = S.K[0], K2 = S.K[1], K3h = S.K[2] / 2 + 1;
-    const int nl = K2 * K3h;
+    const int K1 = S.K[0];
+    const int nl = S.nm2 * S.km;
     const int c = tid % BQ_NC, k0 = tid / BQ_NC;
     const int L = u.y * BQ_NC + c;
     const bool live = L < nl;
@@ -710,22 +785,29 @@ __global__ __launch_bounds__(BQ_NT) void k_bq_cols(BArgs a, const int2* __restri
 // imaginary part.  buf [K3][BQ_KS], then X2 [K2][BQ_KS2].
 __device__ __forceinline__ void bq_planes_inv(const BArgs& a, const BStruct& S, int g1a, int planes, float2* buf,
                                               const float2* tw2, const float2* tw3, int tid) {
-    const int K2 = S.K[1], K3 = S.K[2], K3h = K3 / 2 + 1;
+    const int K2 = S.K[1], K3 = S.K[2], km = S.km;
     float2* X2 = buf + K3 * BQ_KS;
-    const float2* C = slot_ptr<float2>(a, S, S.slot.C) + (size_t)g1a * K2 * K3h;
-    const int rows = planes * K2;
+    const float2* C = slot_ptr<float2>(a, S, S.slot.C) + (size_t)g1a * S.nm2 * km;
+    const int rows = planes * K2, cols = planes * km, count = planes * S.nm2 * km;
     constexpr int PER = (BQ_KAX * BQ_NC2 + BQ_NT - 1) / BQ_NT;
     float2 v[PER];
 #pragma unroll
     for (int q = 0; q < PER; ++q) {
         const int t = tid + q * BQ_NT;
-        if (t < rows * K3h) v[q] = C[t];
+        if (t < count) v[q] = C[t];
     }
-    BqWalk w(tid, K2, K3h);
+    BqWalk w(tid, S);
 #pragma unroll
     for (int q = 0; q < PER; ++q) {
-        if (tid + q * BQ_NT < rows * K3h) X2[w.g2 * BQ_KS2 + w.j * K3h + w.m] = v[q];
+        if (tid + q * BQ_NT < count) X2[w.at()] = v[q];
         w.next();
+    }
+    // the rows of m2 that are not kept
+    {
+        const int c = tid & 63;
+        if (c < cols)
+            for (int e = ((S.nm2 + 1) >> 1) + (tid >> 6); e < ((S.nm2 + 1) >> 1) + K2 - S.nm2; e += BQ_NT / 64)
+                X2[e * BQ_KS2 + c] = make_float2(0.f, 0.f);
     }
     __syncthreads();
     bq_fft_axis2<true>(X2, K2, tw2, tid);
@@ -733,12 +815,12 @@ __device__ __forceinline__ void bq_planes_inv(const BArgs& a, const BStruct& S, 
     {
         const int r = tid & (2 * BQ_NC - 1);
         const int j = r / K2, g2 = r - j * K2;
-        const float2* x = X2 + g2 * BQ_KS2 + j * K3h;
+        const float2* x = X2 + g2 * BQ_KS2 + j * km;
         float2* z = buf + (r >> 1);
         const bool odd = (r & 1) != 0;
         if (r < rows) {   // whole pairs: rows is even
-            for (int m = tid / (2 * BQ_NC); m < K3h; m += BQ_NT / (2 * BQ_NC)) {
-                const float2 own = x[m];
+            for (int m = tid / (2 * BQ_NC); m <= K3 / 2; m += BQ_NT / (2 * BQ_NC)) {
+                const float2 own = m < km ? x[m] : make_float2(0.f, 0.f);
                 const float2 oth = make_float2(__shfl_xor(own.x, 1, 64), __shfl_xor(own.y, 1, 64));
                 if (!odd)
                     z[m * BQ_KS] = make_float2(own.x - oth.y, own.y + oth.x);
@@ -891,9 +973,9 @@ __global__ __launch_bounds__(64) void k_bq_self(BArgs a, const int2* __restrict_
 }
 
 // ------------------------------------------------------------------ CG step
-// One block per structure, one thread per atom in the vector part: the atom's
-// interpolation partials and pair row (eight lanes per atom), the sums of the
-// product, and the CG step that follows it: residual and first direction
+// One block per structure, one thread per atom: the atom's interpolation
+// partials and pair sum, the sums of the product, and the CG step that follows
+// it: residual and first direction
 // (BQ_INIT), update and next direction (BQ_ITER), energies, mu, true residual,
 // forces and the restart decision (BQ_FINAL).
 template <int MODE>
@@ -903,8 +985,7 @@ __global__ __launch_bounds__(1024) void k_bq_step(BArgs a, const int* __restrict
     const BStruct& S = a.st[s];
     BState& T = a.state[s];
     if (!bq_active(T, MODE)) return;
-    long long t0 = wall_clock64();
-    __shared__ double sp[1024], yv[1024];
+    const long long t0 = wall_clock64();
     const int tid = threadIdx.x, n = S.n, p = a.p;
     const double Q = S.q_tot;
     if (MODE == BQ_INIT && (long long)T.nnz > S.pcap) {   // uniform
@@ -920,9 +1001,14 @@ __global__ __launch_bounds__(1024) void k_bq_step(BArgs a, const int* __restrict
     double* rv = slot_vec(a, S, V_R);
     double* pv = slot_vec(a, S, V_P);
     const double* src = MODE == BQ_ITER ? pv : qv;
-    double vi = 0.0, Ji = 0.0, dsi = 0.0, chi = 0.0, dinv = 0.0, ri = 0.0, qi = 0.0;
+    const float* mpart = slot_ptr<float>(a, S, S.slot.mpart);
+    double vi = 0.0, yi = 0.0, Ji = 0.0, dsi = 0.0, chi = 0.0, dinv = 0.0, ri = 0.0, qi = 0.0;
     if (live) {
+        float mp[QEQ_MAXP];
+#pragma unroll
+        for (int k = 0; k < QEQ_MAXP; ++k) mp[k] = k < p ? mpart[(size_t)k * n + tid] : 0.f;
         vi = src[tid];
+        yi = slot_vec(a, S, V_Y)[tid];
         Ji = slot_vec(a, S, V_J)[tid];
         dsi = slot_vec(a, S, V_DSELF)[tid];
         dinv = slot_vec(a, S, V_DINV)[tid];
@@ -931,78 +1017,30 @@ __global__ __launch_bounds__(1024) void k_bq_step(BArgs a, const int* __restrict
             ri = rv[tid];
             qi = qv[tid];
         }
-        sp[tid] = vi;
-    }
-    __syncthreads();
-    const float* mpart = slot_ptr<float>(a, S, S.slot.mpart);
-    const int2* rows = slot_ptr<int2>(a, S, S.slot.row);
-    const int* col = slot_ptr<int>(a, S, S.slot.col);
-    const float* kval = slot_ptr<float>(a, S, S.slot.kval);
-    const float4* pdr = slot_ptr<float4>(a, S, S.slot.pdr);
-    const int l = tid & (BQ_L - 1);
-    for (int ib = 0; ib < n; ib += 1024 / BQ_L) {
-        const int i = ib + tid / BQ_L;
-        double v[7] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-        if (i < n) {
-            const int2 row = rows[i];
-            if (l < p) {
-                v[0] = (double)mpart[(size_t)l * n + i];
-                if (FIN)
-                    for (int c = 1; c < 4; ++c) v[c] = (double)mpart[(size_t)(c * QEQ_MAXP + l) * n + i];
+#pragma unroll
+        for (int k = 0; k < QEQ_MAXP; ++k) yi += (double)mp[k];
+        if (FIN && a.forces) {
+            double du[3] = {0.0, 0.0, 0.0};
+            for (int c = 0; c < 3; ++c)
+                for (int k = 0; k < p; ++k) du[c] += (double)mpart[(size_t)((c + 1) * QEQ_MAXP + k) * n + tid];
+            if (a.self_corr) {
+                const double* sg = slot_ptr<double>(a, S, S.slot.selfgrad);
+                for (int c = 0; c < 3; ++c) du[c] -= 0.5 * vi * sg[3 * tid + c];
             }
-            for (int e0 = row.x + l; e0 < row.y; e0 += 4 * BQ_L) {
-                int cj[4];
-                float kv[4];
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const int e = e0 + q * BQ_L;
-                    cj[q] = e < row.y ? col[e] : 0;
-                    kv[q] = e < row.y ? kval[e] : 0.f;
-                }
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const double vj = sp[cj[q]];
-                    v[0] += (double)kv[q] * vj;
-                    if (FIN && e0 + q * BQ_L < row.y) {
-                        const float4 d = pdr[e0 + q * BQ_L];
-                        const double c = (double)d.w * vj;
-                        v[4] += c * d.x;
-                        v[5] += c * d.y;
-                        v[6] += c * d.z;
-                    }
-                }
-            }
-        }
-#pragma unroll
-        for (int t = 0; t < (FIN ? 7 : 1); ++t) {
-#pragma unroll
-            for (int d = BQ_L / 2; d > 0; d >>= 1) v[t] += __shfl_xor(v[t], d, 64);
-        }
-        if (i < n && l == 0) {
-            yv[i] = v[0];
-            if (FIN && a.forces) {
-                const double xi = sp[i];
-                double du[3] = {v[1], v[2], v[3]};
-                if (a.self_corr) {
-                    const double* sg = slot_ptr<double>(a, S, S.slot.selfgrad);
-                    for (int c = 0; c < 3; ++c) du[c] -= 0.5 * xi * sg[3 * i + c];
-                }
-                double* f = a.forces + 3 * (size_t)(S.off + slot_ptr<int>(a, S, S.slot.perm)[i]);
-                for (int c = 0; c < 3; ++c) {
-                    double g = 0.0;
-                    for (int b = 0; b < 3; ++b) g += (double)S.K[b] * S.Hinv[c * 3 + b] * du[b];
-                    f[c] = -xi * g - xi * v[4 + c];
-                }
+            const double* fp = slot_ptr<double>(a, S, S.slot.fpair);
+            double* f = a.forces + 3 * (size_t)(S.off + slot_ptr<int>(a, S, S.slot.perm)[tid]);
+            for (int c = 0; c < 3; ++c) {
+                double g = 0.0;
+                for (int b = 0; b < 3; ++b) g += (double)S.K[b] * S.Hinv[c * 3 + b] * du[b];
+                f[c] = -vi * g - vi * fp[3 * tid + c];
             }
         }
     }
-    __syncthreads();
-    if (tid == 0) t0 = bq_lap(T, PH_INTERP, t0);
     const double chi_norm = T.chi_norm;
     if (FIN) {
         double t5[5] = {0.0, 0.0, 0.0, 0.0, 0.0}, g = 0.0;
         if (live) {
-            const double y = yv[tid] + dsi * vi;
+            const double y = yi + dsi * vi;
             const double sg = slot_vec(a, S, V_SIG)[tid];
             g = y + Ji * vi + chi;
             t5[0] = vi * y;
@@ -1048,7 +1086,7 @@ __global__ __launch_bounds__(1024) void k_bq_step(BArgs a, const int* __restrict
     } else {
         double t2[2] = {0.0, 0.0}, y = 0.0;
         if (live) {
-            y = yv[tid] + dsi * vi + Ji * vi;
+            y = yi + dsi * vi + Ji * vi;
             t2[0] = vi * y;
             t2[1] = y;
         }
@@ -1228,6 +1266,7 @@ size_t slot_layout(BStruct& S) {
     L.mpart = place(sizeof(float) * 4 * QEQ_MAXP * n);
     L.hstart = place(sizeof(int) * (BQ_KAX + 1));
     L.perm = place(sizeof(int) * n);
+    L.fpair = place(sizeof(double) * 3 * n);
     return o;
 }
 
@@ -1276,11 +1315,15 @@ BatchState* batch_state(qeq_plan* pl) {
 // structure has the same block number modulo 8 in every kernel and finds what
 // the previous kernel of the product wrote in its XCD's L2; short lists are
 // filled up with (-1, 0).
-void deal_units(const std::vector<int>& work, const std::vector<int>& pieces, const std::vector<int>& xcd,
-                std::vector<int2>& out) {
+void deal_units(const std::vector<int>& work, const std::vector<int>& pieces, int atoms, const std::vector<int>& xcd,
+                std::vector<int2>& out, const std::vector<BStruct>* st = nullptr) {
     std::vector<int2> lane[8];
-    for (size_t w = 0; w < work.size(); ++w)
+    for (size_t w = 0; w < work.size(); ++w) {
+        // chunks of `atoms` atoms first, as pieces -1, -2, ...
+        if (atoms)
+            for (int c = 0; c * atoms < (*st)[work[w]].n; ++c) lane[xcd[w]].push_back(make_int2(work[w], -1 - c));
         for (int t = 0; t < pieces[w]; ++t) lane[xcd[w]].push_back(make_int2(work[w], t));
+    }
     size_t most = 0;
     for (const auto& v : lane) most = std::max(most, v.size());
     out.assign(8 * most, make_int2(-1, 0));
@@ -1299,7 +1342,7 @@ int run_wave(qeq_plan* pl, BatchState* b, BArgs& a, std::vector<BStruct>& st, co
     for (int w = 0; w < ns; ++w) {
         const BStruct& S = st[work[w]];
         nA[w] = (S.K[0] + S.pb - 1) / S.pb;
-        nB[w] = (S.K[1] * (S.K[2] / 2 + 1) + BQ_NC - 1) / BQ_NC;
+        nB[w] = (S.nm2 * S.km + BQ_NC - 1) / BQ_NC;
         nP[w] = (S.n + BQ_PAIR_ATOMS - 1) / BQ_PAIR_ATOMS;
         nG[w] = (S.nhalf + BQ_GREEN - 1) / BQ_GREEN;
         nS[w] = (S.n + 63) / 64;
@@ -1307,9 +1350,10 @@ int run_wave(qeq_plan* pl, BatchState* b, BArgs& a, std::vector<BStruct>& st, co
         xcd[w] = (int)(std::min_element(load, load + 8) - load);   // longest first: balanced
         load[xcd[w]] += S.nhalf;
     }
-    std::vector<int2> uA, uB, uP, uG, uS, uT;
-    deal_units(work, nA, xcd, uA);
-    deal_units(work, nB, xcd, uB);
+    std::vector<int2> uA, uB, uV, uP, uG, uS, uT;
+    deal_units(work, nA, 0, xcd, uA);
+    deal_units(work, nB, 0, xcd, uB);
+    deal_units(work, nB, BQ_NT / BQ_L, xcd, uV, &st);   // with the pair products
     auto plain = [&](const std::vector<int>& pieces, std::vector<int2>& out) {
         for (int w = 0; w < ns; ++w)
             for (int t = 0; t < pieces[w]; ++t) out.push_back(make_int2(work[w], t));
@@ -1331,7 +1375,7 @@ int run_wave(qeq_plan* pl, BatchState* b, BArgs& a, std::vector<BStruct>& st, co
     const size_t oSt = place(sizeof(BStruct) * n_struct), oState = place(sizeof(BState) * n_struct),
                  oCount = place(sizeof(BCount)), oOrder = place(sizeof(int) * ns), oTw = place(sizeof(float2) * twh.size()),
                  oBm = place(sizeof(float) * bmh.size()), oA = place(sizeof(int2) * uA.size()),
-                 oB = place(sizeof(int2) * uB.size()), oP = place(sizeof(int2) * uP.size()),
+                 oB = place(sizeof(int2) * uB.size()), oV = place(sizeof(int2) * uV.size()), oP = place(sizeof(int2) * uP.size()),
                  oG = place(sizeof(int2) * uG.size()), oS = place(sizeof(int2) * uS.size()),
                  oT = place(sizeof(int2) * uT.size());
     if (o > b->staging_cap) {
@@ -1363,6 +1407,7 @@ int run_wave(qeq_plan* pl, BatchState* b, BArgs& a, std::vector<BStruct>& st, co
     put(oBm, bmh.data(), sizeof(float) * bmh.size());
     put(oA, uA.data(), sizeof(int2) * uA.size());
     put(oB, uB.data(), sizeof(int2) * uB.size());
+    put(oV, uV.data(), sizeof(int2) * uV.size());
     put(oP, uP.data(), sizeof(int2) * uP.size());
     put(oG, uG.data(), sizeof(int2) * uG.size());
     put(oS, uS.data(), sizeof(int2) * uS.size());
@@ -1376,6 +1421,7 @@ int run_wave(qeq_plan* pl, BatchState* b, BArgs& a, std::vector<BStruct>& st, co
     a.scratch = b->scratch;
     const int* order = (const int*)(b->tables + oOrder);
     const int2 *dA = (const int2*)(b->tables + oA), *dB = (const int2*)(b->tables + oB),
+               *dV = (const int2*)(b->tables + oV),
                *dP = (const int2*)(b->tables + oP), *dG = (const int2*)(b->tables + oG),
                *dS = (const int2*)(b->tables + oS), *dT = (const int2*)(b->tables + oT);
     size_t shA = 0, shB = 0, shC = 0;
@@ -1409,7 +1455,7 @@ int run_wave(qeq_plan* pl, BatchState* b, BArgs& a, std::vector<BStruct>& st, co
     QEQ_TRY(qeq_check(hipGetLastError()));
     auto product = [&](int mode) {
         hipLaunchKernelGGL(k_bq_fwd, dim3((unsigned)uA.size()), dim3(BQ_NT), shA, stream, a, dA, mode);
-        hipLaunchKernelGGL(k_bq_cols<false>, dim3((unsigned)uB.size()), dim3(BQ_NT), shB, stream, a, dB, mode);
+        hipLaunchKernelGGL(k_bq_cols<false>, dim3((unsigned)uV.size()), dim3(BQ_NT), shB, stream, a, dV, mode);
         if (mode == BQ_FINAL) {
             hipLaunchKernelGGL(k_bq_inv<true>, dim3((unsigned)uA.size()), dim3(BQ_NT), shC, stream, a, dA, mode);
             hipLaunchKernelGGL(k_bq_step<BQ_FINAL>, dim3(ns), dim3(1024), 0, stream, a, order);
@@ -1533,7 +1579,10 @@ int batched_impl(qeq_plan* pl, int n_struct, const int32_t* offs, const double* 
             hstatus[s] = QEQ_EPLAN;
             continue;
         }
-        S.nhalf = K[0] * K[1] * (K[2] / 2 + 1);
+        const double kcut = sqrt(2.0 * 30.0 * 0.69314718055994530942) / prm.eta;
+        S.km = std::min(K[2] / 2 + 1, (int)std::min(1e6, kcut * lengths[2] / (2 * PI_H)) + 1);
+        S.nm2 = std::min(K[1], 2 * (int)std::min(1e6, kcut * lengths[1] / (2 * PI_H)) + 1);
+        S.nhalf = K[0] * S.nm2 * S.km;
         S.green_pref = 4.0 * PI_H / det;
         S.bg_pref = 2.0 * PI_H / det;
         S.q_tot = q_tot[s];
@@ -1547,7 +1596,7 @@ int batched_impl(qeq_plan* pl, int n_struct, const int32_t* offs, const double* 
         }
         for (int x = 0; x < 3; ++x)
             if (std::find(Ks.begin(), Ks.end(), K[x]) == Ks.end()) Ks.push_back(K[x]);
-        S.pb = std::max(1, std::min({2 * BQ_NC / K[1], BQ_NC2 / (K[2] / 2 + 1), K[0] - p + 1, BQ_PB}));
+        S.pb = std::max(1, std::min({2 * BQ_NC / K[1], BQ_NC2 / S.km, K[0] - p + 1, BQ_PB}));
         // pair capacity: mean neighbour count of a uniform density plus a
         // generous Poisson tail
         const double dens = n / det;

@@ -12,20 +12,43 @@ import numpy as np
 import pytest
 
 LENGTHS = (12, 16, 20, 24, 32, 36, 40, 48, 60, 64)
-NC, KS, NC2, KS2, NT, PB, KAX = 64, 65, 66, 67, 512, 8, 64
+NC, KS, NC2, KS2, NT, PB, KAX = 64, 65, 56, 57, 512, 8, 64
 
 
-def planes_per_block(K, p):
-    return max(1, min(2 * NC // K[1], NC2 // (K[2] // 2 + 1), K[0] - p + 1, PB))
+def planes_per_block(K, km, p):
+    return max(1, min(2 * NC // K[1], NC2 // km, K[0] - p + 1, PB))
+
+
+def walk(nm2, km, K2, count):
+    """BqWalk: (m2, plane, m3) of the elements t = tid + q NT, by its carries."""
+    tid = np.arange(NT)
+    dr, dm = NT // km, NT % km
+    r, m = tid // km, tid % km
+    j, e = r // nm2, r % nm2
+    out = np.zeros((count, 3), dtype=int)
+    for q in range(-(-count // NT)):
+        t = tid + q * NT
+        ok = t < count
+        out[t[ok]] = np.stack([np.where(e < (nm2 + 1) // 2, e, e + K2 - nm2), j, m], 1)[ok]
+        m, e = m + dm, e + dr
+        c = m >= km
+        m, e = np.where(c, m - km, m), np.where(c, e + 1, e)
+        j, e = j + e // nm2, e % nm2
+    return out
 
 
 @pytest.mark.parametrize("p", [4, 6, 8])
 def test_blocks_stay_inside_their_buffers(p):
-    for K in itertools.product([k for k in LENGTHS if k >= 2 * p], repeat=3):
+    # kept modes: all of them, the usual four fifths, and very few
+    shares = (1.0, 0.8, 0.1)
+    for (K, share) in itertools.product(itertools.product([k for k in LENGTHS if k >= 2 * p], repeat=3), shares):
         K1, K2, K3 = K
-        K3h, pb = K3 // 2 + 1, planes_per_block(K, p)
+        km = min(K3 // 2 + 1, int(share * K3 / 2) + 1)
+        nm2 = min(K2, 2 * int(share * K2 / 2) + 1)
+        assert (nm2 == K2 or nm2 % 2 == 1) and 1 <= nm2 <= K2
+        pb = planes_per_block(K, km, p)
         rw = pb * K2
-        assert rw <= 2 * NC and rw % 2 == 0 and pb * K3h <= NC2 < KS2 and pb <= PB
+        assert rw <= 2 * NC and rw % 2 == 0 and pb * km <= NC2 < KS2 and NC2 <= 64 and pb <= PB
         assert pb + p - 1 <= K1                        # a block's candidate planes never overlap themselves
         two = K3 * KS + K2 * KS2                       # buf + X2, complex
         lds_fwd = max(two * 8, K3 * rw * 8)
@@ -42,21 +65,31 @@ def test_blocks_stay_inside_their_buffers(p):
             g1a, planes = y * pb, min(pb, K1 - y * pb)
             done[g1a:g1a + planes] += 1
             rows = planes * K2
-            # loads and stores of the half spectra: PER register slots cover rows * K3h elements
+            # loads and stores of the half spectra: PER register slots cover all elements
+            count = planes * nm2 * km
             per = -(-KAX * NC2 // NT)
-            assert rows * K3h <= per * NT
+            assert count <= per * NT
             r = np.arange(rows)
             j, g2 = r // K2, r % K2
-            cols = j[:, None] * K3h + np.arange(K3h)[None, :]
+            cols = j[:, None] * km + np.arange(km)[None, :]
             assert cols.max() < NC2 and (g2[:, None] * KS2 + cols).max() < K2 * KS2
             # packed rows: row pairs stay in one plane (K2 even)
             assert np.all((r[0::2] // K2) == (r[1::2] // K2)) and rows // 2 <= NC
-            assert (g1a * K2 * K3h + rows * K3h) <= K1 * K2 * K3h
+            assert (g1a + planes) * nm2 * km <= K1 * nm2 * km
+            if y == 0 and K1 == K3:
+                got = walk(nm2, km, K2, count)
+                tt = np.arange(count)
+                e, m = (tt // km) % nm2, tt % km
+                m2 = np.where(e < (nm2 + 1) // 2, e, e + K2 - nm2)
+                assert np.array_equal(got, np.stack([m2, tt // km // nm2, m], 1))
+                # kept rows and cleared rows together are all rows
+                half = (nm2 + 1) // 2
+                assert sorted(set(m2.tolist()) | set(range(half, half + K2 - nm2))) == list(range(K2))
         assert np.all(done == 1)
         # potential reads of the interpolation: 2 (g3 KS + (r >> 1)) + (r & 1)
         assert 2 * ((K3 - 1) * KS + ((pb * K2 - 1) >> 1)) + 1 < 2 * K3 * KS
         # axis-1 line blocks
-        nl = K2 * K3h
+        nl = nm2 * km
         nb = -(-nl // NC)
         L = np.arange(nb * NC)
         assert np.array_equal(L[L < nl], np.arange(nl))
