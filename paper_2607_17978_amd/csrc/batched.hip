@@ -477,33 +477,31 @@ __device__ __forceinline__ void bq_fft_lines(float2* buf, int K, const float2* t
     }
 }
 
-// Element t = (j nm2 + e) km + m of a block's half spectra, for t = tid, tid +
-// BQ_NT, ...: carries instead of two divisions per element.  at: its place in
-// X2[m2][j km + m].
+// A thread's elements of a block's half spectra C[j nm2 + e][m]: 32 lanes along
+// m (at most two steps: km <= 33), BQ_NT / 32 rows at a time, so that a step
+// costs a carry instead of two divisions.  at: the row's place in X2[m2][j km].
 struct BqWalk {
-    int nm2, km, half, skip, dr, dm, j, e, m;
+    static constexpr int ROWS = BQ_NT / 32;
+    int nm2, km, half, skip, j, e, row;
     __device__ __forceinline__ BqWalk(int tid, const BStruct& S) : nm2(S.nm2), km(S.km) {
         half = (nm2 + 1) >> 1;
         skip = S.K[1] - nm2;
-        dr = BQ_NT / km;
-        dm = BQ_NT - dr * km;
-        const int r = tid / km;
-        m = tid - r * km;
-        j = r / nm2;
-        e = r - j * nm2;
+        row = tid >> 5;
+        j = 0;
+        e = row;
+        carry();
     }
-    __device__ __forceinline__ int at() const { return (e < half ? e : e + skip) * BQ_KS2 + j * km + m; }
-    __device__ __forceinline__ void next() {
-        m += dm;
-        e += dr;
-        if (m >= km) {
-            m -= km;
-            ++e;
-        }
+    __device__ __forceinline__ void carry() {
         while (e >= nm2) {
             e -= nm2;
             ++j;
         }
+    }
+    __device__ __forceinline__ int at() const { return (e < half ? e : e + skip) * BQ_KS2 + j * km; }
+    __device__ __forceinline__ void next() {
+        row += ROWS;
+        e += ROWS;
+        carry();
     }
 };
 
@@ -523,6 +521,12 @@ __device__ __forceinline__ void bq_ranges(const int* hs, int K1, int n, int p, i
         for (int j = 0; j < planes; ++j) off[j + 1] += off[j];
     }
     __syncthreads();
+}
+
+// A 64-bit sum below 2^51 as FP32, rounded once: exact in FP64 (the conversion
+// that hipcc expands for 64-bit integers takes three times the instructions).
+__device__ __forceinline__ float bq_float(long long x) {
+    return (float)fma((double)(int)(x >> 32), 4294967296.0, (double)(unsigned)x);
 }
 
 // Spread, real-to-complex along axis 3 and axis 2 forward of a block's planes.
@@ -575,10 +579,12 @@ __global__ __launch_bounds__(BQ_NT) void k_bq_fwd(BArgs a, const int2* __restric
     (void)frexp(v[0] > 0.0 ? v[0] : 1.0, &ex);
     const float scale = ldexpf(1.0f, max(-126, min(126, 50 - ex)));
     constexpr double RND = 6755399441055744.0;   // 1.5 * 2^52
-    const int k2 = tid & (BQ_L - 1);
-    if (k2 < p) {
-        const int items = off[planes];
-        for (int t = tid / BQ_L; t < items; t += BQ_NT / BQ_L) {
+    // two lanes per (atom, plane), half of the axis-2 rows each: a row's set-up
+    // is shared by p terms and an item's by p^2 / 2 (eight lanes with one row
+    // each took 2.4 times the instructions)
+    {
+        const int items = off[planes], hp = p >> 1, k20 = (tid & 1) * hp;
+        for (int t = tid >> 1; t < items; t += BQ_NT / 2) {
             int j = 0;
             while (t >= off[j + 1]) ++j;
             int i = first[j] + (t - off[j]);
@@ -586,22 +592,30 @@ __global__ __launch_bounds__(BQ_NT) void k_bq_fwd(BArgs a, const int2* __restric
             const int4 hm = *reinterpret_cast<const int4*>(home + 4 * i);
             int k1 = hm.x - (g1a + j);
             if (k1 < 0) k1 += K1;
-            int g2 = hm.y - k2;
-            if (g2 < 0) g2 += K2;
             const float* w = wts + (size_t)i * 3 * QEQ_MAXP;
-            const float a0 = (float)src[i] * w[k1] * w[QEQ_MAXP + k2] * scale;
+            const float a1 = (float)src[i] * w[k1];
             const float4 wa = *reinterpret_cast<const float4*>(w + 2 * QEQ_MAXP);
             const float4 wb = *reinterpret_cast<const float4*>(w + 2 * QEQ_MAXP + 4);
-            const float w3[8] = {wa.x, wa.y, wa.z, wa.w, wb.x, wb.y, wb.z, wb.w};
-            const int r = j * K2 + g2;
+            const double w3[8] = {wa.x, wa.y, wa.z, wa.w, wb.x, wb.y, wb.z, wb.w};
+            int g2 = hm.y - k20;
+            if (g2 < 0) g2 += K2;
+            unsigned long long* col[QEQ_MAXP];
 #pragma unroll
             for (int k3 = 0; k3 < QEQ_MAXP; ++k3) {
-                if (k3 >= p) break;
                 int g3 = hm.z - k3;
                 if (g3 < 0) g3 += K3;
-                const long long b = __double_as_longlong(fma((double)a0, (double)w3[k3], RND));
-                const unsigned hi = (unsigned)(b >> 32) - 0x43380000u;
-                atomicAdd(acc_u + g3 * RW + r, ((unsigned long long)hi << 32) | (unsigned)b);
+                col[k3] = acc_u + g3 * RW + j * K2;
+            }
+            for (int q = 0; q < hp; ++q) {
+                const double a0 = (double)(a1 * w[QEQ_MAXP + k20 + q] * scale);
+#pragma unroll
+                for (int k3 = 0; k3 < QEQ_MAXP; ++k3) {
+                    if (k3 >= p) break;
+                    const long long b = __double_as_longlong(fma(a0, w3[k3], RND));
+                    const unsigned hi = (unsigned)(b >> 32) - 0x43380000u;
+                    atomicAdd(col[k3] + g2, ((unsigned long long)hi << 32) | (unsigned)b);
+                }
+                g2 = g2 == 0 ? K2 - 1 : g2 - 1;
             }
         }
     }
@@ -617,8 +631,10 @@ __global__ __launch_bounds__(BQ_NT) void k_bq_fwd(BArgs a, const int2* __restric
         for (int q = 0; q < PER; ++q) {
             const int t = tid + q * BQ_NT, g3 = t / BQ_NC, c = t % BQ_NC;
             z[q] = make_float2(0.f, 0.f);
-            if (g3 < K3 && c < half)
-                z[q] = make_float2((float)acc[g3 * RW + 2 * c] * inv, (float)acc[g3 * RW + 2 * c + 1] * inv);
+            if (g3 < K3 && c < half) {
+                const longlong2 x = *reinterpret_cast<const longlong2*>(acc + g3 * RW + 2 * c);
+                z[q] = make_float2(bq_float(x.x) * inv, bq_float(x.y) * inv);
+            }
         }
         __syncthreads();
 #pragma unroll
@@ -651,9 +667,9 @@ __global__ __launch_bounds__(BQ_NT) void k_bq_fwd(BArgs a, const int2* __restric
     __syncthreads();
     bq_fft_axis2<false>(X2, K2, tw2, tid);
     float2* C = slot_ptr<float2>(a, S, S.slot.C) + (size_t)g1a * S.nm2 * km;
-    const int count = planes * S.nm2 * km;
-    BqWalk w(tid, S);
-    for (int t = tid; t < count; t += BQ_NT, w.next()) C[t] = X2[w.at()];
+    const int kept = planes * S.nm2;
+    for (BqWalk w(tid, S); w.row < kept; w.next())
+        for (int m = tid & 31; m < km; m += 32) C[w.row * km + m] = X2[w.at() + m];
     if (tid == 0) bq_lap(T, PH_FFT, t0);
 }
 
@@ -788,18 +804,25 @@ __device__ __forceinline__ void bq_planes_inv(const BArgs& a, const BStruct& S, 
     const int K2 = S.K[1], K3 = S.K[2], km = S.km;
     float2* X2 = buf + K3 * BQ_KS;
     const float2* C = slot_ptr<float2>(a, S, S.slot.C) + (size_t)g1a * S.nm2 * km;
-    const int rows = planes * K2, cols = planes * km, count = planes * S.nm2 * km;
-    constexpr int PER = (BQ_KAX * BQ_NC2 + BQ_NT - 1) / BQ_NT;
-    float2 v[PER];
+    const int rows = planes * K2, cols = planes * km, kept = planes * S.nm2;
+    // every load of the thread first, then the LDS stores
+    constexpr int PER = 2 * BQ_NC / BqWalk::ROWS;
+    float2 v[PER], ve[PER];
+    const int m0 = tid & 31;
 #pragma unroll
     for (int q = 0; q < PER; ++q) {
-        const int t = tid + q * BQ_NT;
-        if (t < count) v[q] = C[t];
+        const int row = (tid >> 5) + q * BqWalk::ROWS;
+        if (row < kept && m0 < km) v[q] = C[row * km + m0];
+        if (row < kept && m0 + 32 < km) ve[q] = C[row * km + m0 + 32];
     }
     BqWalk w(tid, S);
 #pragma unroll
     for (int q = 0; q < PER; ++q) {
-        if (tid + q * BQ_NT < count) X2[w.at()] = v[q];
+        if (w.row < kept) {
+            float2* x = X2 + w.at();
+            if (m0 < km) x[m0] = v[q];
+            if (m0 + 32 < km) x[m0 + 32] = ve[q];
+        }
         w.next();
     }
     // the rows of m2 that are not kept
@@ -836,8 +859,8 @@ __device__ __forceinline__ void bq_planes_inv(const BArgs& a, const BStruct& S, 
 // Inverse transforms of a block's planes and, from LDS, the part of every
 // atom's interpolation that lies on them: mpart[k1][i] for the plane h1 - k1
 // (eq. matvec: the integral of the potential over the atom's distribution).
-// With FIN also the three derivative sums, mpart[8 (1 + c) + k1][i].  Eight
-// lanes per (atom, plane), one axis-2 row each.
+// With FIN also the three derivative sums, mpart[8 (1 + c) + k1][i].  Two
+// lanes per (atom, plane), half of the axis-2 rows each, as in the spread.
 template <bool FIN>
 __global__ __launch_bounds__(BQ_NT) void k_bq_inv(BArgs a, const int2* __restrict__ units, int mode) {
     extern __shared__ float2 lds[];
@@ -862,11 +885,10 @@ __global__ __launch_bounds__(BQ_NT) void k_bq_inv(BArgs a, const int2* __restric
     const float* wts = slot_ptr<float>(a, S, S.slot.wts);
     const float* dwts = slot_ptr<float>(a, S, S.slot.dwts);
     float* mpart = slot_ptr<float>(a, S, S.slot.mpart);
-    const int k2 = tid & (BQ_L - 1);
-    const int items = off[planes];
-    const int rounds = (items + BQ_NT / BQ_L - 1) / (BQ_NT / BQ_L);
+    const int items = off[planes], hp = p >> 1, k20 = (tid & 1) * hp;
+    const int rounds = (items + BQ_NT / 2 - 1) / (BQ_NT / 2);
     for (int rd = 0; rd < rounds; ++rd) {
-        const int t = rd * (BQ_NT / BQ_L) + tid / BQ_L;
+        const int t = rd * (BQ_NT / 2) + (tid >> 1);
         const bool live = t < items;
         float s = 0.f, s2 = 0.f, s3 = 0.f, w1 = 0.f, dw1 = 0.f;
         int i = 0, k1 = 0;
@@ -882,37 +904,44 @@ __global__ __launch_bounds__(BQ_NT) void k_bq_inv(BArgs a, const int2* __restric
             const float* dw = dwts + (size_t)i * 3 * QEQ_MAXP;
             w1 = w[k1];
             if (FIN) dw1 = dw[k1];
-            if (k2 < p) {
-                int g2 = hm.y - k2;
-                if (g2 < 0) g2 += K2;
-                const int r = j * K2 + g2;
-                const float* row = bf + 2 * (r >> 1) + (r & 1);
+            const float4 wa = *reinterpret_cast<const float4*>(w + 2 * QEQ_MAXP);
+            const float4 wb = *reinterpret_cast<const float4*>(w + 2 * QEQ_MAXP + 4);
+            const float w3[8] = {wa.x, wa.y, wa.z, wa.w, wb.x, wb.y, wb.z, wb.w};
+            int g2 = hm.y - k20;
+            if (g2 < 0) g2 += K2;
+            const float* col[QEQ_MAXP];
+#pragma unroll
+            for (int k3 = 0; k3 < QEQ_MAXP; ++k3) {
+                int g3 = hm.z - k3;
+                if (g3 < 0) g3 += K3;
+                col[k3] = bf + 2 * g3 * BQ_KS;
+            }
+            const int r0 = j * K2;
+            for (int q = 0; q < hp; ++q) {
+                const int at = r0 + g2;   // rows r and r ^ 1 share a complex value (r0 is even)
                 float x = 0.f, x3 = 0.f;
 #pragma unroll
                 for (int k3 = 0; k3 < QEQ_MAXP; ++k3) {
                     if (k3 >= p) break;
-                    int g3 = hm.z - k3;
-                    if (g3 < 0) g3 += K3;
-                    const float g = row[2 * g3 * BQ_KS];
-                    x += w[2 * QEQ_MAXP + k3] * g;
+                    const float g = col[k3][at];
+                    x += w3[k3] * g;
                     if (FIN) x3 += dw[2 * QEQ_MAXP + k3] * g;
                 }
-                s = w[QEQ_MAXP + k2] * x;
+                const float w2 = w[QEQ_MAXP + k20 + q];
+                s += w2 * x;
                 if (FIN) {
-                    s2 = dw[QEQ_MAXP + k2] * x;
-                    s3 = w[QEQ_MAXP + k2] * x3;
+                    s2 += dw[QEQ_MAXP + k20 + q] * x;
+                    s3 += w2 * x3;
                 }
+                g2 = g2 == 0 ? K2 - 1 : g2 - 1;
             }
         }
-#pragma unroll
-        for (int d = BQ_L / 2; d > 0; d >>= 1) {
-            s += __shfl_xor(s, d, 64);
-            if (FIN) {
-                s2 += __shfl_xor(s2, d, 64);
-                s3 += __shfl_xor(s3, d, 64);
-            }
+        s += __shfl_xor(s, 1, 64);
+        if (FIN) {
+            s2 += __shfl_xor(s2, 1, 64);
+            s3 += __shfl_xor(s3, 1, 64);
         }
-        if (live && k2 == 0) {
+        if (live && (tid & 1) == 0) {
             mpart[(size_t)k1 * n + i] = w1 * s;
             if (FIN) {
                 mpart[(size_t)(QEQ_MAXP + k1) * n + i] = dw1 * s;

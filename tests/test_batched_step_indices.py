@@ -19,22 +19,22 @@ def planes_per_block(K, km, p):
     return max(1, min(2 * NC // K[1], NC2 // km, K[0] - p + 1, PB))
 
 
-def walk(nm2, km, K2, count):
-    """BqWalk: (m2, plane, m3) of the elements t = tid + q NT, by its carries."""
-    tid = np.arange(NT)
-    dr, dm = NT // km, NT % km
-    r, m = tid // km, tid % km
-    j, e = r // nm2, r % nm2
-    out = np.zeros((count, 3), dtype=int)
-    for q in range(-(-count // NT)):
-        t = tid + q * NT
-        ok = t < count
-        out[t[ok]] = np.stack([np.where(e < (nm2 + 1) // 2, e, e + K2 - nm2), j, m], 1)[ok]
-        m, e = m + dm, e + dr
-        c = m >= km
-        m, e = np.where(c, m - km, m), np.where(c, e + 1, e)
-        j, e = j + e // nm2, e % nm2
-    return out
+def walk(nm2, km, K2, kept):
+    """BqWalk: (m2, plane) of the rows tid >> 5, + NT / 32, ..., by its carries."""
+    out = {}
+    step = NT // 32
+    for first in range(step):
+        row, j, e = first, 0, first
+        while True:
+            while e >= nm2:
+                e, j = e - nm2, j + 1
+            if row >= kept:
+                break
+            assert row not in out
+            out[row] = (e if e < (nm2 + 1) // 2 else e + K2 - nm2, j)
+            row, e = row + step, e + step
+    assert kept <= step * (2 * NC // step)      # register slots of the loads
+    return [out[r] for r in range(kept)]
 
 
 @pytest.mark.parametrize("p", [4, 6, 8])
@@ -65,10 +65,8 @@ def test_blocks_stay_inside_their_buffers(p):
             g1a, planes = y * pb, min(pb, K1 - y * pb)
             done[g1a:g1a + planes] += 1
             rows = planes * K2
-            # loads and stores of the half spectra: PER register slots cover all elements
-            count = planes * nm2 * km
-            per = -(-KAX * NC2 // NT)
-            assert count <= per * NT
+            kept = planes * nm2
+            assert km <= 64                                # two steps of 32 lanes
             r = np.arange(rows)
             j, g2 = r // K2, r % K2
             cols = j[:, None] * km + np.arange(km)[None, :]
@@ -77,11 +75,10 @@ def test_blocks_stay_inside_their_buffers(p):
             assert np.all((r[0::2] // K2) == (r[1::2] // K2)) and rows // 2 <= NC
             assert (g1a + planes) * nm2 * km <= K1 * nm2 * km
             if y == 0 and K1 == K3:
-                got = walk(nm2, km, K2, count)
-                tt = np.arange(count)
-                e, m = (tt // km) % nm2, tt % km
+                rr = np.arange(kept)
+                e = rr % nm2
                 m2 = np.where(e < (nm2 + 1) // 2, e, e + K2 - nm2)
-                assert np.array_equal(got, np.stack([m2, tt // km // nm2, m], 1))
+                assert walk(nm2, km, K2, kept) == list(zip(m2.tolist(), (rr // nm2).tolist()))
                 # kept rows and cleared rows together are all rows
                 half = (nm2 + 1) // 2
                 assert sorted(set(m2.tolist()) | set(range(half, half + K2 - nm2))) == list(range(K2))
