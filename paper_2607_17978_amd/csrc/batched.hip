@@ -37,6 +37,7 @@ constexpr int BQ_NC2 = 56;      // half-spectrum columns of a block along axis 2
 constexpr int BQ_KS2 = 57;      // their LDS row stride
 constexpr int BQ_NT = 512;      // threads of the plane and line kernels
 constexpr int BQ_PB = 8;        // most planes of a block
+constexpr size_t BQ_ACC = 38400;   // most bytes of a block's accumulator
 constexpr int BQ_L = 8;         // lanes per atom in the interpolation and pair loops
 constexpr int BQ_PAIR_ATOMS = 32;   // atoms of a block of the pair-list kernel
 constexpr int BQ_GREEN = 4096;  // Green's function values of a block
@@ -56,7 +57,8 @@ struct BSlot {
 
 // Per-structure constants prepared on the host.
 struct BStruct {
-    int n, off, nhalf, pb;      // atoms, first atom, kept half-spectrum points, planes of a block
+    int n, off, nhalf;          // atoms, first atom, kept half-spectrum points
+    int pf, pb;                 // planes of a block of k_bq_fwd and of k_bq_inv
     int km, nm2;                // kept modes: m3 < km, nm2 of the K2 axis-2 ones (|m2| <= (nm2 - 1) / 2, or all)
     int K[3], tw_off[3], bm_off[3];
     int mm[3], nn[3];           // ranges of the C_eta k-space and lattice sums
@@ -552,12 +554,12 @@ __global__ __launch_bounds__(BQ_NT) void k_bq_fwd(BArgs a, const int2* __restric
     __shared__ int first[BQ_PB], off[BQ_PB + 1];
     const int tid = threadIdx.x, n = S.n, p = a.p;
     const int K1 = S.K[0], K2 = S.K[1], K3 = S.K[2], km = S.km;
-    const int g1a = u.y * S.pb, planes = min(S.pb, K1 - g1a);
-    const int RW = S.pb * K2;                                // accumulator rows
+    const int g1a = u.y * S.pf, planes = min(S.pf, K1 - g1a);
+    const int RW = S.pf * K2;                                // accumulator rows
     long long* acc = reinterpret_cast<long long*>(lds);      // [K3][RW]
     unsigned long long* acc_u = reinterpret_cast<unsigned long long*>(lds);
     float2* buf = lds;                                       // [K3][BQ_KS], in its place
-    float2* X2 = lds + K3 * BQ_KS;                           // [K2][BQ_KS2]
+    float2* X2 = lds;                                        // [K2][BQ_KS2], in its place again
     const double* src = slot_vec(a, S, mode == BQ_ITER ? V_P : V_Q);
     const int* home = slot_ptr<int>(a, S, S.slot.home);
     const float* wts = slot_ptr<float>(a, S, S.slot.wts);
@@ -649,18 +651,31 @@ __global__ __launch_bounds__(BQ_NT) void k_bq_fwd(BArgs a, const int2* __restric
     const int rows = planes * K2;
     {
         const int r = tid & (2 * BQ_NC - 1);
-        if (r < rows) {
-            const int j = r / K2, g2 = r - j * K2;
-            const float2* z = buf + (r >> 1);
-            float2* x = X2 + g2 * BQ_KS2 + j * km;
-            for (int m = tid / (2 * BQ_NC); m < km; m += BQ_NT / (2 * BQ_NC)) {
-                const float2 Z = z[m * BQ_KS];
-                float2 Zc = z[(m == 0 ? 0 : K3 - m) * BQ_KS];
+        const int j = r / K2, g2 = r - j * K2;
+        const float2* line = buf + (r >> 1);
+        float2* x = X2 + g2 * BQ_KS2 + j * km;
+        constexpr int STEP = BQ_NT / (2 * BQ_NC), PM = (BQ_KAX / 2 + STEP) / STEP;
+        const int mf = tid / (2 * BQ_NC);
+        float2 xv[PM];
+#pragma unroll
+        for (int q = 0; q < PM; ++q) {
+            const int m = mf + q * STEP;
+            if (m < km) {
+                const float2 Z = line[m * BQ_KS];
+                float2 Zc = line[(m == 0 ? 0 : K3 - m) * BQ_KS];
                 Zc.y = -Zc.y;
                 const float2 d = csub(Z, Zc);
                 const float2 ev = make_float2(0.5f * (Z.x + Zc.x), 0.5f * (Z.y + Zc.y));
                 const float2 od = make_float2(0.5f * d.y, -0.5f * d.x);
-                x[m] = (r & 1) ? od : ev;
+                xv[q] = (r & 1) ? od : ev;
+            }
+        }
+        __syncthreads();
+        if (r < rows) {
+#pragma unroll
+            for (int q = 0; q < PM; ++q) {
+                const int m = mf + q * STEP;
+                if (m < km) x[m] = xv[q];
             }
         }
     }
@@ -798,11 +813,13 @@ __global__ __launch_bounds__(BQ_NT) void k_bq_cols(BArgs a, const int2* __restri
 // r = j K2 + g2 at g3 is bf[2 (g3 BQ_KS + (r >> 1)) + (r & 1)].  Two rows a, b
 // of half spectra form Z(m) = X_a(m) + i X_b(m) over the full axis (Hermitian
 // extension); the inverse transform returns row a in the real and row b in the
-// imaginary part.  buf [K3][BQ_KS], then X2 [K2][BQ_KS2].
+// imaginary part.  buf [K3][BQ_KS] and X2 [K2][BQ_KS2] share their place: 33 KB at
+// most, so that four blocks share a CU (two with both side by side:
+// INV_BEFORE -> INV_AFTER us a launch for 1,024 structures).
 __device__ __forceinline__ void bq_planes_inv(const BArgs& a, const BStruct& S, int g1a, int planes, float2* buf,
                                               const float2* tw2, const float2* tw3, int tid) {
     const int K2 = S.K[1], K3 = S.K[2], km = S.km;
-    float2* X2 = buf + K3 * BQ_KS;
+    float2* X2 = buf;   // the packed lines take its place through registers
     const float2* C = slot_ptr<float2>(a, S, S.slot.C) + (size_t)g1a * S.nm2 * km;
     const int rows = planes * K2, cols = planes * km, kept = planes * S.nm2;
     // every load of the thread first, then the LDS stores
@@ -841,14 +858,22 @@ __device__ __forceinline__ void bq_planes_inv(const BArgs& a, const BStruct& S, 
         const float2* x = X2 + g2 * BQ_KS2 + j * km;
         float2* z = buf + (r >> 1);
         const bool odd = (r & 1) != 0;
+        constexpr int STEP = BQ_NT / (2 * BQ_NC), PM = (BQ_KAX / 2 + STEP) / STEP;
+        const int mf = tid / (2 * BQ_NC);
+        float2 zv[PM];
+#pragma unroll
+        for (int q = 0; q < PM; ++q) {
+            const int m = mf + q * STEP;
+            const float2 own = r < rows && m < km ? x[m] : make_float2(0.f, 0.f);
+            const float2 oth = make_float2(__shfl_xor(own.x, 1, 64), __shfl_xor(own.y, 1, 64));
+            zv[q] = odd ? make_float2(oth.x + own.y, own.x - oth.y) : make_float2(own.x - oth.y, own.y + oth.x);
+        }
+        __syncthreads();
         if (r < rows) {   // whole pairs: rows is even
-            for (int m = tid / (2 * BQ_NC); m <= K3 / 2; m += BQ_NT / (2 * BQ_NC)) {
-                const float2 own = m < km ? x[m] : make_float2(0.f, 0.f);
-                const float2 oth = make_float2(__shfl_xor(own.x, 1, 64), __shfl_xor(own.y, 1, 64));
-                if (!odd)
-                    z[m * BQ_KS] = make_float2(own.x - oth.y, own.y + oth.x);
-                else if (m > 0 && 2 * m < K3)
-                    z[(K3 - m) * BQ_KS] = make_float2(oth.x + own.y, own.x - oth.y);
+#pragma unroll
+            for (int q = 0; q < PM; ++q) {
+                const int m = mf + q * STEP;
+                if (odd ? m > 0 && 2 * m < K3 : 2 * m <= K3) z[(odd ? K3 - m : m) * BQ_KS] = zv[q];
             }
         }
     }
@@ -1366,11 +1391,12 @@ int run_wave(qeq_plan* pl, BatchState* b, BArgs& a, std::vector<BStruct>& st, co
              const std::vector<float2>& twh, const std::vector<float>& bmh, std::vector<BState>& state) {
     hipStream_t stream = pl->stream;
     const int ns = (int)work.size();
-    std::vector<int> nA(ns), nB(ns), nP(ns), nG(ns), nS(ns), nT(ns), xcd(ns);
+    std::vector<int> nA(ns), nB(ns), nC(ns), nP(ns), nG(ns), nS(ns), nT(ns), xcd(ns);
     double load[8] = {0.0};
     for (int w = 0; w < ns; ++w) {
         const BStruct& S = st[work[w]];
-        nA[w] = (S.K[0] + S.pb - 1) / S.pb;
+        nA[w] = (S.K[0] + S.pf - 1) / S.pf;
+        nC[w] = (S.K[0] + S.pb - 1) / S.pb;
         nB[w] = (S.nm2 * S.km + BQ_NC - 1) / BQ_NC;
         nP[w] = (S.n + BQ_PAIR_ATOMS - 1) / BQ_PAIR_ATOMS;
         nG[w] = (S.nhalf + BQ_GREEN - 1) / BQ_GREEN;
@@ -1379,9 +1405,10 @@ int run_wave(qeq_plan* pl, BatchState* b, BArgs& a, std::vector<BStruct>& st, co
         xcd[w] = (int)(std::min_element(load, load + 8) - load);   // longest first: balanced
         load[xcd[w]] += S.nhalf;
     }
-    std::vector<int2> uA, uB, uV, uP, uG, uS, uT;
+    std::vector<int2> uA, uB, uC, uV, uP, uG, uS, uT;
     deal_units(work, nA, 0, xcd, uA);
     deal_units(work, nB, 0, xcd, uB);
+    deal_units(work, nC, 0, xcd, uC);
     deal_units(work, nB, BQ_NT / BQ_L, xcd, uV, &st);   // with the pair products
     auto plain = [&](const std::vector<int>& pieces, std::vector<int2>& out) {
         for (int w = 0; w < ns; ++w)
@@ -1404,7 +1431,8 @@ int run_wave(qeq_plan* pl, BatchState* b, BArgs& a, std::vector<BStruct>& st, co
     const size_t oSt = place(sizeof(BStruct) * n_struct), oState = place(sizeof(BState) * n_struct),
                  oCount = place(sizeof(BCount)), oOrder = place(sizeof(int) * ns), oTw = place(sizeof(float2) * twh.size()),
                  oBm = place(sizeof(float) * bmh.size()), oA = place(sizeof(int2) * uA.size()),
-                 oB = place(sizeof(int2) * uB.size()), oV = place(sizeof(int2) * uV.size()), oP = place(sizeof(int2) * uP.size()),
+                 oB = place(sizeof(int2) * uB.size()), oV = place(sizeof(int2) * uV.size()),
+                 oC = place(sizeof(int2) * uC.size()), oP = place(sizeof(int2) * uP.size()),
                  oG = place(sizeof(int2) * uG.size()), oS = place(sizeof(int2) * uS.size()),
                  oT = place(sizeof(int2) * uT.size());
     if (o > b->staging_cap) {
@@ -1437,6 +1465,7 @@ int run_wave(qeq_plan* pl, BatchState* b, BArgs& a, std::vector<BStruct>& st, co
     put(oA, uA.data(), sizeof(int2) * uA.size());
     put(oB, uB.data(), sizeof(int2) * uB.size());
     put(oV, uV.data(), sizeof(int2) * uV.size());
+    put(oC, uC.data(), sizeof(int2) * uC.size());
     put(oP, uP.data(), sizeof(int2) * uP.size());
     put(oG, uG.data(), sizeof(int2) * uG.size());
     put(oS, uS.data(), sizeof(int2) * uS.size());
@@ -1450,15 +1479,14 @@ int run_wave(qeq_plan* pl, BatchState* b, BArgs& a, std::vector<BStruct>& st, co
     a.scratch = b->scratch;
     const int* order = (const int*)(b->tables + oOrder);
     const int2 *dA = (const int2*)(b->tables + oA), *dB = (const int2*)(b->tables + oB),
-               *dV = (const int2*)(b->tables + oV),
+               *dV = (const int2*)(b->tables + oV), *dC = (const int2*)(b->tables + oC),
                *dP = (const int2*)(b->tables + oP), *dG = (const int2*)(b->tables + oG),
                *dS = (const int2*)(b->tables + oS), *dT = (const int2*)(b->tables + oT);
     size_t shA = 0, shB = 0, shC = 0;
     for (int s : work) {
         const BStruct& S = st[s];
-        const size_t two = sizeof(float2) * ((size_t)S.K[2] * BQ_KS + (size_t)S.K[1] * BQ_KS2);
-        shC = std::max(shC, two);
-        shA = std::max({shA, two, sizeof(long long) * (size_t)S.K[2] * S.pb * S.K[1]});
+        shC = std::max({shC, sizeof(float2) * (size_t)S.K[2] * BQ_KS, sizeof(float2) * (size_t)S.K[1] * BQ_KS2});
+        shA = std::max({shA, shC, sizeof(long long) * (size_t)S.K[2] * S.pf * S.K[1]});
         shB = std::max(shB, sizeof(float2) * (size_t)S.K[0] * BQ_KS);
     }
     auto window = [](const void* fn, size_t sh) {
@@ -1486,10 +1514,10 @@ int run_wave(qeq_plan* pl, BatchState* b, BArgs& a, std::vector<BStruct>& st, co
         hipLaunchKernelGGL(k_bq_fwd, dim3((unsigned)uA.size()), dim3(BQ_NT), shA, stream, a, dA, mode);
         hipLaunchKernelGGL(k_bq_cols<false>, dim3((unsigned)uV.size()), dim3(BQ_NT), shB, stream, a, dV, mode);
         if (mode == BQ_FINAL) {
-            hipLaunchKernelGGL(k_bq_inv<true>, dim3((unsigned)uA.size()), dim3(BQ_NT), shC, stream, a, dA, mode);
+            hipLaunchKernelGGL(k_bq_inv<true>, dim3((unsigned)uC.size()), dim3(BQ_NT), shC, stream, a, dC, mode);
             hipLaunchKernelGGL(k_bq_step<BQ_FINAL>, dim3(ns), dim3(1024), 0, stream, a, order);
         } else {
-            hipLaunchKernelGGL(k_bq_inv<false>, dim3((unsigned)uA.size()), dim3(BQ_NT), shC, stream, a, dA, mode);
+            hipLaunchKernelGGL(k_bq_inv<false>, dim3((unsigned)uC.size()), dim3(BQ_NT), shC, stream, a, dC, mode);
             if (mode == BQ_INIT)
                 hipLaunchKernelGGL(k_bq_step<BQ_INIT>, dim3(ns), dim3(1024), 0, stream, a, order);
             else
@@ -1625,7 +1653,8 @@ int batched_impl(qeq_plan* pl, int n_struct, const int32_t* offs, const double* 
         }
         for (int x = 0; x < 3; ++x)
             if (std::find(Ks.begin(), Ks.end(), K[x]) == Ks.end()) Ks.push_back(K[x]);
-        S.pb = std::max(1, std::min({2 * BQ_NC / K[1], BQ_NC2 / S.km, K[0] - p + 1, BQ_PB}));
+        S.pf = S.pb = std::max(1, std::min({2 * BQ_NC / K[1], BQ_NC2 / S.km, K[0] - p + 1, BQ_PB}));
+        S.pf = std::max(1, std::min(S.pf, (int)(BQ_ACC / (sizeof(long long) * (size_t)K[1] * K[2]))));
         // pair capacity: mean neighbour count of a uniform density plus a
         // generous Poisson tail
         const double dens = n / det;
