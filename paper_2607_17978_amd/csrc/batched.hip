@@ -540,8 +540,12 @@ __device__ __forceinline__ float bq_float(long long x) {
 // term is rounded to an integer by one FP64 fused multiply-add with 1.5 * 2^52
 // (its bit pattern minus the constant's is the integer, exact below 2^51).
 // Planes of a block: as many as fill 128 real rows (64 complex lines of two)
-// and 56 half-spectrum columns; its barriers then pass with two to five planes'
-// work behind them and two blocks share a CU.
+// and 56 half-spectrum columns, so that its barriers pass with several planes'
+// work behind them, and whose accumulator takes at most 38,400 bytes, so that
+// four blocks share a CU: the block waits at its barriers, not for the VALU (58
+// KB, two blocks a CU: 226 us a launch for 1,024 structures, 18.1 for 48; now
+// 172 and 15.4.  Accumulating the planes in two halves instead kept the wide
+// blocks but took 95 registers: 272 us).
 __global__ __launch_bounds__(BQ_NT) void k_bq_fwd(BArgs a, const int2* __restrict__ units, int mode) {
     extern __shared__ float2 lds[];
     const int2 u = units[blockIdx.x];
@@ -815,7 +819,7 @@ __global__ __launch_bounds__(BQ_NT) void k_bq_cols(BArgs a, const int2* __restri
 // extension); the inverse transform returns row a in the real and row b in the
 // imaginary part.  buf [K3][BQ_KS] and X2 [K2][BQ_KS2] share their place: 33 KB at
 // most, so that four blocks share a CU (two with both side by side:
-// INV_BEFORE -> INV_AFTER us a launch for 1,024 structures).
+// 228 -> 147 us a launch for 1,024 structures).
 __device__ __forceinline__ void bq_planes_inv(const BArgs& a, const BStruct& S, int g1a, int planes, float2* buf,
                                               const float2* tw2, const float2* tw3, int tid) {
     const int K2 = S.K[1], K3 = S.K[2], km = S.km;

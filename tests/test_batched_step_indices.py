@@ -15,8 +15,13 @@ LENGTHS = (12, 16, 20, 24, 32, 36, 40, 48, 60, 64)
 NC, KS, NC2, KS2, NT, PB, KAX = 64, 65, 56, 57, 512, 8, 64
 
 
+ACC = 38400
+
+
 def planes_per_block(K, km, p):
-    return max(1, min(2 * NC // K[1], NC2 // km, K[0] - p + 1, PB))
+    """pf, pb: planes of a block of the forward and of the inverse kernel."""
+    pb = max(1, min(2 * NC // K[1], NC2 // km, K[0] - p + 1, PB))
+    return max(1, min(pb, ACC // (8 * K[1] * K[2]))), pb
 
 
 def walk(nm2, km, K2, kept):
@@ -46,13 +51,15 @@ def test_blocks_stay_inside_their_buffers(p):
         km = min(K3 // 2 + 1, int(share * K3 / 2) + 1)
         nm2 = min(K2, 2 * int(share * K2 / 2) + 1)
         assert (nm2 == K2 or nm2 % 2 == 1) and 1 <= nm2 <= K2
-        pb = planes_per_block(K, km, p)
-        rw = pb * K2
-        assert rw <= 2 * NC and rw % 2 == 0 and pb * km <= NC2 < KS2 and NC2 <= 64 and pb <= PB
+        pf, pb = planes_per_block(K, km, p)
+        assert 1 <= pf <= pb
+        rw = pf * K2
+        assert pb * K2 <= 2 * NC and rw <= 2 * NC and rw % 2 == 0 and pb * km <= NC2 < KS2 and NC2 <= 64 and pb <= PB
         assert pb + p - 1 <= K1                        # a block's candidate planes never overlap themselves
-        two = K3 * KS + K2 * KS2                       # buf + X2, complex
-        lds_fwd = max(two * 8, K3 * rw * 8)
-        assert lds_fwd <= 160 * 1024 - 4096
+        lds = max(K3 * KS * 8, K2 * KS2 * 8, K3 * rw * 8)   # lines, columns and accumulator share their place
+        assert lds <= ACC
+        # unpacking / packing slots: m = tid / 128 + 4 q, q < 9
+        assert 4 * ((KAX // 2 + 4) // 4) > K3 // 2
         # clears (int4), conversion (t -> (g3, c)), unpacking and packing
         assert (K3 * rw) % 2 == 0
         t = np.arange(KAX * NC)
@@ -60,6 +67,10 @@ def test_blocks_stay_inside_their_buffers(p):
         ok = (g3 < K3) & (c < rw // 2)
         assert (g3 * rw + 2 * c + 1)[ok].max() < K3 * rw and ok.sum() == K3 * rw // 2
         assert (g3 * KS + c)[g3 < K3].max() < K3 * KS
+        fwd = np.zeros(K1, dtype=int)
+        for y in range(-(-K1 // pf)):
+            fwd[y * pf:y * pf + min(pf, K1 - y * pf)] += 1
+        assert np.all(fwd == 1)
         done = np.zeros(K1, dtype=int)
         for y in range(-(-K1 // pb)):
             g1a, planes = y * pb, min(pb, K1 - y * pb)
