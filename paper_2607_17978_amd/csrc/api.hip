@@ -589,7 +589,8 @@ void chunk_key(const qeq_plan* pl, std::vector<unsigned char>& key) {
                           (const void*)(size_t)pl->ew_active, pl->ew_modes, pl->ew_w, pl->ew_sf, pl->ew_y,
                           pl->ew_yrec, (const void*)(size_t)pl->ew_nm, (const void*)(size_t)pl->ew_fs,
                           (const void*)(size_t)pl->ew_ms, (const void*)(size_t)pl->pw_active, pl->pw_ones,
-                          pl->pw_y, pl->pw_f};
+                          pl->pw_y, pl->pw_f, (const void*)(size_t)pl->pw_tiles, pl->pw_tstart, pl->pw_astart,
+                          pl->pw_rec, pl->pw_amp, pl->pw_ent, pl->pw_part};
     key.resize(sizeof(KParams) + sizeof(ptrs) + sizeof(DeviceAxes) + sizeof(PwGeom));
     unsigned char* k = key.data();
     memcpy(k, &pl->kp, sizeof(KParams));

@@ -71,6 +71,9 @@ struct PwGeom {
     float ext2, ext3; // sqrt(G33 / det23), sqrt(G22 / det23): in-plane extents per unit radius
     float HK[9];      // H[a][c] / K_a: Cartesian offset of one grid step along axis a
     float c2;         // (support radius / sigma)^2
+    float bext2, bext3;   // sqrt((G^-1)_22), sqrt((G^-1)_33): extents along the other axes
+    float hdiag;      // half diagonal of a 4 x 4 x 4 tile (bohr, rounded up)
+    float rmax;       // widest support radius (bohr)
     float wpref;      // dV / (2 pi)^{3/2}: theta = wpref / sigma^3 exp(-d^T G d / (2 sigma^2))
 };
 
@@ -289,6 +292,18 @@ struct qeq_plan {
     double* pw_y = nullptr;       // operator product, sorted order
     double* pw_f = nullptr;       // forces of the final product, sorted order
     double* pw_smax = nullptr;    // per-block maxima of sigma (host read once per set-up)
+    // support of every atom by 4 x 4 x 4 grid tiles (planewave.hip)
+    bool pw_tiles = false;        // built for the current geometry
+    int* pw_tcount = nullptr;     // [tiles + 1] entries per tile, then the fill cursors
+    int* pw_tstart = nullptr;     // [tiles + 1]
+    int* pw_acount = nullptr;     // [n] tiles per atom
+    int* pw_astart = nullptr;     // [n + 1]
+    size_t pw_cap_t = 0;          // tiles allocated
+    void* pw_rec = nullptr;       // float4 (fraction inside the grid cell, log2(e) / (2 sigma^2)) per atom
+    double* pw_amp = nullptr;     // dV / ((2 pi)^{3/2} sigma^3) per atom
+    void* pw_ent = nullptr;       // int4 (atom, tile offset 1 | 2 << 16, offset 3, slot) by tile
+    float* pw_part = nullptr;     // per slot: the tile's part of the atom's integral
+    size_t pw_cap_e = 0;          // entries allocated
     bool fused_inverse = true;    // fused inverse axis-2 + complex-to-real slab pass where it fits
     bool fused_forward = true;    // fused spread + axis-3 + axis-2 forward plane pass where it fits
     bool fused_interp = true;     // CG products: complex-to-real pass fused with the interpolation
@@ -430,6 +445,9 @@ bool rows_compiled(int K2, int nr);
 size_t qeq_mesh_max_smem(const KParams& k);
 // Inverse transforms only (grid_c already holds a spectrum) -> grid_r.
 int launch_mesh_inverse(qeq_plan* pl);
+// Real-to-complex transform along axis 3 of grid_r into grid_c (tiles of at most
+// LEN_TW rows: KParams::TW <= 16).
+int launch_mesh_r2c(qeq_plan* pl, const int* done);
 // Passes 2-5 (axis-2 FFT, axis-1 FFT + Green's function + inverse, inverse
 // axes 2 and 3) on a half spectrum that another pass 1 wrote into grid_c.
 int launch_mesh_from_spectrum(qeq_plan* pl, const int* done);

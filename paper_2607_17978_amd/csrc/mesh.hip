@@ -868,6 +868,10 @@ int launch_mesh_cg(qeq_plan* pl, const double* src, const int* done, bool* parti
     return c2r_interp_pass(pl, done);
 }
 
+int launch_mesh_r2c(qeq_plan* pl, const int* done) {
+    return mesh_len({pl, LEN_R2C, nullptr, 0, nullptr, nullptr, nullptr, nullptr, done, nullptr, nullptr}, pl->kp.K3);
+}
+
 int launch_mesh_from_spectrum(qeq_plan* pl, const int* done) {
     QEQ_TRY(rows_pass(pl, 0, done));
     QEQ_TRY(cols_pass(pl, MESH_FWD | MESH_GREEN | MESH_INV, nullptr, done));

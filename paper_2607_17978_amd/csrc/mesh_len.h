@@ -5,7 +5,7 @@
 
 #include "internal.h"
 
-enum LenPass { LEN_SPREAD, LEN_ROWS_FWD, LEN_ROWS_INV, LEN_COLS, LEN_VIRIAL, LEN_C2R, LEN_C2R_INTERP };
+enum LenPass { LEN_SPREAD, LEN_ROWS_FWD, LEN_ROWS_INV, LEN_COLS, LEN_VIRIAL, LEN_C2R, LEN_C2R_INTERP, LEN_R2C };
 
 struct LenCall {
     qeq_plan* pl;

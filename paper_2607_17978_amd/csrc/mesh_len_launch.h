@@ -54,6 +54,9 @@ int len_launch(const LenCall& c) {
         case LEN_C2R:
             LEN_GO((k_c2r<KC, TW, true>), k.K1 * k.ntile, sh_half + cx * (size_t)KC * (TW / 2), pl->axes.ax[2],
                    pl->grid_c, pl->grid_r, c.done);
+        case LEN_R2C:
+            LEN_GO((k_r2c<KC, TW>), k.K1 * k.ntile, cx * (KC + (size_t)KC * (TW / 2)), pl->axes.ax[2], pl->grid_r,
+                   pl->grid_c, c.done);
         case LEN_C2R_INTERP:
             if (k.p == 6)
                 LEN_GO((k_c2r_interp<KC, TW, 6, true>), k.K1 * k.ntile, sh_half, pl->axes.ax[2], pl->grid_c,

@@ -331,6 +331,60 @@ __global__ __launch_bounds__(NT) void k_spread_r2c(KParams k, FftAxis ax3, const
     }
 }
 
+// Pass 1 for a density that is already on the real grid (the Gaussian-on-grid
+// operator): real-to-complex along axis 3 of a (g1, row tile), two real rows per
+// complex line, as the spread's second half.  TWC is the widest tile.
+template <int KC, int TWC>
+__global__ __launch_bounds__(NT) void k_r2c(KParams k, FftAxis ax3, const float* __restrict__ R,
+                                           float2* __restrict__ C, const int* __restrict__ done) {
+    if (done && *done) return;
+    extern __shared__ float2 sm[];
+    float2* tw = sm;
+    float2* buf = sm + KC;
+    float* acc = reinterpret_cast<float*>(buf);   // [g3][row]
+    const int tid = threadIdx.x;
+    const int K1 = k.K1, K2 = k.K2;
+    const int blk = xcd_remap(blockIdx.x, gridDim.x);
+    const int g1 = blk / k.ntile;
+    int g20, W;
+    tile_of<true>(blk - g1 * k.ntile, k.ntile, K2, TWC, g20, W);
+    constexpr int NCS = TWC / 2, N4 = TWC * (KC / 4);
+    // lanes: 16 rows times 4 pieces of 16 bytes
+    stage2_ct<KC, N4, NT, float4>(
+        tid, [&](int t) { const float2 w = ax3.tw[t]; return make_float4(w.x, w.y, 0.f, 0.f); },
+        [&](int t, float4 v) { tw[t] = make_float2(v.x, v.y); },
+        [&](int t) {
+            const int r = t % TWC, c4 = t / TWC;
+            return r < W ? *reinterpret_cast<const float4*>(R + ((size_t)g1 * K2 + g20 + r) * KC + 4 * c4)
+                         : make_float4(0.f, 0.f, 0.f, 0.f);
+        },
+        [&](int t, float4 v) {
+            const int r = t % TWC, c4 = t / TWC;
+            acc[(4 * c4) * TWC + r] = v.x;
+            acc[(4 * c4 + 1) * TWC + r] = v.y;
+            acc[(4 * c4 + 2) * TWC + r] = v.z;
+            acc[(4 * c4 + 3) * TWC + r] = v.w;
+        });
+    __syncthreads();
+    fft_ct<KC, NCS, NCS, NT, false>(buf, tw, tid);
+    constexpr int NW = (KC / 2 + 1) * TWC, PW = (NW + NT - 1) / NT;
+#pragma unroll
+    for (int u = 0; u < PW; ++u) {
+        const int t = tid + u * NT;
+        if (NW % NT == 0 || t < NW) {
+            const int m = t / TWC, r = t - m * TWC, pr = r >> 1;
+            if (m >= k.K3h || r >= W) continue;
+            const float2 Z = buf[m * NCS + pr];
+            float2 Zc = buf[(m == 0 ? 0 : KC - m) * NCS + pr];
+            Zc.y = -Zc.y;
+            const float2 ev = make_float2(0.5f * (Z.x + Zc.x), 0.5f * (Z.y + Zc.y));
+            const float2 d = csub(Z, Zc);
+            const float2 od = make_float2(0.5f * d.y, -0.5f * d.x);
+            C[((size_t)m * K1 + g1) * K2 + g20 + r] = (r & 1) ? od : ev;
+        }
+    }
+}
+
 // ------------------------------------------------------------------ passes 2 / 4
 // LDS layout [k][row] with row stride NR + 1 (odd) for the compile-time path,
 // which keeps the transposing loads and stores free of bank conflicts.

@@ -19,14 +19,20 @@
 // self term and no background correction.
 //
 // Passes per product:
-//   1. zero the real grid; 2. spread, one wave per atom, FP32 global atomic
-//   additions (the support of ~10^3-10^4 points per atom does not fit the
-//   LDS tiles of the spline spread); 3. R2C along axis 3 in LDS tiles;
-//   4. the spline path's axis-2 / axis-1 (+ Green's function with eta = 0
-//   and unit moduli) / inverse passes; 5. integration, one wave per atom.
-// Inside a wave the points of one grid plane of the support ellipsoid's
-// bounding box are spread over the lanes with an incremental (row, column)
-// counter, so that no lane divides per point.
+//   1. spread: one wave per 4 x 4 x 4 grid tile, a lane per point, over the
+//   tile's list of atoms whose support meets it (built once per geometry), the
+//   sum in a register; 2. R2C along axis 3 in LDS tiles; 3. the spline path's
+//   axis-2 / axis-1 (+ Green's function with eta = 0 and unit moduli) / inverse
+//   passes; 4. integration: the same tiles and lists, each entry's 64 products
+//   summed over the wave, and a sum over each atom's tiles.
+// Against atoms walking their supports (FP32 global atomics in the spread, a
+// gather per atom in the integration): 4,096 atoms on 96^3, spread 87 + 4 (zero
+// fill) -> 21 us, integration 47 -> 31 us (a solve 9.2 -> 3.5 ms), and the sums have one
+// order.  Where the lists do not fit (PW_ENT_MAX entries) the walks remain: one
+// wave per atom, the points of one grid plane of the support ellipsoid's
+// bounding box spread over the lanes with an incremental (row, column) counter,
+// so that no lane divides per point.  The final product with forces always
+// walks.
 #include <math.h>
 #include <string.h>
 
@@ -34,6 +40,7 @@
 #include <vector>
 
 #include "internal.h"
+#include "mesh_len.h"
 
 namespace {
 
@@ -134,6 +141,252 @@ __device__ __forceinline__ void pw_walk(const KParams& k, const PwGeom& g, const
             }
         }
     }
+}
+
+// ------------------------------------------------------------------ tile lists
+constexpr int PW_E = 4;                          // points of a tile per axis (K_a % 4 == 0)
+constexpr size_t PW_ENT_MAX = (size_t)1 << 28;   // most list entries (5.4 GB)
+
+// Tiles that an atom's support can meet, over the lanes: f(tile index, offsets of
+// the tile's first point from the atom's grid cell, order among the atom's
+// tiles).  A tile is taken when its centre lies within the support radius plus
+// the tile's largest half diagonal (in the metric G): never too few.
+template <typename F>
+__device__ __forceinline__ int pw_tiles_of(const KParams& k, const PwGeom& g, const PwAtom& a, float hdiag, int lane,
+                                           F f) {
+    if (!(a.R2 > 0.f)) return 0;
+    const float R = sqrtf(a.R2), rr = (R + hdiag) * (R + hdiag) * 1.0001f;
+    const float ext[3] = {sqrtf(a.R2) * g.ext1, sqrtf(a.R2) * g.bext2, sqrtf(a.R2) * g.bext3};
+    const int Kt[3] = {k.K1 / PW_E, k.K2 / PW_E, k.K3 / PW_E};
+    int lo[3], cnt[3];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        const int p0 = a.fl[c] + (int)floorf(a.du[c] - ext[c]), p1 = a.fl[c] + (int)ceilf(a.du[c] + ext[c]);
+        lo[c] = (p0 - (((p0 % PW_E) + PW_E) % PW_E)) / PW_E;   // floor(p0 / 4)
+        cnt[c] = (p1 - (((p1 % PW_E) + PW_E) % PW_E)) / PW_E - lo[c] + 1;
+    }
+    const int total = cnt[0] * cnt[1] * cnt[2];
+    int found = 0;
+    for (int b = 0; b < total; b += 64) {
+        const int t = b + lane;
+        const int t3 = t % cnt[2], t2 = (t / cnt[2]) % cnt[1], t1 = t / (cnt[2] * cnt[1]);
+        const int T[3] = {lo[0] + t1, lo[1] + t2, lo[2] + t3};
+        int o[3];
+        float d[3];
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            o[c] = T[c] * PW_E - a.fl[c];
+            d[c] = (float)o[c] + 0.5f * (PW_E - 1) - a.du[c];
+        }
+        const float Q = g.G[0] * d[0] * d[0] + g.G[1] * d[1] * d[1] + g.G[2] * d[2] * d[2] +
+                        2.f * (g.G[3] * d[0] * d[1] + g.G[4] * d[0] * d[2] + g.G[5] * d[1] * d[2]);
+        const bool in = t < total && Q <= rr;
+        const unsigned long long m = __ballot(in);
+        if (in) {
+            const int tile = (pw_wrap(T[0], Kt[0]) * Kt[1] + pw_wrap(T[1], Kt[1])) * Kt[2] + pw_wrap(T[2], Kt[2]);
+            f(tile, o, found + __popcll(m & ((1ull << lane) - 1)));
+        }
+        found += __popcll(m);
+    }
+    return found;
+}
+
+// One wave per atom: its record, its tile count, the tiles' entry counts.
+__global__ __launch_bounds__(PW_NT) void k_pw_count(KParams k, PwGeom g, const double* __restrict__ frac,
+                                                  const double* __restrict__ sig, float4* __restrict__ rec,
+                                                  double* __restrict__ amp, int* __restrict__ acount,
+                                                  int* __restrict__ tcount) {
+    const int lane = threadIdx.x & 63;
+    const int i = (blockIdx.x * PW_NT + threadIdx.x) >> 6;
+    if (i >= k.n) return;
+    const double s = sig[i];
+    const PwAtom a = pw_atom(k, g, frac, s, i);
+    const int c = pw_tiles_of(k, g, a, g.hdiag, lane, [&](int tile, const int*, int) { atomicAdd(tcount + tile, 1); });
+    if (lane == 0) {
+        rec[i] = make_float4(a.du[0], a.du[1], a.du[2], a.lsc);
+        amp[i] = (double)g.wpref / (s * s * s);
+        acount[i] = c;
+    }
+}
+
+__global__ __launch_bounds__(PW_NT) void k_pw_fill(KParams k, PwGeom g, const double* __restrict__ frac,
+                                                 const double* __restrict__ sig, const int* __restrict__ astart,
+                                                 const int* __restrict__ tstart, int* __restrict__ cursor,
+                                                 int4* __restrict__ ent) {
+    const int lane = threadIdx.x & 63;
+    const int i = (blockIdx.x * PW_NT + threadIdx.x) >> 6;
+    if (i >= k.n) return;
+    const PwAtom a = pw_atom(k, g, frac, sig[i], i);
+    const int slot0 = astart[i];
+    pw_tiles_of(k, g, a, g.hdiag, lane, [&](int tile, const int* o, int order) {
+        // offsets stay within four grid lengths (the support check of the set-up)
+        const int at = tstart[tile] + atomicAdd(cursor + tile, 1);
+        ent[at] = make_int4(i, (o[0] & 0xffff) | (o[1] << 16), o[2], slot0 + order);
+    });
+}
+
+// One wave per tile: its entries in slot order (so by atom), whatever order the
+// fill's cursor gave them.  Short lists by rank within the wave, long ones by
+// rank over global memory.
+__global__ __launch_bounds__(PW_NT) void k_pw_order(int ntiles, const int* __restrict__ tstart,
+                                                  const int4* __restrict__ in, int4* __restrict__ out) {
+    const int lane = threadIdx.x & 63;
+    const int tile = (blockIdx.x * PW_NT + threadIdx.x) >> 6;
+    if (tile >= ntiles) return;
+    const int e0 = tstart[tile], cnt = tstart[tile + 1] - e0;
+    for (int b = 0; b < cnt; b += 64) {
+        const bool live = b + lane < cnt;
+        const int4 mine = live ? in[e0 + b + lane] : make_int4(0, 0, 0, 0);
+        int rank = 0;
+        for (int c = 0; c < cnt; c += 64) {
+            const int other = c + lane < cnt ? in[e0 + c + lane].w : 0x7fffffff;
+            const int m = min(64, cnt - c);
+            for (int t = 0; t < m; ++t) rank += __shfl(other, t, 64) < mine.w ? 1 : 0;
+        }
+        if (live) out[e0 + rank] = mine;
+    }
+}
+
+// Records of up to 64 entries of a tile, one per lane, in the wave's LDS: offsets
+// of the tile from the atom, the atom's fraction and exponent, R^2 and amplitude.
+struct PwRec {
+    float4 o;   // offsets 1, 2, 3, (c sigma)^2
+    float4 d;   // fractions 1, 2, 3, log2(e) / (2 sigma^2)
+    float amp;
+    int slot;
+    float pad[2];
+};
+
+__device__ __forceinline__ void pw_stage(const int4* ent, int e, bool live, const float4* rec, const double* amp,
+                                         const double* src, float c2, PwRec* out) {
+    if (!live) return;
+    const int4 t = ent[e];
+    PwRec r;
+    r.d = rec[t.x];
+    // (c sigma)^2 from the exponent: c^2 log2(e) / (2 lsc)
+    r.o = make_float4((float)(short)(t.y & 0xffff), (float)(t.y >> 16), (float)t.z, c2 * (0.5f * PW_LOG2E) / r.d.w);
+    r.amp = src ? (float)(src[t.x] * amp[t.x]) : 0.f;
+    r.slot = t.w;
+    *out = r;
+}
+
+// theta / amplitude of an entry at the lane's point (0 outside the support).
+template <bool ORTHO>
+__device__ __forceinline__ float pw_theta(const PwGeom& g, const PwRec& r, float a1, float a2, float a3) {
+    const float d1 = (r.o.x + a1) - r.d.x, d2 = (r.o.y + a2) - r.d.y, d3 = (r.o.z + a3) - r.d.z;
+    float Q;
+    if (ORTHO)
+        Q = g.G[0] * d1 * d1 + (g.G[1] * d2 * d2 + g.G[2] * d3 * d3);
+    else
+        Q = g.G[0] * d1 * d1 + d2 * (2.f * g.G[3] * d1 + g.G[1] * d2 + 2.f * g.G[5] * d3) +
+            d3 * (2.f * g.G[4] * d1 + g.G[2] * d3);
+    const float e = __builtin_amdgcn_exp2f(-Q * r.d.w);
+    return Q <= r.o.w ? e : 0.f;
+}
+
+// One wave per tile, a lane per point: Q(g) = sum over the tile's entries.
+// VALU-bound: about 20 instructions per entry and wave, 39 entries per tile at
+// 0.01 atoms per bohr^3 (30 of them reach a given point).
+template <bool ORTHO>
+__global__ __launch_bounds__(PW_NT) void k_pw_tile_spread(KParams k, PwGeom g, int ntiles,
+                                                        const int* __restrict__ tstart, const int4* __restrict__ ent,
+                                                        const float4* __restrict__ rec, const double* __restrict__ amp,
+                                                        const double* __restrict__ src, float* __restrict__ grid,
+                                                        const int* __restrict__ done) {
+    if (done && *done) return;
+    __shared__ PwRec recs[PW_NT / 64][64];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int tile = xcd_remap(blockIdx.x, gridDim.x) * (PW_NT / 64) + w;
+    if (tile >= ntiles) return;   // whole waves; no block barriers below
+    const int e0 = tstart[tile], e1 = tstart[tile + 1];
+    const float a1 = (float)(lane >> 4), a2 = (float)((lane >> 2) & 3), a3 = (float)(lane & 3);
+    float q = 0.f;
+    for (int e = e0; e < e1; e += 64) {
+        const int m = min(64, e1 - e);
+        __builtin_amdgcn_wave_barrier();
+        pw_stage(ent, e + lane, lane < m, rec, amp, src, g.c2, &recs[w][lane]);
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll 4
+        for (int t = 0; t < m; ++t) {
+            const PwRec& r = recs[w][t];
+            q += r.amp * pw_theta<ORTHO>(g, r, a1, a2, a3);
+        }
+    }
+    const int Kt2 = k.K2 / PW_E, Kt3 = k.K3 / PW_E;
+    const int T3 = tile % Kt3, T2 = (tile / Kt3) % Kt2, T1 = tile / (Kt3 * Kt2);
+    grid[((size_t)(T1 * PW_E + (lane >> 4)) * k.K2 + T2 * PW_E + ((lane >> 2) & 3)) * k.K3 + T3 * PW_E + (lane & 3)] = q;
+}
+
+// Sum over each row of 16 lanes, in all of them (rotations within the row).
+__device__ __forceinline__ float pw_row_sum(float x) {
+    x += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x128, 0xf, 0xf, false));   // row_ror:8
+    x += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x124, 0xf, 0xf, false));   // row_ror:4
+    x += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x122, 0xf, 0xf, false));   // row_ror:2
+    x += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x121, 0xf, 0xf, false));   // row_ror:1
+    return x;
+}
+
+// The integration's part of a tile: part[slot] = sum over the tile's points of
+// theta phi / amplitude.  An entry's products are added within each row of 16
+// lanes; lane t of every row keeps entry t of 16, and two exchanges add the four
+// rows of all 16 (exchanging the entries' products by halving, 32 at a time, took
+// 140 registers and 190 us at 4,096 atoms).
+template <bool ORTHO>
+__global__ __launch_bounds__(PW_NT) void k_pw_tile_interp(KParams k, PwGeom g, int ntiles,
+                                                        const int* __restrict__ tstart, const int4* __restrict__ ent,
+                                                        const float4* __restrict__ rec, const float* __restrict__ grid,
+                                                        float* __restrict__ part, const int* __restrict__ done) {
+    if (done && *done) return;
+    __shared__ PwRec recs[PW_NT / 64][64];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int tile = xcd_remap(blockIdx.x, gridDim.x) * (PW_NT / 64) + w;
+    if (tile >= ntiles) return;
+    const int e0 = tstart[tile], e1 = tstart[tile + 1];
+    const float a1 = (float)(lane >> 4), a2 = (float)((lane >> 2) & 3), a3 = (float)(lane & 3);
+    const int Kt2 = k.K2 / PW_E, Kt3 = k.K3 / PW_E;
+    const int T3 = tile % Kt3, T2 = (tile / Kt3) % Kt2, T1 = tile / (Kt3 * Kt2);
+    const float phi =
+        grid[((size_t)(T1 * PW_E + (lane >> 4)) * k.K2 + T2 * PW_E + ((lane >> 2) & 3)) * k.K3 + T3 * PW_E + (lane & 3)];
+    for (int e = e0; e < e1; e += 64) {
+        const int m = min(64, e1 - e);
+        __builtin_amdgcn_wave_barrier();
+        pw_stage(ent, e + lane, lane < m, rec, nullptr, nullptr, g.c2, &recs[w][lane]);
+        __builtin_amdgcn_wave_barrier();
+        for (int b = 0; b < m; b += 16) {
+            float keep = 0.f;
+#pragma unroll 4
+            for (int t = 0; t < 16; ++t) {
+                if (b + t >= m) break;   // uniform
+                const float x = pw_row_sum(phi * pw_theta<ORTHO>(g, recs[w][b + t], a1, a2, a3));
+                keep = (lane & 15) == t ? x : keep;
+            }
+            keep += __shfl_xor(keep, 16, 64);
+            keep += __shfl_xor(keep, 32, 64);
+            if (lane < 16 && b + lane < m) part[recs[w][b + lane].slot] = keep;
+        }
+    }
+}
+
+// y_i = amplitude sum over the atom's tiles, 16 lanes per atom.
+__global__ __launch_bounds__(PW_NT) void k_pw_tile_sum(int n, const int* __restrict__ astart,
+                                                     const float* __restrict__ part, const double* __restrict__ amp,
+                                                     double* __restrict__ y, const int* __restrict__ done) {
+    if (done && *done) return;
+    const int l = threadIdx.x & 15, i = (blockIdx.x * PW_NT + threadIdx.x) >> 4;
+    double v = 0.0;
+    if (i < n) {
+        const int e1 = astart[i + 1];
+#pragma unroll 4
+        for (int e = astart[i] + l; e < e1; e += 16) v += (double)part[e];
+    }
+#pragma unroll
+    for (int d = 8; d > 0; d >>= 1) v += __shfl_xor(v, d, 64);
+    if (i < n && l == 0) y[i] = amp[i] * v;
+}
+
+__global__ __launch_bounds__(PW_NT) void k_pw_clear(int* __restrict__ x, size_t m) {
+    const size_t t = (size_t)blockIdx.x * PW_NT + threadIdx.x;
+    if (t < m) x[t] = 0;
 }
 
 __global__ __launch_bounds__(PW_NT) void k_pw_zero(float4* __restrict__ grid, size_t n4, const int* __restrict__ done) {
@@ -328,13 +581,90 @@ bool invert3(const double m[9], double out[9]) {
 
 }  // namespace
 
+// Sized by the current lists (also after a failed allocation).
+static void pw_free_entries(qeq_plan* pl) {
+    if (pl->pw_ent) (void)hipFree(pl->pw_ent);
+    if (pl->pw_part) (void)hipFree(pl->pw_part);
+    pl->pw_ent = nullptr;
+    pl->pw_part = nullptr;
+    pl->pw_cap_e = 0;
+}
+
 void pw_free(qeq_plan* pl) {
-    void* ptrs[] = {pl->pw_ones, pl->pw_y, pl->pw_f, pl->pw_smax};
+    void* ptrs[] = {pl->pw_ones,   pl->pw_y,      pl->pw_f,      pl->pw_smax, pl->pw_tcount,
+                    pl->pw_tstart, pl->pw_acount, pl->pw_astart, pl->pw_rec,  pl->pw_amp};
     for (void* q : ptrs)
         if (q) (void)hipFree(q);
+    pw_free_entries(pl);
+    pl->pw_tcount = pl->pw_tstart = pl->pw_acount = pl->pw_astart = nullptr;
+    pl->pw_rec = nullptr;
+    pl->pw_amp = nullptr;
+    pl->pw_cap_t = 0;
+    pl->pw_tiles = false;
     pl->pw_ones = nullptr;
     pl->pw_y = pl->pw_f = pl->pw_smax = nullptr;
     pl->pw_cap_n = pl->pw_cap_k = 0;
+}
+
+// Tile lists of the current geometry (pw_tiles = false, and the walks instead,
+// where they have more than PW_ENT_MAX entries or do not fit the free memory;
+// the axis-3 pass takes tiles of at most LEN_TW rows).  One host
+// synchronisation for their length.
+static int pw_lists(qeq_plan* pl) {
+    const KParams& k = pl->kp;
+    pl->pw_tiles = false;
+    if (k.TW > LEN_TW) return QEQ_OK;
+    const size_t nt = (size_t)(k.K1 / PW_E) * (k.K2 / PW_E) * (k.K3 / PW_E);
+    if (nt > pl->pw_cap_t) {
+        QEQ_TRY(pw_alloc(&pl->pw_tcount, nt + 1));
+        QEQ_TRY(pw_alloc(&pl->pw_tstart, nt + 1));
+        pl->pw_cap_t = nt;
+    }
+    const int nb = (int)(((size_t)k.n * 64 + PW_NT - 1) / PW_NT);
+    const unsigned cb = (unsigned)((nt + PW_NT - 1) / PW_NT), ob = (unsigned)((nt * 64 + PW_NT - 1) / PW_NT);
+    hipStream_t st = pl->stream;
+    // bound on the entries: the bounding box of the widest support, every atom
+    // (counts past 2^31 cannot arise below it)
+    const double widest = 2.0 * pl->pw_geom.rmax;
+    double most = (double)k.n;
+    const float be[3] = {pl->pw_geom.ext1, pl->pw_geom.bext2, pl->pw_geom.bext3};
+    for (int a = 0; a < 3; ++a) most *= widest * be[a] / PW_E + 3.0;
+    if (most > 2.0e9) return QEQ_OK;
+    hipLaunchKernelGGL(k_pw_clear, dim3(cb), dim3(PW_NT), 0, st, pl->pw_tcount, nt);
+    hipLaunchKernelGGL(k_pw_count, dim3(nb), dim3(PW_NT), 0, st, k, pl->pw_geom, pl->frac, pl->sig,
+                       (float4*)pl->pw_rec, pl->pw_amp, pl->pw_acount, pl->pw_tcount);
+    QEQ_TRY(launch_scan(pl, pl->pw_tcount, pl->pw_tstart, (int)nt));
+    QEQ_TRY(launch_scan(pl, pl->pw_acount, pl->pw_astart, k.n));
+    int total = 0;
+    QEQ_HIP(hipMemcpyAsync(&total, pl->pw_astart + k.n, sizeof(int), hipMemcpyDeviceToHost, st));
+    QEQ_HIP(hipStreamSynchronize(st));
+    if (total < 0 || (size_t)total > PW_ENT_MAX) return QEQ_OK;
+    if ((size_t)total > pl->pw_cap_e) {
+        pw_free_entries(pl);
+        const size_t cap = std::min(PW_ENT_MAX, (size_t)total + (size_t)total / 8 + 1024);
+        // the entries twice: as filled, and in order
+        if (hipMalloc(&pl->pw_ent, 2 * cap * sizeof(int4)) != hipSuccess) {
+            pl->pw_ent = nullptr;
+            (void)hipGetLastError();
+            return QEQ_OK;
+        }
+        if (hipMalloc((void**)&pl->pw_part, cap * sizeof(float)) != hipSuccess) {
+            pl->pw_part = nullptr;
+            pw_free_entries(pl);
+            (void)hipGetLastError();
+            return QEQ_OK;
+        }
+        debug_poison(pl->pw_part, cap * sizeof(float));
+        pl->pw_cap_e = cap;
+    }
+    int4* ent = (int4*)pl->pw_ent;
+    hipLaunchKernelGGL(k_pw_clear, dim3(cb), dim3(PW_NT), 0, st, pl->pw_tcount, nt);
+    hipLaunchKernelGGL(k_pw_fill, dim3(nb), dim3(PW_NT), 0, st, k, pl->pw_geom, pl->frac, pl->sig, pl->pw_astart,
+                       pl->pw_tstart, pl->pw_tcount, ent + pl->pw_cap_e);
+    hipLaunchKernelGGL(k_pw_order, dim3(ob), dim3(PW_NT), 0, st, (int)nt, pl->pw_tstart, ent + pl->pw_cap_e, ent);
+    QEQ_TRY(qeq_check(hipGetLastError()));
+    pl->pw_tiles = true;
+    return QEQ_OK;
 }
 
 // Geometry of the current cell and grid; buffers grown as needed.  One host
@@ -353,6 +683,10 @@ int pw_setup(qeq_plan* pl) {
         QEQ_TRY(pw_alloc(&pl->pw_y, nn));
         QEQ_TRY(pw_alloc(&pl->pw_f, 3 * nn));
         QEQ_TRY(pw_alloc(&pl->pw_smax, (nn + PW_NT - 1) / PW_NT));
+        QEQ_TRY(pw_alloc(&pl->pw_acount, nn + 1));
+        QEQ_TRY(pw_alloc(&pl->pw_astart, nn + 1));
+        QEQ_TRY(pw_alloc((float4**)&pl->pw_rec, nn));
+        QEQ_TRY(pw_alloc(&pl->pw_amp, nn));
         pl->pw_cap_n = pl->n_max;
     }
     const int Kd[3] = {k.K1, k.K2, k.K3};
@@ -374,6 +708,18 @@ int pw_setup(qeq_plan* pl) {
     g.inv_det23 = (float)(1.0 / det23);
     g.ext2 = (float)sqrt(G[8] / det23);
     g.ext3 = (float)sqrt(G[4] / det23);
+    g.bext2 = (float)sqrt(Gi[4]);
+    g.bext3 = (float)sqrt(Gi[8]);
+    // half diagonal of a tile (first to last point), over its four diagonals
+    double hd = 0.0;
+    for (int sgn = 0; sgn < 4; ++sgn) {
+        const double h[3] = {0.5 * (PW_E - 1), (sgn & 1 ? -0.5 : 0.5) * (PW_E - 1), (sgn & 2 ? -0.5 : 0.5) * (PW_E - 1)};
+        double q2 = 0.0;
+        for (int a = 0; a < 3; ++a)
+            for (int b = 0; b < 3; ++b) q2 += h[a] * h[b] * G[a * 3 + b];
+        hd = std::max(hd, q2);
+    }
+    g.hdiag = (float)(1.0001 * sqrt(hd));
     for (int a = 0; a < 3; ++a)
         for (int c = 0; c < 3; ++c) g.HK[a * 3 + c] = (float)(k.H[a * 3 + c] / Kd[a]);
     g.c2 = (float)(pl->pw_support * pl->pw_support);
@@ -390,9 +736,10 @@ int pw_setup(qeq_plan* pl) {
     double sm = 0.0;
     for (double v : smax) sm = std::max(sm, v);
     const double R = pl->pw_support * sm;
+    g.rmax = (float)R;
     for (int a = 0; a < 3; ++a)
         if (R * sqrt(Gi[a * 4]) > 4.0 * Kd[a]) return QEQ_EPLAN;
-    return QEQ_OK;
+    return pw_lists(pl);
 }
 
 static int pw_interp_launch(qeq_plan* pl, const double* src, const int* done, bool fin, int nb) {
@@ -412,6 +759,32 @@ int launch_pw_rec(qeq_plan* pl, const double* src, const int* done, bool fin) {
     const size_t sh = sizeof(float2) * ((size_t)k.K3 + (size_t)k.K3 * (k.TW / 2));
     const int nb = pw_blocks(k.n);
     const size_t nreal = (size_t)k.K1 * k.K2 * k.K3;   // a multiple of 4 (K_a % 4 == 0)
+    if (pl->pw_tiles) {
+        const int nt = (int)(nreal / 64);
+        const dim3 tb((unsigned)((nt + PW_NT / 64 - 1) / (PW_NT / 64)));
+        const PwGeom& g = pl->pw_geom;
+        const bool ortho = g.G[3] == 0.f && g.G[4] == 0.f && g.G[5] == 0.f;
+        const int4* ent = (const int4*)pl->pw_ent;
+        const float4* rec = (const float4*)pl->pw_rec;
+        if (ortho)
+            hipLaunchKernelGGL(k_pw_tile_spread<true>, tb, dim3(PW_NT), 0, pl->stream, k, g, nt, pl->pw_tstart, ent, rec,
+                               pl->pw_amp, src, pl->grid_r, done);
+        else
+            hipLaunchKernelGGL(k_pw_tile_spread<false>, tb, dim3(PW_NT), 0, pl->stream, k, g, nt, pl->pw_tstart, ent,
+                               rec, pl->pw_amp, src, pl->grid_r, done);
+        QEQ_TRY(launch_mesh_r2c(pl, done));
+        QEQ_TRY(launch_mesh_from_spectrum(pl, done));
+        if (fin) return pw_interp_launch(pl, src, done, fin, nb);
+        if (ortho)
+            hipLaunchKernelGGL(k_pw_tile_interp<true>, tb, dim3(PW_NT), 0, pl->stream, k, g, nt, pl->pw_tstart, ent, rec,
+                               pl->grid_r, pl->pw_part, done);
+        else
+            hipLaunchKernelGGL(k_pw_tile_interp<false>, tb, dim3(PW_NT), 0, pl->stream, k, g, nt, pl->pw_tstart, ent,
+                               rec, pl->grid_r, pl->pw_part, done);
+        hipLaunchKernelGGL(k_pw_tile_sum, dim3((unsigned)((k.n * 16 + PW_NT - 1) / PW_NT)), dim3(PW_NT), 0, pl->stream,
+                           k.n, pl->pw_astart, pl->pw_part, pl->pw_amp, pl->pw_y, done);
+        return qeq_check(hipGetLastError());
+    }
     hipLaunchKernelGGL(k_pw_zero, dim3((unsigned)((nreal / 4 + PW_NT - 1) / PW_NT)), dim3(PW_NT), 0, pl->stream,
                        (float4*)pl->grid_r, nreal / 4, done);
     hipLaunchKernelGGL(k_pw_spread, dim3(nb), dim3(PW_NT), 0, pl->stream, k, pl->pw_geom, src, pl->frac, pl->sig,
