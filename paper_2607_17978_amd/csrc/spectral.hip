@@ -272,11 +272,11 @@ __global__ __launch_bounds__(256) void k_spc_gemm(int ncp, const double* __restr
         acc0 = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b0, acc0, 0, 0, 0);
         acc1 = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b1, acc1, 0, 0, 0);
     }
-    // D layout: lane l holds rows 4 (l/16) + j of column l%16
+    // D layout of the FP64 instruction: lane l holds rows l/16 + 4 j of column l%16
     double* C = Cpart + (size_t)blockIdx.z * ncp * ncp;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-        const size_t o = (size_t)(row0 + 4 * g + j) * ncp + col0 + r;
+        const size_t o = (size_t)(row0 + g + 4 * j) * ncp + col0 + r;
         C[o] = acc0[j];
         C[o + 16] = acc1[j];
     }
