@@ -586,17 +586,19 @@ void chunk_key(const qeq_plan* pl, std::vector<unsigned char>& key) {
                           (const void*)(size_t)pl->spc_npad, (const void*)(size_t)pl->direct, pl->np_pos,
                           pl->np_ypart, (const void*)(size_t)pl->np_nsplit, (const void*)(size_t)pl->np_per,
                           pl->np_mat, (const void*)(size_t)pl->np_ld,
-                          (const void*)(size_t)pl->ew_active, pl->ew_modes, pl->ew_w, pl->ew_sf, pl->ew_y,
-                          pl->ew_yrec, (const void*)(size_t)pl->ew_nm, (const void*)(size_t)pl->ew_fs,
+                          (const void*)(size_t)pl->ew_active, pl->ew_rows, pl->ew_tiles, pl->ew_units, pl->ew_tab,
+                          pl->ew_w, pl->ew_F, pl->ew_y, pl->ew_yrec, (const void*)(size_t)pl->ew_use_tab,
+                          (const void*)(size_t)pl->ew_nrt, (const void*)(size_t)pl->ew_nu,
                           (const void*)(size_t)pl->ew_ms, (const void*)(size_t)pl->pw_active, pl->pw_ones,
                           pl->pw_y, pl->pw_f, (const void*)(size_t)pl->pw_tiles, pl->pw_tstart, pl->pw_astart,
                           pl->pw_rec, pl->pw_amp, pl->pw_ent, pl->pw_part};
-    key.resize(sizeof(KParams) + sizeof(ptrs) + sizeof(DeviceAxes) + sizeof(PwGeom));
+    key.resize(sizeof(KParams) + sizeof(ptrs) + sizeof(DeviceAxes) + sizeof(PwGeom) + sizeof(EwGeom));
     unsigned char* k = key.data();
     memcpy(k, &pl->kp, sizeof(KParams));
     memcpy(k + sizeof(KParams), ptrs, sizeof(ptrs));
     memcpy(k + sizeof(KParams) + sizeof(ptrs), &pl->axes, sizeof(DeviceAxes));
     memcpy(k + sizeof(KParams) + sizeof(ptrs) + sizeof(DeviceAxes), &pl->pw_geom, sizeof(PwGeom));
+    memcpy(k + sizeof(KParams) + sizeof(ptrs) + sizeof(DeviceAxes) + sizeof(PwGeom), &pl->ew_geom, sizeof(EwGeom));
 }
 
 void drop_graph(qeq_plan* pl) {

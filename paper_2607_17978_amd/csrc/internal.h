@@ -77,6 +77,15 @@ struct PwGeom {
     float wpref;      // dV / (2 pi)^{3/2}: theta = wpref / sigma^3 exp(-d^T G d / (2 sigma^2))
 };
 
+// Mode layout of the direct Ewald sums: axis slots 0, 1 (a row) and 2 (m_c).
+struct EwGeom {
+    int ax[3];        // cell axis of each slot
+    int lim[3];       // largest multiple of each slot
+    int toff[3];      // first table line of each slot
+    int ntab;         // lines of the phase table
+    double kmax2;
+};
+
 // Scalars that live on the device between CG kernels.
 struct CgScalars {
     double rz[2];             // r.z of the current direction, double-buffered by parity
@@ -259,13 +268,20 @@ struct qeq_plan {
     // reciprocal part by direct Ewald sums instead of the mesh (qeq_use_ewald)
     bool ewald = false;           // requested for later periodic solves
     bool ew_active = false;       // the current solve's operator uses it
-    int ew_nm = 0, ew_fs = 1, ew_fper = 0, ew_ms = 1, ew_mper = 0;   // modes, atom / mode splits
-    int ew_cap_m = 0, ew_cap_n = 0;
-    void* ew_modes = nullptr;     // int4 (m1, m2, m3, 0) per mode
-    double* ew_w = nullptr;       // weights 2 (4 pi / V) exp(-eta^2 k^2 / 2) / k^2
-    double* ew_sf = nullptr;      // [atom split][mode][2] structure-factor partials
-    double* ew_y = nullptr;       // [mode split][atom] potential partials
-    double* ew_f = nullptr;       // [mode split][atom][3] force partials
+    EwGeom ew_geom{};
+    bool ew_use_tab = false;      // phases from the table (else computed in place)
+    int ew_nrt = 0, ew_nu = 0, ew_ms = 1;   // row tiles, (row tile, m_c tile) units, row splits
+    size_t ew_cap_l = 0, ew_cap_u = 0, ew_cap_t = 0;
+    int ew_cap_n = 0;
+    void* ew_lists = nullptr;     // the three lists below, one allocation
+    void* ew_rows = nullptr;      // int4 (m_a, m_b, longest |m_c|, 0), padded to tiles of 16
+    void* ew_tiles = nullptr;     // int2 (first K step in F, K steps) per row tile
+    void* ew_units = nullptr;     // int2 (row tile, m_c tile)
+    double* ew_tab = nullptr;     // phase table [axis slot and multiple][atom], complex
+    double* ew_w = nullptr;       // [unit][m_c][row] weights w+, w-: 2 (4 pi / V) exp(-eta^2 k^2 / 2) / k^2
+    double* ew_F = nullptr;       // [K step][4 combinations][m_c of 4][row of 16] weighted structure factors
+    double* ew_y = nullptr;       // [row split][atom] potential partials
+    double* ew_f = nullptr;       // [row split][atom][3] force partials
     double* ew_yrec = nullptr;    // reciprocal product, sorted order
     double* ew_frec = nullptr;    // reciprocal forces of the final product
     // SQNM instead of CG for qeq_solve (qeq_use_sqnm)
