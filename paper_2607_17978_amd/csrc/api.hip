@@ -1,5 +1,6 @@
 // Host side of the library: plans (device workspace, FFT tables, cell cache),
 // the solve / matvec orchestration on the plan's stream, and the C ABI.
+#include <limits.h>
 #include <math.h>
 #include <stdio.h>
 #include <stdlib.h>
@@ -719,6 +720,18 @@ int operator_product(qeq_plan* pl, const double* src, double* dst) {
 
 namespace {
 
+// Iterations per replayed graph.  Every replay costs the device about 10 us
+// at its start, and on average half a chunk of early-returning kernels (2 us
+// each, eight an iteration) runs past convergence; solves take 10 iterations
+// (64 atoms) to 90 (131,072).  At 64 / 512 / 4,096 / 32,768 atoms chunks of 4
+// took 603 / 907 / 1,541 / 4,878 us, of 6 597 / 855 / 1,556 / 4,796, of 12 755 /
+// 928 / 1,532 / 4,744; the spectral preconditioner (14 to 23 iterations) is
+// fastest at 6 as well.  From 16,384 atoms on, where the iterations are many
+// and the early returns are a small part of each, 12.
+constexpr int CG_CHUNK = 6;
+constexpr int CG_CHUNK_LARGE = 12;
+constexpr int CG_LARGE = 16384;
+
 // Projected CG from q0 (or Q/N) to the tolerance, with the true-residual
 // restart, then the final matvec: energies, mu, true residual and forces are
 // computed; q_out / energies / forces_out (caller order) may be NULL.
@@ -728,11 +741,8 @@ int cg_run(qeq_plan* pl, const double* q0, double* q_out, double* energies, doub
     pl->warm_rejected = false;
     // initial guess (projected onto the constraint plane)
     QEQ_TRY(launch_cg_init_q(pl, q0));
-    // iterations per replayed graph: 12 for the Jacobi solves (57-125
-    // iterations here), 4 with the spectral preconditioner (17-29), whose
-    // early-returning launches after convergence would outweigh the saved
-    // graph launches of longer chunks
-    const int chunk = pl->spc_active ? 4 : 12;
+    const int chunk = pl->kp.n >= CG_LARGE && !pl->spc_active ? CG_CHUNK_LARGE : CG_CHUNK;
+    double res0 = 1.0;   // residual of the starting point (q = 0: 1)
     int it = 0;
     bool conv = false;
     // The recursive residual of CG drifts from the true one by the FP32 error
@@ -761,6 +771,7 @@ int cg_run(qeq_plan* pl, const double* q0, double* q_out, double* energies, doub
             QEQ_HIP(hipMemcpyAsync(pl->sc_host, pl->sc, sizeof(CgScalars), hipMemcpyDeviceToHost, pl->stream));
             QEQ_HIP(hipStreamSynchronize(pl->stream));
             const bool worse = pl->kp.q_tot == 0.0 ? !(pl->sc_host->e_start < 0.0) : !(pl->sc_host->res <= 1.0);
+            res0 = worse ? 1.0 : pl->sc_host->res;
             if (worse) {
                 pl->warm_rejected = true;
                 QEQ_TRY(launch_cg_init_q(pl, nullptr));
@@ -771,23 +782,35 @@ int cg_run(qeq_plan* pl, const double* q0, double* q_out, double* energies, doub
         }
         conv = false;
         int local = 0;
-        // Each chunk's scalars are copied to a pinned ring slot behind it.
-        // While the last residual seen is far above the tolerance (more than
-        // two chunks of CG reduction away), the next chunk is launched before
-        // the host waits for the copy, so the GPU does not idle during the
-        // read-back; near convergence the host waits after every chunk, so
-        // at most one chunk of early-returning kernels is ever launched in
-        // vain.
+        // Each chunk's scalars are copied to a pinned ring slot behind it.  The
+        // residuals seen so far give the iteration at which the tolerance will
+        // be met (the reduction per iteration of the last chunk, carried on):
+        // up to there the next chunk is launched before the host waits for the
+        // copy, so the GPU does not idle during the read-back; the last chunk
+        // is cut to the iterations that are still expected, and then the host
+        // waits.  What is launched past convergence returns early.
         if (!pl->ring_ev[0]) {
             for (int e = 0; e < 2; ++e)
                 QEQ_HIP(hipEventCreateWithFlags(&pl->ring_ev[e], hipEventDisableTiming));
         }
         int slot = 0, prev = -1;
-        double res_seen = 1e300;
-        const double ahead_thr = 20.0 * pl->prm.tol;
+        int launched[2] = {0, 0};           // iterations launched up to each slot's copy
+        // last iteration whose residual was read; where the tolerance is
+        // expected (a restart: within the first chunk)
+        int it_seen = 0, need = restart ? chunk : INT_MAX;
+        double res_seen = restart ? pl->out_host[3] : res0;
+        auto seen = [&](int sl) {
+            const double res = pl->sc_ring[sl].res, rate = log(res_seen / res) / (launched[sl] - it_seen);
+            need = rate > 0.0 ? (int)std::min(1e9, launched[sl] + ceil(log(res / pl->prm.tol) / rate)) : INT_MAX;
+            res_seen = res;
+            it_seen = launched[sl];
+            return pl->sc_ring[sl].done != 0;
+        };
         bool stop = false;
         while (it < pl->prm.max_iter && !stop) {
             int m = std::min(chunk, pl->prm.max_iter - it);
+            if (need - local < m) m = std::max(2, need - local + ((need - local) & 1));
+            m = std::min(m, pl->prm.max_iter - it);
             // per-stage timers need eager launches (events recorded inside a
             // graph cannot be read back with hipEventElapsedTime)
             if (m == chunk && (local & 1) == 0 && pl->use_graphs && pl->prof_mask == 0) {
@@ -805,18 +828,17 @@ int cg_run(qeq_plan* pl, const double* q0, double* q_out, double* energies, doub
             QEQ_HIP(hipMemcpyAsync(&pl->sc_ring[slot], pl->sc, sizeof(CgScalars), hipMemcpyDeviceToHost,
                                    pl->stream));
             QEQ_HIP(hipEventRecord(pl->ring_ev[slot], pl->stream));
+            launched[slot] = local;
             if (prev >= 0) {   // the chunk before this one
                 QEQ_HIP(hipEventSynchronize(pl->ring_ev[prev]));
-                if (pl->sc_ring[prev].done) break;
-                res_seen = pl->sc_ring[prev].res;
+                if (seen(prev)) break;
                 prev = -1;
             }
-            if (res_seen > ahead_thr && pl->prof_mask == 0) {
+            if (need > local && pl->prof_mask == 0) {
                 prev = slot;   // go on without waiting for this chunk
             } else {
                 QEQ_HIP(hipEventSynchronize(pl->ring_ev[slot]));
-                stop = pl->sc_ring[slot].done != 0;
-                res_seen = pl->sc_ring[slot].res;
+                stop = seen(slot);
             }
             slot ^= 1;
         }
