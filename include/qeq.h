@@ -347,8 +347,10 @@ int qeq_use_graphs(qeq_plan* plan, int32_t enable);
    in the LDS of one compute unit (grids 96^3 and 192^3 with K1 >= 64), the
    inverse axis-2 transform and the axis-3 complex-to-real transform run as one
    pass (eq. matvec's back-transform without the intermediate grid round
-   trip); enable = 0 runs them as two passes.  Both give the same potential
-   up to FP32 rounding.  Default on. */
+   trip); enable = 0 runs them as two passes.  Where axes 1 and 2 are at most
+   64 points, the forward axis-2, axis-1 and inverse axis-2 transforms run as
+   one pass over the m3 planes; enable = 0 runs them as three.  Each way gives
+   the same potential up to FP32 rounding.  Default on. */
 int qeq_use_fused_inverse(qeq_plan* plan, int32_t enable);
 
 /* Where a g1 plane of the half spectrum fits in the LDS of one compute unit

@@ -424,6 +424,12 @@ int launch_np_matvec(qeq_plan* pl, const double* src, double* dst, int mode);   
 void np_free(qeq_plan* pl);
 int launch_final_tail(qeq_plan* pl, double* q_out, double* energies, double* forces_out);
 // direct Ewald reciprocal part (ewald.hip)
+// ------------------------------------------------------------------ mesh_mid.hip
+constexpr int MID_MAX = 64;    // longest axis 1 or 2 of the one-pass middle
+bool mid_available(const qeq_plan* pl);
+int launch_mid(qeq_plan* pl, const float* b1, const float* b2, const float* b3, const int* done, hipEvent_t e0,
+               hipEvent_t e1);
+
 int ew_setup(qeq_plan* pl);
 int launch_ew_rec(qeq_plan* pl, const double* src, const int* done, bool fin);
 int launch_ew_forces_add(qeq_plan* pl);

@@ -801,20 +801,38 @@ int plane_fwd_pass(qeq_plan* pl, const double* src, const int* done) {
     return QEQ_EPLAN;
 }
 
-// Spread and forward axis-2 transform: the fused plane kernel where it
-// applies, else the spread pass and the axis-2 pass.
-int forward_head(qeq_plan* pl, const double* src, const int* done) {
-    if (plane_fwd_available(pl)) return plane_fwd_pass(pl, src, done);
-    QEQ_TRY(spread_pass(pl, src, done));
-    return rows_pass(pl, 0, done);
+// Forward axis-2, axis-1 with the Green's function, inverse axis-2: one pass
+// where the planes fit.
+int middle(qeq_plan* pl, bool fwd, bool inv, const int* done) {
+    if (fwd && inv && mid_available(pl)) {
+        ProfScope ps(pl, PK_COLS_GREEN);
+        const bool pw = pl->pw_active;
+        return launch_mid(pl, pw ? pl->pw_ones : pl->bmod[0], pw ? pl->pw_ones : pl->bmod[1],
+                          pw ? pl->pw_ones : pl->bmod[2], done, ps.start(), ps.stop());
+    }
+    if (fwd) QEQ_TRY(rows_pass(pl, 0, done));
+    QEQ_TRY(cols_pass(pl, MESH_FWD | MESH_GREEN | MESH_INV, nullptr, done));
+    return inv ? rows_pass(pl, 1, done) : QEQ_OK;
 }
 
-// Inverse transforms after the axis-1 pass: the fused slab kernel where it
-// applies, else the inverse axis-2 pass and the complex-to-real pass.
+// From the axis-3 half spectrum to the potential: the axis-2 transforms are
+// left out where the fused plane kernel (forward) did, or the fused slab kernel
+// (inverse) does them.
+int after_axis3(qeq_plan* pl, bool fwd, const int* done) {
+    const bool slab = slab_available(pl);
+    QEQ_TRY(middle(pl, fwd, !slab, done));
+    return slab ? slab_inv_pass(pl, done) : c2r_pass(pl, done);
+}
+
 int inverse_tail(qeq_plan* pl, const int* done) {
     if (slab_available(pl)) return slab_inv_pass(pl, done);
     QEQ_TRY(rows_pass(pl, 1, done));
     return c2r_pass(pl, done);
+}
+
+// Spread, axis-3 and, with the plane kernel, axis-2 transform.
+int forward_head(qeq_plan* pl, const double* src, const int* done) {
+    return plane_fwd_available(pl) ? plane_fwd_pass(pl, src, done) : spread_pass(pl, src, done);
 }
 
 }  // namespace
@@ -852,8 +870,7 @@ size_t qeq_mesh_max_smem(const KParams& k) {
 
 int launch_mesh_potential(qeq_plan* pl, const double* src, const int* done) {
     QEQ_TRY(forward_head(pl, src, done));
-    QEQ_TRY(cols_pass(pl, MESH_FWD | MESH_GREEN | MESH_INV, nullptr, done));
-    return inverse_tail(pl, done);
+    return after_axis3(pl, !plane_fwd_available(pl), done);
 }
 
 int launch_mesh_cg(qeq_plan* pl, const double* src, const int* done, bool* partials) {
@@ -861,22 +878,16 @@ int launch_mesh_cg(qeq_plan* pl, const double* src, const int* done, bool* parti
     const bool slab = slab_interp_available(pl);
     if (!slab && !c2r_interp_available(pl)) return launch_mesh_potential(pl, src, done);
     QEQ_TRY(forward_head(pl, src, done));
-    QEQ_TRY(cols_pass(pl, MESH_FWD | MESH_GREEN | MESH_INV, nullptr, done));
+    QEQ_TRY(middle(pl, !plane_fwd_available(pl), !slab, done));
     *partials = true;
-    if (slab) return slab_interp_pass(pl, done);
-    QEQ_TRY(rows_pass(pl, 1, done));
-    return c2r_interp_pass(pl, done);
+    return slab ? slab_interp_pass(pl, done) : c2r_interp_pass(pl, done);
 }
 
 int launch_mesh_r2c(qeq_plan* pl, const int* done) {
     return mesh_len({pl, LEN_R2C, nullptr, 0, nullptr, nullptr, nullptr, nullptr, done, nullptr, nullptr}, pl->kp.K3);
 }
 
-int launch_mesh_from_spectrum(qeq_plan* pl, const int* done) {
-    QEQ_TRY(rows_pass(pl, 0, done));
-    QEQ_TRY(cols_pass(pl, MESH_FWD | MESH_GREEN | MESH_INV, nullptr, done));
-    return inverse_tail(pl, done);
-}
+int launch_mesh_from_spectrum(qeq_plan* pl, const int* done) { return after_axis3(pl, true, done); }
 
 // One pass on its own (for timing): the spread, or the complex-to-real pass
 // that the CG products run (interpolating from LDS where they do).
