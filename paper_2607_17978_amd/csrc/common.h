@@ -512,12 +512,54 @@ __device__ __forceinline__ void stage_rt(int count, int tid, int nth, Ld ld, St 
 }
 
 // ---------------------------------------------------------------------------
-// FP64 block reductions (wave64 shuffles, then LDS across waves)
+// Wave and block reductions: register moves within a wave, LDS across waves.
+//
+// The sums add lanes l and l ^ off for off = 32, 16, 8, 4, 2, 1 in turn, as a
+// butterfly of shuffles would (bit for bit): a shuffle of a double is two LDS
+// round trips of some 100 cycles each, six in a row; a row rotation or half
+// swap is an ordinary register instruction.  Rotation by off equals l ^ off
+// once the row repeats with period 2 off.  Solves of
+// 4,096 / 32,768 atoms 1.52 -> 1.47 and 4.72 -> 4.61 ms, every kernel of the CG
+// loop that ends in a sum 0.3 to 0.6 us shorter.
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+__device__ __forceinline__ int ror_bits(int x, int c) {
+    switch (c) {
+        case 8: return __builtin_amdgcn_update_dpp(0, x, 0x128, 0xf, 0xf, false);
+        case 4: return __builtin_amdgcn_update_dpp(0, x, 0x124, 0xf, 0xf, false);
+        case 2: return __builtin_amdgcn_update_dpp(0, x, 0x122, 0xf, 0xf, false);
+        default: return __builtin_amdgcn_update_dpp(0, x, 0x121, 0xf, 0xf, false);
+    }
+}
+__device__ __forceinline__ float row_ror(float v, int c) { return __int_as_float(ror_bits(__float_as_int(v), c)); }
+__device__ __forceinline__ double row_ror(double v, int c) {
+    return __hiloint2double(ror_bits(__double2hiint(v), c), ror_bits(__double2loint(v), c));
+}
+
+// Sum over each row of 16 lanes, in all of them; every lane of the wave active.
+template <typename T>
+__device__ __forceinline__ T row16_sum(T v) {
+    v += row_ror(v, 8);
+    v += row_ror(v, 4);
+    v += row_ror(v, 2);
+    v += row_ror(v, 1);
     return v;
+}
+
+// Sum over the wave, in all lanes; every lane active.
+__device__ __forceinline__ double wave_sum(double v) {
+    {
+        const unsigned h = __double2hiint(v), l = __double2loint(v);
+        const auto a = __builtin_amdgcn_permlane32_swap(h, h, false, false);
+        const auto b = __builtin_amdgcn_permlane32_swap(l, l, false, false);
+        v = __hiloint2double(a[0], b[0]) + __hiloint2double(a[1], b[1]);
+    }
+    {
+        const unsigned h = __double2hiint(v), l = __double2loint(v);
+        const auto a = __builtin_amdgcn_permlane16_swap(h, h, false, false);
+        const auto b = __builtin_amdgcn_permlane16_swap(l, l, false, false);
+        v = __hiloint2double(a[0], b[0]) + __hiloint2double(a[1], b[1]);
+    }
+    return row16_sum(v);
 }
 
 // Sum NV values over the block; result valid in thread 0.  blockDim <= 1024.

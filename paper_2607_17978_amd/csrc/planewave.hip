@@ -317,15 +317,6 @@ __global__ __launch_bounds__(PW_NT) void k_pw_tile_spread(KParams k, PwGeom g, i
     grid[((size_t)(T1 * PW_E + (lane >> 4)) * k.K2 + T2 * PW_E + ((lane >> 2) & 3)) * k.K3 + T3 * PW_E + (lane & 3)] = q;
 }
 
-// Sum over each row of 16 lanes, in all of them (rotations within the row).
-__device__ __forceinline__ float pw_row_sum(float x) {
-    x += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x128, 0xf, 0xf, false));   // row_ror:8
-    x += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x124, 0xf, 0xf, false));   // row_ror:4
-    x += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x122, 0xf, 0xf, false));   // row_ror:2
-    x += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x121, 0xf, 0xf, false));   // row_ror:1
-    return x;
-}
-
 // The integration's part of a tile: part[slot] = sum over the tile's points of
 // theta phi / amplitude.  An entry's products are added within each row of 16
 // lanes; lane t of every row keeps entry t of 16, and two exchanges add the four
@@ -357,7 +348,7 @@ __global__ __launch_bounds__(PW_NT) void k_pw_tile_interp(KParams k, PwGeom g, i
 #pragma unroll 4
             for (int t = 0; t < 16; ++t) {
                 if (b + t >= m) break;   // uniform
-                const float x = pw_row_sum(phi * pw_theta<ORTHO>(g, recs[w][b + t], a1, a2, a3));
+                const float x = row16_sum(phi * pw_theta<ORTHO>(g, recs[w][b + t], a1, a2, a3));
                 keep = (lane & 15) == t ? x : keep;
             }
             keep += __shfl_xor(keep, 16, 64);
@@ -379,8 +370,7 @@ __global__ __launch_bounds__(PW_NT) void k_pw_tile_sum(int n, const int* __restr
 #pragma unroll 4
         for (int e = astart[i] + l; e < e1; e += 16) v += (double)part[e];
     }
-#pragma unroll
-    for (int d = 8; d > 0; d >>= 1) v += __shfl_xor(v, d, 64);
+    v = row16_sum(v);
     if (i < n && l == 0) y[i] = amp[i] * v;
 }
 

@@ -286,8 +286,7 @@ __global__ __launch_bounds__(QEQ_BLOCK) void k_pairs_fused(
             }
             v += (double)mp;
         }
-#pragma unroll
-        for (int off = G / 2; off > 0; off >>= 1) v += __shfl_xor(v, off, G);
+        v = row16_sum(v);
         if (i < n && lane == 0) {
             double y = v;
             if (do_self) y += ds * vi;
@@ -413,17 +412,25 @@ __device__ __forceinline__ void load_strided(const double* part, int nparts, dou
     }
 }
 
+// Every thread adds up the waves itself, in block_sum's order: one barrier.
+// One call per kernel and NV (the LDS is not guarded for a second one).
 template <int NV>
 __device__ __forceinline__ void block_total(double* v) {
-    __shared__ double tot[NV];
-    block_sum<NV>(v);
-    if (threadIdx.x == 0) {
+    __shared__ double red[16][NV];
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6, nw = blockDim.x >> 6;
 #pragma unroll
-        for (int t = 0; t < NV; ++t) tot[t] = v[t];
+    for (int t = 0; t < NV; ++t) v[t] = wave_sum(v[t]);
+    if (lane == 0) {
+#pragma unroll
+        for (int t = 0; t < NV; ++t) red[wid][t] = v[t];
     }
     __syncthreads();
 #pragma unroll
-    for (int t = 0; t < NV; ++t) v[t] = tot[t];
+    for (int t = 0; t < NV; ++t) v[t] = red[0][t];
+    for (int w = 1; w < nw; ++w) {
+#pragma unroll
+        for (int t = 0; t < NV; ++t) v[t] += red[w][t];
+    }
 }
 
 // alpha = r.z / p.A p; q += alpha p; r -= alpha (A p - mean(A p)).

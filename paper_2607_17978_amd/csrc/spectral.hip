@@ -356,8 +356,7 @@ __global__ __launch_bounds__(256) void k_spc_fwd(int npad, int ncp, int fsplit, 
         const float sv = up ? v[0] : v[1], kv = up ? v[1] : v[0];
         v[0] = kv + __shfl_xor(sv, 16, 64);
     }
-#pragma unroll
-    for (int off = 8; off > 0; off >>= 1) v[0] += __shfl_xor(v[0], off, 64);
+    v[0] = row16_sum(v[0]);
     // lane 16 b + ... holds row 2 (bit 5) + (bit 4)
     if ((lane & 15) == 0) tpart[(size_t)sp * ncp + a0 + 2 * ((lane >> 5) & 1) + ((lane >> 4) & 1)] = (double)v[0];
 }
