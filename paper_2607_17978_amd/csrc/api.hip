@@ -640,6 +640,7 @@ int cg_matvec(qeq_plan* pl, const double* src, int parity) {
 
 int cg_iteration(qeq_plan* pl, int parity) {
     QEQ_TRY(cg_matvec(pl, pl->pvec, parity));
+    if (cg_step_available(pl)) return launch_cg_step(pl, parity);
     QEQ_TRY(launch_cg_update(pl, parity));
     return next_direction(pl, parity, 0, true);
 }

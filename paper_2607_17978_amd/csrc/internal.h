@@ -490,6 +490,8 @@ int launch_cg_init_q(qeq_plan* pl, const double* q0);
 int launch_cg_init_r(qeq_plan* pl);
 int launch_start_energy(qeq_plan* pl);
 int launch_cg_update(qeq_plan* pl, int parity);
+bool cg_step_available(const qeq_plan* pl);
+int launch_cg_step(qeq_plan* pl, int parity);   // update and direction
 int launch_cg_dir(qeq_plan* pl, int parity, int init);
 int launch_final(qeq_plan* pl, double* q_out, double* energies, double* forces_out);
 int launch_matvec_io(qeq_plan* pl, const double* v_orig, double* y_orig, int stage);

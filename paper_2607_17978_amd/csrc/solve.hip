@@ -514,6 +514,89 @@ __global__ void k_cg_dir(KParams k, const double* __restrict__ r, const double* 
     }
 }
 
+// k_cg_update and k_cg_dir in one block for systems of at most CG_STEP_MAX
+// atoms: both are bound by their launch and by dependent loads, and the sums
+// between them need no second launch when one block holds all atoms.
+// Thread t holds atoms t, t + NT, ...
+// 64 atoms 2.7 us for both (2.8 + 2.5 us apart), 2,000
+// atoms 4.8; solves of 64 / 512 / 1,000 / 2,000 atoms 531 / 793 / 1,000 / 1,315
+// us -> 505 / 754 / 968 / 1,261.  4,096 atoms in one block took 6.7 us, the two
+// kernels' 4.1 + 2.6: the line is at 2,048.
+constexpr int CG_STEP_MAX = 2048;
+
+// Totals over a block of NW <= 16 waves in every thread, one barrier; red is
+// used by one call only.
+template <int NV, int NW>
+__device__ __forceinline__ void step_total(double* v, double (*red)[16]) {
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+#pragma unroll
+    for (int t = 0; t < NV; ++t) {
+        v[t] = wave_sum(v[t]);
+        if (lane == 0) red[t][w] = v[t];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int t = 0; t < NV; ++t) v[t] = row16_sum((lane & 15) < NW ? red[t][lane & 15] : 0.0);
+}
+
+template <int NT, int R>
+__global__ __launch_bounds__(NT) void k_cg_step(KParams k, double* __restrict__ p, const double* __restrict__ y,
+                                                const double* __restrict__ dinv, double* __restrict__ q,
+                                                double* __restrict__ r, const double* __restrict__ part_in,
+                                                int nparts, CgScalars* sc, int parity) {
+    __shared__ double red[5][16];
+    const int done = sc->done;
+    const double rzp = sc->rz[parity], dinv_sum = sc->dinv_sum, chi_norm = sc->chi_norm;
+    const int iters = sc->iters;
+    double pi[R], yi[R], qi[R], ri[R], di[R];
+#pragma unroll
+    for (int u = 0; u < R; ++u) {
+        const int i = threadIdx.x + u * NT;
+        const bool in = i < k.n;
+        pi[u] = in ? p[i] : 0.0;
+        yi[u] = in ? y[i] : 0.0;
+        qi[u] = in ? q[i] : 0.0;
+        ri[u] = in ? r[i] : 0.0;
+        di[u] = in ? dinv[i] : 0.0;
+    }
+    double tot[2];
+    load_strided<2>(part_in, nparts, tot);
+    if (done) return;
+    step_total<2, NT / 64>(tot, red);
+    const double alpha = rzp / tot[0];
+    const double ymean = tot[1] / (double)k.n;
+    double acc[3] = {0.0, 0.0, 0.0};
+#pragma unroll
+    for (int u = 0; u < R; ++u) {
+        const int i = threadIdx.x + u * NT;
+        if (i < k.n) {
+            q[i] = qi[u] + alpha * pi[u];
+            ri[u] -= alpha * (yi[u] - ymean);
+            r[i] = ri[u];
+            acc[0] += di[u] * ri[u];
+            acc[1] += di[u] * ri[u] * ri[u];
+            acc[2] += ri[u] * ri[u];
+        }
+    }
+    step_total<3, NT / 64>(acc, red + 2);
+    const double c = acc[0] / dinv_sum;
+    const double rz = acc[1] - c * acc[0];
+    const double beta = rz / rzp;
+    const double res = chi_norm > 0.0 ? sqrt(acc[2]) / chi_norm : sqrt(acc[2]);
+#pragma unroll
+    for (int u = 0; u < R; ++u) {
+        const int i = threadIdx.x + u * NT;
+        if (i < k.n) p[i] = di[u] * (ri[u] - c) + beta * pi[u];
+    }
+    if (threadIdx.x == 0) {
+        sc->alpha = alpha;
+        sc->iters = iters + 1;
+        sc->rz[parity ^ 1] = rz;
+        sc->res = res;
+        if (res <= k.tol || !(res == res)) sc->done = 1;
+    }
+}
+
 // Final: reduce energy partials, the mean gradient (= mu up to the background
 // constant) and the deviation of the gradient from it; scatter outputs.
 __global__ void k_final2(KParams k, const double* __restrict__ q_s, const double* __restrict__ f_s,
@@ -682,6 +765,29 @@ int launch_cg_update(qeq_plan* pl, int parity) {
                        pl->dinv, pl->q, pl->r, part_buf(pl, 0), interp_blocks(pl->kp.n), part_buf(pl, 1),
                        pl->sc, parity, pl->spc_active ? pl->spc_sd : nullptr,
                        pl->spc_active ? pl->spc_u : nullptr);
+    return qeq_check(hipGetLastError());
+}
+
+// Jacobi only: the spectral preconditioner comes between update and
+// direction.  Isolated systems keep the two kernels.
+bool cg_step_available(const qeq_plan* pl) { return pl->kp.n <= CG_STEP_MAX && !pl->spc_active && !pl->direct; }
+
+int launch_cg_step(qeq_plan* pl, int parity) {
+    const int n = pl->kp.n;
+    ProfScope ps(pl, PK_CG_UPDATE);
+#define X(NT, RR)                                                                                               \
+    hipExtLaunchKernelGGL((k_cg_step<NT, RR>), dim3(1), dim3(NT), 0, pl->stream, ps.start(), ps.stop(), 0,       \
+                          pl->kp, pl->pvec, pl->y, pl->dinv, pl->q, pl->r, part_buf(pl, 0), interp_blocks(n),    \
+                          pl->sc, parity)
+    if (n <= 256)
+        X(256, 1);
+    else if (n <= 512)
+        X(512, 1);
+    else if (n <= 1024)
+        X(1024, 1);
+    else
+        X(1024, 2);
+#undef X
     return qeq_check(hipGetLastError());
 }
 
