@@ -1009,23 +1009,34 @@ __global__ __launch_bounds__(BQ_NT) void k_bq_theta(BArgs a, const int2* __restr
     if (tid == 0) bq_lap(T, PH_MESHPREP, t0);
 }
 
-// Mesh self-correction of 64 atoms.
+// Mesh self-correction of 64 atoms, 16 lanes each.
 template <int PC>
-__global__ __launch_bounds__(64) void k_bq_self(BArgs a, const int2* __restrict__ units) {
+__global__ __launch_bounds__(256) void k_bq_self(BArgs a, const int2* __restrict__ units) {
     const int2 u = units[blockIdx.x];
     const BStruct& S = a.st[u.x];
     BState& T = a.state[u.x];
     if (T.finished) return;
     const long long t0 = wall_clock64();
-    const int i = u.y * 64 + threadIdx.x;
-    if (i < S.n) {
-        const double* frac = slot_ptr<double>(a, S, S.slot.frac);
-        const double x[3] = {frac[3 * i] * S.K[0], frac[3 * i + 1] * S.K[1], frac[3 * i + 2] * S.K[2]};
+    constexpr int NPM = SelfRows<PC>::NPM;
+    __shared__ double tab[NPM * NPM * NPM];
+    __shared__ SelfRows<PC> rows[16];
+    const int np = 2 * a.p - 1;
+    const double* tab_g = slot_ptr<double>(a, S, S.slot.tab);
+    const double* frac = slot_ptr<double>(a, S, S.slot.frac);
+    for (int t = threadIdx.x; t < np * np * np; t += 256) tab[t] = tab_g[t];
+    SelfRows<PC>& w = rows[threadIdx.x >> 4];
+    const int end = min(S.n, (u.y + 1) * 64);
+    for (int i0 = u.y * 64; i0 < end; i0 += 16) {
+        const int i = i0 + (threadIdx.x >> 4), ic = min(i, S.n - 1);
+        if (i0 > u.y * 64) __syncthreads();   // the rows' LDS is free
+        mesh_self_prepare<PC>(frac[3 * ic] * S.K[0], frac[3 * ic + 1] * S.K[1], frac[3 * ic + 2] * S.K[2], a.p, w);
         double v, g[3];
-        mesh_self_term<PC>(x, a.p, slot_ptr<double>(a, S, S.slot.tab), &v, g);
-        slot_vec(a, S, V_DSELF)[i] += T.c_eta - v;
-        double* sg = slot_ptr<double>(a, S, S.slot.selfgrad);
-        for (int c = 0; c < 3; ++c) sg[3 * i + c] = g[c];
+        mesh_self_sum<PC, true>(a.p, tab, w, &v, g);
+        if (i < S.n && (threadIdx.x & 15) == 0) {
+            slot_vec(a, S, V_DSELF)[i] += T.c_eta - v;
+            double* sg = slot_ptr<double>(a, S, S.slot.selfgrad);
+            for (int c = 0; c < 3; ++c) sg[3 * i + c] = g[c];
+        }
     }
     if (threadIdx.x == 0) bq_lap(T, PH_MESHPREP, t0);
 }
@@ -1509,9 +1520,9 @@ int run_wave(qeq_plan* pl, BatchState* b, BArgs& a, std::vector<BStruct>& st, co
         hipLaunchKernelGGL(k_bq_cols<true>, dim3((unsigned)uB.size()), dim3(BQ_NT), shB, stream, a, dB, (int)BQ_FINAL);
         hipLaunchKernelGGL(k_bq_theta, dim3((unsigned)uT.size()), dim3(BQ_NT), shC, stream, a, dT);
         if (a.p == 6)
-            hipLaunchKernelGGL(k_bq_self<6>, dim3((unsigned)uS.size()), dim3(64), 0, stream, a, dS);
+            hipLaunchKernelGGL(k_bq_self<6>, dim3((unsigned)uS.size()), dim3(256), 0, stream, a, dS);
         else
-            hipLaunchKernelGGL(k_bq_self<0>, dim3((unsigned)uS.size()), dim3(64), 0, stream, a, dS);
+            hipLaunchKernelGGL(k_bq_self<0>, dim3((unsigned)uS.size()), dim3(256), 0, stream, a, dS);
     }
     QEQ_TRY(qeq_check(hipGetLastError()));
     auto product = [&](int mode) {

@@ -634,62 +634,95 @@ __device__ __forceinline__ void pair_kernel(double r, double gam, double eta, do
 // sits inside its grid cell.  With separable spline weights W_a,
 //   theta_i^T Theta theta_i = sum_d Theta(d) R_1(d_1) R_2(d_2) R_3(d_3),
 //   R_a(d) = sum_{k' - k = d} W_a[k] W_a[k'],  |d_a| <= p - 1,
-// where tab holds Theta(d) on the (2p-1)^3 offsets (d_1 slowest).  Returns the
-// value and its derivative with respect to the grid coordinates u_a.
+// where tab holds Theta(d) on the (2p-1)^3 offsets (d_1 slowest).
+//
+// A row of 16 lanes works on one atom: the R_a and their derivatives go to LDS
+// (an offset a lane, 2p - 1 <= 15), then each lane takes every 16th of the
+// (2p-1)^2 table rows.  A thread per atom is a serial chain of (2p-1)^3 = 1,331
+// table reads: 28 us for 64 atoms and 36 for 32,768, now 6 and 21 (bound by
+// LDS reads; 131,072 atoms 49 and 60); the six strain tables 135 -> 32 us.
 // ---------------------------------------------------------------------------
-// PC: the spline order at compile time (every loop unrolls, the arrays stay in
-// registers) or 0 for the order p_rt at run time.
 template <int PC>
-__device__ inline void mesh_self_term(const double* u, int p_rt, const double* __restrict__ tab, double* val,
-                                      double* grad) {
-    constexpr int PM = PC ? PC : QEQ_MAXP;
-    constexpr int NPM = 2 * PM - 1;
-    const int p = PC ? PC : p_rt;
-    const int np = 2 * p - 1;
-    double R[3][NPM], dR[3][NPM];
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-        const double w = u[a] - floor(u[a]);
+struct SelfRows {
+    static constexpr int PM = PC ? PC : QEQ_MAXP, NPM = 2 * PM - 1;
+    double c[3][PM], dc[3][PM], R[3][NPM], dR[3][NPM];
+};
+
+// R_a and dR_a of the row's atom at grid coordinates u_a.  Called by the whole
+// block (it holds barriers).  PC: the spline order at compile time, or 0 for
+// the order p_rt at run time.
+template <int PC>
+__device__ __forceinline__ void mesh_self_prepare(double u0, double u1, double u2, int p_rt, SelfRows<PC>& w) {
+    const int p = PC ? PC : p_rt, lane = threadIdx.x & 15;
+    if (lane < 3) {
+        const double u = lane == 0 ? u0 : (lane == 1 ? u1 : u2);
         double c[QEQ_MAXP], dc[QEQ_MAXP];
-        bspline_weights<double>(w, p, c, dc);
+        bspline_weights<double>(u - floor(u), p, c, dc);
 #pragma unroll
-        for (int d = 0; d < NPM; ++d) {
-            R[a][d] = 0.0;
-            dR[a][d] = 0.0;
+        for (int k = 0; k < SelfRows<PC>::PM; ++k) {
+            w.c[lane][k] = k < p ? c[k] : 0.0;
+            w.dc[lane][k] = k < p ? dc[k] : 0.0;
         }
+    }
+    __syncthreads();
+    if (lane < 2 * p - 1) {
+        const int d = lane - (p - 1);
 #pragma unroll
-        for (int k1 = 0; k1 < PM; ++k1)
+        for (int a = 0; a < 3; ++a) {
+            double s = 0.0, ds = 0.0;
 #pragma unroll
-            for (int k2 = 0; k2 < PM; ++k2) {
-                if (!PC && (k1 >= p || k2 >= p)) continue;
-                const int d = k2 - k1 + (p - 1);
-                R[a][d] += c[k1] * c[k2];
-                dR[a][d] += dc[k1] * c[k2] + c[k1] * dc[k2];
+            for (int k1 = 0; k1 < SelfRows<PC>::PM; ++k1) {   // entries past the order are zero
+                const int k2 = k1 + d;
+                const bool in = k2 >= 0 && k2 < SelfRows<PC>::PM;
+                const double c2 = in ? w.c[a][in ? k2 : 0] : 0.0, dc2 = in ? w.dc[a][in ? k2 : 0] : 0.0;
+                s += w.c[a][k1] * c2;
+                ds += w.dc[a][k1] * c2 + w.c[a][k1] * dc2;
             }
+            w.R[a][lane] = s;
+            w.dR[a][lane] = ds;
+        }
+    }
+    __syncthreads();
+}
+
+// The value and (GRAD) its derivative with respect to the grid coordinates, in
+// all lanes of the row.
+template <int PC, bool GRAD>
+__device__ __forceinline__ void mesh_self_sum(int p_rt, const double* __restrict__ tab, const SelfRows<PC>& w,
+                                              double* val, double* grad) {
+    constexpr int NPM = SelfRows<PC>::NPM;
+    const int np = 2 * (PC ? PC : p_rt) - 1, lane = threadIdx.x & 15;
+    double r2[NPM], dr2[NPM];
+#pragma unroll
+    for (int c = 0; c < NPM; ++c) {
+        r2[c] = c < np ? w.R[2][c] : 0.0;
+        if (GRAD) dr2[c] = c < np ? w.dR[2][c] : 0.0;
     }
     double s = 0.0, g0 = 0.0, g1 = 0.0, g2 = 0.0;
+    for (int x = lane; x < np * np; x += 16) {
+        const int a = x / np, b = x - a * np;
+        const double* row = tab + x * np;
+        double t = 0.0, t1 = 0.0;
 #pragma unroll
-    for (int a = 0; a < NPM; ++a)
-#pragma unroll
-        for (int b = 0; b < NPM; ++b) {
-            if (!PC && (a >= np || b >= np)) continue;
-            double t = 0.0, t1 = 0.0;
-            const double* row = tab + (a * np + b) * np;
-#pragma unroll
-            for (int c = 0; c < NPM; ++c) {
-                if (!PC && c >= np) continue;
-                t += row[c] * R[2][c];
-                t1 += row[c] * dR[2][c];
-            }
-            s += R[0][a] * R[1][b] * t;
-            g0 += dR[0][a] * R[1][b] * t;
-            g1 += R[0][a] * dR[1][b] * t;
-            g2 += R[0][a] * R[1][b] * t1;
+        for (int c = 0; c < NPM; ++c) {
+            if (!PC && c >= np) continue;
+            t += row[c] * r2[c];
+            if (GRAD) t1 += row[c] * dr2[c];
         }
-    *val = s;
-    grad[0] = g0;
-    grad[1] = g1;
-    grad[2] = g2;
+        const double ra = w.R[0][a], rb = w.R[1][b];
+        s += ra * rb * t;
+        if (GRAD) {
+            g0 += w.dR[0][a] * rb * t;
+            g1 += ra * w.dR[1][b] * t;
+            g2 += ra * rb * t1;
+        }
+    }
+    *val = row16_sum(s);
+    if (GRAD) {
+        grad[0] = row16_sum(g0);
+        grad[1] = row16_sum(g1);
+        grad[2] = row16_sum(g2);
+    }
 }
 
 __device__ __forceinline__ int wrap_idx(int i, int K) {

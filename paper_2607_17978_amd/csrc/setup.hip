@@ -405,20 +405,25 @@ __global__ void k_theta_extract(KParams k, const float* __restrict__ grid, doubl
     tab[t] = (double)grid[((size_t)g1 * k.K2 + g2) * k.K3 + g3];
 }
 
+constexpr int SELF_ATOMS = QEQ_BLOCK / 16;   // atoms of a block: one a row of 16 lanes
+
 template <int PC>
-__global__ void k_selfcorr(KParams k, const double* __restrict__ frac, const double* __restrict__ tab_g,
-                           double* __restrict__ dself, double* __restrict__ selfgrad) {
+__global__ __launch_bounds__(QEQ_BLOCK) void k_selfcorr(KParams k, const double* __restrict__ frac,
+                                                       const double* __restrict__ tab_g,
+                                                       double* __restrict__ dself, double* __restrict__ selfgrad) {
     // the table is read by every atom: stage it in LDS
-    __shared__ double tab[(2 * QEQ_MAXP - 1) * (2 * QEQ_MAXP - 1) * (2 * QEQ_MAXP - 1)];
+    constexpr int NPM = SelfRows<PC>::NPM;
+    __shared__ double tab[NPM * NPM * NPM];
+    __shared__ SelfRows<PC> rows[SELF_ATOMS];
     const int np = 2 * k.p - 1;
-    for (int t = threadIdx.x; t < np * np * np; t += blockDim.x) tab[t] = tab_g[t];
-    __syncthreads();
-    int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= k.n) return;
-    const double u[3] = {frac[3 * i] * (double)k.K1, frac[3 * i + 1] * (double)k.K2,
-                         frac[3 * i + 2] * (double)k.K3};
+    const int i = blockIdx.x * SELF_ATOMS + (threadIdx.x >> 4), ic = min(i, k.n - 1);
+    SelfRows<PC>& w = rows[threadIdx.x >> 4];
+    for (int t = threadIdx.x; t < np * np * np; t += QEQ_BLOCK) tab[t] = tab_g[t];
+    mesh_self_prepare<PC>(frac[3 * ic] * (double)k.K1, frac[3 * ic + 1] * (double)k.K2, frac[3 * ic + 2] * (double)k.K3,
+                          k.p, w);
     double s, g[3];
-    mesh_self_term<PC>(u, k.p, tab, &s, g);
+    mesh_self_sum<PC, true>(k.p, tab, w, &s, g);
+    if (i >= k.n || (threadIdx.x & 15) != 0) return;
     dself[i] += k.c_eta - s;
     selfgrad[3 * i + 0] = g[0];
     selfgrad[3 * i + 1] = g[1];
@@ -427,38 +432,39 @@ __global__ void k_selfcorr(KParams k, const double* __restrict__ frac, const dou
 
 // Virial of the self-correction: per atom theta_i^T dTheta_ab theta_i for the
 // six strain components (one table staged in LDS at a time), weighted by q^2;
-// also sum q^2 and sum q sigma^2 for the C_eta and background terms.
+// also sum q^2 and sum q sigma^2 for the C_eta and background terms.  Sixteen
+// lanes an atom as above; many atoms a block, since each block reads the six
+// tables (64 KB).
+constexpr int STRAIN_NT = 1024, STRAIN_ATOMS = STRAIN_NT / 16;
+
 template <int PC>
-__global__ __launch_bounds__(QEQ_BLOCK) void k_self_strain(KParams k, const double* __restrict__ frac,
+__global__ __launch_bounds__(STRAIN_NT) void k_self_strain(KParams k, const double* __restrict__ frac,
                                                           const double* __restrict__ tabs,
                                                           const double* __restrict__ q,
                                                           const double* __restrict__ sig,
                                                           double* __restrict__ part) {
-    __shared__ double tab[(2 * QEQ_MAXP - 1) * (2 * QEQ_MAXP - 1) * (2 * QEQ_MAXP - 1)];
-    const int np = 2 * k.p - 1;
-    const int np3 = np * np * np;
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    const bool act = i < k.n;
+    constexpr int NPM = SelfRows<PC>::NPM;
+    extern __shared__ double sm[];
+    double* tab = sm;                                                          // NPM^3
+    SelfRows<PC>* rows = reinterpret_cast<SelfRows<PC>*>(tab + NPM * NPM * NPM);   // STRAIN_ATOMS
+    const int np = 2 * k.p - 1, np3 = np * np * np;
+    const int i = blockIdx.x * STRAIN_ATOMS + (threadIdx.x >> 4), ic = min(i, k.n - 1);
+    const bool act = i < k.n && (threadIdx.x & 15) == 0;
+    SelfRows<PC>& w = rows[threadIdx.x >> 4];
     double acc[QEQ_NPART];
 #pragma unroll
     for (int t = 0; t < QEQ_NPART; ++t) acc[t] = 0.0;
     const double qi = act ? q[i] : 0.0;
     if (tabs) {
-        double u[3] = {0.0, 0.0, 0.0};
-        if (act) {
-            u[0] = frac[3 * i] * (double)k.K1;
-            u[1] = frac[3 * i + 1] * (double)k.K2;
-            u[2] = frac[3 * i + 2] * (double)k.K3;
-        }
+        mesh_self_prepare<PC>(frac[3 * ic] * (double)k.K1, frac[3 * ic + 1] * (double)k.K2,
+                              frac[3 * ic + 2] * (double)k.K3, k.p, w);
         for (int comp = 0; comp < 6; ++comp) {
             __syncthreads();
-            for (int t = threadIdx.x; t < np3; t += blockDim.x) tab[t] = tabs[(size_t)comp * np3 + t];
+            for (int t = threadIdx.x; t < np3; t += STRAIN_NT) tab[t] = tabs[(size_t)comp * np3 + t];
             __syncthreads();
-            if (act) {
-                double s, g[3];
-                mesh_self_term<PC>(u, k.p, tab, &s, g);
-                acc[comp] = qi * qi * s;
-            }
+            double s;
+            mesh_self_sum<PC, false>(k.p, tab, w, &s, nullptr);
+            if (act) acc[comp] = qi * qi * s;
         }
     }
     if (act) {
@@ -630,10 +636,10 @@ int launch_theta(qeq_plan* pl) {
 
 int launch_selfcorr(qeq_plan* pl) {
     if (pl->kp.p == 6)
-        hipLaunchKernelGGL(k_selfcorr<6>, dim3(nblocks(pl->kp.n)), dim3(QEQ_BLOCK), 0, pl->stream, pl->kp,
+        hipLaunchKernelGGL(k_selfcorr<6>, dim3(nblocks(pl->kp.n, SELF_ATOMS)), dim3(QEQ_BLOCK), 0, pl->stream, pl->kp,
                            pl->frac, pl->theta_tab, pl->dself, pl->selfgrad);
     else
-        hipLaunchKernelGGL(k_selfcorr<0>, dim3(nblocks(pl->kp.n)), dim3(QEQ_BLOCK), 0, pl->stream, pl->kp,
+        hipLaunchKernelGGL(k_selfcorr<0>, dim3(nblocks(pl->kp.n, SELF_ATOMS)), dim3(QEQ_BLOCK), 0, pl->stream, pl->kp,
                            pl->frac, pl->theta_tab, pl->dself, pl->selfgrad);
     return qeq_check(hipGetLastError());
 }
@@ -651,13 +657,19 @@ int launch_theta_strain(qeq_plan* pl, double* tabs) {
     return QEQ_OK;
 }
 
-int launch_self_strain(qeq_plan* pl, const double* tabs, double* part) {
+int self_strain_blocks(int n) { return nblocks(n, STRAIN_ATOMS); }
+
+template <int PC>
+static int self_strain_launch(qeq_plan* pl, const double* tabs, double* part) {
     const KParams& k = pl->kp;
-    if (k.p == 6)
-        hipLaunchKernelGGL(k_self_strain<6>, dim3(nblocks(k.n)), dim3(QEQ_BLOCK), 0, pl->stream, k, pl->frac, tabs,
-                           pl->q, pl->sig, part);
-    else
-        hipLaunchKernelGGL(k_self_strain<0>, dim3(nblocks(k.n)), dim3(QEQ_BLOCK), 0, pl->stream, k, pl->frac, tabs,
-                           pl->q, pl->sig, part);
+    constexpr int NPM = SelfRows<PC>::NPM;
+    constexpr size_t sh = sizeof(double) * NPM * NPM * NPM + sizeof(SelfRows<PC>) * STRAIN_ATOMS;
+    QEQ_HIP(hipFuncSetAttribute((const void*)k_self_strain<PC>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh));
+    hipLaunchKernelGGL(k_self_strain<PC>, dim3(self_strain_blocks(k.n)), dim3(STRAIN_NT), sh, pl->stream, k, pl->frac,
+                       tabs, pl->q, pl->sig, part);
     return qeq_check(hipGetLastError());
+}
+
+int launch_self_strain(qeq_plan* pl, const double* tabs, double* part) {
+    return pl->kp.p == 6 ? self_strain_launch<6>(pl, tabs, part) : self_strain_launch<0>(pl, tabs, part);
 }
