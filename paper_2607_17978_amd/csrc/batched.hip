@@ -302,11 +302,12 @@ __global__ __launch_bounds__(1024) void k_bq_stage(BArgs a, const int* __restric
 
 // Images n of the pair (i, j) with |x_a + n_a| <= rho_a on every axis, where
 // x = s_j - s_i is wrapped to [-1/2, 1/2], and |r_j + n H - r_i| < r_cut.
-// EMIT writes K, (r_i - r_j(image), K'/r) and j at out[0..).
+// EMIT writes j, r_i - r_j(image) and, in the places of K'/r and K, the two
+// halves of the FP64 distance.
 template <bool EMIT>
 __device__ __forceinline__ int bq_pair_images(const BStruct& S, const double* si, const double* sj, bool same,
-                                              double rc2, double eta, double gam, int j, int* col, float* kval,
-                                              float4* pdr, long long at, long long cap) {
+                                              double rc2, int j, int* col, float* kval, float4* pdr, long long at,
+                                              long long cap) {
     double x[3];
     int lo[3], hi[3];
 #pragma unroll
@@ -329,11 +330,11 @@ __device__ __forceinline__ int bq_pair_images(const BStruct& S, const double* si
                 const double r2 = dx * dx + dy * dy + dz * dz;
                 if (r2 >= rc2) continue;
                 if (EMIT && at + c < cap) {
-                    double K, dKr;
-                    pair_kernel(sqrt(r2), gam, eta, &K, &dKr);
+                    const double rr = sqrt(r2);
                     col[at + c] = j;
-                    kval[at + c] = (float)K;
-                    pdr[at + c] = make_float4((float)(-dx), (float)(-dy), (float)(-dz), (float)dKr);
+                    kval[at + c] = __int_as_float(__double2loint(rr));
+                    pdr[at + c] =
+                        make_float4((float)(-dx), (float)(-dy), (float)(-dz), __int_as_float(__double2hiint(rr)));
                 }
                 ++c;
             }
@@ -343,6 +344,10 @@ __device__ __forceinline__ int bq_pair_images(const BStruct& S, const double* si
 // Pair list of 32 atoms: count, one reservation of the block's rows in the
 // structure's list, fill (8 lanes per atom, in j order; where a row starts
 // does not matter to any sum).  Past the capacity only the count goes on.
+// The fill writes distances and a second pass over the row turns them into
+// kernel values: about one candidate in four is a pair, and the error functions
+// inside the fill ran for a whole wave wherever one lane had one (1,024
+// structures 1.50 -> 1.09 ms, 48 structures 132 -> 107 us).
 __global__ __launch_bounds__(256) void k_bq_pairs(BArgs a, const int2* __restrict__ units) {
     const int2 u = units[blockIdx.x];
     const BStruct& S = a.st[u.x];
@@ -365,7 +370,7 @@ __global__ __launch_bounds__(256) void k_bq_pairs(BArgs a, const int2* __restric
     if (i < n) {
         for (int t = 0; t < 3; ++t) si[t] = fr[3 * i + t];
         for (int j = l; j < n; j += BQ_L)
-            c += bq_pair_images<false>(S, si, fr + 3 * j, i == j, a.rc2, a.eta, 1.0, j, nullptr, nullptr, nullptr, 0, 0);
+            c += bq_pair_images<false>(S, si, fr + 3 * j, i == j, a.rc2, j, nullptr, nullptr, nullptr, 0, 0);
     }
 #pragma unroll
     for (int off = BQ_L / 2; off > 0; off >>= 1) c += __shfl_xor(c, off, 64);
@@ -381,6 +386,9 @@ __global__ __launch_bounds__(256) void k_bq_pairs(BArgs a, const int2* __restric
         }
     }
     __syncthreads();
+    int* col = slot_ptr<int>(a, S, S.slot.col);
+    float* kval = slot_ptr<float>(a, S, S.slot.kval);
+    float4* pdr = slot_ptr<float4>(a, S, S.slot.pdr);
     if (i < n) {
         long long cursor = rowat[r];
         if (l == 0) {
@@ -388,16 +396,11 @@ __global__ __launch_bounds__(256) void k_bq_pairs(BArgs a, const int2* __restric
             // rows past the capacity are never read (the structure goes again)
             row[i] = cursor + c <= S.pcap ? make_int2((int)cursor, (int)cursor + c) : make_int2(0, 0);
         }
-        int* col = slot_ptr<int>(a, S, S.slot.col);
-        float* kval = slot_ptr<float>(a, S, S.slot.kval);
-        float4* pdr = slot_ptr<float4>(a, S, S.slot.pdr);
-        const double sgi = sgs[i];
         for (int jb = 0; jb < n; jb += BQ_L) {
             const int j = jb + l;
             int k = 0;
             if (j < n)
-                k = bq_pair_images<false>(S, si, fr + 3 * j, i == j, a.rc2, a.eta, 1.0, j, nullptr, nullptr, nullptr, 0,
-                                          0);
+                k = bq_pair_images<false>(S, si, fr + 3 * j, i == j, a.rc2, j, nullptr, nullptr, nullptr, 0, 0);
             int incl = k;
 #pragma unroll
             for (int d = 1; d < BQ_L; d <<= 1) {
@@ -406,9 +409,22 @@ __global__ __launch_bounds__(256) void k_bq_pairs(BArgs a, const int2* __restric
             }
             const int total = __shfl(incl, BQ_L - 1, BQ_L);
             if (k)
-                bq_pair_images<true>(S, si, fr + 3 * j, i == j, a.rc2, a.eta, sqrt(sgi * sgi + sgs[j] * sgs[j]), j, col,
-                                     kval, pdr, cursor + incl - k, S.pcap);
+                bq_pair_images<true>(S, si, fr + 3 * j, i == j, a.rc2, j, col, kval, pdr, cursor + incl - k, S.pcap);
             cursor += total;
+        }
+    }
+    __syncthreads();   // the rows' entries, written by other lanes
+    if (i < n) {
+        const double sgi = sgs[i];
+        const long long e1 = min(rowat[r] + cnt[r], S.pcap);
+        for (long long e = rowat[r] + l; e < e1; e += BQ_L) {
+            const float hi = pdr[e].w, lo = kval[e];
+            const double sj = sgs[col[e]];
+            double K, dKr;
+            pair_kernel(__hiloint2double(__float_as_int(hi), __float_as_int(lo)), sqrt(sgi * sgi + sj * sj), a.eta, &K,
+                        &dKr);
+            kval[e] = (float)K;
+            pdr[e].w = (float)dKr;
         }
     }
     if (tid == 0) bq_lap(T, PH_PAIRS, t0);
