@@ -545,7 +545,7 @@ int prepare(qeq_plan* pl, int n, const double* cell, double q_tot) {
     }
     k.c_eta = pl->c_eta;
     if (k.self_corr && !pl->theta_valid) {
-        QEQ_TRY(launch_theta(pl));
+        QEQ_TRY(launch_theta(pl, false, pl->theta_tab));
         pl->theta_valid = true;
     }
     for (int t = 0; t < 9; ++t) pl->cell_cached[t] = cell[t];
@@ -1040,7 +1040,7 @@ int qeq_plan_destroy(qeq_plan* pl) {
     dfree(pl->perm); dfree(pl->key); dfree(pl->frac); dfree(pl->home); dfree(pl->wts); dfree(pl->dwts);
     dfree(pl->sig); dfree(pl->Jv); dfree(pl->chi); dfree(pl->chi_raw); dfree(pl->dself); dfree(pl->dinv);
     dfree(pl->selfgrad); dfree(pl->q); dfree(pl->r); dfree(pl->pvec); dfree(pl->y); dfree(pl->forces_s);
-    dfree(pl->gtmp); dfree(pl->q_adj); dfree(pl->y_adj); dfree(pl->chi_adj); dfree(pl->adj_scratch); dfree(pl->tq); dfree(pl->rowptr); dfree(pl->rowcnt); dfree(pl->lanecnt); dfree(pl->theta_tab); dfree(pl->part);
+    dfree(pl->gtmp); dfree(pl->q_adj); dfree(pl->y_adj); dfree(pl->chi_adj); dfree(pl->adj_scratch); dfree(pl->tq); dfree(pl->rowptr); dfree(pl->rowcnt); dfree(pl->lanecnt); dfree(pl->theta_tab); dfree(pl->theta_plane); dfree(pl->part);
     dfree(pl->strain_tab); dfree(pl->vir_part); dfree(pl->mpart);
     spc_free(pl);
     np_free(pl);

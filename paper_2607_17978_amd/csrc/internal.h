@@ -150,6 +150,8 @@ struct qeq_plan {
     bool theta_valid = false;
     double c_eta = 0.0;
     double* theta_tab = nullptr;                    // (2p-1)^3 mesh kernel values
+    double* theta_plane = nullptr;                  // per m3 plane sums of the tables
+    size_t theta_cap = 0;                           // doubles
     // virial: strain derivatives of the self-correction (d C_eta / d eps and
     // the six tables d Theta / d eps_ab), valid for the same cell as theta_tab
     bool strain_valid = false;
@@ -400,10 +402,10 @@ int launch_gather(qeq_plan* pl, const double* pos, const double* sigma, const do
 int launch_cells_and_pairs(qeq_plan* pl);
 int launch_pair_fill(qeq_plan* pl);
 int grow_pairs(qeq_plan* pl, size_t cap);
-int launch_theta(qeq_plan* pl);          // mesh kernel table for the self-correction
+// mesh kernel table for the self-correction ((2p-1)^3), or (strain) the six
+// d Theta / d eps_ab tables for the virial
+int launch_theta(qeq_plan* pl, bool strain, double* tab);
 int launch_selfcorr(qeq_plan* pl);
-// the six d Theta / d eps_ab tables (6 x (2p-1)^3) for the virial
-int launch_theta_strain(qeq_plan* pl, double* tabs);
 // per block [sum q^2 theta^T dTheta_ab theta (6; 0 if tabs is null), sum q^2,
 // sum q sigma^2]; nblocks(n) blocks of QEQ_NPART
 int self_strain_blocks(int n);
@@ -466,8 +468,6 @@ bool mesh_tile_compiled(int K1, int K3, int tw, int p);
 // whether the axis-2 pass has a kernel for nr rows of this length in mesh.hip
 bool rows_compiled(int K2, int nr);
 size_t qeq_mesh_max_smem(const KParams& k);
-// Inverse transforms only (grid_c already holds a spectrum) -> grid_r.
-int launch_mesh_inverse(qeq_plan* pl);
 // Real-to-complex transform along axis 3 of grid_r into grid_c (tiles of at most
 // LEN_TW rows: KParams::TW <= 16).
 int launch_mesh_r2c(qeq_plan* pl, const int* done);
@@ -476,9 +476,6 @@ int launch_mesh_r2c(qeq_plan* pl, const int* done);
 int launch_mesh_from_spectrum(qeq_plan* pl, const int* done);
 // One launch of a single mesh pass (PK_SPREAD_R2C from src, or PK_C2R).
 int launch_mesh_stage(qeq_plan* pl, int kind, const double* src);
-int launch_write_green(qeq_plan* pl);
-// G(m) d ln G / d eps_ab (component comp of 00, 11, 22, 01, 02, 12) into grid_c.
-int launch_write_green_strain(qeq_plan* pl, int comp);
 // Mesh virial partials of the charges src: spread, forward transforms and per
 // block [sum e, sum e c k_a k_b]; mesh_virial_blocks() blocks of QEQ_NPART.
 int launch_mesh_virial(qeq_plan* pl, const double* src, double* part);

@@ -499,46 +499,6 @@ __global__ __launch_bounds__(SLAB_NT) void k_slab_inv(KParams k, FftAxis ax2, Ff
     }
 }
 
-__global__ void k_write_green(KParams k, float2* __restrict__ C, const float* __restrict__ b1,
-                              const float* __restrict__ b2, const float* __restrict__ b3) {
-    const size_t t = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const size_t total = (size_t)k.K3h * k.K1 * k.K2;
-    if (t >= total) return;
-    const int m2 = (int)(t % k.K2);
-    const int m1 = (int)((t / k.K2) % k.K1);
-    const int m3 = (int)(t / ((size_t)k.K2 * k.K1));
-    C[t] = make_float2(green_value(k, m1, m2, m3, b1, b2, b3), 0.f);
-}
-
-// Component order of symmetric 3x3 tensors: 00, 11, 22, 01, 02, 12.
-__device__ __forceinline__ void sym_pair(int comp, int& a, int& b) {
-    a = comp < 3 ? comp : (comp == 5 ? 1 : 0);
-    b = comp < 3 ? comp : (comp == 3 ? 1 : 2);
-}
-
-// G(m) d ln G / d eps_ab on the half spectrum: its inverse transform is the
-// strain derivative of the mesh kernel Theta (for the self-correction term).
-__global__ void k_write_green_strain(KParams k, float2* __restrict__ C, const float* __restrict__ b1,
-                                     const float* __restrict__ b2, const float* __restrict__ b3, int comp) {
-    const size_t t = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const size_t total = (size_t)k.K3h * k.K1 * k.K2;
-    if (t >= total) return;
-    const int m2 = (int)(t % k.K2);
-    const int m1 = (int)((t / k.K2) % k.K1);
-    const int m3 = (int)(t / ((size_t)k.K2 * k.K1));
-    const float g = green_value(k, m1, m2, m3, b1, b2, b3);
-    float v = 0.f;
-    if (g != 0.f) {
-        float kv[3];
-        const float k2 = mode_kvec(k, m1, m2, m3, kv);
-        const float eta = (float)k.eta;
-        int a, b;
-        sym_pair(comp, a, b);
-        v = g * ((a == b ? -1.f : 0.f) + 2.f * (1.f / k2 + 0.5f * eta * eta) * kv[a] * kv[b]);
-    }
-    C[t] = make_float2(v, 0.f);
-}
-
 size_t smem_spread(const KParams& k) {
     return sizeof(float2) * (size_t)k.K3 + sizeof(int) * (size_t)k.K3 * k.TWS;
 }
@@ -824,12 +784,6 @@ int after_axis3(qeq_plan* pl, bool fwd, const int* done) {
     return slab ? slab_inv_pass(pl, done) : c2r_pass(pl, done);
 }
 
-int inverse_tail(qeq_plan* pl, const int* done) {
-    if (slab_available(pl)) return slab_inv_pass(pl, done);
-    QEQ_TRY(rows_pass(pl, 1, done));
-    return c2r_pass(pl, done);
-}
-
 // Spread, axis-3 and, with the plane kernel, axis-2 transform.
 int forward_head(qeq_plan* pl, const double* src, const int* done) {
     return plane_fwd_available(pl) ? plane_fwd_pass(pl, src, done) : spread_pass(pl, src, done);
@@ -900,27 +854,6 @@ int launch_mesh_stage(qeq_plan* pl, int kind, const double* src) {
         return slab_available(pl) ? slab_inv_pass(pl, nullptr) : c2r_pass(pl, nullptr);
     }
     return QEQ_EINVAL;
-}
-
-int launch_mesh_inverse(qeq_plan* pl) {
-    QEQ_TRY(cols_pass(pl, MESH_INV, nullptr, nullptr));
-    return inverse_tail(pl, nullptr);
-}
-
-int launch_write_green(qeq_plan* pl) {
-    const KParams& k = pl->kp;
-    const size_t total = (size_t)k.K3h * k.K1 * k.K2;
-    hipLaunchKernelGGL(k_write_green, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, pl->stream, k,
-                       pl->grid_c, pl->bmod[0], pl->bmod[1], pl->bmod[2]);
-    return qeq_check(hipGetLastError());
-}
-
-int launch_write_green_strain(qeq_plan* pl, int comp) {
-    const KParams& k = pl->kp;
-    const size_t total = (size_t)k.K3h * k.K1 * k.K2;
-    hipLaunchKernelGGL(k_write_green_strain, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, pl->stream, k,
-                       pl->grid_c, pl->bmod[0], pl->bmod[1], pl->bmod[2], comp);
-    return qeq_check(hipGetLastError());
 }
 
 int mesh_virial_blocks(const KParams& k) { return k.K3h * k.ntile; }

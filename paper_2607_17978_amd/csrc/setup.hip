@@ -394,17 +394,6 @@ __global__ __launch_bounds__(QEQ_BLOCK) void k_pairs(KParams k, const double* __
 //   theta_i^T Theta theta_i = sum_d Theta(d) R_1(d_1) R_2(d_2) R_3(d_3),
 //   R_a(d) = sum_{k' - k = d} W_a[k] W_a[k'],  |d_a| <= p - 1.
 // ---------------------------------------------------------------------------
-__global__ void k_theta_extract(KParams k, const float* __restrict__ grid, double* __restrict__ tab) {
-    int np = 2 * k.p - 1;
-    int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= np * np * np) return;
-    int d3 = t % np - (k.p - 1);
-    int d2 = (t / np) % np - (k.p - 1);
-    int d1 = t / (np * np) - (k.p - 1);
-    int g1 = wrap_idx(d1, k.K1), g2 = wrap_idx(d2, k.K2), g3 = wrap_idx(d3, k.K3);
-    tab[t] = (double)grid[((size_t)g1 * k.K2 + g2) * k.K3 + g3];
-}
-
 constexpr int SELF_ATOMS = QEQ_BLOCK / 16;   // atoms of a block: one a row of 16 lanes
 
 template <int PC>
@@ -625,15 +614,6 @@ int grow_pairs(qeq_plan* pl, size_t cap) {
     return QEQ_OK;
 }
 
-int launch_theta(qeq_plan* pl) {
-    QEQ_TRY(launch_write_green(pl));
-    QEQ_TRY(launch_mesh_inverse(pl));
-    int np = 2 * pl->kp.p - 1;
-    hipLaunchKernelGGL(k_theta_extract, dim3(nblocks(np * np * np)), dim3(QEQ_BLOCK), 0, pl->stream,
-                       pl->kp, pl->grid_r, pl->theta_tab);
-    return qeq_check(hipGetLastError());
-}
-
 int launch_selfcorr(qeq_plan* pl) {
     if (pl->kp.p == 6)
         hipLaunchKernelGGL(k_selfcorr<6>, dim3(nblocks(pl->kp.n, SELF_ATOMS)), dim3(QEQ_BLOCK), 0, pl->stream, pl->kp,
@@ -642,19 +622,6 @@ int launch_selfcorr(qeq_plan* pl) {
         hipLaunchKernelGGL(k_selfcorr<0>, dim3(nblocks(pl->kp.n, SELF_ATOMS)), dim3(QEQ_BLOCK), 0, pl->stream, pl->kp,
                            pl->frac, pl->theta_tab, pl->dself, pl->selfgrad);
     return qeq_check(hipGetLastError());
-}
-
-int launch_theta_strain(qeq_plan* pl, double* tabs) {
-    const int np = 2 * pl->kp.p - 1;
-    const int np3 = np * np * np;
-    for (int comp = 0; comp < 6; ++comp) {
-        QEQ_TRY(launch_write_green_strain(pl, comp));
-        QEQ_TRY(launch_mesh_inverse(pl));
-        hipLaunchKernelGGL(k_theta_extract, dim3(nblocks(np3)), dim3(QEQ_BLOCK), 0, pl->stream, pl->kp,
-                           pl->grid_r, tabs + (size_t)comp * np3);
-        QEQ_TRY(qeq_check(hipGetLastError()));
-    }
-    return QEQ_OK;
 }
 
 int self_strain_blocks(int n) { return nblocks(n, STRAIN_ATOMS); }

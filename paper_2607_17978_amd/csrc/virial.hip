@@ -123,7 +123,7 @@ int virial_impl(qeq_plan* pl, double* virial) {
             QEQ_TRY(alloc_doubles(&pl->strain_tab, (size_t)6 * np1 * np1 * np1));
         }
         reciprocal_self_strain(k.H, k.Hinv, k.vol, k.eta, pl->dc_eta);
-        QEQ_TRY(launch_theta_strain(pl, pl->strain_tab));
+        QEQ_TRY(launch_theta(pl, true, pl->strain_tab));
         pl->strain_valid = true;
     }
     QEQ_TRY(launch_mesh_virial(pl, pl->q, pm));
