@@ -134,7 +134,8 @@ __global__ __launch_bounds__(256) void k_theta_tab(KParams k, const double2* __r
     if (threadIdx.x >= np) return;
     double v = 0.0;
     for (int u = 0; u < 16; ++u) v += red[u][threadIdx.x];
-    tab[((size_t)blockIdx.y * np * np + x) * np + threadIdx.x] = v;
+    // to FP32, the precision of G and of the mesh products that the table corrects
+    tab[((size_t)blockIdx.y * np * np + x) * np + threadIdx.x] = (double)(float)v;
 }
 
 }  // namespace
