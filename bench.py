@@ -42,22 +42,22 @@ MEASURED_TRAFFIC = {
     # (spread, axis-3 and axis-2 transforms of one g1 plane per block)
     "spread_r2c": {"kernel": "k_plane_fwd", "file": "paper_2607_17978_amd/csrc/mesh.hip",
                    "grid": (192, 192, 192), "spread_rows": None,
-                   "source_sha256_16": "265cfb73d912eb58",
-                   "fetch_kib": 2589.5625, "fetch_scale": 2.0, "write_kib": 27936.0, "write_scale": 1.0},
+                   "source_sha256_16": "ddf3491a41fc569f",
+                   "fetch_kib": 2563.5625, "fetch_scale": 2.0, "write_kib": 18018.0, "write_scale": 1.0},
     # the complex-to-real pass of the CG products at 192^3: the plane kernel
     # (inverse axis-2 and axis-3 transforms, then the back-interpolation
     # partials), whose blocks hold whole planes (no tile width)
     "c2r": {"kernel": "k_slab_inv", "file": "paper_2607_17978_amd/csrc/mesh.hip",
             "grid": (192, 192, 192), "spread_rows": None,
-            "source_sha256_16": "2663c72b68804186",
-            "fetch_kib": 16359.5625, "fetch_scale": 2.0, "write_kib": 1536.5, "write_scale": 1.0},
+            "source_sha256_16": "79209d0e4f21ff73",
+            "fetch_kib": 11623.5625, "fetch_scale": 2.0, "write_kib": 1536.5, "write_scale": 1.0},
 }
 
 
-# HBM traffic of one k_batched launch (1,024 structures, order 6, spacing 0.8,
-# 1,024-thread workgroups, one per CU): FETCH_SIZE 5.067e7 KiB x 2.0 +
-# WRITE_SIZE 6.425e7 KiB x 1.0 (profiles/batched_1024_structures_counters.md)
-BATCH_TRAFFIC = 1024.0 * (5.067e7 * 2.0 + 6.425e7)
+# HBM traffic of one batched solve (1,024 structures, order 6, spacing 0.8):
+# FETCH_SIZE 8.788e6 KiB x 2.0 + WRITE_SIZE 9.740e6 KiB x 1.0 over its kernels
+# (profiles/batched_1024_structures_counters.md)
+BATCH_TRAFFIC = 1024.0 * (8.788e6 * 2.0 + 9.740e6)
 
 
 def kernel_source_hash(path, kernel):
@@ -86,7 +86,18 @@ def measured_traffic(name, tiles=(0, 0, 0), grid=(192, 192, 192)):
     return 1024.0 * (m["fetch_kib"] * m["fetch_scale"] + m["write_kib"] * m["write_scale"])
 
 
-def algorithmic_bytes(K, n, nnz, fused=True):
+def kept_modes(K, cell=None, eta=2.0):
+    """(m3 planes, m2 values) of the half spectrum that the passes carry: modes
+    with exp(-eta^2 k^2 / 2) below 2^-30 whatever their other indices are left
+    out.  cell None: all."""
+    if cell is None:
+        return K[2] // 2 + 1, K[1]
+    kcut = np.sqrt(2.0 * 30.0 * np.log(2.0)) / eta
+    m2, m3 = (int(kcut * np.linalg.norm(np.asarray(cell)[a]) / (2.0 * np.pi)) for a in (1, 2))
+    return min(K[2] // 2 + 1, m3 + 1), min(K[1], 2 * m2 + 1)
+
+
+def algorithmic_bytes(K, n, nnz, fused=True, cell=None):
     """Minimal HBM bytes each kernel kind must move once per launch.
 
     fused: the CG products' default path, where the complex-to-real pass
@@ -94,19 +105,23 @@ def algorithmic_bytes(K, n, nnz, fused=True):
     data read and 2p = 12 FP32 partials written) and the pair kernel reads
     those partials instead of the real grid (kind "interp_pairs").  Where the
     forward plane pass runs (192^3), kind "spread_r2c" also carries the
-    forward axis-2 transform for the same bytes (per-atom data read, half
-    spectrum written once) and kind "fft_rows_fwd" is not launched."""
+    forward axis-2 transform (per-atom data read, half spectrum written once)
+    and kind "fft_rows_fwd" is not launched; kind "c2r" carries the inverse
+    one.  cell: only the kept modes of the half spectrum count."""
     K1, K2, K3 = K
-    wc = 8.0 * K1 * K2 * (K3 // 2 + 1)      # half-complex grid, complex64
+    n3, n2 = kept_modes(K, cell)
+    wc = 8.0 * K1 * K2 * n3                 # half spectrum before axis 2 (complex64)
+    wk = 8.0 * K1 * n2 * n3                 # after it: the kept m2 only
+    plane = tuple(K) == (192, 192, 192)     # plane passes: axis 2 in the same launch as axis 3
     wr = 4.0 * K1 * K2 * K3                 # real grid, float32
     atom_in = 16 + 3 * 6 * 4 + 8            # home index, 3 x 6 spline weights, source value
     parts = 12 * 4.0                        # interpolation partials per atom
     return {
-        "spread_r2c": wc + atom_in * n,
-        "fft_rows_fwd": 2 * wc,
-        "fft_cols_green": 2 * wc,
-        "fft_rows_inv": 2 * wc,
-        "c2r": wc + (atom_in - 8 + parts) * n if fused else wc + wr,
+        "spread_r2c": (wk if plane else wc) + atom_in * n,
+        "fft_rows_fwd": wc + wk,
+        "fft_cols_green": 2 * wk,
+        "fft_rows_inv": wc + wk,
+        "c2r": (wk if plane else wc) + ((atom_in - 8 + parts) * n if fused else wr),
         # fused: CSR (col + value), row pointers, partials, source and diagonal terms, y
         # grid path: real grid read once, per-atom data, CSR, y and diagonal terms
         "interp_pairs": (8.0 * nnz + 4 * (n + 1) + parts * n + 4 * 8 * n if fused else
@@ -178,10 +193,10 @@ def cpu_baseline():
     }
 
 
-def matvec_record(stage_us, grid, n, nnz):
+def matvec_record(stage_us, grid, n, nnz, cell=None):
     """Per-pass microseconds (live HIP-event averages) and algorithmic bytes of
     one particle-mesh product, and the product's rate against HBM peak."""
-    by = algorithmic_bytes(grid, n, nnz)
+    by = algorithmic_bytes(grid, n, nnz, cell=cell)
     passes = [k for k in KIND_NAMES[:6] if stage_us.get(k, (0.0, 0))[1] > 0]
     us = sum(stage_us[k][0] for k in passes)
     b = sum(by[k] for k in passes)
@@ -269,7 +284,8 @@ def trajectory_record(args, dev, tol=None, profile=True):
                                    spectral_kc=args.spectral_kc, profile_matvec=profile, log=log)
     wall = time.perf_counter() - t0
     nnz = int(round(out["n"] * 0.01 * 4.0 / 3.0 * np.pi * 11.0 ** 3))
-    mv = matvec_record(out.pop("stage_us"), tuple(out["grid"]), out["n"], nnz) if profile else None
+    from inputs import gen
+    mv = matvec_record(out.pop("stage_us"), tuple(out["grid"]), out["n"], nnz, gen.md_initial()[1]) if profile else None
     keep = ("iters", "ms", "ms_with_inference", "all_converged", "q0_rejected")
     starts = {k: {f: (round(v[f], 3) if isinstance(v[f], float) else v[f]) for f in keep if f in v}
               for k, v in out.items() if isinstance(v, dict) and "iters" in v}
@@ -294,7 +310,7 @@ def main():
                     default="cold32k",
                     help="cold32k: the default cold-start solve; warmstart: the 131,072-atom "
                          "trajectory (learned vs cold vs previous-frame start); batch: 1,024 "
-                         "structures in one persistent launch vs one launch sequence per structure; "
+                         "structures advanced together vs one launch sequence per structure; "
                          "nonperiodic: an isolated 16,384-atom cluster (direct pair sum); adjoint: "
                          "the differentiated 32,768-atom workload (forward solve + adjoint backward); ewald: "
                          "direct Ewald sums vs the particle mesh over cell sizes")
@@ -440,7 +456,7 @@ def main():
     nnz = None
     # CSR size is not exported; estimate from the cutoff sphere at this density
     nnz = int(round(s.n * 0.01 * 4.0 / 3.0 * np.pi * 11.0 ** 3))
-    by = algorithmic_bytes(s.grid, s.n, nnz)
+    by = algorithmic_bytes(s.grid, s.n, nnz, cell=s.cell)
     name = KIND_NAMES[dom]
     dur_s = ms_dom[dom] / max(cnt_dom[dom], 1) * 1e-3
     achieved = by[name] / dur_s / 1e9
@@ -513,19 +529,17 @@ def main():
 
 
 def batch_bytes(structs, stats, r_cut=12.0):
-    """Algorithmic bytes of one batched solve: per structure and matvec the
-    five grid passes of its own slot (spread + axis-3 R2C writes the half
-    spectrum; axis-2 forward, axis-1 forward + Green table + inverse, axis-2
-    inverse each read and write it; the C2R pass reads it, writes the real
-    grid and clears the half spectrum), the interpolation's real-grid read,
-    per-atom spline data and the pair list (8 B per stored pair)."""
+    """Algorithmic bytes of one batched solve: per structure and matvec four
+    moves of the kept half spectrum (written by the forward planes, read and
+    written by the axis-1 lines, read by the inverse planes) and its Green
+    table, the atoms' spline data twice, their 12 partials written and read,
+    and the pair list (8 B per stored pair)."""
     tot = 0.0
     for s, st in zip(structs, stats):
-        K1, K2, K3 = s.grid
-        npts = K1 * K2 * K3
-        nh = K1 * K2 * (K3 // 2 + 1)
+        n3, n2 = kept_modes(s.grid, s.cell)
+        nh = s.grid[0] * n2 * n3
         nnz = s.n * 0.01 * 4.0 / 3.0 * np.pi * r_cut ** 3
-        mv = 8.0 * nh * (1 + 2 + 2 + 2 + 2) + 4.0 * nh + 4.0 * npts * 2 + 96.0 * s.n * 2 + 8.0 * nnz
+        mv = 8.0 * nh * 4 + 4.0 * nh + 96.0 * s.n * 2 + 48.0 * s.n * 2 + 8.0 * nnz
         tot += (st["iters"] + 2) * mv
     return tot
 
@@ -665,7 +679,7 @@ def batch_main(args, dev):
         "dtype": "f32",
         "data": "synthetic",
         "config": {"workload": "batched QEq, 1024 triclinic structures (N 32-512, 3 elements, Q in {-1,0,1}), "
-                               "one persistent launch", "n_structures": len(structs), "n_atoms": int(offs[-1]),
+                               "advanced together", "n_structures": len(structs), "n_atoms": int(offs[-1]),
                    "r_cut_bohr": rc_cut, "tol": args.tol,
                    "spline_order": best["spline_order"] if best else 6,
                    "grids": (f"per structure, spacing <= {best['max_spacing']} bohr, order and spacing chosen by "
@@ -675,9 +689,8 @@ def batch_main(args, dev):
                                    "speedup_of_batched": round(seq_ms / ms_step, 2),
                                    "cg_iters_mean": float(np.mean(seq_iters))},
         # bound from counters (profiles/batched_1024_structures_counters.md): the
-        # slots' grids (256 slots of ~3 MB) exceed the Infinity Cache and stream
-        # through HBM, ~170 GB per launch
-        "roofline": {"bound": "hbm", "kernel": "k_batched", "achieved": round(bbytes / (kern_ms * 1e-3) / 1e9, 1),
+        # LDS transforms and their barriers; memory moves 28 GB a solve (1.6 TB/s)
+        "roofline": {"bound": "lds", "kernel": "k_bq_fwd + k_bq_cols + k_bq_inv", "achieved": round(bbytes / (kern_ms * 1e-3) / 1e9, 1),
                      "peak": HBM_PEAK_GBPS, "unit": "GB/s",
                      "frac": round(bbytes / (kern_ms * 1e-3) / 1e9 / HBM_PEAK_GBPS, 4),
                      "traffic": BATCH_TRAFFIC, "bytes_per_launch": bbytes, "us_per_launch": round(kern_ms * 1e3, 1),
@@ -695,14 +708,6 @@ def batch_main(args, dev):
     if not args.no_cpu_baseline:
         out["cpu_baseline"] = cpu_baseline_batch(structs)
     print(json.dumps(out), flush=True)
-
-
-# Arithmetic per pair of the direct pair-sum product, counted from the kernel
-# source (FMA = 2): FP64 differences and squared distance (3 + 5), FP64
-# accumulation (2); FP32 width term, rsqrt, sqrt, products (6), erf (about
-# 15 with its rational approximation) and the division (about 4).
-NP_FLOP_PER_PAIR = 35.0
-FP32_VECTOR_PEAK_TFLOPS = 157.3
 
 
 def cpu_baseline_nonperiodic(n_target, budget_s=30.0):
@@ -756,7 +761,8 @@ def nonperiodic_main(args, dev):
     ms = (time.perf_counter() - t0) * 1e3 / args.steps
     us_prod = plan.time_kernel(9, reps=20)   # one CG product: pair kernel + epilogue
     pairs = float(n) * (n - 1)
-    tflops = pairs * NP_FLOP_PER_PAIR / (us_prod * 1e-6) / 1e12
+    # the product reads the stored FP32 kernel values (n^2, HBM) once
+    gbps = 4.0 * n * n / us_prod / 1e3
     out = {
         "metric": METRIC, "value": round(ms, 4), "unit": "ms", "n_gpus": 1, "steps": args.steps,
         "warmup": args.warmup, "ms_per_step": round(ms, 4), "higher_is_better": False, "scaling": "weak",
@@ -764,10 +770,9 @@ def nonperiodic_main(args, dev):
         "config": {"workload": "non-periodic QEq solve, isolated 16384-atom cluster, Q = +1, direct pair sum",
                    "n_atoms": n, "q_tot": 1.0, "tol": args.tol, "cg_iters": int(np.median(its)),
                    "precision": "f32 kernel values, f64 differences, sums and CG"},
-        "roofline": {"bound": "alu", "kernel": "np_pairs (CG product)", "achieved": round(tflops, 2),
-                     "peak": FP32_VECTOR_PEAK_TFLOPS, "unit": "TFLOP/s",
-                     "frac": round(tflops / FP32_VECTOR_PEAK_TFLOPS, 4), "traffic": None,
-                     "flop_per_pair": NP_FLOP_PER_PAIR, "us_per_launch": round(us_prod, 3),
+        "roofline": {"bound": "hbm", "kernel": "np_mv (CG product)", "achieved": round(gbps, 1),
+                     "peak": HBM_PEAK_GBPS, "unit": "GB/s", "frac": round(gbps / HBM_PEAK_GBPS, 4),
+                     "traffic": None, "bytes_per_launch": 4.0 * n * n, "us_per_launch": round(us_prod, 3),
                      "pairs_per_s": round(pairs / (us_prod * 1e-6), 1)},
         "final_stats": {k: st[k] for k in ("iters", "rel_resid", "true_rel_resid", "e_qeq", "e_elec")},
     }

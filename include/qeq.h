@@ -424,8 +424,9 @@ int qeq_use_ewald(qeq_plan* plan, int32_t enable);
    along an axis.  After such a solve qeq_backward, qeq_virial and
    qeq_element_potentials return QEQ_EINVAL.  Enabling it switches
    qeq_use_ewald off; the batched and non-periodic solves are not affected.
-   The spread adds FP32 values with atomics, so repeated solves agree to FP32
-   rounding, not bit for bit. */
+   The sums run over per-tile atom lists in one order.  Where the lists do not
+   fit (supports wider than the grid, no memory) the spread adds FP32 values
+   with atomics instead, and repeated solves agree to FP32 rounding. */
 int qeq_use_planewave(qeq_plan* plan, int32_t enable, double support);
 
 /* Solver of later qeq_solve calls on this plan: enable != 0 stabilised

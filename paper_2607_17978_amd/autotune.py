@@ -1,8 +1,8 @@
 """Autotuners: the batched solve's spline order, grid spacing and launch
 shape, and the single-structure solve's mesh tile widths.
 
-The batched workload (many small structures, each on its own grid, one
-persistent launch) trades mesh work against accuracy: a higher spline order
+The batched workload (many small structures, each on its own grid, advanced
+together) trades mesh work against accuracy: a higher spline order
 reaches the same accuracy on a coarser grid (fewer FFT points, more spline
 points per atom).  The tuner measures instead of modelling:
 

@@ -349,7 +349,7 @@ class Plan:
         return G
 
     def solve_batched(self, pos, offsets, cells, sigma, J, chi, q_tot, q0=None, forces=True, check=True):
-        """Solve many structures in one persistent launch (see qeq_solve_batched).
+        """Solve many structures together (see qeq_solve_batched).
 
         pos (N_tot x 3), sigma, J, chi (N_tot): device float64; offsets: n_struct + 1
         ints (host); cells: n_struct x 3 x 3 (host); q_tot: n_struct (host).
