@@ -553,8 +553,11 @@ int prepare(qeq_plan* pl, int n, const double* cell, double q_tot) {
 }
 
 // Geometry-dependent setup on the device; one host sync (pair count, input flag).
+// list_only: sorted atoms and the pair list with its distances, without kernel
+// values and self-correction (no operator product may follow).
 int setup_geometry(qeq_plan* pl, const double* pos, const double* sigma, const double* J,
-                   const double* chi) {
+                   const double* chi, bool list_only = false) {
+    pl->list_only = list_only;
     QEQ_TRY(launch_setup_clear(pl));   // CG scalars, bin and cell counters
     QEQ_TRY(launch_stage(pl, pos, sigma, J, chi));
     QEQ_TRY(launch_sort_bins(pl));
@@ -569,7 +572,7 @@ int setup_geometry(qeq_plan* pl, const double* pos, const double* sigma, const d
         QEQ_TRY(grow_pairs(pl, (size_t)(pl->nnz * 1.25) + 1024));
         QEQ_TRY(launch_pair_fill(pl));
     }
-    if (pl->kp.self_corr) QEQ_TRY(launch_selfcorr(pl));
+    if (pl->kp.self_corr && !list_only) QEQ_TRY(launch_selfcorr(pl));
     return QEQ_OK;
 }
 
@@ -1296,7 +1299,7 @@ int qeq_descriptors(qeq_plan* plan, int32_t n, const double* pos, const double* 
         pl->ew_active = false;
         pl->pw_active = false;
         QEQ_TRY(prepare(pl, n, cell, 0.0));
-        QEQ_TRY(setup_geometry(pl, pos, sigma, nullptr, nullptr));
+        QEQ_TRY(setup_geometry(pl, pos, sigma, nullptr, nullptr, true));
         pl->geom_valid = true;
     } else if (!pl->geom_valid || n != pl->kp.n) {
         return QEQ_EINVAL;   // no geometry of this size to reuse

@@ -150,6 +150,7 @@ struct qeq_plan {
     bool theta_valid = false;
     double c_eta = 0.0;
     double* theta_tab = nullptr;                    // (2p-1)^3 mesh kernel values
+    bool list_only = false;                         // the geometry's pair list has no kernel values
     double* theta_plane = nullptr;                  // per m3 plane sums of the tables
     size_t theta_cap = 0;                           // doubles
     // virial: strain derivatives of the self-correction (d C_eta / d eps and

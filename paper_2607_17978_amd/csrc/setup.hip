@@ -264,7 +264,13 @@ __global__ void k_cell_scatter(int n, const int* __restrict__ home, const int* _
 // cell (lane l takes stencil cells l, l + 64, ...), count or write the pairs
 // found there; a wave prefix sum gives each lane its slice of row i, so the
 // row order is fixed (lane-major, cells in stencil order, atoms in cell order).
-template <bool FILL>
+// Work of the pass: count the pairs, write them with their kernel values, or
+// write the list alone (descriptors read columns and distances only; the
+// FP64 error functions are half of the fill: 358 -> 193 us at 131,072 atoms, a
+// trajectory frame with features 11.31 -> 11.10 ms).
+enum { PAIRS_COUNT, PAIRS_FILL, PAIRS_LIST };
+
+template <int WORK>
 __global__ __launch_bounds__(QEQ_BLOCK) void k_pairs(KParams k, const double* __restrict__ frac,
                                                     const int* __restrict__ home, const double* __restrict__ sig,
                                                     const int* __restrict__ cell_start,
@@ -278,6 +284,7 @@ __global__ __launch_bounds__(QEQ_BLOCK) void k_pairs(KParams k, const double* __
     // once per step); longer rows evaluate them in place.  The staged
     // distance is kept in FP64, so staged and in-place rows evaluate the
     // kernel at the same argument.
+    constexpr bool FILL = WORK != PAIRS_COUNT;
     constexpr int PBUF = 128;
     __shared__ float4 st_d[FILL ? (QEQ_BLOCK / 64) * PBUF : 1];
     __shared__ double st_r[FILL ? (QEQ_BLOCK / 64) * PBUF : 1];
@@ -345,8 +352,8 @@ __global__ __launch_bounds__(QEQ_BLOCK) void k_pairs(KParams k, const double* __
                         ++loff;
                     } else {
                         const double sj = sig[j];
-                        double K, dKr;
-                        pair_kernel(sqrt(r2v), sqrt(sgi * sgi + sj * sj), k.eta, &K, &dKr);
+                        double K = 0.0, dKr = 0.0;
+                        if (WORK == PAIRS_FILL) pair_kernel(sqrt(r2v), sqrt(sgi * sgi + sj * sj), k.eta, &K, &dKr);
                         col[off] = j;
                         kval[off] = (float)K;
                         pdr[off] = make_float4((float)(-dx), (float)(-dy), (float)(-dz), (float)dKr);
@@ -376,8 +383,8 @@ __global__ __launch_bounds__(QEQ_BLOCK) void k_pairs(KParams k, const double* __
             const int j = st_j[sbase + e];
             const float4 d = st_d[sbase + e];
             const double sj = sig[j];
-            double K, dKr;
-            pair_kernel(st_r[sbase + e], sqrt(sgi * sgi + sj * sj), k.eta, &K, &dKr);
+            double K = 0.0, dKr = 0.0;
+            if (WORK == PAIRS_FILL) pair_kernel(st_r[sbase + e], sqrt(sgi * sgi + sj * sj), k.eta, &K, &dKr);
             col[e0 + e] = j;
             kval[e0 + e] = (float)K;
             pdr[e0 + e] = make_float4(d.x, d.y, d.z, (float)dKr);
@@ -572,7 +579,7 @@ int launch_cells_and_pairs(qeq_plan* pl) {
     hipLaunchKernelGGL(k_bucket_sort, dim3(nblocks(ncell)), dim3(QEQ_BLOCK), 0, pl->stream, ncell,
                        pl->cell_start, pl->cell_atoms);
     const int pair_blocks = nblocks(k.n * 64);   // one wave per atom
-    hipLaunchKernelGGL(k_pairs<false>, dim3(pair_blocks), dim3(QEQ_BLOCK), 0, pl->stream, k,
+    hipLaunchKernelGGL(k_pairs<PAIRS_COUNT>, dim3(pair_blocks), dim3(QEQ_BLOCK), 0, pl->stream, k,
                        pl->frac, pl->home, pl->sig, pl->cell_start, pl->cell_atoms, pl->rowcnt,
                        pl->rowptr, pl->col, pl->kval, pl->pdr, (long long)0, pl->lanecnt);
     QEQ_TRY(launch_scan(pl, pl->rowcnt, pl->rowptr, k.n));
@@ -590,7 +597,8 @@ int launch_cells_and_pairs(qeq_plan* pl) {
 
 int launch_pair_fill(qeq_plan* pl) {
     const KParams& k = pl->kp;
-    hipLaunchKernelGGL(k_pairs<true>, dim3(nblocks(k.n * 64)), dim3(QEQ_BLOCK), 0, pl->stream, k,
+    auto fill = pl->list_only ? k_pairs<PAIRS_LIST> : k_pairs<PAIRS_FILL>;
+    hipLaunchKernelGGL(fill, dim3(nblocks(k.n * 64)), dim3(QEQ_BLOCK), 0, pl->stream, k,
                        pl->frac, pl->home, pl->sig, pl->cell_start, pl->cell_atoms, pl->rowcnt,
                        pl->rowptr, pl->col, pl->kval, pl->pdr, (long long)pl->nnz_cap, pl->lanecnt);
     return qeq_check(hipGetLastError());
