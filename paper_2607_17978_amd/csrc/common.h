@@ -640,7 +640,7 @@ __device__ __forceinline__ void pair_kernel(double r, double gam, double eta, do
 // (an offset a lane, 2p - 1 <= 15), then each lane takes every 16th of the
 // (2p-1)^2 table rows.  A thread per atom is a serial chain of (2p-1)^3 = 1,331
 // table reads: 28 us for 64 atoms and 36 for 32,768, now 6 and 21 (bound by
-// LDS reads; 131,072 atoms 49 and 60); the six strain tables 135 -> 32 us.
+// LDS reads; 131,072 atoms 49 and 60); the six strain tables 135 -> 13 us (500 atoms).
 // ---------------------------------------------------------------------------
 template <int PC>
 struct SelfRows {

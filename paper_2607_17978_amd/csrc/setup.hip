@@ -430,7 +430,9 @@ __global__ __launch_bounds__(QEQ_BLOCK) void k_selfcorr(KParams k, const double*
 // six strain components (one table staged in LDS at a time), weighted by q^2;
 // also sum q^2 and sum q sigma^2 for the C_eta and background terms.  Sixteen
 // lanes an atom as above; many atoms a block, since each block reads the six
-// tables (64 KB).
+// tables (64 KB).  With few blocks (4,096 atoms) the tables go to blocks of
+// their own as well (gridDim.y = 6): 32 -> 13 us at 500
+// atoms.
 constexpr int STRAIN_NT = 1024, STRAIN_ATOMS = STRAIN_NT / 16;
 
 template <int PC>
@@ -454,22 +456,26 @@ __global__ __launch_bounds__(STRAIN_NT) void k_self_strain(KParams k, const doub
     if (tabs) {
         mesh_self_prepare<PC>(frac[3 * ic] * (double)k.K1, frac[3 * ic + 1] * (double)k.K2,
                               frac[3 * ic + 2] * (double)k.K3, k.p, w);
-        for (int comp = 0; comp < 6; ++comp) {
+        const int c0 = gridDim.y == 6 ? (int)blockIdx.y : 0, c1 = gridDim.y == 6 ? c0 + 1 : 6;
+        for (int comp = c0; comp < c1; ++comp) {
             __syncthreads();
             for (int t = threadIdx.x; t < np3; t += STRAIN_NT) tab[t] = tabs[(size_t)comp * np3 + t];
             __syncthreads();
             double s;
             mesh_self_sum<PC, false>(k.p, tab, w, &s, nullptr);
-            if (act) acc[comp] = qi * qi * s;
+#pragma unroll
+            for (int t = 0; t < 6; ++t)
+                if (act && t == comp) acc[t] = qi * qi * s;
         }
     }
-    if (act) {
+    if (act && blockIdx.y == 0) {
         acc[6] = qi * qi;
         acc[7] = qi * sig[i] * sig[i];
     }
     block_sum<QEQ_NPART>(acc);
     if (threadIdx.x == 0)
-        for (int t = 0; t < QEQ_NPART; ++t) part[(size_t)blockIdx.x * QEQ_NPART + t] = acc[t];
+        for (int t = 0; t < QEQ_NPART; ++t)
+            part[((size_t)blockIdx.y * gridDim.x + blockIdx.x) * QEQ_NPART + t] = acc[t];
 }
 
 }  // namespace
@@ -632,7 +638,15 @@ int launch_selfcorr(qeq_plan* pl) {
     return qeq_check(hipGetLastError());
 }
 
-int self_strain_blocks(int n) { return nblocks(n, STRAIN_ATOMS); }
+static dim3 self_strain_grid(int n) {
+    const int nb = nblocks(n, STRAIN_ATOMS);
+    return dim3(nb, nb <= 64 ? 6 : 1);
+}
+
+int self_strain_blocks(int n) {
+    const dim3 g = self_strain_grid(n);
+    return (int)(g.x * g.y);
+}
 
 template <int PC>
 static int self_strain_launch(qeq_plan* pl, const double* tabs, double* part) {
@@ -640,7 +654,7 @@ static int self_strain_launch(qeq_plan* pl, const double* tabs, double* part) {
     constexpr int NPM = SelfRows<PC>::NPM;
     constexpr size_t sh = sizeof(double) * NPM * NPM * NPM + sizeof(SelfRows<PC>) * STRAIN_ATOMS;
     QEQ_HIP(hipFuncSetAttribute((const void*)k_self_strain<PC>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh));
-    hipLaunchKernelGGL(k_self_strain<PC>, dim3(self_strain_blocks(k.n)), dim3(STRAIN_NT), sh, pl->stream, k, pl->frac,
+    hipLaunchKernelGGL(k_self_strain<PC>, self_strain_grid(k.n), dim3(STRAIN_NT), sh, pl->stream, k, pl->frac,
                        tabs, pl->q, pl->sig, part);
     return qeq_check(hipGetLastError());
 }
