@@ -26,11 +26,11 @@
 #include <new>
 #include <vector>
 
+#include "batched_layout.h"
 #include "internal.h"
 
 namespace qeqb {
 
-constexpr int BQ_KAX = 64;      // longest grid axis of a batched structure
 constexpr int BQ_NC = 64;       // complex lines of a block along axis 3 (two real rows each) and axis 1
 constexpr int BQ_KS = 65;       // their LDS row stride
 constexpr int BQ_NC2 = 56;      // half-spectrum columns of a block along axis 2
@@ -41,19 +41,14 @@ constexpr size_t BQ_ACC = 38400;   // most bytes of a block's accumulator
 constexpr int BQ_L = 8;         // lanes per atom in the interpolation and pair loops
 constexpr int BQ_PAIR_ATOMS = 32;   // atoms of a block of the pair-list kernel
 constexpr int BQ_GREEN = 4096;  // Green's function values of a block
+static_assert(BQ_MAXP == QEQ_MAXP, "one spline order limit");
 constexpr int BQ_OVERFLOW = 100;   // internal status: pair list did not fit
-constexpr int BQ_NV = 11;       // per-atom FP64 vectors in a slot
 
 enum { V_Q = 0, V_R, V_P, V_Y, V_DINV, V_CHI, V_DSELF, V_G, V_J, V_SIG, V_CHIRAW };
 
 // Which product the four kernels work on: the starting residual (source q),
 // an iteration (source p), the final product (source q, forces).
 enum { BQ_INIT = 0, BQ_ITER, BQ_FINAL };
-
-// Byte offsets inside one structure's scratch slot.
-struct BSlot {
-    unsigned C, G, wts, dwts, home, frac, vec, selfgrad, row, col, kval, pdr, tab, mpart, hstart, perm, fpair;
-};
 
 // Per-structure constants prepared on the host.
 struct BStruct {
@@ -111,7 +106,7 @@ struct BArgs {
 };
 
 template <typename T>
-__device__ __forceinline__ T* slot_ptr(const BArgs& a, const BStruct& S, unsigned off) {
+__device__ __forceinline__ T* slot_ptr(const BArgs& a, const BStruct& S, size_t off) {
     return reinterpret_cast<T*>(a.scratch + S.base + off);
 }
 __device__ __forceinline__ double* slot_vec(const BArgs& a, const BStruct& S, int v) {
@@ -1319,41 +1314,9 @@ int grow(T** p, size_t* cap, size_t count) {
     return QEQ_OK;
 }
 
-size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
-
 // Scratch of the structures that are solved together (1,024 structures of
 // 32 .. 512 atoms: 1.6 GB).
 constexpr size_t BQ_SCRATCH = (size_t)8 << 30;
-
-// Offsets of a structure's slot; returns its size.
-size_t slot_layout(BStruct& S) {
-    BSlot& L = S.slot;
-    const size_t n = (size_t)S.n, np = 2 * QEQ_MAXP - 1;
-    size_t o = 0;
-    auto place = [&](size_t bytes) {
-        const size_t at = o;
-        o = align256(o + bytes);
-        return (unsigned)at;
-    };
-    L.C = place(sizeof(float2) * (size_t)S.nhalf);
-    L.G = place(sizeof(float) * (size_t)S.nhalf);
-    L.wts = place(sizeof(float) * 3 * QEQ_MAXP * n);
-    L.dwts = place(sizeof(float) * 3 * QEQ_MAXP * n);
-    L.home = place(sizeof(int) * 4 * n);
-    L.frac = place(sizeof(double) * 3 * n);
-    L.vec = place(sizeof(double) * BQ_NV * n);
-    L.selfgrad = place(sizeof(double) * 3 * n);
-    L.row = place(sizeof(int2) * n);
-    L.col = place(sizeof(int) * (size_t)S.pcap);
-    L.kval = place(sizeof(float) * (size_t)S.pcap);
-    L.pdr = place(sizeof(float4) * (size_t)S.pcap);
-    L.tab = place(sizeof(double) * np * np * np);
-    L.mpart = place(sizeof(float) * 4 * QEQ_MAXP * n);
-    L.hstart = place(sizeof(int) * (BQ_KAX + 1));
-    L.perm = place(sizeof(int) * n);
-    L.fpair = place(sizeof(double) * 3 * n);
-    return o;
-}
 
 }  // namespace qeqb
 
@@ -1759,7 +1722,7 @@ int batched_impl(qeq_plan* pl, int n_struct, const int32_t* offs, const double* 
             size_t used = 0, w1 = w0;
             for (; w1 < work.size(); ++w1) {
                 BStruct& S = st[work[w1]];
-                const size_t bytes = slot_layout(S);
+                const size_t bytes = slot_layout(S.slot, (size_t)S.n, (size_t)S.nhalf, (size_t)S.pcap);
                 if (w1 > w0 && used + bytes > limit) break;
                 S.base = used;
                 used += bytes;
