@@ -158,7 +158,8 @@ int qeq_solve_nonperiodic(qeq_plan* plan, int32_t n, const double* pos, const do
    gamma (n * n_elem, FP64, device, caller order, out).
    Cost: n_elem operator products.  The tape for qeq_backward / qeq_virial is
    kept.  QEQ_EINVAL without a preceding successful solve (or after
-   qeq_matvec / qeq_solve_batched, which replace it) or for bad arguments. */
+   qeq_matvec, qeq_solve_batched or qeq_descriptors with positions, which
+   replace it) or for bad arguments. */
 int qeq_element_potentials(qeq_plan* plan, const int32_t* species, int32_t n_elem, double* gamma);
 
 /* Gradient of a loss L(q, E_QEq, E_elec) through the last solve on this plan

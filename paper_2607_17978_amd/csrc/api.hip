@@ -1295,6 +1295,7 @@ int qeq_descriptors(qeq_plan* plan, int32_t n, const double* pos, const double* 
     if (pos) {
         if (!sigma) return QEQ_EINVAL;
         pl->tape_valid = false;   // the geometry set-up below replaces the solve's tape
+        pl->np_valid = false;     // and the order and number of the atoms of an isolated solve
         pl->geom_valid = false;
         pl->ew_active = false;
         pl->pw_active = false;
