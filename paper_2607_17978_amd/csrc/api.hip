@@ -73,6 +73,20 @@ void debug_poison(void* p, size_t bytes) {
     if (p && bytes && getenv("QEQ_POISON_ALLOC") != nullptr) (void)hipMemset(p, 0xff, bytes);
 }
 
+bool device_grow(size_t& cap, size_t count, std::initializer_list<GrowBuf> bufs) {
+    const bool ok = grow_together(
+        cap, count, bufs,
+        [](const GrowBuf& b, size_t bytes) {
+            void* p = nullptr;
+            if (hipMalloc(&p, bytes) != hipSuccess) return (void*)nullptr;
+            if (b.fp) debug_poison(p, bytes);
+            return p;
+        },
+        [](void* p) { (void)hipFree(p); });
+    if (!ok) (void)hipGetLastError();
+    return ok;
+}
+
 namespace {
 
 const double PI = 3.14159265358979323846;
@@ -510,15 +524,9 @@ int prepare(qeq_plan* pl, int n, const double* cell, double q_tot) {
         if (k.ns[a] > 64) return QEQ_ECELL;
         ncell *= nc;
     }
-    if (ncell + 1 > pl->ncell_alloc) {
-        dfree(pl->cell_count);
-        dfree(pl->cell_start);
-        dfree(pl->cell_fill);
-        QEQ_TRY(dalloc(&pl->cell_count, ncell + 1));
-        QEQ_TRY(dalloc(&pl->cell_start, ncell + 2));
-        QEQ_TRY(dalloc(&pl->cell_fill, ncell + 1));
-        pl->ncell_alloc = ncell + 1;
-    }
+    if (!device_grow(pl->ncell_alloc, (size_t)ncell + 1,
+                     {grow_buf(pl->cell_count), grow_buf(pl->cell_start, 1), grow_buf(pl->cell_fill)}))
+        return QEQ_ENOMEM;
     // with direct Ewald sums the reciprocal part is added from outside the
     // interpolation pass and is exact (no mesh self-correction)
     // The Gaussian-on-grid operator is the whole Coulomb operator of the

@@ -10,6 +10,7 @@
 #include <vector>
 
 #include "common.h"
+#include "grow.h"
 #include "../../include/qeq.h"
 
 #define QEQ_BLOCK 256         // threads per block for per-atom kernels
@@ -190,7 +191,7 @@ struct qeq_plan {
     double* tq = nullptr;         // n x 3: sum_g dtheta_i/du phi_q(g)
 
     // real-space cell list and pair list
-    int ncell_alloc = 0;
+    size_t ncell_alloc = 0;
     int* cell_count = nullptr;
     int* cell_start = nullptr;
     int* cell_fill = nullptr;
@@ -306,7 +307,8 @@ struct qeq_plan {
     bool pw_active = false;       // the current solve's operator uses it
     double pw_support = 6.0;      // support radius in units of sigma_i
     PwGeom pw_geom{};
-    int pw_cap_n = 0, pw_cap_k = 0;
+    int pw_cap_n = 0;
+    size_t pw_cap_k = 0;
     float* pw_ones = nullptr;     // unit moduli for the Green's function pass
     double* pw_y = nullptr;       // operator product, sorted order
     double* pw_f = nullptr;       // forces of the final product, sorted order
@@ -317,7 +319,7 @@ struct qeq_plan {
     int* pw_tstart = nullptr;     // [tiles + 1]
     int* pw_acount = nullptr;     // [n] tiles per atom
     int* pw_astart = nullptr;     // [n + 1]
-    size_t pw_cap_t = 0;          // tiles allocated
+    size_t pw_cap_t = 0, pw_cap_a = 0;   // tiles, atoms allocated
     void* pw_rec = nullptr;       // float4 (fraction inside the grid cell, log2(e) / (2 sigma^2)) per atom
     double* pw_amp = nullptr;     // dV / ((2 pi)^{3/2} sigma^3) per atom
     void* pw_ent = nullptr;       // int4 (atom, tile offset 1 | 2 << 16, offset 3, slot) by tile
@@ -371,6 +373,12 @@ void debug_poison(void* p, size_t bytes);
 template <typename T>
 constexpr bool poisonable = std::is_floating_point<T>::value || std::is_same<T, float2>::value ||
                             std::is_same<T, float4>::value || std::is_same<T, double2>::value;
+// grow_together in device memory; a failed allocation leaves no HIP error behind.
+bool device_grow(size_t& cap, size_t count, std::initializer_list<GrowBuf> bufs);
+template <typename T>
+GrowBuf grow_buf(T*& p, size_t extra = 0) {
+    return {(void**)&p, sizeof(T), extra, poisonable<T>};
+}
 #define QEQ_TRY(x)                                   \
     do {                                             \
         int _rc = (x);                               \

@@ -571,45 +571,38 @@ bool invert3(const double m[9], double out[9]) {
 
 }  // namespace
 
-// Sized by the current lists (also after a failed allocation).
-static void pw_free_entries(qeq_plan* pl) {
-    if (pl->pw_ent) (void)hipFree(pl->pw_ent);
-    if (pl->pw_part) (void)hipFree(pl->pw_part);
-    pl->pw_ent = nullptr;
-    pl->pw_part = nullptr;
-    pl->pw_cap_e = 0;
-}
-
 void pw_free(qeq_plan* pl) {
     void* ptrs[] = {pl->pw_ones,   pl->pw_y,      pl->pw_f,      pl->pw_smax, pl->pw_tcount,
-                    pl->pw_tstart, pl->pw_acount, pl->pw_astart, pl->pw_rec,  pl->pw_amp};
+                    pl->pw_tstart, pl->pw_acount, pl->pw_astart, pl->pw_rec,  pl->pw_amp,  pl->pw_ent,
+                    pl->pw_part};
     for (void* q : ptrs)
         if (q) (void)hipFree(q);
-    pw_free_entries(pl);
+    pl->pw_ent = nullptr;
+    pl->pw_part = nullptr;
     pl->pw_tcount = pl->pw_tstart = pl->pw_acount = pl->pw_astart = nullptr;
     pl->pw_rec = nullptr;
     pl->pw_amp = nullptr;
-    pl->pw_cap_t = 0;
+    pl->pw_cap_t = pl->pw_cap_a = pl->pw_cap_e = 0;
     pl->pw_tiles = false;
     pl->pw_ones = nullptr;
     pl->pw_y = pl->pw_f = pl->pw_smax = nullptr;
-    pl->pw_cap_n = pl->pw_cap_k = 0;
+    pl->pw_cap_n = 0;
+    pl->pw_cap_k = 0;
 }
 
 // Tile lists of the current geometry (pw_tiles = false, and the walks instead,
 // where they have more than PW_ENT_MAX entries or do not fit the free memory;
 // the axis-3 pass takes tiles of at most LEN_TW rows).  One host
 // synchronisation for their length.
-static int pw_lists(qeq_plan* pl) {
+static int pw_build_lists(qeq_plan* pl) {
     const KParams& k = pl->kp;
-    pl->pw_tiles = false;
     if (k.TW > LEN_TW) return QEQ_OK;
     const size_t nt = (size_t)(k.K1 / PW_E) * (k.K2 / PW_E) * (k.K3 / PW_E);
-    if (nt > pl->pw_cap_t) {
-        QEQ_TRY(pw_alloc(&pl->pw_tcount, nt + 1));
-        QEQ_TRY(pw_alloc(&pl->pw_tstart, nt + 1));
-        pl->pw_cap_t = nt;
-    }
+    const GrowBuf rec = {&pl->pw_rec, sizeof(float4), 0, true};
+    if (!device_grow(pl->pw_cap_t, nt, {grow_buf(pl->pw_tcount, 1), grow_buf(pl->pw_tstart, 1)}) ||
+        !device_grow(pl->pw_cap_a, (size_t)pl->n_max,
+                     {grow_buf(pl->pw_acount, 1), grow_buf(pl->pw_astart, 1), rec, grow_buf(pl->pw_amp)}))
+        return QEQ_ENOMEM;
     const int nb = (int)(((size_t)k.n * 64 + PW_NT - 1) / PW_NT);
     const unsigned cb = (unsigned)((nt + PW_NT - 1) / PW_NT), ob = (unsigned)((nt * 64 + PW_NT - 1) / PW_NT);
     hipStream_t st = pl->stream;
@@ -629,23 +622,11 @@ static int pw_lists(qeq_plan* pl) {
     QEQ_HIP(hipMemcpyAsync(&total, pl->pw_astart + k.n, sizeof(int), hipMemcpyDeviceToHost, st));
     QEQ_HIP(hipStreamSynchronize(st));
     if (total < 0 || (size_t)total > PW_ENT_MAX) return QEQ_OK;
+    // the entries twice: as filled, and in order
     if ((size_t)total > pl->pw_cap_e) {
-        pw_free_entries(pl);
         const size_t cap = std::min(PW_ENT_MAX, (size_t)total + (size_t)total / 8 + 1024);
-        // the entries twice: as filled, and in order
-        if (hipMalloc(&pl->pw_ent, 2 * cap * sizeof(int4)) != hipSuccess) {
-            pl->pw_ent = nullptr;
-            (void)hipGetLastError();
-            return QEQ_OK;
-        }
-        if (hipMalloc((void**)&pl->pw_part, cap * sizeof(float)) != hipSuccess) {
-            pl->pw_part = nullptr;
-            pw_free_entries(pl);
-            (void)hipGetLastError();
-            return QEQ_OK;
-        }
-        debug_poison(pl->pw_part, cap * sizeof(float));
-        pl->pw_cap_e = cap;
+        const GrowBuf pairs = {&pl->pw_ent, 2 * sizeof(int4), 0, false};
+        if (!device_grow(pl->pw_cap_e, cap, {pairs, grow_buf(pl->pw_part)})) return QEQ_ENOMEM;
     }
     int4* ent = (int4*)pl->pw_ent;
     hipLaunchKernelGGL(k_pw_clear, dim3(cb), dim3(PW_NT), 0, st, pl->pw_tcount, nt);
@@ -657,26 +638,32 @@ static int pw_lists(qeq_plan* pl) {
     return QEQ_OK;
 }
 
+// The lists, or the walks where there is no memory for them.
+static int pw_lists(qeq_plan* pl) {
+    pl->pw_tiles = false;
+    const int rc = pw_build_lists(pl);
+    if (rc != QEQ_ENOMEM) return rc;
+    (void)hipGetLastError();
+    return QEQ_OK;
+}
+
 // Geometry of the current cell and grid; buffers grown as needed.  One host
 // sync (the largest sigma bounds the support, checked against the grid).
 int pw_setup(qeq_plan* pl) {
     const KParams& k = pl->kp;
-    const int kmax = std::max({k.K1, k.K2, k.K3});
+    const size_t kmax = (size_t)std::max({k.K1, k.K2, k.K3});
     if (kmax > pl->pw_cap_k) {
-        QEQ_TRY(pw_alloc(&pl->pw_ones, (size_t)kmax));
-        std::vector<float> ones((size_t)kmax, 1.0f);
-        QEQ_HIP(hipMemcpy(pl->pw_ones, ones.data(), sizeof(float) * kmax, hipMemcpyHostToDevice));
-        pl->pw_cap_k = kmax;
+        if (!device_grow(pl->pw_cap_k, kmax, {grow_buf(pl->pw_ones)})) return QEQ_ENOMEM;
+        std::vector<float> ones(kmax, 1.0f);
+        const hipError_t e = hipMemcpy(pl->pw_ones, ones.data(), sizeof(float) * kmax, hipMemcpyHostToDevice);
+        if (e != hipSuccess) pl->pw_cap_k = 0;
+        QEQ_HIP(e);
     }
     if (pl->n_max > pl->pw_cap_n) {
         const size_t nn = (size_t)pl->n_max;
         QEQ_TRY(pw_alloc(&pl->pw_y, nn));
         QEQ_TRY(pw_alloc(&pl->pw_f, 3 * nn));
         QEQ_TRY(pw_alloc(&pl->pw_smax, (nn + PW_NT - 1) / PW_NT));
-        QEQ_TRY(pw_alloc(&pl->pw_acount, nn + 1));
-        QEQ_TRY(pw_alloc(&pl->pw_astart, nn + 1));
-        QEQ_TRY(pw_alloc((float4**)&pl->pw_rec, nn));
-        QEQ_TRY(pw_alloc(&pl->pw_amp, nn));
         pl->pw_cap_n = pl->n_max;
     }
     const int Kd[3] = {k.K1, k.K2, k.K3};
