@@ -562,6 +562,15 @@ __device__ __forceinline__ double wave_sum(double v) {
     return row16_sum(v);
 }
 
+// LDS hand-over between lanes of one wave: what they wrote before is read after.
+// The barrier alone orders instructions, not memory; the fences cost no
+// instruction of their own (LDS operations of a wave complete in order).
+__device__ __forceinline__ void wave_exchange() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // Sum NV values over the block; result valid in thread 0.  blockDim <= 1024.
 template <int NV>
 __device__ __forceinline__ void block_sum(double* v) {

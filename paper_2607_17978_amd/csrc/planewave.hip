@@ -303,9 +303,9 @@ __global__ __launch_bounds__(PW_NT) void k_pw_tile_spread(KParams k, PwGeom g, i
     float q = 0.f;
     for (int e = e0; e < e1; e += 64) {
         const int m = min(64, e1 - e);
-        __builtin_amdgcn_wave_barrier();
+        wave_exchange();
         pw_stage(ent, e + lane, lane < m, rec, amp, src, g.c2, &recs[w][lane]);
-        __builtin_amdgcn_wave_barrier();
+        wave_exchange();
 #pragma unroll 4
         for (int t = 0; t < m; ++t) {
             const PwRec& r = recs[w][t];
@@ -340,9 +340,9 @@ __global__ __launch_bounds__(PW_NT) void k_pw_tile_interp(KParams k, PwGeom g, i
         grid[((size_t)(T1 * PW_E + (lane >> 4)) * k.K2 + T2 * PW_E + ((lane >> 2) & 3)) * k.K3 + T3 * PW_E + (lane & 3)];
     for (int e = e0; e < e1; e += 64) {
         const int m = min(64, e1 - e);
-        __builtin_amdgcn_wave_barrier();
+        wave_exchange();
         pw_stage(ent, e + lane, lane < m, rec, nullptr, nullptr, g.c2, &recs[w][lane]);
-        __builtin_amdgcn_wave_barrier();
+        wave_exchange();
         for (int b = 0; b < m; b += 16) {
             float keep = 0.f;
 #pragma unroll 4
