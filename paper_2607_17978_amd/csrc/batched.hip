@@ -106,8 +106,8 @@ struct BArgs {
 };
 
 template <typename T>
-__device__ __forceinline__ T* slot_ptr(const BArgs& a, const BStruct& S, size_t off) {
-    return reinterpret_cast<T*>(a.scratch + S.base + off);
+__device__ __forceinline__ T* slot_ptr(const BArgs& a, const BStruct& S, unsigned off) {
+    return reinterpret_cast<T*>(a.scratch + S.base + slot_bytes(off));
 }
 __device__ __forceinline__ double* slot_vec(const BArgs& a, const BStruct& S, int v) {
     return slot_ptr<double>(a, S, S.slot.vec) + (size_t)v * S.n;

@@ -40,7 +40,7 @@ def run(exe, *args):
                                            (1024, 60 * 60 * 31, 178956970), (1024, 60 * 60 * 31, 210000000),
                                            (1024, 64 * 64 * 33, 281000000)])
 def test_slot_arrays_do_not_overlap(tmp_path, n, nhalf, pairs):
-    members = ", ".join(f"(size_t)L.{name}" for name, _ in ARRAYS)
+    members = ", ".join(f"slot_bytes(L.{name})" for name, _ in ARRAYS)
     exe = host_program(tmp_path, """
         BSlot L{};
         const size_t end = slot_layout(L, strtoull(argv[1], 0, 10), strtoull(argv[2], 0, 10), strtoull(argv[3], 0, 10));
