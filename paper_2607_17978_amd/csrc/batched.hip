@@ -31,13 +31,6 @@
 
 namespace qeqb {
 
-constexpr int BQ_NC = 64;       // complex lines of a block along axis 3 (two real rows each) and axis 1
-constexpr int BQ_KS = 65;       // their LDS row stride
-constexpr int BQ_NC2 = 56;      // half-spectrum columns of a block along axis 2
-constexpr int BQ_KS2 = 57;      // their LDS row stride
-constexpr int BQ_NT = 512;      // threads of the plane and line kernels
-constexpr int BQ_PB = 8;        // most planes of a block
-constexpr size_t BQ_ACC = 38400;   // most bytes of a block's accumulator
 constexpr int BQ_L = 8;         // lanes per atom in the interpolation and pair loops
 constexpr int BQ_PAIR_ATOMS = 32;   // atoms of a block of the pair-list kernel
 constexpr int BQ_GREEN = 4096;  // Green's function values of a block
@@ -425,9 +418,6 @@ __global__ __launch_bounds__(256) void k_bq_pairs(BArgs a, const int2* __restric
     if (tid == 0) bq_lap(T, PH_PAIRS, t0);
 }
 
-// Axis-2 index of the kept row e of a plane of the half spectrum.
-__device__ __forceinline__ int bq_m2(const BStruct& S, int e) { return e < ((S.nm2 + 1) >> 1) ? e : e + (S.K[1] - S.nm2); }
-
 // Green's function of the split times the B-spline moduli (SI "Ewald
 // Summation" Gaussian filter, eq. matvec 4 pi / k^2) on the half spectrum
 // (m3 <= K3 / 2): zero at m = 0 and on the Nyquist planes, as in the
@@ -459,7 +449,7 @@ __global__ __launch_bounds__(256) void k_bq_green(BArgs a, const int2* __restric
     const int end = min(S.nhalf, (u.y + 1) * BQ_GREEN);
     for (int t = u.y * BQ_GREEN + threadIdx.x; t < end; t += 256) {
         const int m3 = t % K3h, r = t / K3h;
-        G[t] = bq_green(S, a.eta, r / nm2, bq_m2(S, r % nm2), m3, b1, b2, b3);
+        G[t] = bq_green(S, a.eta, r / nm2, bq_m2(r % nm2, nm2, S.K[1]), m3, b1, b2, b3);
     }
     if (threadIdx.x == 0) bq_lap(T, PH_MESHPREP, t0);
 }
@@ -489,34 +479,6 @@ __device__ __forceinline__ void bq_fft_lines(float2* buf, int K, const float2* t
 #undef X
     }
 }
-
-// A thread's elements of a block's half spectra C[j nm2 + e][m]: 32 lanes along
-// m (at most two steps: km <= 33), BQ_NT / 32 rows at a time, so that a step
-// costs a carry instead of two divisions.  at: the row's place in X2[m2][j km].
-struct BqWalk {
-    static constexpr int ROWS = BQ_NT / 32;
-    int nm2, km, half, skip, j, e, row;
-    __device__ __forceinline__ BqWalk(int tid, const BStruct& S) : nm2(S.nm2), km(S.km) {
-        half = (nm2 + 1) >> 1;
-        skip = S.K[1] - nm2;
-        row = tid >> 5;
-        j = 0;
-        e = row;
-        carry();
-    }
-    __device__ __forceinline__ void carry() {
-        while (e >= nm2) {
-            e -= nm2;
-            ++j;
-        }
-    }
-    __device__ __forceinline__ int at() const { return (e < half ? e : e + skip) * BQ_KS2 + j * km; }
-    __device__ __forceinline__ void next() {
-        row += ROWS;
-        e += ROWS;
-        carry();
-    }
-};
 
 // The atoms that reach each of a block's planes: those with home planes g1 ..
 // g1 + p - 1, one (wrapped) index range per plane.  first / cnt in LDS, off =
@@ -698,7 +660,7 @@ __global__ __launch_bounds__(BQ_NT) void k_bq_fwd(BArgs a, const int2* __restric
     bq_fft_axis2<false>(X2, K2, tw2, tid);
     float2* C = slot_ptr<float2>(a, S, S.slot.C) + (size_t)g1a * S.nm2 * km;
     const int kept = planes * S.nm2;
-    for (BqWalk w(tid, S); w.row < kept; w.next())
+    for (BqWalk w(tid, S.nm2, km, K2); w.row < kept; w.next())
         for (int m = tid & 31; m < km; m += 32) C[w.row * km + m] = X2[w.at() + m];
     if (tid == 0) bq_lap(T, PH_FFT, t0);
 }
@@ -831,7 +793,7 @@ __global__ __launch_bounds__(BQ_NT) void k_bq_cols(BArgs a, const int2* __restri
 // imaginary part.  buf [K3][BQ_KS] and X2 [K2][BQ_KS2] share their place: 33 KB at
 // most, so that four blocks share a CU (two with both side by side:
 // 228 -> 147 us a launch for 1,024 structures).
-__device__ __forceinline__ void bq_planes_inv(const BArgs& a, const BStruct& S, int g1a, int planes, float2* buf,
+__device__ __forceinline__ void bq_inverse_planes(const BArgs& a, const BStruct& S, int g1a, int planes, float2* buf,
                                               const float2* tw2, const float2* tw3, int tid) {
     const int K2 = S.K[1], K3 = S.K[2], km = S.km;
     float2* X2 = buf;   // the packed lines take its place through registers
@@ -847,7 +809,7 @@ __device__ __forceinline__ void bq_planes_inv(const BArgs& a, const BStruct& S, 
         if (row < kept && m0 < km) v[q] = C[row * km + m0];
         if (row < kept && m0 + 32 < km) ve[q] = C[row * km + m0 + 32];
     }
-    BqWalk w(tid, S);
+    BqWalk w(tid, S.nm2, km, K2);
 #pragma unroll
     for (int q = 0; q < PER; ++q) {
         if (w.row < kept) {
@@ -918,7 +880,7 @@ __global__ __launch_bounds__(BQ_NT) void k_bq_inv(BArgs a, const int2* __restric
     if (tid < K3) tw3[tid] = a.tw[S.tw_off[2] + tid];
     if (tid >= BQ_KAX && tid - BQ_KAX < K2) tw2[tid - BQ_KAX] = a.tw[S.tw_off[1] + tid - BQ_KAX];
     bq_ranges(slot_ptr<int>(a, S, S.slot.hstart), K1, n, p, g1a, planes, tid, first, off);
-    bq_planes_inv(a, S, g1a, planes, lds, tw2, tw3, tid);
+    bq_inverse_planes(a, S, g1a, planes, lds, tw2, tw3, tid);
     if (tid == 0) t0 = bq_lap(T, PH_FFT, t0);
     const float* bf = reinterpret_cast<const float*>(lds);
     const int* home = slot_ptr<int>(a, S, S.slot.home);
@@ -1009,7 +971,7 @@ __global__ __launch_bounds__(BQ_NT) void k_bq_theta(BArgs a, const int2* __restr
     if (tid < K3) tw3[tid] = a.tw[S.tw_off[2] + tid];
     if (tid >= BQ_KAX && tid - BQ_KAX < K2) tw2[tid - BQ_KAX] = a.tw[S.tw_off[1] + tid - BQ_KAX];
     __syncthreads();
-    bq_planes_inv(a, S, d1 < 0 ? d1 + K1 : d1, 1, lds, tw2, tw3, tid);
+    bq_inverse_planes(a, S, d1 < 0 ? d1 + K1 : d1, 1, lds, tw2, tw3, tid);
     const float* bf = reinterpret_cast<const float*>(lds);
     double* tab = slot_ptr<double>(a, S, S.slot.tab) + (size_t)u.y * np * np;
     for (int t = tid; t < np * np; t += BQ_NT) {
@@ -1479,9 +1441,9 @@ int run_wave(qeq_plan* pl, BatchState* b, BArgs& a, std::vector<BStruct>& st, co
     size_t shA = 0, shB = 0, shC = 0;
     for (int s : work) {
         const BStruct& S = st[s];
-        shC = std::max({shC, sizeof(float2) * (size_t)S.K[2] * BQ_KS, sizeof(float2) * (size_t)S.K[1] * BQ_KS2});
-        shA = std::max({shA, shC, sizeof(long long) * (size_t)S.K[2] * S.pf * S.K[1]});
-        shB = std::max(shB, sizeof(float2) * (size_t)S.K[0] * BQ_KS);
+        shC = std::max(shC, bq_lds_inv(S.K[1], S.K[2]));
+        shA = std::max(shA, bq_lds_fwd(S.K[1], S.K[2], S.pf));
+        shB = std::max(shB, bq_lds_lines(S.K[0]));
     }
     auto window = [](const void* fn, size_t sh) {
         return sh <= 65536 ? QEQ_OK
@@ -1647,8 +1609,8 @@ int batched_impl(qeq_plan* pl, int n_struct, const int32_t* offs, const double* 
         }
         for (int x = 0; x < 3; ++x)
             if (std::find(Ks.begin(), Ks.end(), K[x]) == Ks.end()) Ks.push_back(K[x]);
-        S.pf = S.pb = std::max(1, std::min({2 * BQ_NC / K[1], BQ_NC2 / S.km, K[0] - p + 1, BQ_PB}));
-        S.pf = std::max(1, std::min(S.pf, (int)(BQ_ACC / (sizeof(long long) * (size_t)K[1] * K[2]))));
+        S.pb = bq_planes_inv(K[0], K[1], S.km, p);
+        S.pf = bq_planes_fwd(S.pb, K[1], K[2]);
         // pair capacity: mean neighbour count of a uniform density plus a
         // generous Poisson tail
         const double dens = n / det;

@@ -1,5 +1,6 @@
-"""Memory layout of the batched solve, from the header that its kernels use
-(csrc/batched_layout.h), compiled for the host."""
+"""Sizes and index rules of the batched solve, from the header that its kernels
+use (csrc/batched_layout.h), compiled for the host: what changes there is what is
+checked here."""
 import os
 import shutil
 import subprocess
@@ -22,7 +23,7 @@ def host_program(tmp_path, body):
     if shutil.which("g++") is None:
         pytest.skip("g++ not available")
     src, exe = tmp_path / "layout.cpp", tmp_path / "layout"
-    src.write_text('#include <cstdio>\n#include <cstdlib>\n#include "batched_layout.h"\nusing namespace qeqb;\n'
+    src.write_text('#include <cstdio>\n#include <cstdlib>\n#include <initializer_list>\n#include "batched_layout.h"\nusing namespace qeqb;\n'
                    "int main(int argc, char** argv) {\n" + body + "\nreturn 0;}\n")
     subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-I", CSRC, str(src), "-o", str(exe)], check=True)
     return str(exe)
@@ -50,3 +51,51 @@ def test_slot_arrays_do_not_overlap(tmp_path, n, nhalf, pairs):
     assert at[0] == 0
     for (name, size), lo, hi in zip(ARRAYS, at[:-1], at[1:]):
         assert lo % 256 == 0 and lo + size(n, nhalf, pairs) <= hi, name
+
+
+# every combination of axis lengths and kept modes: a block's LDS stays below the
+# 64 KB that a launch gets without asking (and four forward blocks share 160 KB),
+# its planes, rows and columns inside the buffers, every plane in one block, and
+# the walk over the kept rows meets each once, at its place
+PLANES = """
+    const int len[] = {12, 16, 20, 24, 32, 36, 40, 48, 60, 64}, p = atoi(argv[1]);
+    long cases = 0, bad = 0;
+    for (int K1 : len) for (int K2 : len) for (int K3 : len) for (int share = 1; share <= 10; share += 3) {
+        if (K1 < 2 * p || K2 < 2 * p || K3 < 2 * p) continue;
+        ++cases;
+        const int km = bq_min(K3 / 2 + 1, share * K3 / 20 + 1), nm2 = bq_min(K2, 2 * (share * K2 / 20) + 1);
+        const int pb = bq_planes_inv(K1, K2, km, p), pf = bq_planes_fwd(pb, K2, K3);
+        bool ok = 1 <= pf && pf <= pb && pb <= BQ_PB && pb + p - 1 <= K1;
+        ok = ok && pb * K2 <= 2 * BQ_NC && (pb * K2) % 2 == 0 && pb * km <= BQ_NC2 && BQ_NC2 < BQ_KS2 && BQ_NC < BQ_KS;
+        const size_t fwd = bq_lds_fwd(K2, K3, pf), inv = bq_lds_inv(K2, K3);
+        ok = ok && fwd <= 40960 && inv <= fwd && bq_lds_lines(K1) <= 65536 && 8 * (size_t)K3 * pf * K2 <= fwd;
+        ok = ok && 8 * ((size_t)(K3 - 1) * BQ_KS + (pb * K2 - 1) / 2 + 1) <= inv && km <= 64;
+        for (int planes : {pf, pb}) {
+            const int kept = planes * nm2;
+            ok = ok && kept <= BqWalk::ROWS * (2 * BQ_NC / BqWalk::ROWS);   // register slots
+            int seen = 0;
+            for (int first = 0; first < BqWalk::ROWS; ++first)
+                for (BqWalk w(32 * first + 31, nm2, km, K2); w.row < kept; w.next(), ++seen) {
+                    const int j = w.row / nm2, m2 = bq_m2(w.row % nm2, nm2, K2);
+                    ok = ok && w.row % BqWalk::ROWS == first && w.at() == m2 * BQ_KS2 + j * km;
+                    ok = ok && 0 <= m2 && m2 < K2 && 8 * (size_t)(w.at() + km) <= inv;
+                }
+            ok = ok && seen == kept;
+        }
+        // kept indices: the lowest and the highest, without a repeat
+        int last = -1;
+        for (int e = 0; e < nm2; ++e) {
+            const int m2 = bq_m2(e, nm2, K2);
+            ok = ok && m2 > last && (m2 <= (nm2 - 1) / 2 || m2 >= K2 - (nm2 - 1) / 2 || nm2 == K2);
+            last = m2;
+        }
+        ok = ok && last == (nm2 == 1 ? 0 : K2 - 1);
+        if (!ok && ++bad < 5) std::fprintf(stderr, "%d %d %d share %d\\n", K1, K2, K3, share);
+    }
+    std::printf("%ld %ld", cases, bad);"""
+
+
+@pytest.mark.parametrize("p", [4, 6, 8])
+def test_blocks_stay_inside_their_buffers(tmp_path, p):
+    lengths = sum(k >= 2 * p for k in (12, 16, 20, 24, 32, 36, 40, 48, 60, 64))
+    assert run(host_program(tmp_path, PLANES), p) == [4 * lengths ** 3, 0]
