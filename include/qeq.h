@@ -136,10 +136,21 @@ int qeq_solve(qeq_plan* plan, int32_t n, const double* pos, const double* cell,
    max_iter apply).  Positions may lie anywhere (coincident atoms are
    allowed: the kernel takes its r -> 0 limit).  The call leaves no tape:
    qeq_backward and qeq_virial return QEQ_EINVAL until the next periodic
-   solve. */
+   solve.
+   The n^2 kernel values are stored in FP32 on the device for the products of
+   the solve, where they take at most 16 GiB (65,536 atoms; see
+   qeq_use_stored_kernel) and half of the memory that is free.  The plan keeps
+   them allocated for its next isolated solves; a matrix above 256 MiB (8,192
+   atoms) is given back when the plan turns to a periodic or batched call. */
 int qeq_solve_nonperiodic(qeq_plan* plan, int32_t n, const double* pos, const double* sigma,
                           const double* J, const double* chi, double q_tot, const double* q0,
                           double* q, double* energies, double* forces, qeq_stats* stats);
+
+/* Most bytes of stored kernel values in later qeq_solve_nonperiodic calls on
+   this plan; a larger matrix that the plan holds is given back at once.  0:
+   the values are evaluated in every product.  Negative: the default, 16 GiB.
+   Results are the same bits either way. */
+int qeq_use_stored_kernel(qeq_plan* plan, int64_t max_bytes);
 
 /* Element-resolved electrostatic potentials of the last solve on this plan:
    the embedding features of the paper's ee4G variant (Electrostatics and
@@ -215,7 +226,7 @@ int qeq_matvec(qeq_plan* plan, int32_t n, const double* pos, const double* cell,
    uneven size (the paper treats structures independently and distributes them
    over ranks; here all advance through CG in step, four launches per
    iteration for the whole batch, as many structures at a time as 8 GiB of
-   scratch hold).  Structure s owns atoms atom_offsets[s] ..
+   scratch hold; the plan keeps what a call took of them).  Structure s owns atoms atom_offsets[s] ..
    atom_offsets[s+1]-1 of the concatenated arrays.
    atom_offsets (n_struct + 1, HOST, non-decreasing), cells (n_struct x 9,
    HOST, rows = lattice vectors), q_tot (n_struct, HOST).

@@ -359,6 +359,7 @@ int prepare(qeq_plan* pl, int n, const double* cell, double q_tot) {
     for (int t = 0; t < 9; ++t)
         if (!isfinite(cell[t])) return QEQ_EINVAL;
     if (!isfinite(q_tot)) return QEQ_EINVAL;
+    np_leave(pl);
     KParams& k = pl->kp;
     memset(&k, 0, sizeof(k));
     double det;
@@ -1167,6 +1168,15 @@ int qeq_use_ewald(qeq_plan* plan, int32_t enable) {
     plan->ewald = enable != 0;
     if (plan->ewald) plan->planewave = false;
     plan->tape_valid = false;
+    drop_graph(plan);
+    return QEQ_OK;
+}
+
+int qeq_use_stored_kernel(qeq_plan* plan, int64_t max_bytes) {
+    if (!plan) return QEQ_EINVAL;
+    if (plan->stream) (void)hipStreamSynchronize(plan->stream);
+    plan->np_mat_max = max_bytes < 0 ? NP_MAT_MAX : (size_t)max_bytes;
+    np_release(plan, plan->np_mat_max);
     drop_graph(plan);
     return QEQ_OK;
 }

@@ -16,9 +16,10 @@
 //
 // The kernel values do not change during a solve, so the FP32 matrix K_ij is
 // evaluated once per solve (k_np_build) and every product without forces reads
-// it from memory (k_np_mv).  Clusters whose matrix does not fit (NP_MAT_MAX,
-// half of the free memory) evaluate the values in every product (k_np_pairs),
-// and so does the final product, which also needs K'(r)/r.
+// it from memory (k_np_mv).  Clusters whose matrix does not fit (the plan's
+// bound, half of the free memory) evaluate the values in every product
+// (k_np_pairs), and so does the final product, which also needs K'(r)/r.  Both
+// add the same FP32 values in the same order in FP64: the same charges.
 #include <math.h>
 #include <string.h>
 
@@ -31,7 +32,7 @@ namespace {
 constexpr int NP_TILE = 256;
 constexpr int NP_SPLIT_MAX = 64;
 constexpr int NP_MT = 64;              // rows and columns of a tile of the stored kernel values
-constexpr size_t NP_MAT_MAX = (size_t)16 << 30;   // most bytes of stored kernel values (65,536 atoms)
+constexpr size_t NP_MAT_KEEP = (size_t)256 << 20;   // bytes that stay with the plan (8,192 atoms)
 constexpr double NP_RSQPI = 0.56418958354775628695;   // 1/sqrt(pi)
 
 // Validate, identity order, per-atom data; partial sums [sum chi, sum 1/D] in
@@ -275,27 +276,37 @@ void np_free(qeq_plan* pl) {
     double* ptrs[] = {pl->np_pos, pl->np_ypart, pl->np_fpart};
     for (double* q : ptrs)
         if (q) (void)hipFree(q);
-    if (pl->np_mat) (void)hipFree(pl->np_mat);
+    np_release(pl, 0);
     pl->np_pos = pl->np_ypart = pl->np_fpart = nullptr;
-    pl->np_mat = nullptr;
     pl->np_cap = 0;
+}
+
+// Gives back stored kernel values of more than `keep` bytes; products that still
+// follow evaluate them.
+void np_release(qeq_plan* pl, size_t keep) {
+    if (pl->np_mat_cap * sizeof(float) <= keep) return;
+    (void)hipFree(pl->np_mat);
+    pl->np_mat = nullptr;
     pl->np_mat_cap = 0;
     pl->np_ld = 0;
 }
 
+// The plan leaves the isolated path: its matrix goes unless it is small (an
+// allocation of 1 GB takes longer than the small solves that would repeat it).
+void np_leave(qeq_plan* pl) { np_release(pl, NP_MAT_KEEP); }
+
 // Room for the kernel values of n atoms; np_ld = 0 (values evaluated in every
-// product) where they exceed NP_MAT_MAX or half of the free memory.
+// product) where they exceed the plan's bound or half of the free memory.
 static void np_matrix_room(qeq_plan* pl, int n) {
     const size_t ld = ((size_t)n + NP_MT - 1) / NP_MT * NP_MT;
     const size_t count = ld * (size_t)n;
     pl->np_ld = 0;
+    if (count * sizeof(float) > pl->np_mat_max) return;
     if (count > pl->np_mat_cap) {
-        if (pl->np_mat) (void)hipFree(pl->np_mat);
-        pl->np_mat = nullptr;
-        pl->np_mat_cap = 0;
+        np_release(pl, 0);
         size_t avail = 0, total = 0;
         if (hipMemGetInfo(&avail, &total) != hipSuccess) return;
-        if (count * sizeof(float) > NP_MAT_MAX || count * sizeof(float) > avail / 2) return;
+        if (count * sizeof(float) > avail / 2) return;
         if (hipMalloc((void**)&pl->np_mat, count * sizeof(float)) != hipSuccess) {
             pl->np_mat = nullptr;
             (void)hipGetLastError();

@@ -128,6 +128,8 @@ struct DeviceAxes {
 
 struct BatchState;   // workspace of the batched solver (batched.hip)
 
+constexpr size_t NP_MAT_MAX = (size_t)16 << 30;   // stored kernel values: 65,536 atoms
+
 struct qeq_plan {
     qeq_params prm;
     int n_max = 0;
@@ -264,6 +266,7 @@ struct qeq_plan {
     int np_ld = 0;                // row length of the stored kernel values (0: none)
     float* np_mat = nullptr;      // K[j][i], n rows of np_ld
     size_t np_mat_cap = 0;        // floats
+    size_t np_mat_max = NP_MAT_MAX;   // most bytes (qeq_use_stored_kernel)
     double* np_pos = nullptr;     // double4 (x, y, z, sigma^2) per atom
     double* np_ypart = nullptr;   // [split][atom] partial products
     double* np_fpart = nullptr;   // [split][atom][3] partial force sums
@@ -434,6 +437,8 @@ int np_setup(qeq_plan* pl, int n, const double* pos, const double* sigma, const 
              double q_tot);
 int launch_np_matvec(qeq_plan* pl, const double* src, double* dst, int mode);   // QEQ_MODE_CG / FINAL
 void np_free(qeq_plan* pl);
+void np_release(qeq_plan* pl, size_t keep);
+void np_leave(qeq_plan* pl);
 int launch_final_tail(qeq_plan* pl, double* q_out, double* energies, double* forces_out);
 // direct Ewald reciprocal part (ewald.hip)
 // ------------------------------------------------------------------ mesh_mid.hip

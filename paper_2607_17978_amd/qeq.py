@@ -104,6 +104,8 @@ def load_library():
     L.qeq_use_ewald.restype = ctypes.c_int
     L.qeq_use_planewave.argtypes = [vp, i32, ctypes.c_double]
     L.qeq_use_planewave.restype = ctypes.c_int
+    L.qeq_use_stored_kernel.argtypes = [vp, ctypes.c_int64]
+    L.qeq_use_stored_kernel.restype = ctypes.c_int
     L.qeq_use_sqnm.argtypes = [vp, i32, i32]
     L.qeq_use_sqnm.restype = ctypes.c_int
     L.qeq_use_spectral_preconditioner.argtypes = [vp, f64]
@@ -420,6 +422,13 @@ class Plan:
         if rc != QEQ_OK:
             raise QEqError(rc, strerror(rc))
         self._last_n = None
+
+    def use_stored_kernel(self, max_bytes=-1):
+        """Most bytes of stored kernel values of isolated solves (0: none, negative:
+        the default of 16 GiB); see qeq_use_stored_kernel."""
+        rc = load_library().qeq_use_stored_kernel(self._h, int(max_bytes))
+        if rc != QEQ_OK:
+            raise QEqError(rc, strerror(rc))
 
     def use_sqnm(self, enable=True, history=10):
         """SQNM (True) or projected CG (False, default) for later solves."""
