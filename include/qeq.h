@@ -257,8 +257,9 @@ int qeq_solve_batched(qeq_plan* plan, int32_t n_struct, const int32_t* atom_offs
    and results and times do not depend on it.  Defaults 1024, 1. */
 int qeq_batched_config(qeq_plan* plan, int32_t threads, int32_t wg_per_cu);
 
-/* Milliseconds of the batched kernels (HIP events) accumulated since the
-   last reset; reset != 0 clears the counter. */
+/* Milliseconds from the first to the end of the last kernel of the batched
+   calls (HIP events; tables and memory are prepared before), accumulated since
+   the last reset; reset != 0 clears the counter. */
 double qeq_batched_last_ms(qeq_plan* plan, int32_t reset);
 
 /* Per-structure time breakdown of the last qeq_solve_batched call, measured

@@ -1294,6 +1294,7 @@ struct BatchState {
     size_t staging_cap = 0;
     BCount* count_host = nullptr;   // pinned: counters of the chunks in flight
     hipEvent_t ev[2] = {nullptr, nullptr};
+    hipEvent_t span[2] = {nullptr, nullptr};   // before a wave's first and after its last kernel
     int threads = 1024;
     int wg_per_cu = 1;
     double last_ms = 0.0;
@@ -1307,7 +1308,7 @@ void batch_free(qeq_plan* pl) {
     if (b->tables) (void)hipFree(b->tables);
     if (b->staging) (void)hipHostFree(b->staging);
     if (b->count_host) (void)hipHostFree(b->count_host);
-    for (hipEvent_t e : b->ev)
+    for (hipEvent_t e : {b->ev[0], b->ev[1], b->span[0], b->span[1]})
         if (e) (void)hipEventDestroy(e);
     delete b;
     pl->batch = nullptr;
@@ -1408,6 +1409,8 @@ int run_wave(qeq_plan* pl, BatchState* b, BArgs& a, std::vector<BStruct>& st, co
     }
     for (hipEvent_t& e : b->ev)
         if (!e) QEQ_HIP(hipEventCreateWithFlags(&e, hipEventDisableTiming));
+    for (hipEvent_t& e : b->span)
+        if (!e) QEQ_HIP(hipEventCreate(&e));
     memset(b->staging + oState, 0, sizeof(BState) * n_struct);
     const BCount c0 = {ns, 0};
     auto put = [&](size_t at, const void* from, size_t bytes) {
@@ -1454,6 +1457,7 @@ int run_wave(qeq_plan* pl, BatchState* b, BArgs& a, std::vector<BStruct>& st, co
     QEQ_TRY(window((const void*)k_bq_inv<true>, shC));
     QEQ_TRY(window((const void*)k_bq_theta, shC));
     // --- set-up
+    QEQ_HIP(hipEventRecord(b->span[0], stream));
     hipLaunchKernelGGL(k_bq_stage, dim3(ns), dim3(1024), 0, stream, a, order);
     hipLaunchKernelGGL(k_bq_pairs, dim3((unsigned)uP.size()), dim3(256), 0, stream, a, dP);
     hipLaunchKernelGGL(k_bq_green, dim3((unsigned)uG.size()), dim3(256), 0, stream, a, dG);
@@ -1512,8 +1516,11 @@ int run_wave(qeq_plan* pl, BatchState* b, BArgs& a, std::vector<BStruct>& st, co
         hipLaunchKernelGGL(k_bq_count_clear, dim3(1), dim3(1), 0, stream, a.count);
         QEQ_TRY(qeq_check(hipGetLastError()));
     }
+    QEQ_HIP(hipEventRecord(b->span[1], stream));
     QEQ_HIP(hipMemcpyAsync(b->staging + oState, a.state, sizeof(BState) * n_struct, hipMemcpyDeviceToHost, stream));
     QEQ_HIP(hipStreamSynchronize(stream));
+    float ms = 0.f;
+    if (hipEventElapsedTime(&ms, b->span[0], b->span[1]) == hipSuccess) b->last_ms += ms;
     const BState* back = (const BState*)(b->staging + oState);
     for (int s : work) state[s] = back[s];
     return QEQ_OK;
@@ -1669,10 +1676,6 @@ int batched_impl(qeq_plan* pl, int n_struct, const int32_t* offs, const double* 
     a.q_out = q;
     a.energies = energies;
     a.forces = forces;
-    hipEvent_t e0 = nullptr, e1 = nullptr;
-    (void)hipEventCreate(&e0);
-    (void)hipEventCreate(&e1);
-    if (e0) (void)hipEventRecord(e0, pl->stream);
     int rc2 = QEQ_OK;
     // structures whose pair list overflowed go again with the measured size
     for (int round = 0; round < 2 && !work.empty() && rc2 == QEQ_OK; ++round) {
@@ -1708,12 +1711,6 @@ int batched_impl(qeq_plan* pl, int n_struct, const int32_t* offs, const double* 
         }
         work.swap(again);
     }
-    if (e1) (void)hipEventRecord(e1, pl->stream);
-    if (e1) (void)hipEventSynchronize(e1);
-    float ms = 0.f;
-    if (rc2 == QEQ_OK && e0 && e1 && hipEventElapsedTime(&ms, e0, e1) == hipSuccess) b->last_ms += ms;
-    if (e0) (void)hipEventDestroy(e0);
-    if (e1) (void)hipEventDestroy(e1);
     if (rc2 != QEQ_OK) {
         (void)hipStreamSynchronize(pl->stream);   // nothing of this call stays in flight
         return rc2;
