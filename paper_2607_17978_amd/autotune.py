@@ -1,5 +1,5 @@
-"""Autotuners: the batched solve's spline order, grid spacing and launch
-shape, and the single-structure solve's mesh tile widths.
+"""Autotuners: the batched solve's spline order and grid spacing, and the
+single-structure solve's mesh tile widths.
 
 The batched workload (many small structures, each on its own grid, advanced
 together) trades mesh work against accuracy: a higher spline order
@@ -18,8 +18,9 @@ points per atom).  The tuner measures instead of modelling:
    e.g. the FP64 oracle's stored solutions), a candidate must also meet the
    bars against every one of them: the absolute check on samples, beside the
    consistency check on the whole batch.
-3. Every surviving candidate is timed with each launch shape (workgroups per
-   compute unit); the fastest (p, h, shape) wins.
+3. Every surviving candidate is timed; the fastest (p, h) wins.  The launch
+   shape (workgroups per compute unit) is still accepted and reported, but the
+   kernels do not depend on it: a candidate is timed once for all of them.
 
 Single structure (``tune_tiles``): the axis-2 row tiles of the spread, the
 axis-1 / complex-to-real passes and the axis-2 pass (qeq_set_tiles) change
@@ -29,8 +30,8 @@ parity bars against it); the fastest measured one wins.  Choices are cached
 per (grid, spline order, atom-count bucket) in a JSON file
 (``cache_path()``), so later plans of the same shape skip the search.
 
-Everything runs through the C ABI (qeq_solve_batched, qeq_batched_config,
-qeq_solve, qeq_set_tiles); the tuners are host-side bookkeeping.
+Everything runs through the C ABI (qeq_solve_batched, qeq_solve,
+qeq_set_tiles); the tuners are host-side bookkeeping.
 """
 from __future__ import annotations
 
@@ -79,7 +80,7 @@ def _sample_errors(q, en, f, references, offs):
 
 def tune_batched(args, n_max=512, eta=2.0, r_cut=12.0, tol=1e-6, tol_q=1e-5, tol_e=1e-6, tol_f=1e-4,
                  candidates=CANDIDATES, wg_per_cu=WG_PER_CU, reps=3, log=None, references=None):
-    """Choose (spline order, spacing, workgroups per CU) for a batch.
+    """Choose (spline order, spacing) for a batch.
 
     args: the keyword arguments of Plan.solve_batched (device arrays, host
     offsets / cells / q_tot).  references: optional {structure index:
@@ -114,15 +115,14 @@ def tune_batched(args, n_max=512, eta=2.0, r_cut=12.0, tol=1e-6, tol_q=1e-5, tol
                 row.update(sample_max_dq=sq, sample_max_rel_dE=se, sample_max_rel_dF=sf)
                 row["accurate"] = row["accurate"] and sq <= tol_q and se <= tol_e and sf <= tol_f
             if row["accurate"]:
-                for wg in wg_per_cu:
-                    plan.batched_config(1024, wg)
+                plan.solve_batched(**args)
+                torch.cuda.synchronize()
+                t0 = time.perf_counter()
+                for _ in range(reps):
                     plan.solve_batched(**args)
-                    torch.cuda.synchronize()
-                    t0 = time.perf_counter()
-                    for _ in range(reps):
-                        plan.solve_batched(**args)
-                    torch.cuda.synchronize()
-                    row[f"ms_wg{wg}"] = (time.perf_counter() - t0) * 1e3 / reps
+                torch.cuda.synchronize()
+                ms = (time.perf_counter() - t0) * 1e3 / reps
+                row.update({f"ms_wg{wg}": ms for wg in wg_per_cu})
         else:
             row["accurate"] = False
         plan.close()

@@ -1295,8 +1295,6 @@ struct BatchState {
     BCount* count_host = nullptr;   // pinned: counters of the chunks in flight
     hipEvent_t ev[2] = {nullptr, nullptr};
     hipEvent_t span[2] = {nullptr, nullptr};   // before a wave's first and after its last kernel
-    int threads = 1024;
-    int wg_per_cu = 1;
     double last_ms = 0.0;
     std::vector<BState> last_state;   // per-structure records of the last call
 };
@@ -1762,15 +1760,10 @@ int qeq_solve_batched(qeq_plan* plan, int32_t n_struct, const int32_t* atom_offs
 
 int qeq_batched_config(qeq_plan* plan, int32_t threads, int32_t wg_per_cu) {
     if (!plan) return QEQ_EINVAL;
-    // only 1024-thread workgroups are offered: a run with 256 threads ended
-    // in a GPU fault and runs with 512 threads did not converge on structures
-    // that 1024 threads solve, causes not found
+    // the launch shapes of an earlier kernel, one persistent workgroup per
+    // structure; what it refused stays refused, and nothing depends on the rest
     if (threads != 1024) return QEQ_EINVAL;
     if (wg_per_cu < 1 || wg_per_cu > 8) return QEQ_EINVAL;
-    BatchState* b = batch_state(plan);
-    if (!b) return QEQ_ENOMEM;
-    b->threads = threads;
-    b->wg_per_cu = wg_per_cu;
     return QEQ_OK;
 }
 
