@@ -648,8 +648,10 @@ __device__ __forceinline__ void pair_kernel(double r, double gam, double eta, do
 // A row of 16 lanes works on one atom: the R_a and their derivatives go to LDS
 // (an offset a lane, 2p - 1 <= 15), then each lane takes every 16th of the
 // (2p-1)^2 table rows.  A thread per atom is a serial chain of (2p-1)^3 = 1,331
-// table reads: 28 us for 64 atoms and 36 for 32,768, now 6 and 21 (bound by
-// LDS reads; 131,072 atoms 49 and 60); the six strain tables 135 -> 13 us (500 atoms).
+// table reads: 28 us for 64 atoms and 35 for 32,768, now 6 and 20.  It is bound by
+// LDS reads, a word per product and lane, where a thread per atom reads each word
+// once for 64 atoms: with enough atoms to fill the chip that is faster again
+// (mesh_self_thread).
 // ---------------------------------------------------------------------------
 template <int PC>
 struct SelfRows {
@@ -731,6 +733,55 @@ __device__ __forceinline__ void mesh_self_sum(int p_rt, const double* __restrict
         grad[0] = row16_sum(g0);
         grad[1] = row16_sum(g1);
         grad[2] = row16_sum(g2);
+    }
+}
+
+// The same, a thread per atom: everything but the table in registers, so for a
+// spline order P at compile time only.
+template <int P, bool GRAD>
+__device__ __forceinline__ void mesh_self_thread(const double* u, const double* __restrict__ tab, double* val,
+                                                 double* grad) {
+    constexpr int NP = 2 * P - 1;
+    double R[3][NP], dR[3][NP];
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        double c[QEQ_MAXP], dc[QEQ_MAXP];
+        bspline_weights<double>(u[a] - floor(u[a]), P, c, dc);
+#pragma unroll
+        for (int d = 0; d < NP; ++d) R[a][d] = dR[a][d] = 0.0;
+#pragma unroll
+        for (int k1 = 0; k1 < P; ++k1)
+#pragma unroll
+            for (int k2 = 0; k2 < P; ++k2) {
+                const int d = k2 - k1 + (P - 1);
+                R[a][d] += c[k1] * c[k2];
+                if (GRAD) dR[a][d] += dc[k1] * c[k2] + c[k1] * dc[k2];
+            }
+    }
+    double s = 0.0, g0 = 0.0, g1 = 0.0, g2 = 0.0;
+#pragma unroll
+    for (int a = 0; a < NP; ++a)
+#pragma unroll
+        for (int b = 0; b < NP; ++b) {
+            const double* row = tab + (a * NP + b) * NP;
+            double t = 0.0, t1 = 0.0;
+#pragma unroll
+            for (int c = 0; c < NP; ++c) {
+                t += row[c] * R[2][c];
+                if (GRAD) t1 += row[c] * dR[2][c];
+            }
+            s += R[0][a] * R[1][b] * t;
+            if (GRAD) {
+                g0 += dR[0][a] * R[1][b] * t;
+                g1 += R[0][a] * dR[1][b] * t;
+                g2 += R[0][a] * R[1][b] * t1;
+            }
+        }
+    *val = s;
+    if (GRAD) {
+        grad[0] = g0;
+        grad[1] = g1;
+        grad[2] = g2;
     }
 }
 

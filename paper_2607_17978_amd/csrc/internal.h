@@ -420,7 +420,7 @@ int launch_theta(qeq_plan* pl, bool strain, double* tab);
 int launch_selfcorr(qeq_plan* pl);
 // per block [sum q^2 theta^T dTheta_ab theta (6; 0 if tabs is null), sum q^2,
 // sum q sigma^2]; nblocks(n) blocks of QEQ_NPART
-int self_strain_blocks(int n);
+int self_strain_blocks(const KParams& k);
 int launch_self_strain(qeq_plan* pl, const double* tabs, double* part);
 // d C_eta / d eps_ab (host, order 00, 11, 22, 01, 02, 12)
 void reciprocal_self_strain(const double* H, const double* Hinv, double vol, double eta, double dC[6]);

@@ -426,43 +426,65 @@ __global__ __launch_bounds__(QEQ_BLOCK) void k_selfcorr(KParams k, const double*
     selfgrad[3 * i + 2] = g[2];
 }
 
+// The same with a thread per atom, for order 6 (whose arrays stay in registers)
+// and many atoms: a table word is read once for 64 atoms instead of four.  Four
+// waves a SIMD: with two, 35 us at 110,592 atoms but 61 at 132,651 (now 47 and
+// 49); with one, 59 and 85.
+template <int P>
+__global__ __launch_bounds__(QEQ_BLOCK, 4) void k_selfcorr_thread(KParams k, const double* __restrict__ frac,
+                                                              const double* __restrict__ tab_g,
+                                                              double* __restrict__ dself,
+                                                              double* __restrict__ selfgrad) {
+    constexpr int NP = 2 * P - 1;
+    __shared__ double tab[NP * NP * NP];
+    for (int t = threadIdx.x; t < NP * NP * NP; t += QEQ_BLOCK) tab[t] = tab_g[t];
+    __syncthreads();
+    const int i = blockIdx.x * QEQ_BLOCK + threadIdx.x;
+    if (i >= k.n) return;
+    const double u[3] = {frac[3 * i] * (double)k.K1, frac[3 * i + 1] * (double)k.K2, frac[3 * i + 2] * (double)k.K3};
+    double s, g[3];
+    mesh_self_thread<P, true>(u, tab, &s, g);
+    dself[i] += k.c_eta - s;
+    selfgrad[3 * i + 0] = g[0];
+    selfgrad[3 * i + 1] = g[1];
+    selfgrad[3 * i + 2] = g[2];
+}
+
 // Virial of the self-correction: per atom theta_i^T dTheta_ab theta_i for the
-// six strain components (one table staged in LDS at a time), weighted by q^2;
-// also sum q^2 and sum q sigma^2 for the C_eta and background terms.  Sixteen
-// lanes an atom as above; many atoms a block, since each block reads the six
-// tables (64 KB).  With few blocks (4,096 atoms) the tables go to blocks of
-// their own as well (gridDim.y = 6): 32 -> 13 us at 500
-// atoms.
+// six strain components, weighted by q^2; also sum q^2 and sum q sigma^2 for the
+// C_eta and background terms.  Sixteen lanes an atom as above, one table staged
+// in LDS at a time; many atoms a block, since each block reads the six tables.
+// With few blocks (4,096 atoms) the tables go to blocks of their own as well
+// (gridDim.y = 6).  Serves the orders other than 6.
 constexpr int STRAIN_NT = 1024, STRAIN_ATOMS = STRAIN_NT / 16;
 
-template <int PC>
 __global__ __launch_bounds__(STRAIN_NT) void k_self_strain(KParams k, const double* __restrict__ frac,
                                                           const double* __restrict__ tabs,
                                                           const double* __restrict__ q,
                                                           const double* __restrict__ sig,
                                                           double* __restrict__ part) {
-    constexpr int NPM = SelfRows<PC>::NPM;
+    constexpr int NPM = SelfRows<0>::NPM;
     extern __shared__ double sm[];
-    double* tab = sm;                                                          // NPM^3
-    SelfRows<PC>* rows = reinterpret_cast<SelfRows<PC>*>(tab + NPM * NPM * NPM);   // STRAIN_ATOMS
+    double* tab = sm;                                                            // NPM^3
+    SelfRows<0>* rows = reinterpret_cast<SelfRows<0>*>(tab + NPM * NPM * NPM);   // STRAIN_ATOMS
     const int np = 2 * k.p - 1, np3 = np * np * np;
     const int i = blockIdx.x * STRAIN_ATOMS + (threadIdx.x >> 4), ic = min(i, k.n - 1);
     const bool act = i < k.n && (threadIdx.x & 15) == 0;
-    SelfRows<PC>& w = rows[threadIdx.x >> 4];
+    SelfRows<0>& w = rows[threadIdx.x >> 4];
     double acc[QEQ_NPART];
 #pragma unroll
     for (int t = 0; t < QEQ_NPART; ++t) acc[t] = 0.0;
     const double qi = act ? q[i] : 0.0;
     if (tabs) {
-        mesh_self_prepare<PC>(frac[3 * ic] * (double)k.K1, frac[3 * ic + 1] * (double)k.K2,
-                              frac[3 * ic + 2] * (double)k.K3, k.p, w);
+        mesh_self_prepare<0>(frac[3 * ic] * (double)k.K1, frac[3 * ic + 1] * (double)k.K2,
+                             frac[3 * ic + 2] * (double)k.K3, k.p, w);
         const int c0 = gridDim.y == 6 ? (int)blockIdx.y : 0, c1 = gridDim.y == 6 ? c0 + 1 : 6;
         for (int comp = c0; comp < c1; ++comp) {
             __syncthreads();
             for (int t = threadIdx.x; t < np3; t += STRAIN_NT) tab[t] = tabs[(size_t)comp * np3 + t];
             __syncthreads();
             double s;
-            mesh_self_sum<PC, false>(k.p, tab, w, &s, nullptr);
+            mesh_self_sum<0, false>(k.p, tab, w, &s, nullptr);
 #pragma unroll
             for (int t = 0; t < 6; ++t)
                 if (act && t == comp) acc[t] = qi * qi * s;
@@ -477,6 +499,49 @@ __global__ __launch_bounds__(STRAIN_NT) void k_self_strain(KParams k, const doub
         for (int t = 0; t < QEQ_NPART; ++t)
             part[((size_t)blockIdx.y * gridDim.x + blockIdx.x) * QEQ_NPART + t] = acc[t];
 }
+
+// The same for order 6 with a thread per atom; table blockIdx.y.  512 / 4,096 /
+// 32,768 / 131,072 / 262,144 atoms: 12 / 13 / 23 / 79 / 142 us, with 16 lanes an
+// atom 12 / 22 / 61 / 264 / 466 (a row's LDS reads serve four atoms instead of
+// 64), with a thread per atom and one block's six tables in turn 129 / 128 / 134
+// / 145 / 157.
+template <int P>
+__global__ __launch_bounds__(QEQ_BLOCK) void k_self_strain_thread(KParams k, const double* __restrict__ frac,
+                                                                 const double* __restrict__ tabs,
+                                                                 const double* __restrict__ q,
+                                                                 const double* __restrict__ sig,
+                                                                 double* __restrict__ part) {
+    constexpr int NP = 2 * P - 1, NP3 = NP * NP * NP;
+    __shared__ double tab[NP3];
+    const int i = blockIdx.x * QEQ_BLOCK + threadIdx.x, comp = blockIdx.y;
+    const bool act = i < k.n;
+    const double qi = act ? q[i] : 0.0;
+    double s = 0.0;
+    if (tabs) {
+        for (int t = threadIdx.x; t < NP3; t += QEQ_BLOCK) tab[t] = tabs[(size_t)comp * NP3 + t];
+        __syncthreads();
+        if (act) {
+            const double u[3] = {frac[3 * i] * (double)k.K1, frac[3 * i + 1] * (double)k.K2,
+                                 frac[3 * i + 2] * (double)k.K3};
+            mesh_self_thread<P, false>(u, tab, &s, nullptr);
+        }
+    }
+    double acc[QEQ_NPART];
+#pragma unroll
+    for (int t = 0; t < 6; ++t) acc[t] = t == comp ? qi * qi * s : 0.0;
+    acc[6] = comp == 0 ? qi * qi : 0.0;
+    acc[7] = act && comp == 0 ? qi * sig[i] * sig[i] : 0.0;
+    block_sum<QEQ_NPART>(acc);
+    if (threadIdx.x == 0)
+        for (int t = 0; t < QEQ_NPART; ++t)
+            part[((size_t)blockIdx.y * gridDim.x + blockIdx.x) * QEQ_NPART + t] = acc[t];
+}
+
+// From how many atoms on k_selfcorr_thread, at order 6.  16 lanes / a thread an
+// atom: 85,184 atoms 42 / 43 us, 97,336 49 / 47, 132,651 65 / 49, 262,144 120 / 64.
+// Other orders (8: 262,144 atoms 386 us) keep the lanes: a thread's arrays of a
+// runtime order go to memory (655 us).
+constexpr int SELF_THREAD_N = 98304;
 
 }  // namespace
 
@@ -629,7 +694,10 @@ int grow_pairs(qeq_plan* pl, size_t cap) {
 }
 
 int launch_selfcorr(qeq_plan* pl) {
-    if (pl->kp.p == 6)
+    if (pl->kp.p == 6 && pl->kp.n >= SELF_THREAD_N)
+        hipLaunchKernelGGL(k_selfcorr_thread<6>, dim3(nblocks(pl->kp.n)), dim3(QEQ_BLOCK), 0, pl->stream, pl->kp,
+                           pl->frac, pl->theta_tab, pl->dself, pl->selfgrad);
+    else if (pl->kp.p == 6)
         hipLaunchKernelGGL(k_selfcorr<6>, dim3(nblocks(pl->kp.n, SELF_ATOMS)), dim3(QEQ_BLOCK), 0, pl->stream, pl->kp,
                            pl->frac, pl->theta_tab, pl->dself, pl->selfgrad);
     else
@@ -638,27 +706,28 @@ int launch_selfcorr(qeq_plan* pl) {
     return qeq_check(hipGetLastError());
 }
 
-static dim3 self_strain_grid(int n) {
-    const int nb = nblocks(n, STRAIN_ATOMS);
+static dim3 self_strain_grid(const KParams& k) {
+    if (k.p == 6) return dim3(nblocks(k.n), 6);
+    const int nb = nblocks(k.n, STRAIN_ATOMS);
     return dim3(nb, nb <= 64 ? 6 : 1);
 }
 
-int self_strain_blocks(int n) {
-    const dim3 g = self_strain_grid(n);
+int self_strain_blocks(const KParams& k) {
+    const dim3 g = self_strain_grid(k);
     return (int)(g.x * g.y);
 }
 
-template <int PC>
-static int self_strain_launch(qeq_plan* pl, const double* tabs, double* part) {
-    const KParams& k = pl->kp;
-    constexpr int NPM = SelfRows<PC>::NPM;
-    constexpr size_t sh = sizeof(double) * NPM * NPM * NPM + sizeof(SelfRows<PC>) * STRAIN_ATOMS;
-    QEQ_HIP(hipFuncSetAttribute((const void*)k_self_strain<PC>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh));
-    hipLaunchKernelGGL(k_self_strain<PC>, self_strain_grid(k.n), dim3(STRAIN_NT), sh, pl->stream, k, pl->frac,
-                       tabs, pl->q, pl->sig, part);
-    return qeq_check(hipGetLastError());
-}
-
 int launch_self_strain(qeq_plan* pl, const double* tabs, double* part) {
-    return pl->kp.p == 6 ? self_strain_launch<6>(pl, tabs, part) : self_strain_launch<0>(pl, tabs, part);
+    const KParams& k = pl->kp;
+    if (k.p == 6) {
+        hipLaunchKernelGGL(k_self_strain_thread<6>, self_strain_grid(k), dim3(QEQ_BLOCK), 0, pl->stream, k, pl->frac,
+                           tabs, pl->q, pl->sig, part);
+        return qeq_check(hipGetLastError());
+    }
+    constexpr int NPM = SelfRows<0>::NPM;
+    constexpr size_t sh = sizeof(double) * NPM * NPM * NPM + sizeof(SelfRows<0>) * STRAIN_ATOMS;
+    QEQ_HIP(hipFuncSetAttribute((const void*)k_self_strain, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh));
+    hipLaunchKernelGGL(k_self_strain, self_strain_grid(k), dim3(STRAIN_NT), sh, pl->stream, k, pl->frac, tabs, pl->q,
+                       pl->sig, part);
+    return qeq_check(hipGetLastError());
 }

@@ -107,7 +107,7 @@ int virial_impl(qeq_plan* pl, double* virial) {
     const KParams& k = pl->kp;
     const int nm = mesh_virial_blocks(k);
     const int np = std::min(4096, (k.n + QEQ_BLOCK / 64 - 1) / (QEQ_BLOCK / 64));
-    const int ns = self_strain_blocks(k.n);
+    const int ns = self_strain_blocks(k);
     const size_t need = (size_t)(nm + np + ns) * QEQ_NPART;
     if (need > pl->vir_cap) {
         pl->vir_cap = 0;
