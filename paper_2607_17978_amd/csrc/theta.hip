@@ -10,12 +10,19 @@
 // A table took five launches with full-size transforms through memory (write G,
 // axis 1, axis 2, axis 3, pick the offsets), the six strain tables thirty; now
 // two each: 12 us and 17 us at 40 x 60 x 60 where they took 19 and 116, and two
-// steps of a 500-atom triclinic cell with virials 2.83 -> 2.65 ms.
+// steps of a 500-atom triclinic cell with virials 2.83 -> 2.65 ms.  One table /
+// six at order 6, us, with the transforms and now: 96^3 29 / 238 and 21 / 24,
+// 192^3 58 / 368 and 29 / 93, 320^3 230 / 1,404 and 73 / 310, 384^3 1,935 / 11,600
+// and 105 / 628, 512 x 512 x 12 665 / 3,966 and 50 / 57.  Bound by the FP64
+// multiply-adds, 2 p a mode, and the Green's function.
+#include <algorithm>
+
 #include "mesh_passes.h"
 
 namespace {
 
 constexpr int TH_W = 8;                  // waves of a plane block
+constexpr int TH_BLOCKS = 512;           // plane blocks that the launch aims at
 constexpr int TH_NP = 2 * QEQ_MAXP - 1;  // most offsets along an axis
 
 // Component order of symmetric 3x3 tensors: 00, 11, 22, 01, 02, 12.
@@ -37,8 +44,9 @@ __device__ __forceinline__ float theta_green(const KParams& k, int m1, int m2, i
     return g * ((a == b ? -1.f : 0.f) + 2.f * (1.f / k2 + 0.5f * eta * eta) * kv[a] * kv[b]);
 }
 
-// Block (m3, table): 64 columns m2 at a time, a lane each; the waves share
+// Block (m3, table, z): 64 columns m2 at a time, a lane each; the waves share
 // m1 and add up through LDS; then a thread per (d_1, d_2) takes the columns in.
+// Every gridDim.z-th group of 64 columns.
 // T[table][m3][d_1][d_2].
 __global__ __launch_bounds__(64 * TH_W) void k_theta_plane(KParams k, const float* __restrict__ b1,
                                                            const float* __restrict__ b2,
@@ -60,7 +68,7 @@ __global__ __launch_bounds__(64 * TH_W) void k_theta_plane(KParams k, const floa
     const int od1 = tid / np - (p - 1), od2 = tid - (tid / np) * np - (p - 1);   // offsets of this thread's output
     const bool out = tid < np * np;
     double2 acc = make_double2(0.0, 0.0);
-    for (int c0 = 0; c0 < K2; c0 += 64) {
+    for (int c0 = 64 * blockIdx.z; c0 < K2; c0 += 64 * gridDim.z) {
         const int m2 = c0 + lane;
         const bool in = m2 < K2 && m2_kept(k, m2);
         double C[QEQ_MAXP], D[QEQ_MAXP];
@@ -111,12 +119,12 @@ __global__ __launch_bounds__(64 * TH_W) void k_theta_plane(KParams k, const floa
         }
         __syncthreads();
     }
-    if (out) T[((size_t)blockIdx.y * k.K3h + m3) * np * np + tid] = acc;
+    if (out) T[(((size_t)blockIdx.y * k.K3h + m3) * gridDim.z + blockIdx.z) * np * np + tid] = acc;
 }
 
 // tab[table][d_1][d_2][d_3] = sum over m3 of the half spectrum; block (d_1 d_2,
 // table), a thread per d_3 and part of the m3.
-__global__ __launch_bounds__(256) void k_theta_tab(KParams k, const double2* __restrict__ T,
+__global__ __launch_bounds__(256) void k_theta_tab(KParams k, int nz, const double2* __restrict__ T,
                                                    double* __restrict__ tab) {
     __shared__ double red[16][16];
     const int np = 2 * k.p - 1, x = blockIdx.x, l = threadIdx.x & 15, q = threadIdx.x >> 4;
@@ -124,7 +132,12 @@ __global__ __launch_bounds__(256) void k_theta_tab(KParams k, const double2* __r
     double s = 0.0;
     if (l < np)
         for (int m3 = q; m3 < k.K3h; m3 += 16) {
-            const double2 t = T[((size_t)blockIdx.y * k.K3h + m3) * np * np + x];
+            const double2* pl = T + ((size_t)blockIdx.y * k.K3h + m3) * nz * np * np + x;
+            double2 t = pl[0];
+            for (int z = 1; z < nz; ++z) {
+                t.x += pl[(size_t)z * np * np].x;
+                t.y += pl[(size_t)z * np * np].y;
+            }
             double sn, cs;
             sincospi(2.0 * (double)(m3 * d3) / k.K3, &sn, &cs);
             s += (m3 == 0 ? 1.0 : 2.0) * (t.x * cs - t.y * sn);
@@ -145,7 +158,12 @@ __global__ __launch_bounds__(256) void k_theta_tab(KParams k, const double2* __r
 int launch_theta(qeq_plan* pl, bool strain, double* tab) {
     const KParams& k = pl->kp;
     const int np = 2 * k.p - 1, nt = strain ? 6 : 1;
-    const size_t need = (size_t)nt * k.K3h * np * np * 2;
+    // With few planes their columns go to blocks of their own: two blocks a CU
+    // (one table, a block a plane: 192^3 60 us at order 6 and 67 at order 8, where
+    // the transforms took 58 and 57; 512 x 512 x 12 319 us).
+    const int groups = (k.K2 + 63) / 64, planes = k.K3h * nt;
+    const int nz = std::max(1, std::min(groups, (TH_BLOCKS + planes - 1) / planes));
+    const size_t need = (size_t)planes * nz * np * np * 2;
     if (need > pl->theta_cap) {
         pl->theta_cap = 0;
         if (pl->theta_plane) (void)hipFree(pl->theta_plane);
@@ -157,8 +175,8 @@ int launch_theta(qeq_plan* pl, bool strain, double* tab) {
     double2* T = reinterpret_cast<double2*>(pl->theta_plane);
     const size_t sh = sizeof(double2) * (k.K1 + k.K2) + sizeof(double) * TH_W * 2 * k.p * 64;
     QEQ_HIP(hipFuncSetAttribute((const void*)k_theta_plane, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh));
-    hipLaunchKernelGGL(k_theta_plane, dim3(k.K3h, nt), dim3(64 * TH_W), sh, pl->stream, k, pl->bmod[0], pl->bmod[1],
+    hipLaunchKernelGGL(k_theta_plane, dim3(k.K3h, nt, nz), dim3(64 * TH_W), sh, pl->stream, k, pl->bmod[0], pl->bmod[1],
                        pl->bmod[2], strain ? 0 : -1, T);
-    hipLaunchKernelGGL(k_theta_tab, dim3(np * np, nt), dim3(256), 0, pl->stream, k, T, tab);
+    hipLaunchKernelGGL(k_theta_tab, dim3(np * np, nt), dim3(256), 0, pl->stream, k, nz, T, tab);
     return qeq_check(hipGetLastError());
 }
