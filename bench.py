@@ -629,7 +629,7 @@ def batch_main(args, dev):
     seq_ms = (time.perf_counter() - t0) * 1e3
     for pl in plans.values():
         pl.close()
-    # autotuned discretisation and launch shape (untimed search, then timed);
+    # autotuned discretisation (untimed search, then timed);
     # candidates are also gated on the stored FP64 oracle solutions of sampled
     # structures (tests/golden/batch1024_samples.npz, written by the oracle alone)
     from paper_2607_17978_amd import autotune
@@ -688,9 +688,10 @@ def batch_main(args, dev):
         "per_structure_launches": {"ms": round(seq_ms, 2), "structures_per_s": round(len(structs) / (seq_ms * 1e-3), 1),
                                    "speedup_of_batched": round(seq_ms / ms_step, 2),
                                    "cg_iters_mean": float(np.mean(seq_iters))},
-        # bound from counters (profiles/batched_1024_structures_counters.md): the
-        # LDS transforms and their barriers; memory moves 28 GB a solve (1.6 TB/s)
-        "roofline": {"bound": "lds", "kernel": "k_bq_fwd + k_bq_cols + k_bq_inv", "achieved": round(bbytes / (kern_ms * 1e-3) / 1e9, 1),
+        # bounds from counters (profiles/batched_1024_structures_counters.md): the
+        # plane kernels (fwd, inv) by their LDS transforms and barriers, the line
+        # kernel (cols) by memory, 3.7 TB/s; 28 GB a solve in all, 1.6 TB/s
+        "roofline": {"bound": "lds (fwd, inv), hbm (cols)", "kernel": "k_bq_fwd + k_bq_cols + k_bq_inv", "achieved": round(bbytes / (kern_ms * 1e-3) / 1e9, 1),
                      "peak": HBM_PEAK_GBPS, "unit": "GB/s",
                      "frac": round(bbytes / (kern_ms * 1e-3) / 1e9 / HBM_PEAK_GBPS, 4),
                      "traffic": BATCH_TRAFFIC, "bytes_per_launch": bbytes, "us_per_launch": round(kern_ms * 1e3, 1),

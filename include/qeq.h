@@ -203,8 +203,7 @@ int qeq_backward(qeq_plan* plan, const double* dL_dq, double dL_dEelec, double d
    also after qeq_matvec or qeq_descriptors, which replace the geometry).
    Runs one charge spread and two forward transform passes, the pair list and
    per-atom terms; the first call for a cell also builds six strain tables of
-   the mesh self-correction (six inverse mesh transforms).  Synchronises the
-   plan's stream. */
+   the mesh self-correction.  Synchronises the plan's stream. */
 int qeq_virial(qeq_plan* plan, double* virial);
 
 /* y = E v with the plan's particle-mesh operator (no J), for checking the
@@ -347,12 +346,12 @@ int mlp_train_step_noalloc(const float* G, const int32_t* species, const double*
                            float* adam_v, int32_t step, float lr, float* loss, float* grad_out,
                            void* stream);
 
-/* The CG loop of qeq_solve / qeq_backward runs as a replayed HIP graph of
-   12 iterations, 4 with the spectral preconditioner (captured on a private
-   stream, launched on the plan's stream,
-   re-captured when the geometry or buffers change); enable = 0 launches every
-   kernel separately instead.  Results are the same either way up to the
-   rounding order of the mesh atomics.  Default on.  While per-stage timers
+/* The CG loop of qeq_solve / qeq_backward runs as a replayed HIP graph of 6
+   iterations, 12 from 16,384 atoms on without the spectral preconditioner
+   (captured on a private stream, launched on the plan's stream, re-captured
+   when the cell or buffers change; a last chunk that is cut short is launched
+   kernel by kernel); enable = 0 launches every kernel separately instead.
+   Results are the same either way.  Default on.  While per-stage timers
    are enabled (qeq_profile) the loop launches kernels one by one. */
 int qeq_use_graphs(qeq_plan* plan, int32_t enable);
 
@@ -492,7 +491,10 @@ int qeq_use_spectral_preconditioner(qeq_plan* plan, double k_cut);
      4 axis-3 C2R FFT               5 interpolation + pair product (CG)
      6 CG update                    7 CG direction
      8 final energies / forces
-   CG-loop launches that found the solve already converged are not counted. */
+   CG-loop launches that found the solve already converged are not counted.
+   Where one launch does the work of several kinds it counts as one of them:
+   spread + axis-3 + axis-2 as 0, axis-2 + axis-1 + axis-2 as 2, axis-2 + axis-3
+   as 4, CG update + direction (up to 2,048 atoms) as 6. */
 int qeq_profile(qeq_plan* plan, uint32_t kind_mask);
 
 /* Copies accumulated milliseconds and launch counts for the first n_kinds

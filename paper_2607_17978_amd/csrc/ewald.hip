@@ -197,9 +197,9 @@ __global__ __launch_bounds__(64 * EW_SW) void k_ew_sf(int n, EwGeom g, const int
 // Potential (and with FIN the force sums) of 16 atoms from every
 // EW_PW * splits-th row tile: per tile the product of F with the c phases,
 // then one complex product with the row's phase.
-// 512 atoms 31 -> 5.5 us and against a thread per atom with a sine and cosine
-// per (mode, atom); 4,096 atoms (4.4e4 modes) 98 us.  Bound by latency and by
-// the reads of F, which each 16 atoms make from L2.  A solve of 512
+// 512 atoms 31 -> 5.5 us and 4,096 atoms (4.4e4 modes) 1,600 -> 98 us against
+// a thread per atom with a sine and cosine per (mode, atom); bound by latency
+// and by the reads of F, which each 16 atoms make from L2.  A solve of 512
 // atoms 2.68 -> 1.17 ms, of 4,096 atoms 57.5 -> 8.9 ms.
 template <bool FIN, bool TAB>
 __global__ __launch_bounds__(64 * EW_PW) void k_ew_pot(int n, int nrt, EwGeom g, const int4* __restrict__ rows,

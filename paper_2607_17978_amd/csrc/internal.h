@@ -441,12 +441,6 @@ void np_release(qeq_plan* pl, size_t keep);
 void np_leave(qeq_plan* pl);
 int launch_final_tail(qeq_plan* pl, double* q_out, double* energies, double* forces_out);
 // direct Ewald reciprocal part (ewald.hip)
-// ------------------------------------------------------------------ mesh_mid.hip
-constexpr int MID_MAX = 64;    // longest axis 1 or 2 of the one-pass middle
-bool mid_available(const qeq_plan* pl);
-int launch_mid(qeq_plan* pl, const float* b1, const float* b2, const float* b3, const int* done, hipEvent_t e0,
-               hipEvent_t e1);
-
 int ew_setup(qeq_plan* pl);
 int launch_ew_rec(qeq_plan* pl, const double* src, const int* done, bool fin);
 int launch_ew_forces_add(qeq_plan* pl);
@@ -494,6 +488,12 @@ int launch_mesh_stage(qeq_plan* pl, int kind, const double* src);
 // block [sum e, sum e c k_a k_b]; mesh_virial_blocks() blocks of QEQ_NPART.
 int launch_mesh_virial(qeq_plan* pl, const double* src, double* part);
 int mesh_virial_blocks(const KParams& k);
+
+// ------------------------------------------------------------------ one-pass middle (mesh_mid.hip)
+constexpr int MID_MAX = 64;    // longest axis 1 or 2 of the one-pass middle
+bool mid_available(const qeq_plan* pl);
+int launch_mid(qeq_plan* pl, const float* b1, const float* b2, const float* b3, const int* done, hipEvent_t e0,
+               hipEvent_t e1);
 
 // ------------------------------------------------------------------ solver kernels (solve.hip)
 int launch_interp(qeq_plan* pl, const double* src, double* dst, int mode, int parity,

@@ -145,7 +145,7 @@ __device__ __forceinline__ void pw_walk(const KParams& k, const PwGeom& g, const
 
 // ------------------------------------------------------------------ tile lists
 constexpr int PW_E = 4;                          // points of a tile per axis (K_a % 4 == 0)
-constexpr size_t PW_ENT_MAX = (size_t)1 << 28;   // most list entries (5.4 GB)
+constexpr size_t PW_ENT_MAX = (size_t)1 << 28;   // most list entries (9.7 GB)
 
 // Tiles that an atom's support can meet, over the lanes: f(tile index, offsets of
 // the tile's first point from the atom's grid cell, order among the atom's
