@@ -73,6 +73,11 @@ void debug_poison(void* p, size_t bytes) {
     if (p && bytes && getenv("QEQ_POISON_ALLOC") != nullptr) (void)hipMemset(p, 0xff, bytes);
 }
 
+int upload(qeq_plan* pl, void* dst, const void* src, size_t bytes) {
+    QEQ_HIP(hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, pl->stream));
+    return qeq_check(hipStreamSynchronize(pl->stream));
+}
+
 bool device_grow(size_t& cap, size_t count, std::initializer_list<GrowBuf> bufs) {
     const bool ok = grow_together(
         cap, count, bufs,
@@ -321,13 +326,13 @@ int ensure_grid(qeq_plan* pl, const int K[3]) {
             tw[j] = make_float2((float)cos(ang), (float)sin(ang));
         }
         QEQ_TRY(dalloc(&pl->tw[a], K[a]));
-        QEQ_HIP(hipMemcpy(pl->tw[a], tw.data(), sizeof(float2) * K[a], hipMemcpyHostToDevice));
+        QEQ_TRY(upload(pl, pl->tw[a], tw.data(), sizeof(float2) * K[a]));
         ax.tw = pl->tw[a];
         pl->axes.ax[a] = ax;
         std::vector<float> bm;
         bspline_moduli(K[a], p, bm);
         QEQ_TRY(dalloc(&pl->bmod[a], K[a]));
-        QEQ_HIP(hipMemcpy(pl->bmod[a], bm.data(), sizeof(float) * K[a], hipMemcpyHostToDevice));
+        QEQ_TRY(upload(pl, pl->bmod[a], bm.data(), sizeof(float) * K[a]));
     }
     size_t nreal = (size_t)K[0] * K[1] * K[2];
     size_t ncplx = (size_t)(K[2] / 2 + 1) * K[0] * K[1];

@@ -376,6 +376,10 @@ void debug_poison(void* p, size_t bytes);
 template <typename T>
 constexpr bool poisonable = std::is_floating_point<T>::value || std::is_same<T, float2>::value ||
                             std::is_same<T, float4>::value || std::is_same<T, double2>::value;
+// Copy from pageable host memory on the plan's stream, complete on return.  Not
+// hipMemcpy, which uses the legacy stream: it fails while another thread captures
+// a graph and breaks that capture.
+int upload(qeq_plan* pl, void* dst, const void* src, size_t bytes);
 // grow_together in device memory; a failed allocation leaves no HIP error behind.
 bool device_grow(size_t& cap, size_t count, std::initializer_list<GrowBuf> bufs);
 template <typename T>

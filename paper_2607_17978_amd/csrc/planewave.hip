@@ -655,9 +655,9 @@ int pw_setup(qeq_plan* pl) {
     if (kmax > pl->pw_cap_k) {
         if (!device_grow(pl->pw_cap_k, kmax, {grow_buf(pl->pw_ones)})) return QEQ_ENOMEM;
         std::vector<float> ones(kmax, 1.0f);
-        const hipError_t e = hipMemcpy(pl->pw_ones, ones.data(), sizeof(float) * kmax, hipMemcpyHostToDevice);
-        if (e != hipSuccess) pl->pw_cap_k = 0;
-        QEQ_HIP(e);
+        const int rc = upload(pl, pl->pw_ones, ones.data(), sizeof(float) * kmax);
+        if (rc != QEQ_OK) pl->pw_cap_k = 0;
+        QEQ_TRY(rc);
     }
     if (pl->n_max > pl->pw_cap_n) {
         const size_t nn = (size_t)pl->n_max;
